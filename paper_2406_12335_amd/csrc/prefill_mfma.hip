@@ -1,4 +1,4 @@
-// Prompt-pass scoring on the matrix cores (bf16 inputs, head_dim 128, gfx950).
+// Prompt-pass scoring on the matrix cores (bf16 inputs, head_dim 64 or 128, gfx950).
 //
 // Accumulated attention score after the prompt (paper Eq. 2 with t = L-1):
 //     S_i = sum_{j>=i} a_i^j ,   a^j = softmax over keys i<=j of c*<q_j,k_i>   (Eq. 1).
@@ -18,12 +18,12 @@
 //
 // Streaming.  Stages are copied global -> LDS by the load unit itself
 // (global_load_lds_dwordx4: each lane's 16 bytes land at LDS base + 16*lane, no registers),
-// three stages ahead of the one being consumed, into a ring of four 16 KiB buffers; one
+// three stages ahead of the one being consumed, into a ring of four 16 KiB (head_dim 64: 8 KiB) buffers; one
 // s_barrier per stage.  The copies are issued from inline assembly, so their completion is
 // tracked by hand: a wavefront waits until at most the copies of the younger stages are
-// outstanding (s_waitcnt vmcnt) before the barrier that publishes a stage.  LDS rows are 256
-// bytes; chunk c of row r sits at chunk c ^ (r & 15), which the copy realises on the source
-// side (the lane that fills LDS chunk p of row r fetches global chunk p ^ (r & 15)).
+// outstanding (s_waitcnt vmcnt) before the barrier that publishes a stage.  The 16-byte chunks
+// of an LDS row are permuted by the row (Rows::slot), which the copy realises on the source side
+// (the lane that fills LDS chunk p of row r fetches the global chunk that belongs there).
 //
 // The exponentials cost more vector-ALU time than the contraction costs matrix time, so the
 // two are overlapped inside every wavefront: while the 16 MFMAs of one pair of tiles (32
@@ -54,7 +54,7 @@
 // stage's attention rows, already averaged, once.
 //
 // The contraction index (head dimension) may be permuted freely as long as both operands
-// agree: lane half g takes the 16-byte chunk  s + 8g  of a row for MFMA step s.
+// agree: lane half g takes the 16-byte chunk  s + (D/16) g  of a row for MFMA step s.
 #include <type_traits>
 
 #include "vatp_device.h"
@@ -65,15 +65,12 @@ namespace {
 
 typedef __attribute__((address_space(3))) char lds_char;
 
-constexpr int kD = 128;            // head_dim
 constexpr int kStage = 64;         // streamed rows per LDS stage
 constexpr int kRing = 4;           // LDS stage buffers
 constexpr unsigned kComputeUnits = 256;
 constexpr int kAhead = kRing - 1;  // stages in flight beyond the one being consumed
 constexpr int kWaveCols = 64;      // stationary rows per wavefront
 constexpr int kBlockCols = 256;    // stationary rows per workgroup
-constexpr int kChunksPerRow = kD * 2 / 16;   // 16-byte chunks per row = 16
-constexpr int kStageBytes = kStage * kD * 2; // 16 KiB
 #ifndef VATP_LEAD_VALU
 #define VATP_LEAD_VALU 12
 #endif
@@ -82,6 +79,23 @@ constexpr int kStageBytes = kStage * kD * 2; // 16 KiB
 #endif
 constexpr int kLeadValu = VATP_LEAD_VALU;    // vector instructions asked for between the LDS reads and the first MFMA
 constexpr int kSlotValu = VATP_SLOT_VALU;    // vector instructions asked for after every MFMA
+
+// What the head dimension decides.  A wavefront's 1 KiB copy instruction covers 4 rows of 128 elements or 8 of 64,
+// a tile takes 8 or 4 MFMA steps, so at 64 every MFMA carries twice the exponentials and the vector ALU alone bounds
+// the pass; the smaller operand leaves room for three wavefronts per SIMD.  Measured, 4 x 16 heads of 64, 2048 rows:
+// 0.069 ms for both passes and the norms, 0.99 ms with fp32 FMAs.
+template <int D>
+struct Rows {
+    static constexpr int kChunks = D * 2 / 16;          // 16-byte chunks per row
+    static constexpr int kSteps = D / 16;               // MFMA steps per 32 x 32 tile
+    static constexpr int kStageBytes = kStage * D * 2;  // 16 or 8 KiB
+    static constexpr int kCopyRows = 64 / kChunks;      // rows per copy instruction
+    static constexpr int kCopies = 16 / kCopyRows;      // copy instructions per wavefront and stage
+    static constexpr int kPieces = 16 / (2 * kSteps);   // sixteenths of the pending pair's work after every MFMA
+    // LDS slot of chunk c of row r: 16 consecutive rows that read one chunk index hit 16 different 16-byte slots of
+    // the 64 banks (two rows of 64 elements share a span of the banks, so there the row pair is what is permuted by)
+    __device__ static __forceinline__ int slot(int r, int c) { return D == 128 ? c ^ (r & 15) : c ^ ((r >> 1) & 7); }
+};
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
@@ -194,29 +208,30 @@ struct Epilogue {
     }
 };
 
-// Norms of 64 consecutive value rows by one wavefront.  Same arithmetic as l1norm_kernel: 16 lanes per
-// row, 8 elements each in order, then an all-reduce over the row's 16 lanes; all 16 loads of a lane are
+// Norms of 64 consecutive value rows by one wavefront.  Same arithmetic as l1norm_kernel: D / 8 lanes per
+// row, 8 elements each in order, then an all-reduce over the row's lanes; all loads of a lane are
 // issued before the first is used.
-template <int kNorm>
+template <int D, int kNorm>
 __device__ __forceinline__ void value_norms_64(const uint4 *__restrict__ Vu, float *__restrict__ nu, int row0, int len,
                                                int lane)
 {
-    const int sub = lane & 15, rr = lane >> 4;
-    uint4 raw[16];
+    using R = Rows<D>;
+    const int sub = lane % R::kChunks, rr = lane / R::kChunks;
+    uint4 raw[R::kChunks];
 #pragma unroll
-    for (int p = 0; p < 16; ++p) {
-        const int row = row0 + 4 * p + rr;
-        raw[p] = row < len ? Vu[static_cast<size_t>(row) * kChunksPerRow + sub] : make_uint4(0, 0, 0, 0);
+    for (int p = 0; p < R::kChunks; ++p) {
+        const int row = row0 + R::kCopyRows * p + rr;
+        raw[p] = row < len ? Vu[static_cast<size_t>(row) * R::kChunks + sub] : make_uint4(0, 0, 0, 0);
     }
 #pragma unroll
-    for (int p = 0; p < 16; ++p) {
-        const int row = row0 + 4 * p + rr;
-        const float value = row_norm<bf16_t, 16>(kNorm, raw[p]);
+    for (int p = 0; p < R::kChunks; ++p) {
+        const int row = row0 + R::kCopyRows * p + rr;
+        const float value = row_norm<bf16_t, R::kChunks>(kNorm, raw[p]);
         if (sub == 0 && row < len) nu[row] = value;
     }
 }
 
-template <bool kColsum, int kHalves, bool kWindow = false, bool kGrouped = false>
+template <int D, bool kColsum, int kHalves, bool kWindow = false, bool kGrouped = false>
 __global__ __launch_bounds__(256 * kHalves) void prefill_mfma_kernel(const bf16_t *__restrict__ Q,
                                                            const bf16_t *__restrict__ K,
                                                            float *__restrict__ lse2,
@@ -228,13 +243,15 @@ __global__ __launch_bounds__(256 * kHalves) void prefill_mfma_kernel(const bf16_
 {
     static_assert(!kWindow || kHalves == 1, "the windowed passes use 4-wavefront workgroups");
     static_assert(!kGrouped || kColsum, "only the column-sum passes loop over a group's query heads");
+    using R = Rows<D>;
+    constexpr int kD = D, kChunksPerRow = R::kChunks, kSteps = R::kSteps;
     constexpr bool kSplitKeys = kWindow && !kColsum;      // windowed row statistics: one (block, key range) per workgroup
     // A ring slot holds kHalves sub-stages of 64 streamed rows; wavefront w works on sub-stage
     // w / 4 of every slot for the 64 stationary rows of column group w % 4.  With kHalves = 2
     // a workgroup has two wavefronts per SIMD (used when the grid has too few workgroups for
     // two of them to share a compute unit).
     constexpr int kSlotRows = kStage * kHalves;
-    constexpr int kSlotBytes = kStageBytes * kHalves;
+    constexpr int kSlotBytes = R::kStageBytes * kHalves;
     __shared__ uint4 stage[kRing][kSlotRows * kChunksPerRow];   // filled by the load unit
     __shared__ __attribute__((aligned(16))) float lse_stage[kRing][kSlotRows];
     __shared__ float merge_buf[kHalves == 2 ? 2 : 1][kBlockCols];
@@ -282,16 +299,16 @@ __global__ __launch_bounds__(256 * kHalves) void prefill_mfma_kernel(const bf16_
     const unsigned lds_lse0 = static_cast<unsigned>(reinterpret_cast<size_t>((lds_char *)(char *)&lse_stage[0][0]));
 
     // Copy stage t (kSlotRows streamed rows) into ring slot `slot`.  This wavefront moves rows
-    // 16*wave .. 16*wave+15, four rows (1 KiB) per instruction.  Rows past the end of the
+    // 16*wave .. 16*wave+15, four or eight rows (1 KiB) per instruction.  Rows past the end of the
     // sequence are redirected to its last row (any finite data: they are masked later).
     auto copy_stage = [&](int t, int slot) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int r = 16 * wave + 4 * i + (lane >> 4);           // row inside the stage
-            const int c = (lane & 15) ^ (r & 15);                    // global chunk for LDS chunk lane&15
+        for (int i = 0; i < R::kCopies; ++i) {
+            const int r = 16 * wave + R::kCopyRows * i + lane / kChunksPerRow;      // row inside the stage
+            const int c = R::slot(r, lane % kChunksPerRow);          // global chunk for this lane's LDS chunk
             const int grow = min(t * kSlotRows + r, len - 1);
             const unsigned voff = static_cast<unsigned>(grow) * (kD * 2) + c * 16;
-            const unsigned m0v = lds_stage0 + slot * kSlotBytes + (16 * wave + 4 * i) * (kD * 2);
+            const unsigned m0v = lds_stage0 + slot * kSlotBytes + (16 * wave + R::kCopyRows * i) * (kD * 2);
             asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(m0v), "v"(voff), "s"(strm)
                          : "memory");
         }
@@ -310,7 +327,7 @@ __global__ __launch_bounds__(256 * kHalves) void prefill_mfma_kernel(const bf16_
     // (Windowed column sums of a group, kBand, go through the heads inside the stage loop instead: see there.)
     constexpr bool kBand = kWindow && kColsum && kGrouped;
     const int n_qh = (kGrouped && !kBand) ? __builtin_amdgcn_readfirstlane(group / splits) : 1;
-    bf16x8 Bf[2][8] = {};
+    bf16x8 Bf[2][kSteps] = {};
     Running<kColsum> run;
     for (int it = 0, n_it = (kSplitKeys ? 1 : 2) * n_qh; it < n_it; ++it) {
         const int job = kGrouped ? (it >= n_qh ? 1 : 0) : it, qh = kGrouped ? it - job * n_qh : 0;     // (at most two jobs)
@@ -364,23 +381,23 @@ __global__ __launch_bounds__(256 * kHalves) void prefill_mfma_kernel(const bf16_
                 const uint4 *Vu = reinterpret_cast<const uint4 *>(V + unit * cap * kD);
                 float *nu = nrm + unit * cap;
                 switch (norm) {
-                case VATP_NORM_L1: value_norms_64<VATP_NORM_L1>(Vu, nu, w0, len, lane); break;
-                case VATP_NORM_L2: value_norms_64<VATP_NORM_L2>(Vu, nu, w0, len, lane); break;
-                case VATP_NORM_LINF: value_norms_64<VATP_NORM_LINF>(Vu, nu, w0, len, lane); break;
-                default: value_norms_64<VATP_NORM_NONE>(Vu, nu, w0, len, lane); break;
+                case VATP_NORM_L1: value_norms_64<D, VATP_NORM_L1>(Vu, nu, w0, len, lane); break;
+                case VATP_NORM_L2: value_norms_64<D, VATP_NORM_L2>(Vu, nu, w0, len, lane); break;
+                case VATP_NORM_LINF: value_norms_64<D, VATP_NORM_LINF>(Vu, nu, w0, len, lane); break;
+                default: value_norms_64<D, VATP_NORM_NONE>(Vu, nu, w0, len, lane); break;
                 }
             }
         }
 
-        // stationary operand: 2 column blocks x 8 MFMA steps, 8 bf16 per lane each
+        // stationary operand: 2 column blocks x kSteps MFMA steps, 8 bf16 per lane each
         if (qh == 0) {
 #pragma unroll
             for (int cb = 0; cb < 2; ++cb) {
                 const int row = w0 + 32 * cb + n;
 #pragma unroll
-                for (int s = 0; s < 8; ++s) {
+                for (int s = 0; s < kSteps; ++s) {
                     uint4 raw = make_uint4(0, 0, 0, 0);
-                    if (row < len) raw = stat[static_cast<size_t>(row) * kChunksPerRow + s + 8 * g];
+                    if (row < len) raw = stat[static_cast<size_t>(row) * kChunksPerRow + s + kSteps * g];
                     Bf[cb][s] = as_bf16x8(raw);
                 }
             }
@@ -395,7 +412,7 @@ __global__ __launch_bounds__(256 * kHalves) void prefill_mfma_kernel(const bf16_
 #pragma unroll
         for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
-            for (int s = 0; s < 8; ++s) asm volatile("" ::"v"(Bf[cb][s]));
+            for (int s = 0; s < kSteps; ++s) asm volatile("" ::"v"(Bf[cb][s]));
         // a neutral pending pair: -inf logits turn into zeros in both epilogues
         Pending<kColsum> pend;
 #pragma unroll
@@ -412,9 +429,9 @@ __global__ __launch_bounds__(256 * kHalves) void prefill_mfma_kernel(const bf16_
             // (kBand: t is the virtual stage index)
             const int younger = kBand ? min(n_virtual - 1 - t, kAhead - 1) : min(t_end - t, kAhead - 1);
             if (younger == 2) {
-                if (extra_copy) wait_copies_then_barrier<10>(); else wait_copies_then_barrier<8>();
+                if (extra_copy) wait_copies_then_barrier<2 * R::kCopies + 2>(); else wait_copies_then_barrier<2 * R::kCopies>();
             } else if (younger == 1) {
-                if (extra_copy) wait_copies_then_barrier<5>(); else wait_copies_then_barrier<4>();
+                if (extra_copy) wait_copies_then_barrier<R::kCopies + 1>(); else wait_copies_then_barrier<R::kCopies>();
             } else {
                 wait_copies_then_barrier<0>();
             }
@@ -455,10 +472,10 @@ __global__ __launch_bounds__(256 * kHalves) void prefill_mfma_kernel(const bf16_
                     for (int kb = 0; kb < 2; ++kb) {
                         Pending<kColsum> next;
                         const int ar = kStage * half + 32 * kb + n;   // this lane's row of the streamed tile
-                        bf16x8 a[8];
+                        bf16x8 a[kSteps];
 #pragma unroll
-                        for (int s = 0; s < 8; ++s)
-                            a[s] = as_bf16x8(stage[slot][ar * kChunksPerRow + swizzled_chunk(ar, s + 8 * g)]);
+                        for (int s = 0; s < kSteps; ++s)
+                            a[s] = as_bf16x8(stage[slot][ar * kChunksPerRow + R::slot(ar, s + kSteps * g)]);
                         if (kColsum) {
 #pragma unroll
                             for (int q4 = 0; q4 < 4; ++q4) {
@@ -487,13 +504,16 @@ __global__ __launch_bounds__(256 * kHalves) void prefill_mfma_kernel(const bf16_
                         }
                         Epilogue<kColsum> epi;
 #pragma unroll
-                        for (int s = 0; s < 8; ++s) {
-                            next.acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s], Bf[0][s], next.acc[0], 0, 0, 0);
-                            // (the pending pair is the other pair: of the previous virtual stage for kb = 0)
-                            epi.template piece<kStoreMode>(2 * s, pend, run, scale, hist_rsrc, cap * 4, group_sum[kBand ? 1 - kb : 0]);
-                            next.acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s], Bf[1][s], next.acc[1], 0, 0, 0);
-                            epi.template piece<kStoreMode>(2 * s + 1, pend, run, scale, hist_rsrc, cap * 4, group_sum[kBand ? 1 - kb : 0]);
-                        }
+                        for (int s = 0; s < kSteps; ++s)
+#pragma unroll
+                            for (int cb = 0; cb < 2; ++cb) {
+                                next.acc[cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s], Bf[cb][s], next.acc[cb], 0, 0, 0);
+                                // (the pending pair is the other pair: of the previous virtual stage for kb = 0)
+#pragma unroll
+                                for (int i = 0; i < R::kPieces; ++i)
+                                    epi.template piece<kStoreMode>((2 * s + cb) * R::kPieces + i, pend, run, scale, hist_rsrc,
+                                                                   cap * 4, group_sum[kBand ? 1 - kb : 0]);
+                            }
                         epi.finish(pend, run, scale);
                         // keep the pending pair's results inside this block (no sinking past it)
                         if constexpr (kColsum) asm volatile("" : "+v"(run.col[0]), "+v"(run.col[1]));
@@ -502,10 +522,13 @@ __global__ __launch_bounds__(256 * kHalves) void prefill_mfma_kernel(const bf16_
                         // work, then one MFMA per slice of exponentials.  (LDS reads are left to the
                         // scheduler: pinning them makes it drop the whole request.)
                         __builtin_amdgcn_sched_group_barrier(0x002, kLeadValu, 0);
-                        sched_two_slots<kSlotValu, kSlotValu>(); sched_two_slots<kSlotValu, kSlotValu>();
-                        sched_two_slots<kSlotValu, kSlotValu>(); sched_two_slots<kSlotValu, kSlotValu>();
-                        sched_two_slots<kSlotValu, kSlotValu>(); sched_two_slots<kSlotValu, kSlotValu>();
-                        sched_two_slots<kSlotValu, kSlotValu>(); sched_two_slots<kSlotValu, kSlotValu>();
+                        constexpr int kSlot = kSlotValu * R::kPieces;
+                        sched_two_slots<kSlot, kSlot>(); sched_two_slots<kSlot, kSlot>();
+                        sched_two_slots<kSlot, kSlot>(); sched_two_slots<kSlot, kSlot>();
+                        if constexpr (kSteps == 8) {
+                            sched_two_slots<kSlot, kSlot>(); sched_two_slots<kSlot, kSlot>();
+                            sched_two_slots<kSlot, kSlot>(); sched_two_slots<kSlot, kSlot>();
+                        }
                         if constexpr (kMasked) {
                             // -inf above the diagonal of the finished pair and, for streamed
                             // queries, in rows past the end of the sequence
@@ -716,7 +739,10 @@ bool prefill_mfma_window_fits(int window, int cap, int n_units)
     return 8.0 * n_qb * prefill_window_splits(cap) * ((n_units + 7) / 8) < 2147483648.0;
 }
 
-hipError_t launch_prefill_mfma_window(const void *Q, const void *K, const void *V, float *S, float *nrm, float *lse2,
+namespace {
+
+template <int D>
+hipError_t launch_window(const void *Q, const void *K, const void *V, float *S, float *nrm, float *lse2,
                                       float *lse_part, int window, float *hist, const BatchMeta &meta,
                                       const Geometry &g, hipStream_t st)
 {
@@ -733,7 +759,7 @@ hipError_t launch_prefill_mfma_window(const void *Q, const void *K, const void *
     win.n_splits = ((g.max_len + kStage - 1) / kStage + kSplitStages - 1) / kSplitStages;
     const int window_blocks = (window + 1 + kBlockCols - 1) / kBlockCols + 1;     // blocks a window can straddle
     win.n_qb = window_blocks < n_blocks ? window_blocks : n_blocks;
-    hipLaunchKernelGGL((prefill_mfma_kernel<false, 1, true>), dim3(8u * win.n_qb * win.n_splits * ((q_units + 7) / 8)),
+    hipLaunchKernelGGL((prefill_mfma_kernel<D, false, 1, true>), dim3(8u * win.n_qb * win.n_splits * ((q_units + 7) / 8)),
                        dim3(256), 0, st, q, k, lse2, S, meta, q_heads, q_units, g.cap, n_blocks, g.scale_log2, win, nullptr,
                        nullptr, 0, g.group, 1);
     const int merge_rows = window + 1 + kStage;
@@ -741,13 +767,23 @@ hipError_t launch_prefill_mfma_window(const void *Q, const void *K, const void *
                        meta, q_heads, q_units, g.cap, window, win.n_splits);
     const dim3 grid(8u * ((n_blocks + 1) / 2) * ((kv_units + 7) / 8));
     if (g.group > 1)
-        hipLaunchKernelGGL((prefill_mfma_kernel<true, 1, true, true>), grid, dim3(256), 0, st, q, k, lse2, S, meta, g.n_heads,
+        hipLaunchKernelGGL((prefill_mfma_kernel<D, true, 1, true, true>), grid, dim3(256), 0, st, q, k, lse2, S, meta, g.n_heads,
                            kv_units, g.cap, n_blocks, g.scale_log2, win, static_cast<const bf16_t *>(V), nrm, g.norm,
                            g.group, 1);
     else
-        hipLaunchKernelGGL((prefill_mfma_kernel<true, 1, true>), grid, dim3(256), 0, st, q, k, lse2, S, meta, g.n_heads,
+        hipLaunchKernelGGL((prefill_mfma_kernel<D, true, 1, true>), grid, dim3(256), 0, st, q, k, lse2, S, meta, g.n_heads,
                            kv_units, g.cap, n_blocks, g.scale_log2, win, static_cast<const bf16_t *>(V), nrm, g.norm, 1, 1);
     return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_prefill_mfma_window(int head_dim, const void *Q, const void *K, const void *V, float *S, float *nrm,
+                                      float *lse2, float *lse_part, int window, float *hist, const BatchMeta &meta,
+                                      const Geometry &g, hipStream_t st)
+{
+    return head_dim == 64 ? launch_window<64>(Q, K, V, S, nrm, lse2, lse_part, window, hist, meta, g, st)
+                          : launch_window<128>(Q, K, V, S, nrm, lse2, lse_part, window, hist, meta, g, st);
 }
 
 namespace {
@@ -765,10 +801,8 @@ __global__ __launch_bounds__(256) void merge_group_partials_kernel(const float *
     S[unit * cap + i] = s * inv_group;
 }
 
-}  // namespace
-
-hipError_t launch_prefill_mfma(const void *Q, const void *K, const void *V, float *S, float *nrm, float *lse2,
-                               float *s_part, bool have_lse, const BatchMeta &meta, const Geometry &g, hipStream_t st)
+template <int D>
+hipError_t launch_full(const void *Q, const void *K, const void *V, float *S, float *nrm, float *lse2, float *s_part, bool have_lse, const BatchMeta &meta, const Geometry &g, hipStream_t st)
 {
     if (g.max_len <= 0) return hipSuccess;
     const int n_blocks = (g.max_len + kBlockCols - 1) / kBlockCols;
@@ -783,11 +817,11 @@ hipError_t launch_prefill_mfma(const void *Q, const void *K, const void *V, floa
     const unsigned wg_q = 8u * n_pairs * ((q_units + 7) / 8);
     if (!have_lse) {    // row statistics are computed here unless the caller supplied them
         if (wg_q >= 2u * kComputeUnits)
-            hipLaunchKernelGGL((prefill_mfma_kernel<false, 1>), dim3(wg_q), dim3(256), 0, st, q, k, lse2, S, meta,
+            hipLaunchKernelGGL((prefill_mfma_kernel<D, false, 1>), dim3(wg_q), dim3(256), 0, st, q, k, lse2, S, meta,
                                g.n_heads * g.group, q_units, g.cap, n_blocks, g.scale_log2, WindowPass{}, nullptr,
                                nullptr, 0, g.group, 1);
         else
-            hipLaunchKernelGGL((prefill_mfma_kernel<false, 2>), dim3(wg_q), dim3(512), 0, st, q, k, lse2, S, meta,
+            hipLaunchKernelGGL((prefill_mfma_kernel<D, false, 2>), dim3(wg_q), dim3(512), 0, st, q, k, lse2, S, meta,
                                g.n_heads * g.group, q_units, g.cap, n_blocks, g.scale_log2, WindowPass{}, nullptr,
                                nullptr, 0, g.group, 1);
     }
@@ -805,7 +839,7 @@ hipError_t launch_prefill_mfma(const void *Q, const void *K, const void *V, floa
     const unsigned wg_kv = 8u * n_pairs * ((slots + 7) / 8);
     float *dst = splits > 1 ? s_part : S;
 #define VATP_COLSUM(HALVES, GROUPED)                                                                              \
-    hipLaunchKernelGGL((prefill_mfma_kernel<true, HALVES, false, GROUPED>), dim3(wg_kv), dim3(256 * HALVES), 0, st, q, k, \
+    hipLaunchKernelGGL((prefill_mfma_kernel<D, true, HALVES, false, GROUPED>), dim3(wg_kv), dim3(256 * HALVES), 0, st, q, k, \
                        lse2, dst, meta, g.n_heads, slots, g.cap, n_blocks, g.scale_log2, WindowPass{}, v, nrm, g.norm,   \
                        g.group, splits)
     if (wg_kv >= 2u * kComputeUnits) {
@@ -818,6 +852,15 @@ hipError_t launch_prefill_mfma(const void *Q, const void *K, const void *V, floa
         hipLaunchKernelGGL(merge_group_partials_kernel, dim3((g.max_len + 255) / 256, kv_units), dim3(256), 0, st, s_part, S,
                            meta, g.n_heads, kv_units, g.cap, splits, 1.f / static_cast<float>(g.group));
     return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_prefill_mfma(int head_dim, const void *Q, const void *K, const void *V, float *S, float *nrm, float *lse2,
+                               float *s_part, bool have_lse, const BatchMeta &meta, const Geometry &g, hipStream_t st)
+{
+    return head_dim == 64 ? launch_full<64>(Q, K, V, S, nrm, lse2, s_part, have_lse, meta, g, st)
+                          : launch_full<128>(Q, K, V, S, nrm, lse2, s_part, have_lse, meta, g, st);
 }
 
 }  // namespace vatp

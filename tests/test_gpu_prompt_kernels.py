@@ -1,0 +1,54 @@
+"""Prompt scores of the kernel variants a grid of some size selects, at the edges of their tiles."""
+import sys
+
+import pytest
+import torch
+
+import parity
+import vatp_synth as vs
+from oracle import vatp_oracle as orc
+from paper_2406_12335_amd.runner import PrunedKVCache
+
+pytestmark = pytest.mark.gpu
+
+
+def _check_scores(dev, dtype, d, g, H, lens, window, units, seed):
+    """S and nrm of the given (sequence, K/V head) units against the oracle; rows past the end hold junk."""
+    cfg = vs.scaled(vs.CONFIGS["llama7b_layer"], batch=len(lens), n_heads=H, head_dim=d, dtype=dtype, q_per_kv=g,
+                    prompt_len=max(lens), decode_steps=0, n_sinks=1)
+    print("[case] %s d=%d g=%d H=%d lens=%s window=%s" % (dtype, d, g, H, lens, window), flush=True)
+    sys.stdout.flush()
+    inp = vs.make_inputs(cfg, seed=seed)
+    for t in (inp.Q, inp.K, inp.V):
+        for b, L in enumerate(lens):
+            t[b, :, L:] = 77.0
+    cache = PrunedKVCache(cfg.batch, H, d, cfg.torch_dtype(), 0, 0, [max(lens)] * len(lens), dev, window=window, q_per_kv=g)
+    try:
+        cache.prefill_score(inp.Q.to(dev), inp.K.to(dev), inp.V.to(dev), lens)
+        torch.cuda.synchronize()
+        S, nrm = cache.S_prompt.cpu(), cache.nrm_prompt.cpu()
+        hist = cache.hist_prompt.cpu() if window is not None else None
+    finally:
+        cache.close()
+    rtol = parity.rtol_for(cfg.torch_dtype())
+    for b, h in units:
+        L = lens[b]
+        Kh = inp.K[b, h, :L].double().numpy()
+        Qg = inp.Q[b, h * g:(h + 1) * g, :L].double().numpy()
+        if window is None:
+            want = orc.prefill_scores_group(Qg, Kh)
+        else:
+            want, rows = orc.prefill_window_group(Qg, Kh, window)
+        parity.assert_scores_close(S[b, h, :L].numpy(), want, rtol, "S len %d head %d" % (L, h))
+        parity.assert_scores_close(nrm[b, h, :L].numpy(), orc.l1norm(inp.V[b, h, :L].double().numpy()), rtol, "nrm")
+        if window is not None:
+            first = max(0, L - 1 - window)
+            for j in range(first, L):
+                parity.assert_scores_close(hist[b, h, j - first, :j + 1].numpy(), rows[j - first, :j + 1], rtol, "row %d" % j)
+
+
+# 256 heads and more fill the chip with the four-wavefront workgroups of the bf16 passes
+@pytest.mark.parametrize("g", [1, 2])
+def test_heads_of_64_on_a_full_grid(gpu_device, g):
+    lens = [770, 1, 63, 64, 65, 255, 256, 257]
+    _check_scores(gpu_device, "bf16", 64, g, 32, lens, None, [(b, 31 if b % 2 else 0) for b in range(len(lens))], 201 + g)
