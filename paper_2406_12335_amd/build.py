@@ -33,11 +33,12 @@ def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 
 
-# per-file additions.  prefill_mfma.hip never produces a NaN by construction (masked logits are
-# -inf and are only ever added to finite values), which lets fmax compile to bare v_max; its
+# per-file additions.  The prompt passes never produce a NaN by construction (masked logits are
+# -inf and are only ever added to finite values), which lets fmax compile to bare v_max; their
 # accumulators stay in architectural VGPRs so the exponentials can read them directly.
 EXTRA_FLAGS = {
     "prefill_mfma.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form"],
+    "prefill_direct.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form"],
 }
 
 

@@ -228,10 +228,10 @@ vatp_status prefill_score_impl(vatp_ctx *ctx, const vatp_params *p, const void *
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     float *lse2 = static_cast<float *>(ws);
     if (have_lse && launch_lse_to_base2(lse, lse2, pr.meta, pr.g, stream) != hipSuccess) return VATP_E_DEVICE;
-    // bf16 runs on the matrix cores, fp32 (and a history window too large for 32-bit offsets) on the fp32 FMA kernels
+    // bf16 streams through LDS; fp32, and a history window too large for 32-bit offsets, straight into registers
     const bool mfma = p->dtype == VATP_BF16;
     hipError_t e;
-    if (mfma && window < 0) {                 // (the matrix-core column-sum pass writes the norms as well)
+    if (mfma && window < 0) {                 // (all prompt passes write the norms as well)
         float *s_part = pr.g.group > 1 ? lse2 + align_up(units * pr.g.group * p->cap * sizeof(float)) / sizeof(float) : nullptr;
         e = launch_prefill_mfma(p->head_dim, Q, K, V, S, nrm, lse2, s_part, have_lse, pr.meta, pr.g, stream);
     } else if (mfma && prefill_mfma_window_fits(window, p->cap, static_cast<int>(units * pr.g.group))) {
@@ -239,8 +239,7 @@ vatp_status prefill_score_impl(vatp_ctx *ctx, const vatp_params *p, const void *
                                        lse2 + align_up(units * pr.g.group * p->cap * sizeof(float)) / sizeof(float), window,
                                        hist, pr.meta, pr.g, stream);
     } else {
-        if (launch_l1norm(p->dtype, p->head_dim, V, nrm, pr.meta, pr.g, stream) != hipSuccess) return VATP_E_DEVICE;
-        e = launch_prefill_generic(p->dtype, p->head_dim, Q, K, S, lse2, have_lse, window, hist, pr.meta, pr.g, stream);
+        e = launch_prefill_direct(p->dtype, p->head_dim, Q, K, V, S, nrm, lse2, have_lse, window, hist, pr.meta, pr.g, stream);
     }
     if (e != hipSuccess) return VATP_E_DEVICE;
     return VATP_OK;

@@ -1,0 +1,350 @@
+// Prompt-pass scoring on the matrix cores without staging: float32 inputs of any size (true fp32 contraction,
+// v_mfma_f32_32x32x2_f32, needed for the 1e-5 bar), and history windows of bf16 inputs too large for the staged
+// kernels' 32-bit offsets.
+//
+// The accumulated score of the paper's Eq. 2 after the prompt, S_i = sum_{j>=i} a_i^j, is a column sum of the causal
+// softmax matrix of Eq. 1.  The matrix is never stored:
+//   rowstat  queries stationary, keys streamed:  per query row j  lse2_j = log2 sum_{i<=j} 2^(t_ji)
+//   colsum   keys stationary, queries streamed:  S_i = sum_j 2^(t_ji - lse2_j), and the norms of the value rows
+// with t = c*log2(e)*<q,k>.
+//
+// A workgroup owns 32 stationary rows, which every one of its wavefronts holds in registers (the B operand, columns of
+// the 32 x 32 logit tile); the tiles of 32 streamed rows are dealt out to the wavefronts, which read them straight into
+// the A operand's registers -- chunk s of the next tile is requested as soon as the MFMAs of chunk s of this one are
+// issued, so a tile's loads have a whole tile's time to arrive.  A lane owns one stationary column and 16 streamed
+// rows of a tile: the reductions run inside the lane and the lane halves and wavefronts are merged once, through LDS.
+// There are no barriers in the loop and no atomics.
+//
+// What bounds it: in fp32 the matrix cores (64 cycles for 2 contraction elements: a tile of 32 x 32 x 128 takes 4096
+// cycles against 320 of vector work), and fp32 MFMAs do not overlap with vector instructions: a register-only loop
+// reaches 155 TFLOP/s, 129 with two FMAs per MFMA and 118 with four.  Splitting the streamed rows over the wavefronts
+// instead of the columns keeps a short prompt's chain short: at 256 rows a wavefront has one tile.  Measured against
+// 64 x 64 tiles of fp32 FMAs through LDS (both passes, fp32): 4 heads of 64 x 256 rows 69.5 -> 14.3 us; 64 heads x 2048
+// rows 1015 -> 332 us with 64 elements (104 TFLOP/s over both passes), 1871 -> 650 us with 128.
+//
+// History-window scores (Eq. 3 after the prompt: only the last w+1 query rows count) use the same two kernels with
+// `window` = w >= 0: query tiles wholly before row len-1-w are skipped, and colsum also stores the window's attention
+// rows, p = a_i^j at row j - j_first of a [w+1, cap] matrix per head.  window < 0 means no window.
+//
+// Grouped queries: rowstat has one unit per query head, colsum one per K/V head whose wavefronts take
+// (tile, query head) items; with attention rows to store, a wavefront takes all heads of a tile and adds their
+// weights in registers first.
+//
+// The contraction index may be permuted freely as long as both operands agree: lane half g takes the 16-byte
+// chunks 2s + g of a row, so that a load covers 32 contiguous bytes of each of the 32 rows.
+#include "vatp_device.h"
+
+namespace vatp {
+
+namespace {
+
+constexpr int kTileRows = 32;      // rows of a tile, streamed and stationary
+
+__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+
+// the MFMAs of chunk s per lane and operand, for every block of 32 stationary rows
+template <typename T, int kCols, int kSteps>
+__device__ __forceinline__ void mfma_chunk(const uint4 &a, const uint4 (&bf)[kCols][kSteps], int s, floatx16 (&acc)[kCols])
+{
+    if constexpr (sizeof(T) == 2) {
+#pragma unroll
+        for (int c = 0; c < kCols; ++c)
+            acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(a), as_bf16x8(bf[c][s]), acc[c], 0, 0, 0);
+    } else {
+        auto step = [&](unsigned x, auto part) __attribute__((always_inline)) {
+#pragma unroll
+            for (int c = 0; c < kCols; ++c)
+                acc[c] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(x), __uint_as_float(part(bf[c][s])), acc[c], 0, 0, 0);
+        };
+        step(a.x, [](const uint4 &b) { return b.x; });
+        step(a.y, [](const uint4 &b) { return b.y; });
+        step(a.z, [](const uint4 &b) { return b.z; });
+        step(a.w, [](const uint4 &b) { return b.w; });
+    }
+}
+
+enum { kRowstat, kColsumPlain, kColsumHist };      // passes
+
+struct DirectArgs {
+    int n_heads;                   // heads per sequence in units (query heads for rowstat, K/V heads for colsum)
+    int n_units, cap, n_blocks;    // n_blocks: blocks of stationary rows of the longest sequence
+    int window, group, norm;
+    float scale_log2;
+};
+
+// Blocks of 64 stationary rows from which a pass runs as workgroups of four wavefronts with 64 columns each (every A
+// chunk, 64 accesses to the vector cache because its 32 rows lie apart, then feeds twice the MFMAs); below it 32
+// columns and eight wavefronts keep more of the chip busy.  Measured, both passes, narrow / wide: 32 heads x 1024 rows
+// (512 blocks) 66 / 71 us with 64 elements, 129 / 130 with 128; 64 x 1024 (1024 blocks) 120 / 109 and 253 / 207;
+// 64 x 2048 373 / 332 and 800 / 650.
+constexpr long kWideGrid = 1024;
+
+template <typename T, int D, int kPass, int kCols, int kWaves>
+__global__ __launch_bounds__(64 * kWaves, 2) void prefill_direct_kernel(const T *__restrict__ Q, const T *__restrict__ K,
+                                                                        const T *__restrict__ V, float *__restrict__ lse2,
+                                                                        float *__restrict__ S, float *__restrict__ nrm,
+                                                                        float *__restrict__ hist, BatchMeta meta,
+                                                                        DirectArgs a)
+{
+    constexpr bool kColsum = kPass != kRowstat, kHist = kPass == kColsumHist;
+    constexpr int kChunks = D * static_cast<int>(sizeof(T)) / 16;     // 16-byte chunks per row
+    constexpr int kSteps = kChunks / 2;
+    constexpr int kAhead = kSteps < 8 ? kSteps : 8;                   // chunks of the A operand in flight
+    constexpr int kBlock = kTileRows * kCols;                         // stationary rows of the workgroup
+    __shared__ float s_part[2 * kWaves][kBlock];
+    __shared__ float s_max[kColsum ? 1 : 2 * kWaves][kBlock];
+    __shared__ __attribute__((aligned(16))) float s_lse[kColsum ? kWaves : 1][kTileRows];
+
+    // Units in the fast dimension: workgroups go to the 8 XCDs round-robin, so with a unit count that is a multiple of 8
+    // a unit's workgroups meet in one L2 and with fewer units they spread over the chip.  The longest columns first.
+    const int unit_i = blockIdx.x % a.n_units, rank = blockIdx.x / a.n_units;
+    const int blk = kColsum ? rank : a.n_blocks - 1 - rank;
+    const int len = meta.len[unit_i / a.n_heads];
+    const int base0 = blk * kBlock;
+    const int q_first = a.window >= 0 ? max(0, len - 1 - a.window) : 0;     // first query row that counts
+    if (base0 >= len || (!kColsum && base0 + kBlock <= q_first)) return;
+    const size_t unit = static_cast<size_t>(unit_i);
+    const int cap = a.cap, group = a.group;
+    const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, n = lane & 31;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+    const uint4 *stat = reinterpret_cast<const uint4 *>((kColsum ? K : Q) + unit * cap * D);
+    const uint4 *strm = reinterpret_cast<const uint4 *>(kColsum ? Q + unit * group * cap * D : K + unit / group * cap * D);
+    const float *lse_u = lse2 + (kColsum ? unit * group : unit) * cap;
+
+    // This wavefront's items: (tile of streamed rows, query head of the group).  Which wavefront takes the first one
+    // changes from workgroup to workgroup, so that a SIMD is not always the one with a tile more.
+    const int first = (wave + rank) % kWaves;
+    const int t_first = kColsum ? max(base0, q_first) / kTileRows : 0;
+    const int n_tiles = (kColsum ? len - 1 : min(base0 + kBlock, len) - 1) / kTileRows + 1 - t_first;
+    const int heads = kColsum ? group : 1;
+    const int n_items = kHist ? max((n_tiles - first + kWaves - 1) / kWaves, 0) * heads
+                              : max((n_tiles * heads - first + kWaves - 1) / kWaves, 0);
+    auto item = [&](int i, int &t, int &h) {
+        if constexpr (kHist) {
+            t = t_first + first + i / heads * kWaves;
+            h = i % heads;
+        } else {
+            const int f = first + i * kWaves;
+            h = heads == 1 ? 0 : f / n_tiles;
+            t = t_first + f - h * n_tiles;
+        }
+    };
+    auto tile_chunks = [&](int t, int h) {
+        return strm + (static_cast<size_t>(h) * cap + min(t * kTileRows + n, len - 1)) * kChunks + g;
+    };
+
+    // The stationary rows are waited for here, with the first streamed ones already requested behind them: in the loop
+    // nothing but a tile's own chunks is pending.  (Rows past the end read the last one: their columns are not stored.)
+    uint4 bf[kCols][kSteps], af[kAhead];
+#pragma unroll
+    for (int c = 0; c < kCols; ++c)
+#pragma unroll
+        for (int s = 0; s < kSteps; ++s)
+            bf[c][s] = stat[static_cast<size_t>(min(base0 + kTileRows * c + n, len - 1)) * kChunks + 2 * s + g];
+    float lse_next = 0.f;
+    int t = 0, h = 0;
+    const uint4 *src = strm;
+    if (n_items > 0) {
+        item(0, t, h);
+        src = tile_chunks(t, h);
+        if (kColsum) lse_next = lse_u[static_cast<size_t>(h) * cap + min(t * kTileRows + n, len - 1)];
+#pragma unroll
+        for (int s = 0; s < kAhead; ++s) af[s] = src[2 * s];
+    }
+#pragma unroll
+    for (int c = 0; c < kCols; ++c)
+#pragma unroll
+        for (int s = 0; s < kSteps; ++s)
+            asm volatile("" : "+v"(bf[c][s].x), "+v"(bf[c][s].y), "+v"(bf[c][s].z), "+v"(bf[c][s].w));
+
+    const float scale = a.scale_log2;
+    const float inv_group = 1.f / static_cast<float>(group);      // (exactly 1 for one head)
+    float m[kCols], l[kCols];                    // rowstat: running maximum and sum; colsum: l is the column sum
+    float group_sum[kHist ? kCols : 1][16];      // with attention rows: the tile's weights over the group so far
+#pragma unroll
+    for (int c = 0; c < kCols; ++c) { m[c] = -1e30f; l[c] = 0.f; }
+    if constexpr (kHist) {
+#pragma unroll
+        for (int c = 0; c < kCols; ++c)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) group_sum[c][v] = 0.f;
+    }
+
+    for (int i = 0; i < n_items; ++i) {
+        floatx16 acc[kCols];
+#pragma unroll
+        for (int c = 0; c < kCols; ++c)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[c][v] = 0.f;
+        // the tile's row statistics arrive one per lane and go through the wavefront's own LDS row (no barrier)
+        if constexpr (kColsum) s_lse[wave][n] = lse_next;
+        const bool more = i + 1 < n_items;
+        int t_next = t, h_next = h;
+        const uint4 *src_next = src;
+        if (more) {
+            item(i + 1, t_next, h_next);
+            src_next = tile_chunks(t_next, h_next);
+            if (kColsum) lse_next = lse_u[static_cast<size_t>(h_next) * cap + min(t_next * kTileRows + n, len - 1)];
+        }
+        auto contract = [&](auto more_tag) __attribute__((always_inline)) {
+#pragma unroll
+            for (int s = 0; s < kSteps; ++s) {
+                mfma_chunk<T, kCols>(af[s % kAhead], bf, s, acc);
+                if (s + kAhead < kSteps) af[s % kAhead] = src[2 * (s + kAhead)];
+                else if constexpr (decltype(more_tag)::value) af[s % kAhead] = src_next[2 * (s + kAhead - kSteps)];
+                __builtin_amdgcn_sched_barrier(0);       // (the compiler would gather the loads behind the last MFMA)
+            }
+        };
+        if (more) contract(std::true_type{}); else contract(std::false_type{});
+
+        float lse_v[kColsum ? 16 : 1];
+        if constexpr (kColsum) {
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+                const float4 x = *reinterpret_cast<const float4 *>(&s_lse[wave][8 * q4 + 4 * g]);
+                lse_v[4 * q4] = x.x; lse_v[4 * q4 + 1] = x.y; lse_v[4 * q4 + 2] = x.z; lse_v[4 * q4 + 3] = x.w;
+            }
+        }
+        // first streamed row this lane holds (the others follow at acc_row(v)), and the masks of the tiles that need them
+        const int r0 = t * kTileRows + 4 * g;
+        if (t * kTileRows < base0 + kBlock || t * kTileRows + kTileRows > len || (kColsum && t * kTileRows < q_first)) {
+#pragma unroll
+            for (int c = 0; c < kCols; ++c) {
+                const int col = base0 + kTileRows * c + n;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int r = r0 + acc_row(v);
+                    const bool ok = kColsum ? (r >= col && r >= q_first && r < len) : (r <= col);
+                    acc[c][v] = ok ? acc[c][v] : -INFINITY;
+                }
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < kCols; ++c) {
+            if constexpr (kColsum) {
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const float p = fast_exp2(fmaf(acc[c][v], scale, -lse_v[v]));
+                    l[c] += p;
+                    if constexpr (kHist) group_sum[c][v] += p;
+                }
+                if constexpr (kHist) {
+                    if (h == heads - 1) {
+                        const int col = base0 + kTileRows * c + n;
+                        float *hu = hist + (unit * static_cast<size_t>(a.window + 1)) * cap + col;
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) {
+                            const int r = r0 + acc_row(v);
+                            if (r >= col && r >= q_first && r < len)
+                                hu[static_cast<size_t>(r - q_first) * cap] = group_sum[c][v] * inv_group;
+                            group_sum[c][v] = 0.f;
+                        }
+                    }
+                }
+            } else {
+                float top = acc[c][0];
+#pragma unroll
+                for (int v = 1; v < 16; ++v) top = fmaxf(top, acc[c][v]);
+                const float ref = fmaxf(m[c], top * scale);
+                float part = 0.f;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) part += fast_exp2(fmaf(acc[c][v], scale, -ref));
+                l[c] = l[c] * fast_exp2(m[c] - ref) + part;
+                m[c] = ref;
+            }
+        }
+        t = t_next;
+        h = h_next;
+        src = src_next;
+    }
+
+    // merge the lane halves (complementary streamed rows of one column) and the wavefronts
+#pragma unroll
+    for (int c = 0; c < kCols; ++c) {
+        s_part[2 * wave + g][kTileRows * c + n] = l[c];
+        if constexpr (!kColsum) s_max[2 * wave + g][kTileRows * c + n] = m[c];
+    }
+    __syncthreads();
+    if (tid < kBlock && base0 + tid < len) {
+        float sum = 0.f;
+        if constexpr (kColsum) {
+#pragma unroll
+            for (int w = 0; w < 2 * kWaves; ++w) sum += s_part[w][tid];
+            S[unit * cap + base0 + tid] = sum * inv_group;
+        } else {
+            float top = s_max[0][tid];
+#pragma unroll
+            for (int w = 1; w < 2 * kWaves; ++w) top = fmaxf(top, s_max[w][tid]);
+#pragma unroll
+            for (int w = 0; w < 2 * kWaves; ++w) sum += s_part[w][tid] * fast_exp2(s_max[w][tid] - top);
+            lse2[unit * cap + base0 + tid] = top + __log2f(sum);
+        }
+    }
+    if constexpr (kColsum) {
+        // norms of the block's value rows (paper Eq. 4), the arithmetic of every kernel that leaves them
+        const uint4 *Vu = reinterpret_cast<const uint4 *>(V + unit * cap * D);
+        for (int r0 = tid / kChunks; r0 < kBlock; r0 += 64 * kWaves / kChunks) {
+            const int row = base0 + r0;
+            const uint4 raw = row < len ? Vu[static_cast<size_t>(row) * kChunks + tid % kChunks] : make_uint4(0, 0, 0, 0);
+            const float value = row_norm<T, kChunks>(a.norm, raw);
+            if (tid % kChunks == 0 && row < len) nrm[unit * cap + row] = value;
+        }
+    }
+}
+
+template <typename T, int D, int kPass, int kCols, int kWaves>
+void launch_pass(const T *Q, const T *K, const T *V, float *S, float *nrm, float *lse2, float *hist, const BatchMeta &meta,
+                 DirectArgs a, int max_len, hipStream_t st)
+{
+    if (kPass == kRowstat) {                                 // one unit per query head
+        a.n_heads *= a.group;
+        a.n_units *= a.group;
+    }
+    a.n_blocks = (max_len + kTileRows * kCols - 1) / (kTileRows * kCols);
+    hipLaunchKernelGGL((prefill_direct_kernel<T, D, kPass, kCols, kWaves>), dim3(static_cast<unsigned>(a.n_units) * a.n_blocks),
+                       dim3(64 * kWaves), 0, st, Q, K, V, lse2, S, nrm, hist, meta, a);
+}
+
+template <typename T, int D>
+hipError_t launch_direct(const T *Q, const T *K, const T *V, float *S, float *nrm, float *lse2, bool have_lse, float *hist,
+                         const BatchMeta &meta, const DirectArgs &a, int max_len, hipStream_t st)
+{
+#define VATP_PASS(PASS, COLS, WAVES) launch_pass<T, D, PASS, COLS, WAVES>(Q, K, V, S, nrm, lse2, hist, meta, a, max_len, st)
+    const long blocks = (max_len + 63) / 64;
+    if (!have_lse) {
+        if (blocks * a.n_units * a.group >= kWideGrid) VATP_PASS(kRowstat, 2, 4); else VATP_PASS(kRowstat, 1, 8);
+    }
+    if (hist != nullptr) VATP_PASS(kColsumHist, 1, 8);
+    else if (blocks * a.n_units >= kWideGrid) VATP_PASS(kColsumPlain, 2, 4);
+    else VATP_PASS(kColsumPlain, 1, 8);
+#undef VATP_PASS
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_prefill_direct(int dtype, int head_dim, const void *Q, const void *K, const void *V, float *S, float *nrm,
+                                 float *lse2, bool have_lse, int window, float *hist, const BatchMeta &meta,
+                                 const Geometry &g, hipStream_t st)
+{
+    if (g.max_len <= 0) return hipSuccess;
+    DirectArgs a;
+    a.n_heads = g.n_heads;
+    a.n_units = g.batch * g.n_heads;
+    a.cap = g.cap;
+    a.window = window;
+    a.group = g.group;
+    a.norm = g.norm;
+    a.scale_log2 = g.scale_log2;
+#define VATP_PD(T, D)                                                                                           \
+    launch_direct<T, D>(static_cast<const T *>(Q), static_cast<const T *>(K), static_cast<const T *>(V), S, nrm, lse2,  \
+                        have_lse, hist, meta, a, g.max_len, st)
+    if (dtype == VATP_F32 && head_dim == 64) return VATP_PD(float, 64);
+    if (dtype == VATP_F32) return VATP_PD(float, 128);
+    if (head_dim == 64) return VATP_PD(bf16_t, 64);
+    return VATP_PD(bf16_t, 128);
+#undef VATP_PD
+}
+
+}  // namespace vatp

@@ -208,7 +208,7 @@ struct Epilogue {
     }
 };
 
-// Norms of 64 consecutive value rows by one wavefront.  Same arithmetic as l1norm_kernel: D / 8 lanes per
+// Norms of 64 consecutive value rows by one wavefront.  Same arithmetic wherever norms are formed (row_norm): D / 8 lanes per
 // row, 8 elements each in order, then an all-reduce over the row's lanes; all loads of a lane are
 // issued before the first is used.
 template <int D, int kNorm>

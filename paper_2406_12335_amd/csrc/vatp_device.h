@@ -402,18 +402,15 @@ __device__ __forceinline__ float group_weight(const float (&t)[kMaxG], const flo
 }
 
 // ---- host-side launchers, one per source file --------------------------------------
-hipError_t launch_l1norm(int dtype, int head_dim, const void *V, float *nrm,
-                         const BatchMeta &meta, const Geometry &g, hipStream_t st);
-
 // window >= 0: history-window scores (Eq. 3), the window's attention rows go to hist (may be NULL)
-hipError_t launch_prefill_generic(int dtype, int head_dim, const void *Q, const void *K,
-                                  float *S, float *lse2, bool have_lse, int window, float *hist,
-                                  const BatchMeta &meta, const Geometry &g, hipStream_t st);
+// (the prompt passes also write the value-row norms)
+hipError_t launch_prefill_direct(int dtype, int head_dim, const void *Q, const void *K, const void *V, float *S, float *nrm,
+                                 float *lse2, bool have_lse, int window, float *hist, const BatchMeta &meta,
+                                 const Geometry &g, hipStream_t st);
 
 hipError_t launch_lse_to_base2(const float *lse, float *lse2, const BatchMeta &meta, const Geometry &g,
                                hipStream_t st);
 
-// (the matrix-core passes also write the value-row norms: no separate launch_l1norm)
 // (s_part: room for group * units * cap floats of partial column sums when query heads are grouped, else unused)
 hipError_t launch_prefill_mfma(int head_dim, const void *Q, const void *K, const void *V, float *S, float *nrm, float *lse2,
                                float *s_part, bool have_lse, const BatchMeta &meta, const Geometry &g, hipStream_t st);

@@ -52,3 +52,11 @@ def _check_scores(dev, dtype, d, g, H, lens, window, units, seed):
 def test_heads_of_64_on_a_full_grid(gpu_device, g):
     lens = [770, 1, 63, 64, 65, 255, 256, 257]
     _check_scores(gpu_device, "bf16", 64, g, 32, lens, None, [(b, 31 if b % 2 else 0) for b in range(len(lens))], 201 + g)
+
+
+# fp32: 32-column workgroups on a small grid, 64-column ones from 1024 blocks of 64 rows on (16 heads x 8 sequences x 9)
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H,g,window", [(2, 1, None), (16, 1, None), (16, 2, None), (2, 3, 40), (2, 1, 0), (16, 1, 100)])
+def test_fp32_scores(gpu_device, d, H, g, window):
+    lens = [513, 1, 31, 32, 33, 64, 65, 255]
+    _check_scores(gpu_device, "fp32", d, g, H, lens, window, [(b, H - 1 if b % 2 else 0) for b in range(len(lens))], 211 + g)
