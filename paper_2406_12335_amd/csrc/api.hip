@@ -228,18 +228,22 @@ vatp_status prefill_score_impl(vatp_ctx *ctx, const vatp_params *p, const void *
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     float *lse2 = static_cast<float *>(ws);
     if (have_lse && launch_lse_to_base2(lse, lse2, pr.meta, pr.g, stream) != hipSuccess) return VATP_E_DEVICE;
-    // bf16 streams through LDS; fp32, and a history window too large for 32-bit offsets, straight into registers
-    const bool mfma = p->dtype == VATP_BF16;
-    hipError_t e;
-    if (mfma && window < 0) {                 // (all prompt passes write the norms as well)
-        float *s_part = pr.g.group > 1 ? lse2 + align_up(units * pr.g.group * p->cap * sizeof(float)) / sizeof(float) : nullptr;
-        e = launch_prefill_mfma(p->head_dim, Q, K, V, S, nrm, lse2, s_part, have_lse, pr.meta, pr.g, stream);
-    } else if (mfma && prefill_mfma_window_fits(window, p->cap, static_cast<int>(units * pr.g.group))) {
-        e = launch_prefill_mfma_window(p->head_dim, Q, K, V, S, nrm, lse2,
-                                       lse2 + align_up(units * pr.g.group * p->cap * sizeof(float)) / sizeof(float), window,
-                                       hist, pr.meta, pr.g, stream);
+    // what follows lse2 in the workspace: partial row statistics of a window, or room for partial column sums of a group
+    float *parts = lse2 + align_up(units * pr.g.group * p->cap * sizeof(float)) / sizeof(float);
+    hipError_t e = hipSuccess;
+    if (window >= 0 && p->dtype == VATP_BF16 && prefill_mfma_window_fits(window, p->cap, static_cast<int>(units * pr.g.group))) {
+        e = launch_prefill_mfma_window(p->head_dim, Q, K, V, S, nrm, lse2, parts, window, hist, pr.meta, pr.g, stream);
     } else {
-        e = launch_prefill_direct(p->dtype, p->head_dim, Q, K, V, S, nrm, lse2, have_lse, window, hist, pr.meta, pr.g, stream);
+        // each pass on the staged kernels where its grid fills the chip with them, else on the direct ones
+        float *s_part = pr.g.group > 1 && window < 0 ? parts : nullptr;
+        for (int pass : {kPassRowstat, kPassColsum}) {          // (the column sums need the row statistics)
+            if (e != hipSuccess || (have_lse && pass == kPassRowstat)) continue;
+            if (window < 0 && p->dtype == VATP_BF16 && prefill_mfma_fills(p->head_dim, pass, pr.g))
+                e = launch_prefill_mfma(p->head_dim, Q, K, V, S, nrm, lse2, s_part, pass, pr.meta, pr.g, stream);
+            else
+                e = launch_prefill_direct(p->dtype, p->head_dim, Q, K, V, S, nrm, lse2, s_part, pass, window, hist, pr.meta, pr.g,
+                                          stream);
+        }
     }
     if (e != hipSuccess) return VATP_E_DEVICE;
     return VATP_OK;

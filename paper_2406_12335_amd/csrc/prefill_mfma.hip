@@ -801,12 +801,42 @@ __global__ __launch_bounds__(256) void merge_group_partials_kernel(const float *
     S[unit * cap + i] = s * inv_group;
 }
 
+}  // namespace
+
+hipError_t launch_merge_group_partials(const float *s_part, float *S, int splits, const BatchMeta &meta, const Geometry &g,
+                                       hipStream_t st)
+{
+    const int kv_units = g.batch * g.n_heads;
+    hipLaunchKernelGGL(merge_group_partials_kernel, dim3((g.max_len + 255) / 256, kv_units), dim3(256), 0, st, s_part, S, meta,
+                       g.n_heads, kv_units, g.cap, splits, 1.f / static_cast<float>(g.group));
+    return hipGetLastError();
+}
+
+namespace {
+
+inline int block_pairs(const Geometry &g) { return ((g.max_len + kBlockCols - 1) / kBlockCols + 1) / 2; }
+
+// Grouped column sums: a K/V head's query heads are walked by one workgroup (no partial sums) when that
+// still fills the chip; otherwise they are dealt out to `splits` workgroups -- the smallest divisor of
+// the group size that does -- whose partial sums a small kernel adds.
+inline int colsum_splits(const Geometry &g)
+{
+    int splits = 1;
+    for (int s = 1; s <= g.group; ++s)
+        if (g.group % s == 0) {
+            splits = s;
+            if (8u * block_pairs(g) * ((g.batch * g.n_heads * s + 7) / 8) >= 2u * kComputeUnits) break;
+        }
+    return splits;
+}
+
 template <int D>
-hipError_t launch_full(const void *Q, const void *K, const void *V, float *S, float *nrm, float *lse2, float *s_part, bool have_lse, const BatchMeta &meta, const Geometry &g, hipStream_t st)
+hipError_t launch_full(const void *Q, const void *K, const void *V, float *S, float *nrm, float *lse2, float *s_part, int passes,
+                       const BatchMeta &meta, const Geometry &g, hipStream_t st)
 {
     if (g.max_len <= 0) return hipSuccess;
     const int n_blocks = (g.max_len + kBlockCols - 1) / kBlockCols;
-    const int n_pairs = (n_blocks + 1) / 2;
+    const int n_pairs = block_pairs(g);
     const bf16_t *q = static_cast<const bf16_t *>(Q), *k = static_cast<const bf16_t *>(K);
     const bf16_t *v = static_cast<const bf16_t *>(V);
     // One unit per query head in the row-statistics pass, one per K/V head in the column-sum pass (the
@@ -815,7 +845,7 @@ hipError_t launch_full(const void *Q, const void *K, const void *V, float *S, fl
     // resident, else 8-wavefront workgroups.
     const int kv_units = g.batch * g.n_heads, q_units = kv_units * g.group;
     const unsigned wg_q = 8u * n_pairs * ((q_units + 7) / 8);
-    if (!have_lse) {    // row statistics are computed here unless the caller supplied them
+    if (passes & kPassRowstat) {
         if (wg_q >= 2u * kComputeUnits)
             hipLaunchKernelGGL((prefill_mfma_kernel<D, false, 1>), dim3(wg_q), dim3(256), 0, st, q, k, lse2, S, meta,
                                g.n_heads * g.group, q_units, g.cap, n_blocks, g.scale_log2, WindowPass{}, nullptr,
@@ -825,16 +855,8 @@ hipError_t launch_full(const void *Q, const void *K, const void *V, float *S, fl
                                g.n_heads * g.group, q_units, g.cap, n_blocks, g.scale_log2, WindowPass{}, nullptr,
                                nullptr, 0, g.group, 1);
     }
-    // Grouped column sums: a K/V head's query heads are walked by one workgroup (no partial sums) when that
-    // still fills the chip; otherwise they are dealt out to `splits` workgroups -- the smallest divisor of
-    // the group size that does -- whose partial sums a small kernel adds.
-    int splits = 1;
-    if (g.group > 1 && s_part != nullptr)
-        for (int s = 1; s <= g.group; ++s)
-            if (g.group % s == 0) {
-                splits = s;
-                if (8u * n_pairs * ((kv_units * s + 7) / 8) >= 2u * kComputeUnits) break;
-            }
+    if (!(passes & kPassColsum)) return hipGetLastError();
+    const int splits = s_part != nullptr ? colsum_splits(g) : 1;
     const int slots = kv_units * splits;
     const unsigned wg_kv = 8u * n_pairs * ((slots + 7) / 8);
     float *dst = splits > 1 ? s_part : S;
@@ -848,19 +870,29 @@ hipError_t launch_full(const void *Q, const void *K, const void *V, float *S, fl
         if (g.group > 1) VATP_COLSUM(2, true); else VATP_COLSUM(2, false);
     }
 #undef VATP_COLSUM
-    if (splits > 1)
-        hipLaunchKernelGGL(merge_group_partials_kernel, dim3((g.max_len + 255) / 256, kv_units), dim3(256), 0, st, s_part, S,
-                           meta, g.n_heads, kv_units, g.cap, splits, 1.f / static_cast<float>(g.group));
+    if (splits > 1) return launch_merge_group_partials(s_part, S, splits, meta, g, st);
     return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_prefill_mfma(int head_dim, const void *Q, const void *K, const void *V, float *S, float *nrm, float *lse2,
-                               float *s_part, bool have_lse, const BatchMeta &meta, const Geometry &g, hipStream_t st)
+// A launch whose eight-wavefront workgroups cover fewer compute units takes as long as a full one (a workgroup's two
+// blocks are one chain), and between one and two of them per compute unit as long as two.  The direct kernels spread
+// the same work over 32- and 64-row workgroups at 0.75 (64 elements: 0.94) of the rate.  Measured, both passes, rows of
+// 128, staged / direct: 32 heads x 2048 rows (128 workgroups) 90 / 73 us, 32 x 4096 (256) 160 / 212, 40 x 4096 (320)
+// 295 / 265, 128 x 1024 (256) 72 / 94; rows of 64: 32 x 2048 67 / 46, 32 x 4096 111 / 122.
+bool prefill_mfma_fills(int head_dim, int pass, const Geometry &g)
 {
-    return head_dim == 64 ? launch_full<64>(Q, K, V, S, nrm, lse2, s_part, have_lse, meta, g, st)
-                          : launch_full<128>(Q, K, V, S, nrm, lse2, s_part, have_lse, meta, g, st);
+    const long units = static_cast<long>(g.batch) * g.n_heads * (pass == kPassRowstat ? g.group : colsum_splits(g));
+    const long jobs = units * block_pairs(g), even = head_dim == 64 ? 240 : 192;
+    return jobs <= kComputeUnits ? jobs >= even : jobs >= 2 * even;
+}
+
+hipError_t launch_prefill_mfma(int head_dim, const void *Q, const void *K, const void *V, float *S, float *nrm, float *lse2,
+                               float *s_part, int passes, const BatchMeta &meta, const Geometry &g, hipStream_t st)
+{
+    return head_dim == 64 ? launch_full<64>(Q, K, V, S, nrm, lse2, s_part, passes, meta, g, st)
+                          : launch_full<128>(Q, K, V, S, nrm, lse2, s_part, passes, meta, g, st);
 }
 
 }  // namespace vatp

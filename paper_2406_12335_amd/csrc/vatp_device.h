@@ -403,17 +403,25 @@ __device__ __forceinline__ float group_weight(const float (&t)[kMaxG], const flo
 
 // ---- host-side launchers, one per source file --------------------------------------
 // window >= 0: history-window scores (Eq. 3), the window's attention rows go to hist (may be NULL)
-// (the prompt passes also write the value-row norms)
+// The two passes of the prompt scores (either may run on the staged or on the direct kernels; both leave the row
+// statistics in lse2, and the column sums come with the value-row norms).
+enum { kPassRowstat = 1, kPassColsum = 2 };
+
 hipError_t launch_prefill_direct(int dtype, int head_dim, const void *Q, const void *K, const void *V, float *S, float *nrm,
-                                 float *lse2, bool have_lse, int window, float *hist, const BatchMeta &meta,
-                                 const Geometry &g, hipStream_t st);
+                                 float *lse2, float *s_part, int pass, int window, float *hist,
+                                 const BatchMeta &meta, const Geometry &g, hipStream_t st);
+// S = (1/g) * sum over `splits` of the partial column sums s_part [splits, K/V heads, cap] of a group's query heads
+hipError_t launch_merge_group_partials(const float *s_part, float *S, int splits, const BatchMeta &meta, const Geometry &g,
+                                       hipStream_t st);
 
 hipError_t launch_lse_to_base2(const float *lse, float *lse2, const BatchMeta &meta, const Geometry &g,
                                hipStream_t st);
 
 // (s_part: room for group * units * cap floats of partial column sums when query heads are grouped, else unused)
 hipError_t launch_prefill_mfma(int head_dim, const void *Q, const void *K, const void *V, float *S, float *nrm, float *lse2,
-                               float *s_part, bool have_lse, const BatchMeta &meta, const Geometry &g, hipStream_t st);
+                               float *s_part, int pass, const BatchMeta &meta, const Geometry &g, hipStream_t st);
+// whether the grid of a pass is one the staged kernels run well
+bool prefill_mfma_fills(int head_dim, int pass, const Geometry &g);
 
 // history-window prompt scores on the matrix cores (bf16); lse_part: workspace of
 // prefill_window_splits(cap) * units * cap floats; usable if prefill_mfma_window_fits(window, cap, units)

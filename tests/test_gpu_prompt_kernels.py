@@ -60,3 +60,12 @@ def test_heads_of_64_on_a_full_grid(gpu_device, g):
 def test_fp32_scores(gpu_device, d, H, g, window):
     lens = [513, 1, 31, 32, 33, 64, 65, 255]
     _check_scores(gpu_device, "fp32", d, g, H, lens, window, [(b, H - 1 if b % 2 else 0) for b in range(len(lens))], 211 + g)
+
+
+# bf16 grids that do not fill the chip: 32-column workgroups, 64-column ones from 512 blocks of 64 rows on (16 heads x
+# 8 sequences x 5), groups with their query heads dealt out to several workgroups (one K/V head) or not
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H,g", [(2, 1), (16, 1), (1, 4), (2, 3), (9, 2)])
+def test_bf16_scores_on_a_small_grid(gpu_device, d, H, g):
+    lens = [319, 1, 31, 32, 33, 64, 65, 255]
+    _check_scores(gpu_device, "bf16", d, g, H, lens, None, [(b, H - 1 if b % 2 else 0) for b in range(len(lens))], 221 + g)
