@@ -13,7 +13,7 @@
 //           the chunk's unnormalised share of the attention output (Eq. 1) in the workspace.
 //   finish  one row per thread: every wavefront merges the unit's few chunk statistics into
 //           log2 sum 2^t and applies S += 2^(t - lse2); 12 bytes per row, a tiny launch
-//           ordered after the first by the stream.
+//           ordered after the first by the stream.  Further workgroups merge the attention outputs.
 #include "vatp_device.h"
 
 namespace vatp {
@@ -357,18 +357,26 @@ __global__ __launch_bounds__(256) void decode_logits_group_kernel(
     }
 }
 
-template <int kMaxG>
+// Workgroups of one unit: row_blocks of 256 rows each, then (with an output) one per query head of the group.
+template <int kMaxG, int D>
 __global__ __launch_bounds__(256) void decode_finish_kernel(float *__restrict__ S,
                                                             const float *__restrict__ ws_logit,
                                                             const float2 *__restrict__ ws_part,
                                                             const float *__restrict__ ws_out,
-                                                            float *__restrict__ out, int head_dim,
-                                                            BatchMeta meta, int n_heads, int cap,
-                                                            int chunks_alloc, int group)
+                                                            float *__restrict__ out, BatchMeta meta, int n_heads,
+                                                            int cap, int chunks_alloc, int group, int row_blocks)
 {
     const size_t unit = blockIdx.x;
     const int b = static_cast<int>(unit / n_heads);
     const int n0 = meta.len[b], n = n0 + 1;
+    const int n_chunks = (n + kDecodeChunk - 1) / kDecodeChunk;
+    const float2 *part = ws_part + unit * group * chunks_alloc;
+    if (static_cast<int>(blockIdx.y) >= row_blocks) {
+        const size_t i = blockIdx.y - row_blocks;
+        merge_head_output<D>(out + (unit * group + i) * D, ws_out + (unit * group + i) * chunks_alloc * D, part + i * chunks_alloc,
+                             n_chunks, 256);
+        return;
+    }
     const int row0 = static_cast<int>(blockIdx.y) * 256;
     const int r = row0 + static_cast<int>(threadIdx.x);          // one row per thread
     if (row0 >= n) return;
@@ -376,15 +384,9 @@ __global__ __launch_bounds__(256) void decode_finish_kernel(float *__restrict__ 
     load_group_logits<kMaxG>(logit, ws_logit + unit * group * cap, cap, group, r, r < n);
     if (r < n && r != n0) s_old = S[unit * cap + r];
     // the softmax denominators from the unit's chunk statistics (per wavefront, one round trip)
-    const int n_chunks = (n + kDecodeChunk - 1) / kDecodeChunk;
-    const float2 *part = ws_part + unit * group * chunks_alloc;
     float lse2[kMaxG];
     merge_group_stats<kMaxG>(part, chunks_alloc, group, n_chunks, lse2);
     if (r < n) S[unit * cap + r] = s_old + group_weight<kMaxG>(logit, lse2, group);
-    // attention output of the new token, per query head: the chunks' partial sums, rescaled to the common maximum
-    if (out && blockIdx.y == 0)
-        merge_group_outputs(out + unit * group * head_dim, ws_out + unit * group * chunks_alloc * head_dim, part, chunks_alloc,
-                            n_chunks, group, head_dim, 256);
 }
 
 }  // namespace
@@ -426,16 +428,23 @@ hipError_t launch_decode(int dtype, int head_dim, const void *q, const void *k, 
 #undef VATP_DEC
 #undef VATP_DEC_S
     if (finish) {   // (the fused decode-and-evict step has its own second launch)
-        const dim3 fgrid(units, (g.max_len + 255) / 256);
-#define VATP_FIN(G)                                                                                               \
-    hipLaunchKernelGGL(decode_finish_kernel<G>, fgrid, block, 0, st, S, ws_logit, ws_part, ws_out, out, head_dim, meta, \
-                       g.n_heads, g.cap, chunks_alloc, g.group)
+        const int row_blocks = (g.max_len + 255) / 256;
+        const dim3 fgrid(units, row_blocks + (out ? g.group : 0));
+#define VATP_FIN_D(G, D)                                                                                          \
+    hipLaunchKernelGGL((decode_finish_kernel<G, D>), fgrid, block, 0, st, S, ws_logit, ws_part, ws_out, out, meta, g.n_heads, \
+                       g.cap, chunks_alloc, g.group, row_blocks)
+#define VATP_FIN(G)                                \
+    do {                                           \
+        if (head_dim == 64) VATP_FIN_D(G, 64);     \
+        else VATP_FIN_D(G, 128);                   \
+    } while (0)
         if (g.group > 8) VATP_FIN(VATP_MAX_GROUP);
         else if (g.group > 4) VATP_FIN(8);
         else if (g.group > 2) VATP_FIN(4);
         else if (g.group > 1) VATP_FIN(2);
         else VATP_FIN(1);
 #undef VATP_FIN
+#undef VATP_FIN_D
     }
     return hipGetLastError();
 }

@@ -11,7 +11,8 @@
 // `recent` rows move per step instead of the whole cache; the scores themselves change in
 // every row and are rewritten in full.
 //
-// Grid: (units, G).  Each of a head's G workgroups repeats the cheap part (12 bytes per row
+// Grid: (units, G), and with an attention output one more workgroup per query head, which merges the chunks' shares of
+// it (vatp_device.h).  Each of a head's G workgroups repeats the cheap part (12 bytes per row
 // from L2: logit, S, nrm) to learn the evicted row by itself, then takes a 1/G share of the
 // stores, so the launch needs no exchange between workgroups and no second pass.
 //
@@ -33,7 +34,7 @@ __global__ __launch_bounds__(kThreads) void decode_prune_kernel(
     int32_t *__restrict__ pos_out, int32_t *__restrict__ kept_idx, const int32_t *__restrict__ synced_in,
     int32_t *__restrict__ synced_out, const float *__restrict__ ws_logit, const float2 *__restrict__ ws_part,
     const float *__restrict__ ws_out, float *__restrict__ out, WindowArgs win, BatchMeta meta, int n_heads,
-    int cap, int cap_out, int chunks_alloc, int n_sink, int recent, int group, int stream)
+    int cap, int cap_out, int chunks_alloc, int n_sink, int recent, int group, int stream, int G)
 {
     constexpr int kE = Elt<T>::kPer16B;
     constexpr int kLanesPerRow = D / kE;
@@ -45,11 +46,19 @@ __global__ __launch_bounds__(kThreads) void decode_prune_kernel(
     // dimension a head's G workgroups meet in one XCD's L2 (unit count a multiple of 8), where the rows
     // they all scan are fetched once
     const size_t unit = blockIdx.x;
-    const int g = blockIdx.y, G = gridDim.y;
+    const int g = blockIdx.y;
     const int b = static_cast<int>(unit / n_heads);
     const int n0 = meta.len[b], n = n0 + 1, B = meta.aux[b];
     const int n_keep = n < B ? n : B;
     const int tid = threadIdx.x;
+    const int n_chunks = (n + kDecodeChunk - 1) / kDecodeChunk;
+    const float2 *part = ws_part + unit * group * chunks_alloc;
+    if (g >= G) {
+        const size_t i = g - G;
+        merge_head_output<D>(out + (unit * group + i) * D, ws_out + (unit * group + i) * chunks_alloc * D, part + i * chunks_alloc,
+                             n_chunks, kThreads);
+        return;
+    }
     const float *Su = S + unit * cap;
     const float *Nu = nrm + unit * cap;
     const float *Lu = ws_logit + unit * group * cap;       // the group's logits: query head i at Lu + i * cap
@@ -85,8 +94,6 @@ __global__ __launch_bounds__(kThreads) void decode_prune_kernel(
     }
 
     // log2 of the softmax denominator of every query head of the group from the chunk statistics
-    const int n_chunks = (n + kDecodeChunk - 1) / kDecodeChunk;
-    const float2 *part = ws_part + unit * group * chunks_alloc;
     float lse2[kMaxG];
     merge_group_stats<kMaxG>(part, chunks_alloc, group, n_chunks, lse2);
 
@@ -220,11 +227,6 @@ __global__ __launch_bounds__(kThreads) void decode_prune_kernel(
             }
         }
     }
-
-    // attention output of the new token (optional), per query head: the chunks' partial sums on a common maximum
-    if (out && g == 0)
-        merge_group_outputs(out + unit * group * D, ws_out + unit * group * chunks_alloc * D, part, chunks_alloc, n_chunks,
-                            group, D, kThreads);
 }
 
 // The whole step in one launch, one workgroup of 16 wavefronts per head: logits of the new query
@@ -494,12 +496,12 @@ hipError_t launch_decode_prune(int dtype, int head_dim, const void *K, const voi
     // (ragged16) 49.8 us with one, 51.2 with two, 56 with four; 64 heads x 4 query heads 28 us with 2 to 8, 35 with 16.
     unsigned G = 512u / (units * static_cast<unsigned>(g.group));
     G = G < 1u ? 1u : (G > 16u ? 16u : G);
-    dim3 grid(units, G), block(kThreads);
-#define VATP_DPG(T, D, G)                                                                                      \
-    hipLaunchKernelGGL((decode_prune_kernel<T, D, G>), grid, block, 0, st, static_cast<const T *>(K),            \
+    dim3 grid(units, G + (out ? static_cast<unsigned>(g.group) : 0u)), block(kThreads);
+#define VATP_DPG(T, D, MAXG)                                                                                   \
+    hipLaunchKernelGGL((decode_prune_kernel<T, D, MAXG>), grid, block, 0, st, static_cast<const T *>(K),            \
                        static_cast<const T *>(V), S, nrm, pos, static_cast<T *>(K_out), static_cast<T *>(V_out), \
                        S_out, nrm_out, pos_out, kept_idx, synced_in, synced_out, ws_logit, ws_part, ws_out, out, \
-                       win, meta, g.n_heads, g.cap, g.cap_out, chunks_alloc, g.n_sink, g.recent, g.group, g.stream)
+                       win, meta, g.n_heads, g.cap, g.cap_out, chunks_alloc, g.n_sink, g.recent, g.group, g.stream, static_cast<int>(G))
     // (instantiated for group sizes up to 2, 4, 8 and 16: the smallest that fits)
 #define VATP_DP(T, D)                                      \
     do {                                                   \
