@@ -67,10 +67,6 @@ __device__ __forceinline__ void mfma_chunk(const uint4 &a, const uint4 (&bf)[kCo
     }
 }
 
-// LDS slot of chunk c of row r of a staged tile: 16 consecutive rows that read one chunk index hit 16 different 16-byte
-// slots of the 64 banks
-template <int kChunks> __device__ __forceinline__ int tile_slot(int r, int c) { return kChunks >= 16 ? c ^ (r & 15) : c ^ ((r >> 1) & 7); }
-
 enum { kRowstat, kColsumPlain, kColsumHist };      // passes
 
 struct DirectArgs {

@@ -22,7 +22,7 @@
 // s_barrier per stage.  The copies are issued from inline assembly, so their completion is
 // tracked by hand: a wavefront waits until at most the copies of the younger stages are
 // outstanding (s_waitcnt vmcnt) before the barrier that publishes a stage.  The 16-byte chunks
-// of an LDS row are permuted by the row (Rows::slot), which the copy realises on the source side
+// of an LDS row are permuted by the row (tile_slot), which the copy realises on the source side
 // (the lane that fills LDS chunk p of row r fetches the global chunk that belongs there).
 //
 // The exponentials cost more vector-ALU time than the contraction costs matrix time, so the
@@ -92,9 +92,6 @@ struct Rows {
     static constexpr int kCopyRows = 64 / kChunks;      // rows per copy instruction
     static constexpr int kCopies = 16 / kCopyRows;      // copy instructions per wavefront and stage
     static constexpr int kPieces = 16 / (2 * kSteps);   // sixteenths of the pending pair's work after every MFMA
-    // LDS slot of chunk c of row r: 16 consecutive rows that read one chunk index hit 16 different 16-byte slots of
-    // the 64 banks (two rows of 64 elements share a span of the banks, so there the row pair is what is permuted by)
-    __device__ static __forceinline__ int slot(int r, int c) { return D == 128 ? c ^ (r & 15) : c ^ ((r >> 1) & 7); }
 };
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -305,7 +302,7 @@ __global__ __launch_bounds__(256 * kHalves) void prefill_mfma_kernel(const bf16_
 #pragma unroll
         for (int i = 0; i < R::kCopies; ++i) {
             const int r = 16 * wave + R::kCopyRows * i + lane / kChunksPerRow;      // row inside the stage
-            const int c = R::slot(r, lane % kChunksPerRow);          // global chunk for this lane's LDS chunk
+            const int c = tile_slot<kChunksPerRow>(r, lane % kChunksPerRow);          // global chunk for this lane's LDS chunk
             const int grow = min(t * kSlotRows + r, len - 1);
             const unsigned voff = static_cast<unsigned>(grow) * (kD * 2) + c * 16;
             const unsigned m0v = lds_stage0 + slot * kSlotBytes + (16 * wave + R::kCopyRows * i) * (kD * 2);
@@ -475,7 +472,7 @@ __global__ __launch_bounds__(256 * kHalves) void prefill_mfma_kernel(const bf16_
                         bf16x8 a[kSteps];
 #pragma unroll
                         for (int s = 0; s < kSteps; ++s)
-                            a[s] = as_bf16x8(stage[slot][ar * kChunksPerRow + R::slot(ar, s + kSteps * g)]);
+                            a[s] = as_bf16x8(stage[slot][ar * kChunksPerRow + tile_slot<kChunksPerRow>(ar, s + kSteps * g)]);
                         if (kColsum) {
 #pragma unroll
                             for (int q4 = 0; q4 < 4; ++q4) {

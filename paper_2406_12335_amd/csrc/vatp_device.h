@@ -284,9 +284,10 @@ typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16;
 __device__ __forceinline__ bf16x8 as_bf16x8(const uint4 &u) { return __builtin_bit_cast(bf16x8, u); }
 __device__ __forceinline__ constexpr int acc_row(int v) { return 8 * (v / 4) + (v % 4); }
-// rows of 256 bytes staged in LDS: 16-byte chunk c of row r sits at chunk c ^ (r & 15), so that the 16 lanes
-// that read one chunk index of 16 consecutive rows hit 16 different bank groups
-__device__ __forceinline__ int swizzled_chunk(int row, int c) { return c ^ (row & 15); }
+// Rows of kChunks 16-byte chunks staged in LDS: where chunk c of row r sits, so that 16 consecutive rows that read one chunk
+// index hit 16 different 16-byte slots of the 64 banks (two 128-byte rows share a span of the banks: there the row pair
+// is what is permuted by).
+template <int kChunks> __device__ __forceinline__ int tile_slot(int r, int c) { return kChunks >= 16 ? c ^ (r & 15) : c ^ ((r >> 1) & 7); }
 
 // Softmax denominator of one decode step from the per-chunk statistics (max_c, sum_c of
 // 2^(t - max_c)) that the logits launch left behind: M = max_c max_c and
