@@ -91,7 +91,9 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_direct_kernel(const T 
     constexpr int kBlock = kTileRows * kCols;                         // stationary rows of the workgroup
     constexpr int kRowBytes = D * static_cast<int>(sizeof(T)), kTileBytes = kTileRows * kRowBytes;
     constexpr int kLoads = kTileBytes / 1024;                         // 16-byte loads per lane and tile
-    __shared__ uint4 s_tile[kStaged ? kWaves : 1][kStaged ? kTileRows * kChunks : 1];
+    constexpr int kThreads = 64 * kWaves, kPieces = kBlock * kChunks, kShare = (kPieces + kThreads - 1) / kThreads;
+    __shared__ uint4 s_tile[kStaged ? kWaves : kCols][kTileRows * kChunks];      // the stationary rows, then streamed tiles
+    static_assert(sizeof(s_tile) >= kPieces * sizeof(uint4), "the stationary rows pass through s_tile");
     __shared__ float s_part[2 * kWaves][kBlock];
     __shared__ float s_max[kColsum ? 1 : 2 * kWaves][kBlock];
     __shared__ __attribute__((aligned(16))) float s_lse[kColsum ? kWaves : 1][kTileRows];
@@ -143,14 +145,18 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_direct_kernel(const T 
         return *reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(head) + off);
     };
 
-    // The stationary rows are waited for here, with the first streamed ones already requested behind them: in the loop
-    // nothing but a tile's own chunks is pending.  (Rows past the end read the last one: their columns are not stored.)
-    uint4 bf[kCols][kSteps], af[kStaged ? kLoads : kAhead];
+    // The stationary rows (and the value rows of the block) are read in order, every row once per workgroup, and reach the
+    // wavefronts' operand layout through LDS, with the first streamed rows requested behind them: in the loop nothing but a
+    // tile's own chunks is pending.  (Straight from memory every wavefront fetched all of them 16 bytes of a row per lane, 64
+    // accesses to the vector cache per load: 4 heads of 64 x 256 fp32 rows 13.4 -> 11.9 us.  Rows past the end read the last one:
+    // their columns are not stored.)
+    uint4 own[kShare], val[kColsum ? kShare : 1], bf[kCols][kSteps], af[kStaged ? kLoads : kAhead];
+    const bool norms = kColsum && split == 0;
 #pragma unroll
-    for (int c = 0; c < kCols; ++c)
-#pragma unroll
-        for (int s = 0; s < kSteps; ++s)
-            bf[c][s] = stat[static_cast<size_t>(min(base0 + kTileRows * c + n, len - 1)) * kChunks + 2 * s + g];
+    for (int i = 0; i < kShare; ++i) {
+        const int p = min(tid + kThreads * i, kPieces - 1);
+        own[i] = stat[static_cast<size_t>(min(base0 + p / kChunks, len - 1)) * kChunks + p % kChunks];
+    }
     float lse_next = 0.f;
     int t = 0, h = 0;
     const uint4 *src = strm;
@@ -161,11 +167,44 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_direct_kernel(const T 
 #pragma unroll
         for (int s = 0; s < (kStaged ? kLoads : kAhead); ++s) af[s] = kStaged ? piece(src, t, s) : src[2 * s];
     }
+    if constexpr (kColsum) {
+        if (norms) {
+            const uint4 *Vu = reinterpret_cast<const uint4 *>(V + unit * cap * D);
+#pragma unroll
+            for (int i = 0; i < kShare; ++i) {
+                const int p = min(tid + kThreads * i, kPieces - 1);
+                val[i] = Vu[static_cast<size_t>(min(base0 + p / kChunks, len - 1)) * kChunks + p % kChunks];
+            }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < kShare; ++i) {
+        const int p = tid + kThreads * i, r = p / kChunks;
+        if (kPieces % kThreads == 0 || p < kPieces) (&s_tile[0][0])[r * kChunks + tile_slot<kChunks>(r, p % kChunks)] = own[i];
+    }
+    lds_barrier();
+#pragma unroll
+    for (int c = 0; c < kCols; ++c)
+#pragma unroll
+        for (int s = 0; s < kSteps; ++s)
+            bf[c][s] = (&s_tile[0][0])[(kTileRows * c + n) * kChunks + tile_slot<kChunks>(n, 2 * s + g)];
 #pragma unroll
     for (int c = 0; c < kCols; ++c)
 #pragma unroll
         for (int s = 0; s < kSteps; ++s)
             asm volatile("" : "+v"(bf[c][s].x), "+v"(bf[c][s].y), "+v"(bf[c][s].z), "+v"(bf[c][s].w));
+    lds_barrier();                               // (the wavefronts' tiles overwrite the stationary rows)
+    if constexpr (kColsum) {
+        // norms of the block's value rows (paper Eq. 4), the arithmetic of every kernel that leaves them
+        if (norms) {
+#pragma unroll
+            for (int i = 0; i < kShare; ++i) {
+                const int p = tid + kThreads * i, row = base0 + p / kChunks;
+                const float value = row_norm<T, kChunks>(a.norm, val[i]);
+                if (p < kPieces && p % kChunks == 0 && row < len) nrm[unit * cap + row] = value;
+            }
+        }
+    }
 
     const float scale = a.scale_log2;
     const float inv_group = 1.f / static_cast<float>(group);      // (exactly 1 for one head)
@@ -307,16 +346,6 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_direct_kernel(const T 
 #pragma unroll
             for (int w = 0; w < 2 * kWaves; ++w) sum += s_part[w][tid] * fast_exp2(s_max[w][tid] - top);
             lse2[unit * cap + base0 + tid] = top + __log2f(sum);
-        }
-    }
-    if (kColsum && split == 0) {
-        // norms of the block's value rows (paper Eq. 4), the arithmetic of every kernel that leaves them
-        const uint4 *Vu = reinterpret_cast<const uint4 *>(V + unit * cap * D);
-        for (int r0 = tid / kChunks; r0 < kBlock; r0 += 64 * kWaves / kChunks) {
-            const int row = base0 + r0;
-            const uint4 raw = row < len ? Vu[static_cast<size_t>(row) * kChunks + tid % kChunks] : make_uint4(0, 0, 0, 0);
-            const float value = row_norm<T, kChunks>(a.norm, raw);
-            if (tid % kChunks == 0 && row < len) nrm[unit * cap + row] = value;
         }
     }
 }
