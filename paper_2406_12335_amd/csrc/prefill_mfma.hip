@@ -54,7 +54,7 @@
 // stage's attention rows, already averaged, once.
 //
 // The contraction index (head dimension) may be permuted freely as long as both operands
-// agree: lane half g takes the 16-byte chunk  s + (D/16) g  of a row for MFMA step s.
+// agree: lane half g takes the 16-byte chunk  2s + g  of a row for MFMA step s.
 #include <type_traits>
 
 #include "vatp_device.h"
@@ -371,6 +371,41 @@ __global__ __launch_bounds__(256 * kHalves) void prefill_mfma_kernel(const bf16_
                 if (t_begin + k <= t_end) copy_stage(t_begin + k, k);
         }
 
+        // stationary operand: 2 column blocks x kSteps MFMA steps, 8 bf16 per lane each.  Read in order, half of the
+        // chunks of 32 rows (one column block) at a time, and brought into the operand's layout by way of this wavefront's
+        // quarter of the ring's last slot, which no copy fills before the first stage has been published; LDS operations
+        // of a wavefront are in order, so without a barrier.  (Straight from memory a load touched 64 rows, 64 accesses
+        // to the vector cache.  Measured, both passes: 32 heads x 4096 rows 161.5 -> 158.2 us, 64 heads of 64 x 2048 68.9 ->
+        // 65.5, 512 heads of 1024..8192 rows 3794 -> 3757.)
+        constexpr int kPart = kChunksPerRow / 2, kPartRows = 64 / kPart, kPartLoads = 32 / kPartRows;
+        static_assert(kAhead < kRing && 32 * kPart * 16 * 4 * kHalves <= kSlotBytes, "a piece of the last slot per wavefront");
+        const int pr = lane / kPart, pc = lane % kPart;
+        if (qh == 0) {
+            uint4 raw[2][2][kPartLoads];
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+                for (int part = 0; part < 2; ++part)
+#pragma unroll
+                    for (int i = 0; i < kPartLoads; ++i)
+                        raw[cb][part][i] = stat[static_cast<size_t>(min(w0 + 32 * cb + kPartRows * i + pr, len - 1)) * kChunksPerRow +
+                                                part * kPart + pc];
+            uint4 *s_own = &stage[kRing - 1][wave * 32 * kPart];
+            auto slot_of = [](int r, int c) { return r * kPart + (c ^ ((kPart == 8 ? r >> 1 : r >> 2) & (kPart - 1))); };
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+                for (int part = 0; part < 2; ++part) {
+#pragma unroll
+                    for (int i = 0; i < kPartLoads; ++i) s_own[slot_of(kPartRows * i + pr, pc)] = raw[cb][part][i];
+#pragma unroll
+                    for (int s = 0; s < kSteps / 2; ++s) Bf[cb][part * (kSteps / 2) + s] = as_bf16x8(s_own[slot_of(n, 2 * s + g)]);
+                }
+            run.m[0] = run.m[1] = -1e30f;
+            run.l[0] = run.l[1] = 0.f;
+            run.col[0] = run.col[1] = 0.f;
+        }
+
         // The column-sum pass visits every block of keys once: it also leaves the norm of the value rows
         // of its block (paper Eq. 4), 64 rows per wavefront, while the first stages are on their way.
         if constexpr (kColsum) {
@@ -384,23 +419,6 @@ __global__ __launch_bounds__(256 * kHalves) void prefill_mfma_kernel(const bf16_
                 default: value_norms_64<D, VATP_NORM_NONE>(Vu, nu, w0, len, lane); break;
                 }
             }
-        }
-
-        // stationary operand: 2 column blocks x kSteps MFMA steps, 8 bf16 per lane each
-        if (qh == 0) {
-#pragma unroll
-            for (int cb = 0; cb < 2; ++cb) {
-                const int row = w0 + 32 * cb + n;
-#pragma unroll
-                for (int s = 0; s < kSteps; ++s) {
-                    uint4 raw = make_uint4(0, 0, 0, 0);
-                    if (row < len) raw = stat[static_cast<size_t>(row) * kChunksPerRow + s + kSteps * g];
-                    Bf[cb][s] = as_bf16x8(raw);
-                }
-            }
-            run.m[0] = run.m[1] = -1e30f;
-            run.l[0] = run.l[1] = 0.f;
-            run.col[0] = run.col[1] = 0.f;
         }
 
         // Make the stationary loads complete here, where the compiler can see it: otherwise it
@@ -472,7 +490,7 @@ __global__ __launch_bounds__(256 * kHalves) void prefill_mfma_kernel(const bf16_
                         bf16x8 a[kSteps];
 #pragma unroll
                         for (int s = 0; s < kSteps; ++s)
-                            a[s] = as_bf16x8(stage[slot][ar * kChunksPerRow + tile_slot<kChunksPerRow>(ar, s + kSteps * g)]);
+                            a[s] = as_bf16x8(stage[slot][ar * kChunksPerRow + tile_slot<kChunksPerRow>(ar, 2 * s + g)]);
                         if (kColsum) {
 #pragma unroll
                             for (int q4 = 0; q4 < 4; ++q4) {
