@@ -407,12 +407,14 @@ __global__ __launch_bounds__(256) void decode_finish_kernel(float *__restrict__ 
     const int row0 = static_cast<int>(blockIdx.y) * 256;
     const int r = row0 + static_cast<int>(threadIdx.x);          // one row per thread
     if (row0 >= n) return;
+    float2 stats[kMaxG];
+    load_group_stats<kMaxG>(part, chunks_alloc, group, n_chunks, stats);
     float logit[kMaxG], s_old = 0.f;
     load_group_logits<kMaxG>(logit, ws_logit + unit * group * cap, cap, group, r, r < n);
     if (r < n && r != n0) s_old = S[unit * cap + r];
     // the softmax denominators from the unit's chunk statistics (per wavefront, one round trip)
     float lse2[kMaxG];
-    merge_group_stats<kMaxG>(part, chunks_alloc, group, n_chunks, lse2);
+    merge_group_stats<kMaxG>(part, chunks_alloc, group, n_chunks, stats, lse2);
     if (r < n) S[unit * cap + r] = s_old + group_weight<kMaxG>(logit, lse2, group);
 }
 

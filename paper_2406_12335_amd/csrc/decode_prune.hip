@@ -12,9 +12,17 @@
 // every row and are rewritten in full.
 //
 // Grid: (units, G), and with an attention output one more workgroup per query head, which merges the chunks' shares of
-// it (vatp_device.h).  Each of a head's G workgroups repeats the cheap part (12 bytes per row
-// from L2: logit, S, nrm) to learn the evicted row by itself, then takes a 1/G share of the
-// stores, so the launch needs no exchange between workgroups and no second pass.
+// it (vatp_device.h).  Each of a head's G workgroups repeats the cheap part (12 bytes per row from L2: logit, S, nrm) to
+// learn the evicted row by itself, then takes a 1/G share of the stores, so the launch needs no exchange between workgroups.
+//
+// What bounds it is a chain of round trips to memory, not bytes, so everything that can be is requested at the start:
+//   own rows    a workgroup owns a range of INPUT rows and scans the head from there on, round the end: what it scans
+//               first is what it stores later, and it still holds those scores when the evicted row is known;
+//   recent rows no row behind e* = n - recent - 1, the last one that may leave, can leave, so they move down by one
+//               whichever row does: loaded with the scan, stored without waiting for the decision.
+// Only rows between min(synced, evicted) and e* are copied afterwards; normally there are none.  This launch, before (scan,
+// then scores, then rows, each with a round trip of its own) / now: 16 sequences of 8 heads x 4 query heads, 307..2457
+// rows, 13.3 / 8.8 us, 32 heads x 2049 rows 6.5 / 6.0, 4 heads x 129 rows 5.5 / 4.7.
 //
 // Arithmetic is the same, operation for operation, as decode_finish_kernel followed by the
 // evict-one gather, so both routes give identical bits.
@@ -26,7 +34,14 @@ namespace {
 
 constexpr int kThreads = 512;
 
-template <typename T, int D, int kMaxG>
+// What a row's new score is made of.
+template <int kMaxG>
+struct ScanRow {
+    float t[kMaxG], s, w, gone, lo;        // logits, old score, norm; windowed: the weight that leaves, low-order part
+    int col;                               // windowed: column of the ring
+};
+
+template <typename T, int D, int kMaxG, bool kWindowed>
 __global__ __launch_bounds__(kThreads) void decode_prune_kernel(
     const T *__restrict__ K, const T *__restrict__ V, const float *__restrict__ S,
     const float *__restrict__ nrm, const int32_t *__restrict__ pos, T *__restrict__ K_out,
@@ -62,170 +77,196 @@ __global__ __launch_bounds__(kThreads) void decode_prune_kernel(
     const float *Su = S + unit * cap;
     const float *Nu = nrm + unit * cap;
     const float *Lu = ws_logit + unit * group * cap;       // the group's logits: query head i at Lu + i * cap
-
-    const int synced = synced_in[unit];
+    const bool evicts = n > B;
     const int lo = n_sink, hi = n - recent;                // rows [lo, hi) may leave
+
+    // this workgroup's rows, in whole 256-byte lines of a row array, and the rows it scans from the first of them on
+    const int share = ((n + G - 1) / G + 63) & ~63;
+    const int own0 = min(g * share, n);
+    const int n_own = min(share, n - own0);
+    const int n_scan = evicts ? n : n_own;
+    auto scan_row = [&](int i) { const int r = own0 + i; return r < n ? r : r - n; };
 
     // history window (Eq. 3): the ring row this step writes, the one that leaves the window, and
     // the column of every row (the appended row takes the free column and has no past)
-    const bool windowed = win.hist != nullptr;
-    const int step = windowed ? win.step[b] : 0;
-    float *h_write = windowed ? win.hist + (unit * win.rows + step % win.rows) * static_cast<size_t>(win.cap_hist) : nullptr;
+    const int step = kWindowed ? win.step[b] : 0;
+    float *h_write = kWindowed ? win.hist + (unit * win.rows + step % win.rows) * static_cast<size_t>(win.cap_hist) : nullptr;
     const float *h_leave =
-        windowed ? win.hist + (unit * win.rows + (step + 1) % win.rows) * static_cast<size_t>(win.cap_hist) : nullptr;
-    const int new_col = windowed ? win.free_in[unit] : 0;
+        kWindowed ? win.hist + (unit * win.rows + (step + 1) % win.rows) * static_cast<size_t>(win.cap_hist) : nullptr;
+    const int new_col = kWindowed ? win.free_in[unit] : 0;
     auto column = [&](int r) { return r == n0 ? new_col : win.hid[unit * cap + r]; };
-    auto leaving = [&](int r) { return windowed && r != n0 ? h_leave[column(r)] : 0.f; };
-    auto low_part = [&](int r) { return windowed && r != n0 ? win.s_lo[unit * cap + r] : 0.f; };
 
-    // the unprotected rows this thread looks at (logit, old score, norm), requested before the
-    // denominator is known so that both round trips to memory overlap
-    constexpr int kScan = kMaxG > 8 ? 1 : 4;                 // rows per thread and round trip (each brings kMaxG logits)
-    float t_r[kScan][kMaxG], s_r[kScan], w_r[kScan], x_r[kScan], l_r[kScan];
+    // kScan rows per thread and round trip (each brings kMaxG logits).  No load is conditional, so that none is waited
+    // for where it is requested: indexes past the end read the last row, and nobody uses what comes back.
+    constexpr int kScan = kMaxG > 8 ? 1 : 4;
+    auto request = [&](ScanRow<kMaxG> (&rows)[kScan], int i0) __attribute__((always_inline)) {
+        if constexpr (kWindowed) {
 #pragma unroll
-    for (int u = 0; u < kScan; ++u) {
-        const int r = lo + tid + u * kThreads;
-        const bool ok = n > B && r < hi;
-        load_group_logits<kMaxG>(t_r[u], Lu, cap, group, r, ok);
-        s_r[u] = ok && r != n0 ? Su[r] : 0.f;
-        w_r[u] = ok ? Nu[r] : 0.f;
-        x_r[u] = ok ? leaving(r) : 0.f;
-        l_r[u] = ok ? low_part(r) : 0.f;
-    }
-
-    // log2 of the softmax denominator of every query head of the group from the chunk statistics
-    float lse2[kMaxG];
-    merge_group_stats<kMaxG>(part, chunks_alloc, group, n_chunks, lse2);
-
+            for (int u = 0; u < kScan; ++u) rows[u].col = win.hid[unit * cap + scan_row(min(i0 + u * kThreads, n - 1))];
+        }
+#pragma unroll
+        for (int u = 0; u < kScan; ++u) {
+            const int r = scan_row(min(i0 + u * kThreads, n - 1));
+#pragma unroll
+            for (int i = 0; i < kMaxG; ++i) rows[u].t[i] = Lu[static_cast<size_t>(min(i, group - 1)) * cap + r];
+            rows[u].s = Su[r];
+            rows[u].w = Nu[r];
+            if constexpr (kWindowed) rows[u].lo = win.s_lo[unit * cap + r];
+        }
+        if constexpr (kWindowed) {
+#pragma unroll
+            for (int u = 0; u < kScan; ++u) {
+                if (scan_row(min(i0 + u * kThreads, n - 1)) == n0) rows[u].col = new_col;
+                rows[u].gone = h_leave[rows[u].col];
+            }
+        }
+    };
     // new score from the old one, this step's attention weight and (windowed) the weight that leaves the
     // window: accumulated scores are one fp32 addition; windowed scores are carried in two floats (window_update),
     // so that adding a weight and subtracting the same float w+1 steps later leaves no residue behind
-    auto combine = [&](float s_old, float lo_old, float p, float gone, float &lo_new) {
-        if (!windowed) { lo_new = 0.f; return s_old + p; }
-        float hi = s_old, lo = lo_old;
-        window_update(hi, lo, gone, p);
-        lo_new = lo;
-        return hi;
+    auto combine = [&](const ScanRow<kMaxG> &row, int r, const float (&lse2)[kMaxG], float &p, float &lo_new) {
+        p = group_weight<kMaxG>(row.t, lse2, group);
+        lo_new = 0.f;
+        float score = r == n0 ? 0.f : row.s;
+        if constexpr (!kWindowed) return score + p;
+        if (r != n0) lo_new = row.lo;
+        window_update(score, lo_new, r == n0 ? 0.f : row.gone, p);
+        return score;
     };
-    float unused_lo;
 
-    // the row that leaves: minimise (importance bits, ~row) over the unprotected rows
+    // requested together: chunk statistics, the first rows of the scan, and the rows behind e* (K and V row, norm,
+    // position, column; kMove passes of them, with G workgroups all there are in most calls)
+    const int synced = synced_in[unit];
+    float2 stats[kMaxG];
+    load_group_stats<kMaxG>(part, chunks_alloc, group, n_chunks, stats);
+    ScanRow<kMaxG> held[kScan];
+    request(held, tid);
+
+    const uint4 *Ku = reinterpret_cast<const uint4 *>(K + unit * cap * D);
+    const uint4 *Vu = reinterpret_cast<const uint4 *>(V + unit * cap * D);
+    uint4 *Ko = reinterpret_cast<uint4 *>(K_out + unit * cap_out * D);
+    uint4 *Vo = reinterpret_cast<uint4 *>(V_out + unit * cap_out * D);
+    const int sub = tid % kLanesPerRow;
+    const int rloc = tid / kLanesPerRow;
+    struct MovedRow { uint4 k, v; float w; int pos, col; };
+    auto fetch = [&](MovedRow &m, int src) __attribute__((always_inline)) {
+        const size_t at = static_cast<size_t>(src) * kLanesPerRow + sub;
+        if (stream) { m.k = load_stream(Ku + at); m.v = load_stream(Vu + at); }       // (uniform)
+        else { m.k = Ku[at]; m.v = Vu[at]; }
+        m.w = Nu[src];
+        m.pos = pos ? pos[unit * cap + src] : 0;
+        m.col = kWindowed ? win.hid[unit * cap + src] : 0;
+    };
+    auto place = [&](const MovedRow &m, int src, int o) __attribute__((always_inline)) {
+        const size_t at = static_cast<size_t>(o) * kLanesPerRow + sub;
+        if (stream) { store_stream(Ko + at, m.k); store_stream(Vo + at, m.v); }
+        else { Ko[at] = m.k; Vo[at] = m.v; }
+        if (sub == 0) {
+            nrm_out[unit * cap_out + o] = m.w;
+            if (pos_out) pos_out[unit * cap_out + o] = m.pos;
+            if constexpr (kWindowed) win.hid_out[unit * cap_out + o] = src == n0 ? new_col : m.col;
+        }
+    };
+    constexpr int kMove = 2;
+    const int after0 = evicts ? hi : n;                     // first row behind e*
+    MovedRow moved[kMove];
+#pragma unroll
+    for (int u = 0; u < kMove; ++u) fetch(moved[u], min(after0 + (u * G + g) * kRowsPerPass + rloc, n - 1));
+
+    // log2 of the softmax denominator of every query head of the group from the chunk statistics
+    float lse2[kMaxG];
+    merge_group_stats<kMaxG>(part, chunks_alloc, group, n_chunks, stats, lse2);
+
+    // the first rows' scores (kept: the workgroup's own rows are among them), then the row that leaves: minimise
+    // (importance bits, ~row) over the unprotected rows
+    float score[kScan], weight[kScan], low[kScan];
+#pragma unroll
+    for (int u = 0; u < kScan; ++u) score[u] = combine(held[u], scan_row(tid + u * kThreads), lse2, weight[u], low[u]);
     int evicted = n;                                       // n <= B: nothing leaves
-    if (n > B) {
+    if (evicts) {
         unsigned long long best = ~0ull;
-        auto consider = [&](int r, float score, float w) {
-            const unsigned key = __float_as_uint(__fmul_rn(score, w));
-            const unsigned long long c =
-                (static_cast<unsigned long long>(key) << 32) | static_cast<unsigned>(~static_cast<unsigned>(r));
-            best = c < best ? c : best;
+        auto consider = [&](int i, float importance) {
+            const int r = scan_row(i);
+            const unsigned long long c = (static_cast<unsigned long long>(__float_as_uint(importance)) << 32) |
+                                         static_cast<unsigned>(~static_cast<unsigned>(r));
+            if (i < n_scan && r >= lo && r < hi) best = c < best ? c : best;
         };
 #pragma unroll
-        for (int u = 0; u < kScan; ++u) {
-            const int r = lo + tid + u * kThreads;
-            if (r < hi) consider(r, combine(s_r[u], l_r[u], group_weight<kMaxG>(t_r[u], lse2, group), x_r[u], unused_lo), w_r[u]);
-        }
-        // further rows, four per thread at a time: loads first, then the arithmetic
-        for (int r0 = lo + tid + kScan * kThreads; r0 < hi; r0 += kScan * kThreads) {
-            float t4[kScan][kMaxG], s4[kScan], w4[kScan], x4[kScan], l4[kScan];
+        for (int u = 0; u < kScan; ++u) consider(tid + u * kThreads, __fmul_rn(score[u], held[u].w));
+        for (int i0 = tid + kScan * kThreads; i0 < n_scan; i0 += kScan * kThreads) {
+            ScanRow<kMaxG> rows[kScan];
+            request(rows, i0);
 #pragma unroll
             for (int u = 0; u < kScan; ++u) {
-                const int r = r0 + u * kThreads;
-                const bool ok = r < hi;
-                load_group_logits<kMaxG>(t4[u], Lu, cap, group, r, ok);
-                s4[u] = ok && r != n0 ? Su[r] : 0.f;
-                w4[u] = ok ? Nu[r] : 0.f;
-                x4[u] = ok ? leaving(r) : 0.f;
-                l4[u] = ok ? low_part(r) : 0.f;
-            }
-#pragma unroll
-            for (int u = 0; u < kScan; ++u) {
-                const int r = r0 + u * kThreads;
-                if (r < hi) consider(r, combine(s4[u], l4[u], group_weight<kMaxG>(t4[u], lse2, group), x4[u], unused_lo), w4[u]);
+                float p, lo_new;
+                consider(i0 + u * kThreads, __fmul_rn(combine(rows[u], scan_row(i0 + u * kThreads), lse2, p, lo_new), rows[u].w));
             }
         }
         best = wave_min_u64(best);
         if ((tid & 63) == 0) s_min[tid >> 6] = best;
-        __syncthreads();
+        lds_barrier();                                     // (LDS only: the rows in flight stay in flight)
         best = s_min[0];
 #pragma unroll
         for (int w = 1; w < kThreads / 64; ++w) best = s_min[w] < best ? s_min[w] : best;
         evicted = static_cast<int>(~static_cast<unsigned>(best & 0xffffffffull));
     }
 
-    // scores and source indices of this workgroup's share of the surviving rows
-    {
-        const int share = (n_keep + G - 1) / G;
-        const int o_end = min(n_keep, (g + 1) * share);
-        for (int o0 = g * share + tid; o0 < o_end; o0 += kScan * kThreads) {
-            float t4[kScan][kMaxG], s4[kScan], x4[kScan], l4[kScan];
-            int c4[kScan];
+    // scores and source indices of this workgroup's rows: from the registers, then (more than kScan * kThreads of them)
+    // formed once more
+    auto emit = [&](int i, float score_new, float p, float lo_new, int col) {
+        const int r = own0 + i;
+        if (i >= n_own || r == evicted) return;
+        const int o = r - (r > evicted ? 1 : 0);
+        S_out[unit * cap_out + o] = score_new;
+        if (kept_idx) kept_idx[unit * cap_out + o] = r;
+        if constexpr (kWindowed) {
+            win.s_lo_out[unit * cap_out + o] = lo_new;
+            h_write[col] = p;
+        }
+    };
 #pragma unroll
-            for (int u = 0; u < kScan; ++u) {           // loads first, then the arithmetic and the stores
-                const int o = o0 + u * kThreads;
-                const int src = o + (o >= evicted ? 1 : 0);
-                const bool ok = o < o_end;
-                load_group_logits<kMaxG>(t4[u], Lu, cap, group, src, ok);
-                s4[u] = ok && src != n0 ? Su[src] : 0.f;
-                x4[u] = ok ? leaving(src) : 0.f;
-                l4[u] = ok ? low_part(src) : 0.f;
-                c4[u] = ok && windowed ? column(src) : 0;
-            }
+    for (int u = 0; u < kScan; ++u) emit(tid + u * kThreads, score[u], weight[u], low[u], held[u].col);
+    for (int i0 = tid + kScan * kThreads; i0 < n_own; i0 += kScan * kThreads) {
+        ScanRow<kMaxG> rows[kScan];
+        request(rows, i0);
 #pragma unroll
-            for (int u = 0; u < kScan; ++u) {
-                const int o = o0 + u * kThreads;
-                if (o >= o_end) continue;
-                const float p = group_weight<kMaxG>(t4[u], lse2, group);
-                float lo_new;
-                S_out[unit * cap_out + o] = combine(s4[u], l4[u], p, x4[u], lo_new);
-                if (windowed) win.s_lo_out[unit * cap_out + o] = lo_new;
-                if (kept_idx) kept_idx[unit * cap_out + o] = o + (o >= evicted ? 1 : 0);
-                if (windowed) h_write[c4[u]] = p;
-            }
+        for (int u = 0; u < kScan; ++u) {
+            float p, lo_new;
+            const float score_new = combine(rows[u], scan_row(i0 + u * kThreads), lse2, p, lo_new);
+            emit(i0 + u * kThreads, score_new, p, lo_new, rows[u].col);
         }
     }
-    if (windowed && g == 0) {
+    if (g == 0 && tid == 0) synced_out[unit] = evicted;
+    if constexpr (kWindowed) {
         // the appended row has received nothing in the steps before this one: clear its column in every
         // ring row but the one written above and the one that leaves (rewritten in full by the next step)
-        for (int s = tid; s < win.rows; s += kThreads)
+        for (int s = g * kThreads + tid; s < win.rows; s += G * kThreads)
             if (s != step % win.rows && s != (step + 1) % win.rows)
                 win.hist[(unit * win.rows + s) * static_cast<size_t>(win.cap_hist) + new_col] = 0.f;
-        if (tid == 0) {
+        if (g == 0 && tid == 0) {
             win.hid[unit * cap + n0] = new_col;
             win.free_out[unit] = evicted < n ? column(evicted) : n;     // a fresh column while the cache grows
         }
     }
 
-    // rows of the other set that are out of date: from the first row in which it differs from
-    // the input set, or from the evicted row if that comes earlier
-    const int first = min(synced, evicted);
-    if (g == 0 && tid == 0) synced_out[unit] = evicted;
-    {
-        const uint4 *Ku = reinterpret_cast<const uint4 *>(K + unit * cap * D);
-        const uint4 *Vu = reinterpret_cast<const uint4 *>(V + unit * cap * D);
-        uint4 *Ko = reinterpret_cast<uint4 *>(K_out + unit * cap_out * D);
-        uint4 *Vo = reinterpret_cast<uint4 *>(V_out + unit * cap_out * D);
-        const int sub = tid % kLanesPerRow;
-        const int rloc = tid / kLanesPerRow;
-        for (int o = first + g * kRowsPerPass + rloc; o < n_keep; o += G * kRowsPerPass) {
-            const int src = o + (o >= evicted ? 1 : 0);
-            uint4 kr, vr;
-            if (stream) {       // (uniform: the whole call either streams or does not)
-                kr = load_stream(Ku + static_cast<size_t>(src) * kLanesPerRow + sub);
-                vr = load_stream(Vu + static_cast<size_t>(src) * kLanesPerRow + sub);
-                store_stream(Ko + static_cast<size_t>(o) * kLanesPerRow + sub, kr);
-                store_stream(Vo + static_cast<size_t>(o) * kLanesPerRow + sub, vr);
-            } else {
-                kr = Ku[static_cast<size_t>(src) * kLanesPerRow + sub];
-                vr = Vu[static_cast<size_t>(src) * kLanesPerRow + sub];
-                Ko[static_cast<size_t>(o) * kLanesPerRow + sub] = kr;
-                Vo[static_cast<size_t>(o) * kLanesPerRow + sub] = vr;
-            }
-            if (sub == 0) {
-                nrm_out[unit * cap_out + o] = Nu[src];
-                if (pos_out) pos_out[unit * cap_out + o] = pos[unit * cap + src];
-                if (windowed) win.hid_out[unit * cap_out + o] = column(src);
-            }
-        }
+    // rows behind e* to their places, one down; then the rows of the other set that are out of date before them: from the
+    // first row in which it differs from the input set, or from the evicted row if that comes earlier
+#pragma unroll
+    for (int u = 0; u < kMove; ++u) {
+        const int src = after0 + (u * G + g) * kRowsPerPass + rloc;
+        if (src < n) place(moved[u], src, src - 1);
+    }
+    for (int src = after0 + (kMove * G + g) * kRowsPerPass + rloc; src < n; src += G * kRowsPerPass) {
+        MovedRow m;
+        fetch(m, src);
+        place(m, src, src - 1);
+    }
+    const int o_end = evicts ? hi - 1 : n_keep;
+    for (int o = min(synced, evicted) + g * kRowsPerPass + rloc; o < o_end; o += G * kRowsPerPass) {
+        const int src = o + (o >= evicted ? 1 : 0);
+        MovedRow m;
+        fetch(m, src);
+        place(m, src, o);
     }
 }
 
@@ -497,8 +538,13 @@ hipError_t launch_decode_prune(int dtype, int head_dim, const void *K, const voi
     unsigned G = 512u / (units * static_cast<unsigned>(g.group));
     G = G < 1u ? 1u : (G > 16u ? 16u : G);
     dim3 grid(units, G + (out ? static_cast<unsigned>(g.group) : 0u)), block(kThreads);
-#define VATP_DPG(T, D, MAXG)                                                                                   \
-    hipLaunchKernelGGL((decode_prune_kernel<T, D, MAXG>), grid, block, 0, st, static_cast<const T *>(K),            \
+#define VATP_DPG(T, D, MAXG)                                   \
+    do {                                                       \
+        if (win.hist) VATP_DPW(T, D, MAXG, true);              \
+        else VATP_DPW(T, D, MAXG, false);                      \
+    } while (0)
+#define VATP_DPW(T, D, MAXG, WINDOWED)                                                                         \
+    hipLaunchKernelGGL((decode_prune_kernel<T, D, MAXG, WINDOWED>), grid, block, 0, st, static_cast<const T *>(K),            \
                        static_cast<const T *>(V), S, nrm, pos, static_cast<T *>(K_out), static_cast<T *>(V_out), \
                        S_out, nrm_out, pos_out, kept_idx, synced_in, synced_out, ws_logit, ws_part, ws_out, out, \
                        win, meta, g.n_heads, g.cap, g.cap_out, chunks_alloc, g.n_sink, g.recent, g.group, g.stream, static_cast<int>(G))
@@ -517,6 +563,7 @@ hipError_t launch_decode_prune(int dtype, int head_dim, const void *K, const voi
     else VATP_DP(bf16_t, 128);
 #undef VATP_DP
 #undef VATP_DPG
+#undef VATP_DPW
     return hipGetLastError();
 }
 

@@ -295,11 +295,17 @@ template <int kChunks> __device__ __forceinline__ int tile_slot(int r, int c) { 
 // lane, lane + 64, ... (one round trip to memory, not one per chunk) and combine across the
 // wavefront (wave_max / wave_sum), which gives every lane the same bits.  The kernels that finish a decode step all
 // call this one function, so they agree bit for bit.
-__device__ __forceinline__ void merge_chunk_stats(const float2 *__restrict__ part, int n_chunks, float &M, float &L)
+// `mine` is the lane's first chunk (load_chunk_stats).
+__device__ __forceinline__ float2 load_chunk_stats(const float2 *__restrict__ part, int n_chunks)
 {
     const int lane = threadIdx.x & 63;
-    float2 mine = make_float2(-INFINITY, 0.f);
-    if (lane < n_chunks) mine = part[lane];
+    const float2 mine = part[min(lane, n_chunks - 1)];           // (not conditional: see where they are used)
+    return lane < n_chunks ? mine : make_float2(-INFINITY, 0.f);
+}
+__device__ __forceinline__ void merge_chunk_stats(const float2 *__restrict__ part, int n_chunks, const float2 &mine, float &M,
+                                                  float &L)
+{
+    const int lane = threadIdx.x & 63;
     float m = mine.x;
     for (int c = lane + 64; c < n_chunks; c += 64) m = fmaxf(m, part[c].x);
     m = wave_max(m);
@@ -307,6 +313,10 @@ __device__ __forceinline__ void merge_chunk_stats(const float2 *__restrict__ par
     for (int c = lane + 64; c < n_chunks; c += 64) l += part[c].y * exp2f(part[c].x - m);
     M = m;
     L = wave_sum(l);
+}
+__device__ __forceinline__ void merge_chunk_stats(const float2 *__restrict__ part, int n_chunks, float &M, float &L)
+{
+    merge_chunk_stats(part, n_chunks, load_chunk_stats(part, n_chunks), M, L);
 }
 
 // Grouped-query attention: g query heads share a K/V head, each with its own softmax, and a row's
@@ -316,36 +326,26 @@ __device__ __forceinline__ void merge_chunk_stats(const float2 *__restrict__ par
 //     group_weight = sum_i 2^(t_i - lse2[i])
 // is that mean.  kMaxG = 1 is plain multi-head attention: the same operations, in the same order,
 // as merge_chunk_stats followed by 2^(t - lse2).
+// The first round of loads (load_group_stats) is apart, so that a kernel can request it before anything else.
 template <int kMaxG>
-__device__ __forceinline__ void merge_group_stats(const float2 *__restrict__ part, int chunks_alloc, int g,
-                                                  int n_chunks, float (&lse2)[kMaxG])
+__device__ __forceinline__ void load_group_stats(const float2 *__restrict__ part, int chunks_alloc, int g, int n_chunks,
+                                                 float2 (&mine)[kMaxG])
 {
-    if constexpr (kMaxG == 1) {
+#pragma unroll
+    for (int i = 0; i < kMaxG; ++i) mine[i] = load_chunk_stats(part + static_cast<size_t>(min(i, g - 1)) * chunks_alloc, n_chunks);
+}
+template <int kMaxG>
+__device__ __forceinline__ void merge_group_stats(const float2 *__restrict__ part, int chunks_alloc, int g, int n_chunks,
+                                                  const float2 (&mine)[kMaxG], float (&lse2)[kMaxG])
+{
+    const float log2g = kMaxG == 1 ? 0.f : log2f(static_cast<float>(g));
+#pragma unroll
+    for (int i = 0; i < kMaxG; ++i) {
+        lse2[i] = 0.f;
+        if (i >= g) continue;
         float M, L;
-        merge_chunk_stats(part, n_chunks, M, L);
-        lse2[0] = M + log2f(L);
-    } else {
-        const int lane = threadIdx.x & 63;
-        float2 mine[kMaxG];
-#pragma unroll
-        for (int i = 0; i < kMaxG; ++i) {           // every head's first round of loads is in flight at once
-            mine[i] = make_float2(-INFINITY, 0.f);
-            if (i < g && lane < n_chunks) mine[i] = part[static_cast<size_t>(i) * chunks_alloc + lane];
-        }
-        const float log2g = log2f(static_cast<float>(g));
-#pragma unroll
-        for (int i = 0; i < kMaxG; ++i) {
-            lse2[i] = 0.f;
-            if (i >= g) continue;
-            const float2 *pi = part + static_cast<size_t>(i) * chunks_alloc;
-            float m = mine[i].x;
-            for (int c = lane + 64; c < n_chunks; c += 64) m = fmaxf(m, pi[c].x);
-            m = wave_max(m);
-            float l = mine[i].y * exp2f(mine[i].x - m);
-            for (int c = lane + 64; c < n_chunks; c += 64) l += pi[c].y * exp2f(pi[c].x - m);
-            l = wave_sum(l);
-            lse2[i] = m + log2f(l) + log2g;
-        }
+        merge_chunk_stats(part + static_cast<size_t>(i) * chunks_alloc, n_chunks, mine[i], M, L);
+        lse2[i] = kMaxG == 1 ? M + log2f(L) : M + log2f(L) + log2g;
     }
 }
 

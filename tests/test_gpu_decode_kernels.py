@@ -8,6 +8,8 @@ import torch
 import parity
 from oracle import vatp_oracle as orc
 import paper_2406_12335_amd as vatp
+from paper_2406_12335_amd.runner import PrunedKVCache
+from test_gpu_fused_step import _seed_state
 
 pytestmark = pytest.mark.gpu
 
@@ -68,3 +70,45 @@ def test_decode_step_at_chunk_edges(gpu_device, dtype, d, g):
                 want, scale = orc.attention_output(q[bb, h * g + r].double().numpy(), Kfull, Vfull)
                 err = np.abs(out[bb, h * g + r].double().numpy() - want)
                 assert np.all(err <= rtol * scale + 1e-12), "output (%d,%d,%d): max err %.3g" % (bb, h, r, err.max())
+
+
+# edges of what the second launch of the fused step requests ahead: a workgroup's share of the rows (64-row steps; one
+# workgroup for all, shares that wrap round the end, shares beyond the rows held in registers) and of the recent window
+@pytest.mark.parametrize("dtype,d,H,g,lens,recent", [
+    ("bf16", 128, 2, 1, [63, 64, 65, 1], 8), ("fp32", 64, 2, 1, [128, 127, 5], 0), ("bf16", 128, 1, 1, [1023, 1025], 1000),
+    ("bf16", 64, 1, 2, [33500], 64), ("bf16", 64, 32, 16, [1100], 300), ("fp32", 128, 43, 4, [260, 513, 90], 40),
+    ("bf16", 128, 65, 8, [2300], 128),
+])
+def test_fused_second_launch_at_the_edges_of_its_shares(gpu_device, dtype, d, H, g, lens, recent):
+    """Bit for bit the state that vatp_decode_attend_step followed by vatp_select_compact leaves."""
+    tdt = torch.float32 if dtype == "fp32" else torch.bfloat16
+    b, dev, F = len(lens), gpu_device, 0 if recent == 0 else 1
+    budgets = [max(n, F + recent) for n in lens]
+    print("[case] fused shares %s d=%d H=%d g=%d lens=%s" % (dtype, d, H, g, lens), flush=True)
+    gen = torch.Generator().manual_seed(7)
+    two, fused = [PrunedKVCache(b, H, d, tdt, F, recent, budgets, dev, cap_cache=max(budgets) + 1, q_per_kv=g) for _ in range(2)]
+    try:
+        weak = [(bb, h, min(F + 37 * h, lens[bb] - 1)) for bb in range(b) for h in range(0, H, 2)]
+        _seed_state([two, fused], lens, gen, d, tdt, dev, weak_rows=weak)
+        ws = torch.empty(vatp.vatp_workspace_bytes(two.ctx, two._p_dec, vatp.CALL_DECODE_ATTEND_STEP) + 256, dtype=torch.uint8,
+                         device=dev)
+        for t in range(4):
+            q = torch.randn(b, H * g, d, generator=gen).to(tdt).to(dev)
+            k, v = (torch.randn(b, H, d, generator=gen).to(tdt).to(dev) for _ in range(2))
+            out_two, out_fused = (torch.full((b, H * g, d), x, device=dev) for x in (0.0, 1.0))
+            c = two.cur
+            two._p_dec.set_len(two.lens)
+            vatp.vatp_decode_attend_step(two.ctx, two._p_dec, q, k, v, two.K[c], two.V[c], two.S[c], two.nrm[c], two.pos[c],
+                                         [900 + t] * b, out_two, ws)
+            two.lens = [n + 1 for n in two.lens]
+            two.prune()
+            fused.decode_prune_step(q, k, v, [900 + t] * b, out=out_fused)
+            assert torch.equal(out_two, out_fused) and two.lens == fused.lens
+            for bb, n in enumerate(two.lens):
+                for name in ("K", "V", "S", "nrm", "pos"):
+                    x, y = getattr(two, name)[two.cur], getattr(fused, name)[fused.cur]
+                    assert torch.equal(x[bb, :, :n], y[bb, :, :n]), (t, bb, name)
+                assert torch.equal(two.kept_idx[bb, :, :n], fused.kept_idx[bb, :, :n]), (t, bb)
+    finally:
+        two.close()
+        fused.close()
