@@ -140,6 +140,8 @@ __global__ __launch_bounds__(256) void decode_logits_kernel(
     }
 }
 
+static __device__ const uint4 zero_row[32] = {};          // the longest row, 128 fp32 elements
+
 // What a thread of the group kernel holds of its chunk: row slots u * kRowsPerPass + tid / kLanesPerRow, 16 bytes each.
 template <typename T, int D>
 struct ChunkRows {
@@ -148,17 +150,19 @@ struct ChunkRows {
     static constexpr int kRowsPerPass = 256 / kLanesPerRow;
     static constexpr int kPasses = kDecodeChunk / kRowsPerPass;
 
-    // Requests the chunk's rows of one cache; the new row (index n0) comes from the step's input.  Rows past it read the
-    // new row again (their logits are -inf, their weights 0), so that no load is conditional: a row merged with a default
-    // value would be waited for where it is requested.
+    // Requests the chunk's rows of one cache; the new row (index n0) comes from the step's input.  Rows past it read `past`
+    // (keys: anything, their logits are -inf; values: zeros, as a weight of 0 does not undo an infinity), so that no load is
+    // conditional: a row merged with a default value would be waited for where it is requested.
     template <bool kStream>
-    __device__ static __forceinline__ void request(uint4 (&raw)[kPasses], const uint4 *cache, const uint4 *fresh, int row0, int n0)
+    __device__ static __forceinline__ void request(uint4 (&raw)[kPasses], const uint4 *cache, const uint4 *fresh, const uint4 *past,
+                                                   int row0, int n0)
     {
         const int sub = threadIdx.x % kLanesPerRow, rloc = threadIdx.x / kLanesPerRow;
 #pragma unroll
         for (int u = 0; u < kPasses; ++u) {
             const int r = row0 + u * kRowsPerPass + rloc;
-            raw[u] = load_rows<kStream>(r >= n0 ? fresh + sub : cache + static_cast<size_t>(r) * kLanesPerRow + sub);
+            const uint4 *beyond = r == n0 ? fresh : past;
+            raw[u] = load_rows<kStream>((r >= n0 ? beyond : cache + static_cast<size_t>(r) * kLanesPerRow) + sub);
         }
     }
 
@@ -257,7 +261,7 @@ __global__ __launch_bounds__(256) void decode_logits_group_kernel(
     }
     const uint4 k_own = knew[sub], v_own = vnew[sub];
     uint4 k_raw[kPasses], v_raw[kAttend ? kPasses : 1];
-    R::template request<kStream>(k_raw, reinterpret_cast<const uint4 *>(K + unit * cap * D), knew, row0, n0);
+    R::template request<kStream>(k_raw, reinterpret_cast<const uint4 *>(K + unit * cap * D), knew, knew, row0, n0);
     if (n0 - row0 < kDecodeChunk && tid < kLanesPerRow)
         R::append(K, V, nrm, pos, unit * cap + n0, k_own, v_own, norm, meta.aux[b]);
 
@@ -328,7 +332,7 @@ __global__ __launch_bounds__(256) void decode_logits_group_kernel(
     }
     lds_barrier();
 
-    if constexpr (kAttend) R::template request<kStream>(v_raw, reinterpret_cast<const uint4 *>(V + unit * cap * D), vnew, row0, n0);
+    if constexpr (kAttend) R::template request<kStream>(v_raw, reinterpret_cast<const uint4 *>(V + unit * cap * D), vnew, zero_row, row0, n0);
     // per query head, by one wavefront (two rows per lane, no exchange between wavefronts): chunk statistics, logits to
     // the workspace, weights relative to the chunk maximum
     for (int i = wave; i < group; i += 4) {

@@ -112,3 +112,29 @@ def test_fused_second_launch_at_the_edges_of_its_shares(gpu_device, dtype, d, H,
     finally:
         two.close()
         fused.close()
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("fp32", 64)])
+@pytest.mark.parametrize("g", [1, 4])
+def test_infinity_in_the_new_value_row_stays_an_infinity(gpu_device, dtype, d, g):
+    """The rows of a chunk past the new one have no part in the outputs, whatever the new row holds."""
+    tdt, dev, n0 = (torch.float32 if dtype == "fp32" else torch.bfloat16), gpu_device, 130
+    print("[case] infinite value %s g=%d" % (dtype, g), flush=True)
+    gen = torch.Generator().manual_seed(3)
+    K, V = (torch.randn(1, 2, n0 + 1, d, generator=gen).to(tdt).to(dev) for _ in range(2))
+    q = torch.randn(1, 2 * g, d, generator=gen).to(tdt).to(dev)
+    k, v = (torch.randn(1, 2, d, generator=gen).to(tdt).to(dev) for _ in range(2))
+    v[:, :, 3] = float("inf")
+    S, N = (torch.zeros(1, 2, n0 + 1, device=dev) for _ in range(2))
+    out = torch.zeros(1, 2 * g, d, device=dev)
+    ctx = vatp.vatp_create(0)
+    try:
+        p = vatp.Params(1, 2, d, tdt, 0, 0, n0 + 1, [n0], None, q_per_kv=g)
+        ws = torch.empty(vatp.vatp_workspace_bytes(ctx, p, vatp.CALL_DECODE_ATTEND_STEP), dtype=torch.uint8, device=dev)
+        vatp.vatp_decode_attend_step(ctx, p, q, k, v, K, V, S, N, None, None, out, ws)
+        torch.cuda.synchronize()
+    finally:
+        vatp.vatp_destroy(ctx)
+    want = torch.zeros(d, dtype=torch.bool)
+    want[3] = True
+    assert torch.equal(torch.isinf(out.cpu()), want.expand(1, 2 * g, d)) and not torch.isnan(out).any()
