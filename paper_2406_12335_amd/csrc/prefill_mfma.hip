@@ -126,8 +126,8 @@ struct Pending {                 // a finished pair of 32x32 tiles awaiting its 
 struct WindowPass {
     int window;                  // w
     float *hist;                 // [units, w + 1, cap] attention rows of the window, may be NULL
-    float *lse_part;             // [n_splits, units, cap] partial row statistics
-    int n_splits, split_stages;  // key ranges per query block, 64-row stages per range
+    float *lse_part;             // [n_splits, units, part_rows] partial row statistics of the window's rows
+    int part_rows, n_splits, split_stages;  // key ranges per query block, 64-row stages per range
     int n_qb;                    // query blocks per head that can touch the window
 };
 
@@ -690,10 +690,11 @@ __global__ __launch_bounds__(256 * kHalves) void prefill_mfma_kernel(const bf16_
             for (int cb = 0; cb < 2; ++cb) {
                 const int idx = w0 + 32 * cb + n;
                 if (idx < len) {
-                    if constexpr (kSplitKeys)
-                        win.lse_part[(static_cast<size_t>(pair % win.n_splits) * n_units + unit) * cap + idx] =
-                            fin_m[cb] + __log2f(fin_l[cb]);
-                    else if (!kColsum) lse_u[idx] = fin_m[cb] + __log2f(fin_l[cb]);
+                    if constexpr (kSplitKeys) {
+                        if (idx >= q_first)
+                            win.lse_part[(static_cast<size_t>(pair % win.n_splits) * n_units + unit) * win.part_rows + idx - q_first] =
+                                fin_m[cb] + __log2f(fin_l[cb]);
+                    } else if (!kColsum) lse_u[idx] = fin_m[cb] + __log2f(fin_l[cb]);
                     else if (kGrouped && splits > 1)     // partial sum [split, K/V head, cap], mean taken by the merge kernel
                         S[(static_cast<size_t>(split) * (n_units / splits) + unit) * cap + idx] = fin_l[cb];
                     else S[unit * cap + idx] = (kGrouped && !kWindow) ? fin_l[cb] * inv_group : fin_l[cb];   // (windowed groups: weights already divided)
@@ -711,7 +712,24 @@ __global__ __launch_bounds__(256 * kHalves) void prefill_mfma_kernel(const bf16_
 
 namespace {
 
-constexpr int kSplitStages = 32;       // keys per workgroup of the windowed row statistics: 32 stages of 64
+// Keys per workgroup of the windowed row statistics: at most 32 stages of 64 (the workspace is sized for that) ...
+constexpr int kSplitStages = 32;
+
+// ... and fewer while the workgroups of the window's query blocks do not fill the chip two to a compute unit, down to 4
+// stages (shorter ranges are all prologue), as far as the partial statistics of a shorter window find room in the same
+// workspace.  Measured, 32 heads x 4096 rows, window of 400, row statistics: ranges of 2048 keys (128 workgroups at work)
+// 37.4 us, of 512 keys (512) 23.6; the
+// whole call 96.7 -> 81.3 us.
+int split_stages_for(int n_stages, int part_rows, int cap, int q_units)
+{
+    const long blocks = static_cast<long>((part_rows + kBlockCols - 1) / kBlockCols) * q_units;
+    const long want = 2l * kComputeUnits / blocks, most = static_cast<long>(prefill_window_splits(cap)) * cap / part_rows;
+    long splits = want < most ? want : most;
+    if (splits > n_stages / 4) splits = n_stages / 4;
+    if (splits < 1) splits = 1;
+    const int stages = static_cast<int>((n_stages + splits - 1) / splits);
+    return stages < kSplitStages ? stages : kSplitStages;
+}
 
 // lse2_j = log2 sum_s 2^(part_s[j]) over the key ranges s that begin at or before row j, for the
 // window's queries; the few rows before the window that share its first 64-row stage get 0 (they
@@ -719,7 +737,7 @@ constexpr int kSplitStages = 32;       // keys per workgroup of the windowed row
 __global__ __launch_bounds__(256) void merge_split_lse_kernel(const float *__restrict__ lse_part,
                                                               float *__restrict__ lse2, BatchMeta meta,
                                                               int n_heads, int n_units, int cap, int window,
-                                                              int n_splits)
+                                                              int part_rows, int n_splits, int split_stages)
 {
     const size_t unit = blockIdx.y;
     const int len = meta.len[unit / n_heads];
@@ -728,12 +746,20 @@ __global__ __launch_bounds__(256) void merge_split_lse_kernel(const float *__res
     if (j >= len) return;
     float out = 0.f;
     if (j >= q_first) {
-        float m = -INFINITY;
-        for (int s = 0; s < n_splits && s * kSplitStages * kStage <= j; ++s)
-            m = fmaxf(m, lse_part[(static_cast<size_t>(s) * n_units + unit) * cap + j]);
-        float l = 0.f;
-        for (int s = 0; s < n_splits && s * kSplitStages * kStage <= j; ++s)
-            l += exp2f(lse_part[(static_cast<size_t>(s) * n_units + unit) * cap + j] - m);
+        const int used = min(n_splits, j / (split_stages * kStage) + 1);
+        float m = -INFINITY, l = 0.f;
+        for (int s0 = 0; s0 < used; s0 += 8) {
+            float v[8], top = m;
+#pragma unroll
+            for (int u = 0; u < 8; ++u)                 // all loads first (ranges past the last one: that one again)
+                v[u] = lse_part[(static_cast<size_t>(min(s0 + u, used - 1)) * n_units + unit) * part_rows + j - q_first];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) top = fmaxf(top, v[u]);
+            l *= exp2f(m - top);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) l += s0 + u < used ? exp2f(v[u] - top) : 0.f;
+            m = top;
+        }
         out = m + log2f(l);
     }
     lse2[unit * cap + j] = out;
@@ -770,8 +796,10 @@ hipError_t launch_window(const void *Q, const void *K, const void *V, float *S, 
     win.window = window;
     win.hist = hist;
     win.lse_part = lse_part;
-    win.split_stages = kSplitStages;
-    win.n_splits = ((g.max_len + kStage - 1) / kStage + kSplitStages - 1) / kSplitStages;
+    const int n_stages = (g.max_len + kStage - 1) / kStage;
+    win.part_rows = window < g.max_len ? window + 1 : g.max_len;
+    win.split_stages = split_stages_for(n_stages, win.part_rows, g.cap, q_units);
+    win.n_splits = (n_stages + win.split_stages - 1) / win.split_stages;
     const int window_blocks = (window + 1 + kBlockCols - 1) / kBlockCols + 1;     // blocks a window can straddle
     win.n_qb = window_blocks < n_blocks ? window_blocks : n_blocks;
     hipLaunchKernelGGL((prefill_mfma_kernel<D, false, 1, true>), dim3(8u * win.n_qb * win.n_splits * ((q_units + 7) / 8)),
@@ -779,7 +807,7 @@ hipError_t launch_window(const void *Q, const void *K, const void *V, float *S, 
                        nullptr, 0, g.group, 1);
     const int merge_rows = window + 1 + kStage;
     hipLaunchKernelGGL(merge_split_lse_kernel, dim3((merge_rows + 255) / 256, q_units), dim3(256), 0, st, lse_part, lse2,
-                       meta, q_heads, q_units, g.cap, window, win.n_splits);
+                       meta, q_heads, q_units, g.cap, window, win.part_rows, win.n_splits, win.split_stages);
     const dim3 grid(8u * ((n_blocks + 1) / 2) * ((kv_units + 7) / 8));
     if (g.group > 1)
         hipLaunchKernelGGL((prefill_mfma_kernel<D, true, 1, true, true>), grid, dim3(256), 0, st, q, k, lse2, S, meta, g.n_heads,

@@ -69,3 +69,13 @@ def test_fp32_scores(gpu_device, d, H, g, window):
 def test_bf16_scores_on_a_small_grid(gpu_device, d, H, g):
     lens = [319, 1, 31, 32, 33, 64, 65, 255]
     _check_scores(gpu_device, "bf16", d, g, H, lens, None, [(b, H - 1 if b % 2 else 0) for b in range(len(lens))], 221 + g)
+
+
+# windowed bf16 prompts: key ranges of 4 stages (the last one shorter) up to as many ranges as the workspace holds, a window
+# as long as the prompt, and grids on which the ranges stay long; blocks one to a workgroup and in pairs
+@pytest.mark.parametrize("d,H,g,window,lens", [
+    (128, 2, 1, 100, [1100, 1, 64, 257, 256]), (64, 3, 1, 400, [900, 385]), (128, 2, 2, 30, [769, 513]), (64, 1, 1, 0, [2300]),
+    (128, 1, 1, 1023, [1024]), (128, 40, 1, 500, [700, 330]), (128, 64, 4, 200, [300]),
+])
+def test_bf16_window_key_ranges(gpu_device, d, H, g, window, lens):
+    _check_scores(gpu_device, "bf16", d, g, H, lens, window, [(b, H - 1 if b % 2 else 0) for b in range(len(lens))], 231 + g)
