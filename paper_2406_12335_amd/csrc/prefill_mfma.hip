@@ -129,6 +129,7 @@ struct WindowPass {
     float *lse_part;             // [n_splits, units, part_rows] partial row statistics of the window's rows
     int part_rows, n_splits, split_stages;  // key ranges per query block, 64-row stages per range
     int n_qb;                    // query blocks per head that can touch the window
+    bool one_block;              // column sums: a workgroup takes one block of keys, not a pair
 };
 
 template <bool kColsum>
@@ -256,7 +257,7 @@ __global__ __launch_bounds__(256 * kHalves) void prefill_mfma_kernel(const bf16_
     // Workgroups are handed to the 8 XCDs round-robin by linear id.  All block pairs of one
     // (batch, head) unit are given ids that are equal mod 8, so the unit's streamed matrix is
     // pulled into one XCD's L2 once instead of into all eight.
-    const int n_pairs = kSplitKeys ? win.n_qb * win.n_splits : (n_blocks + 1) / 2;
+    const int n_pairs = kSplitKeys ? win.n_qb * win.n_splits : kWindow && win.one_block ? n_blocks : (n_blocks + 1) / 2;
     const int xcd = blockIdx.x & 7, in_xcd = blockIdx.x >> 3;
     const int slot_i = xcd + 8 * (in_xcd / n_pairs);
     const int pair = in_xcd % n_pairs;
@@ -330,7 +331,7 @@ __global__ __launch_bounds__(256 * kHalves) void prefill_mfma_kernel(const bf16_
         const int job = kGrouped ? (it >= n_qh ? 1 : 0) : it, qh = kGrouped ? it - job * n_qh : 0;     // (at most two jobs)
         int blk = job == 0 ? pair : n_blocks - 1 - pair;
         if constexpr (kSplitKeys) blk = q_first / kBlockCols + pair / win.n_splits;
-        if (!kSplitKeys && job == 1 && blk == pair) break;   // odd count: the middle block once
+        if (!kSplitKeys && job == 1 && (blk == pair || (kWindow && win.one_block))) break;   // odd count: the middle block once
         const int base0 = blk * kBlockCols;
         if (base0 >= len) continue;
         const int w0 = base0 + cw * kWaveCols;         // first stationary row of this wavefront
@@ -718,8 +719,7 @@ constexpr int kSplitStages = 32;
 // ... and fewer while the workgroups of the window's query blocks do not fill the chip two to a compute unit, down to 4
 // stages (shorter ranges are all prologue), as far as the partial statistics of a shorter window find room in the same
 // workspace.  Measured, 32 heads x 4096 rows, window of 400, row statistics: ranges of 2048 keys (128 workgroups at work)
-// 37.4 us, of 512 keys (512) 23.6; the
-// whole call 96.7 -> 81.3 us.
+// 37.4 us, of 512 keys (512) 23.6; the whole call 96.7 -> 81.3 us.
 int split_stages_for(int n_stages, int part_rows, int cap, int q_units)
 {
     const long blocks = static_cast<long>((part_rows + kBlockCols - 1) / kBlockCols) * q_units;
@@ -808,7 +808,12 @@ hipError_t launch_window(const void *Q, const void *K, const void *V, float *S, 
     const int merge_rows = window + 1 + kStage;
     hipLaunchKernelGGL(merge_split_lse_kernel, dim3((merge_rows + 255) / 256, q_units), dim3(256), 0, st, lse_part, lse2,
                        meta, q_heads, q_units, g.cap, window, win.part_rows, win.n_splits, win.split_stages);
-    const dim3 grid(8u * ((n_blocks + 1) / 2) * ((kv_units + 7) / 8));
+    // Blocks of keys are paired so that workgroups have equal work.  Up to half the prompt, most blocks meet the whole
+    // window, the first ones the most of it, and one block to a workgroup puts twice as many of them on the chip to write
+    // the attention rows.  Measured, pairs / single blocks, whole call: 32 heads x 4096 rows, window of 100 47.2 / 39.7 us,
+    // 400 77.4 / 70.5, 2000 252 / 224; 8 x 4 query heads, window of 400 160 / 98.
+    win.one_block = 2ll * window < g.max_len;
+    const dim3 grid(8u * (win.one_block ? n_blocks : (n_blocks + 1) / 2) * ((kv_units + 7) / 8));
     if (g.group > 1)
         hipLaunchKernelGGL((prefill_mfma_kernel<D, true, 1, true, true>), grid, dim3(256), 0, st, q, k, lse2, S, meta, g.n_heads,
                            kv_units, g.cap, n_blocks, g.scale_log2, win, static_cast<const bf16_t *>(V), nrm, g.norm,
