@@ -306,8 +306,9 @@ def measure(args, workload, steps, warmup, main_line):
     profiled = PROFILED_TRAFFIC_BYTES.get(cfg.name if as_named else None, {})
     traffic = profiled.get("bytes_per_call", {})
     prefill_tflops = flops / (prefill_ms * 1e-3) / 1e12 if prefill_ms > 0 else 0.0
+    # (bf16 grids too small for the chip take the direct kernels as well; the large named workloads do not)
     prefill_kernels = "prefill_mfma_kernel<rowstat> + prefill_mfma_kernel<colsum, value norms inside>" \
-        if mfma and cfg.head_dim == 128 else "l1norm_kernel + prefill_rowstat_generic + prefill_colsum_generic"
+        if mfma else "prefill_direct_kernel<rowstat> + prefill_direct_kernel<colsum, value norms inside>"
     roof_prefill = {"kernel": "vatp_prefill_score = " + prefill_kernels if window is None
                     else "vatp_prefill_score_window = rowstat over key ranges + merge + colsum with rows and norms",
                     "bound": "mfma" if mfma else "alu",
