@@ -208,6 +208,12 @@ size_t vatp_workspace_bytes(const vatp_ctx *, const vatp_params *p, int which_ca
 
 namespace {
 
+bool overlap(const void *a, size_t a_bytes, const void *b, size_t b_bytes)
+{
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return x < y + b_bytes && y < x + a_bytes;
+}
+
 constexpr int kMaxWindow = 1 << 18;      // (the history gather indexes ring rows / 8 with a 16-bit grid dimension)
 
 vatp_status prefill_score_impl(vatp_ctx *ctx, const vatp_params *p, const void *Q, const void *K, const void *V,
@@ -227,7 +233,6 @@ vatp_status prefill_score_impl(vatp_ctx *ctx, const vatp_params *p, const void *
     const size_t units = static_cast<size_t>(p->batch) * p->n_heads;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     float *lse2 = static_cast<float *>(ws);
-    if (have_lse && launch_lse_to_base2(lse, lse2, pr.meta, pr.g, stream) != hipSuccess) return VATP_E_DEVICE;
     // what follows lse2 in the workspace: partial row statistics of a window, or room for partial column sums of a group
     float *parts = lse2 + align_up(units * pr.g.group * p->cap * sizeof(float)) / sizeof(float);
     hipError_t e = hipSuccess;
@@ -238,10 +243,22 @@ vatp_status prefill_score_impl(vatp_ctx *ctx, const vatp_params *p, const void *
         float *s_part = pr.g.group > 1 && window < 0 ? parts : nullptr;
         for (int pass : {kPassRowstat, kPassColsum}) {          // (the column sums need the row statistics)
             if (e != hipSuccess || (have_lse && pass == kPassRowstat)) continue;
-            if (window < 0 && p->dtype == VATP_BF16 && prefill_mfma_fills(p->head_dim, pass, pr.g))
+            const bool staged = window < 0 && p->dtype == VATP_BF16 && prefill_mfma_fills(p->head_dim, pass, pr.g);
+            // Row statistics handed in: the direct kernels take them as they are (unless an output lies over them, since
+            // workgroups write outputs while others still read).  Measured, with the conversion in a launch of its own /
+            // without: 4 heads of 64 x 256 fp32 rows 12.1 / 8.0 us, 2 x 8 x 4 query heads x 700 rows 20.5 / 17.8, 32 heads x
+            // 2000 rows 36.4 / 34.9.  The staged kernels copy them to LDS and have no instruction to spare for them: there
+            // the launch takes 5.6 of 586 us, at 8 x 8 x 4 query heads x 4001 rows.
+            const size_t bytes = units * p->cap * sizeof(float);
+            const bool natural = have_lse && !staged && !overlap(lse, bytes * pr.g.group, S, bytes) &&
+                                 !overlap(lse, bytes * pr.g.group, nrm, bytes);
+            if (have_lse && !natural) e = launch_lse_to_base2(lse, lse2, pr.meta, pr.g, stream);
+            if (e != hipSuccess) break;
+            if (staged)
                 e = launch_prefill_mfma(p->head_dim, Q, K, V, S, nrm, lse2, s_part, pass, pr.meta, pr.g, stream);
             else
-                e = launch_prefill_direct(p->dtype, p->head_dim, Q, K, V, S, nrm, lse2, s_part, pass, window, hist, pr.meta, pr.g,
+                e = launch_prefill_direct(p->dtype, p->head_dim, Q, K, V, S, nrm,
+                                          natural ? const_cast<float *>(lse) : lse2, natural, s_part, pass, window, hist, pr.meta, pr.g,
                                           stream);
         }
     }

@@ -14,7 +14,7 @@ __global__ __launch_bounds__(256) void lse_to_base2_kernel(const float *__restri
     const int b = blockIdx.z, h = blockIdx.y;
     const int r = blockIdx.x * 256 + threadIdx.x;
     const size_t unit = static_cast<size_t>(b) * n_heads + h;
-    if (r < meta.len[b]) lse2[unit * cap + r] = lse[unit * cap + r] * 1.44269504088896340736f;
+    if (r < meta.len[b]) lse2[unit * cap + r] = lse[unit * cap + r] * kLog2e;
 }
 
 }  // namespace

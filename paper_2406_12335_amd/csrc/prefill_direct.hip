@@ -75,6 +75,7 @@ struct DirectArgs {
     int window, group, norm;
     int splits;                    // colsum: workgroups that share a block, each with group / splits query heads (1 with hist)
     float scale_log2;
+    float lse_scale;               // colsum: what takes the row statistics to base 2 (1, or log2(e) for natural ones)
 };
 
 template <typename T, int D, int kPass, int kCols, int kWaves, bool kStaged>
@@ -226,7 +227,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_direct_kernel(const T 
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[c][v] = 0.f;
         // the tile's row statistics arrive one per lane and go through the wavefront's own LDS row (no barrier)
-        if constexpr (kColsum) s_lse[wave][n] = lse_next;
+        if constexpr (kColsum) s_lse[wave][n] = lse_next * a.lse_scale;
         const bool more = i + 1 < n_items;
         int t_next = t, h_next = h;
         const uint4 *src_next = src;
@@ -395,8 +396,8 @@ hipError_t launch_direct(const T *Q, const T *K, const T *V, float *S, float *nr
 }  // namespace
 
 hipError_t launch_prefill_direct(int dtype, int head_dim, const void *Q, const void *K, const void *V, float *S, float *nrm,
-                                 float *lse2, float *s_part, int pass, int window, float *hist, const BatchMeta &meta,
-                                 const Geometry &g, hipStream_t st)
+                                 float *lse2, bool natural_lse, float *s_part, int pass, int window, float *hist,
+                                 const BatchMeta &meta, const Geometry &g, hipStream_t st)
 {
     if (g.max_len <= 0) return hipSuccess;
     DirectArgs a;
@@ -407,6 +408,7 @@ hipError_t launch_prefill_direct(int dtype, int head_dim, const void *Q, const v
     a.group = g.group;
     a.norm = g.norm;
     a.scale_log2 = g.scale_log2;
+    a.lse_scale = natural_lse ? kLog2e : 1.f;
     // The query heads of a group are dealt out to the smallest number of workgroups that brings two to a compute unit, as
     // long as a wavefront keeps four tiles (the partial sums cost a launch).  Measured, one K/V head with 8 query heads of
     // 128: 1024 rows 39.8 -> 20.0 us, 4096 rows 149 -> 80; 2 x 4 heads, 256 rows: 13.9 in one, 15.2 in four.

@@ -404,11 +404,13 @@ __device__ __forceinline__ float group_weight(const float (&t)[kMaxG], const flo
 // ---- host-side launchers, one per source file --------------------------------------
 // window >= 0: history-window scores (Eq. 3), the window's attention rows go to hist (may be NULL)
 // The two passes of the prompt scores (either may run on the staged or on the direct kernels; both leave the row
-// statistics in lse2, and the column sums come with the value-row norms).
+// statistics in lse2, and the column sums come with the value-row norms).  With natural_lse the column sums of the direct
+// kernels take natural logarithms, as an attention kernel hands them over.
+constexpr float kLog2e = 1.44269504088896340736f;
 enum { kPassRowstat = 1, kPassColsum = 2 };
 
 hipError_t launch_prefill_direct(int dtype, int head_dim, const void *Q, const void *K, const void *V, float *S, float *nrm,
-                                 float *lse2, float *s_part, int pass, int window, float *hist,
+                                 float *lse2, bool natural_lse, float *s_part, int pass, int window, float *hist,
                                  const BatchMeta &meta, const Geometry &g, hipStream_t st);
 // S = (1/g) * sum over `splits` of the partial column sums s_part [splits, K/V heads, cap] of a group's query heads
 hipError_t launch_merge_group_partials(const float *s_part, float *S, int splits, const BatchMeta &meta, const Geometry &g,

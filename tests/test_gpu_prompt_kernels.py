@@ -5,6 +5,7 @@ import pytest
 import torch
 
 import parity
+import paper_2406_12335_amd as vatp
 import vatp_synth as vs
 from oracle import vatp_oracle as orc
 from paper_2406_12335_amd.runner import PrunedKVCache
@@ -79,3 +80,29 @@ def test_bf16_scores_on_a_small_grid(gpu_device, d, H, g):
 ])
 def test_bf16_window_key_ranges(gpu_device, d, H, g, window, lens):
     _check_scores(gpu_device, "bf16", d, g, H, lens, window, [(b, H - 1 if b % 2 else 0) for b in range(len(lens))], 231 + g)
+
+
+# row log-sum-exps handed in: taken as they are by the direct kernels, converted first where they lie under an output; the
+# same multiplication either way, so the same bits
+@pytest.mark.parametrize("dtype,d,H,lens", [("fp32", 64, 2, [65, 1, 256]), ("fp32", 128, 1, [97]), ("bf16", 64, 3, [130, 33]), ("bf16", 128, 4, [511])])
+def test_row_lse_under_an_output(gpu_device, dtype, d, H, lens):
+    print("[case] lse %s d=%d H=%d lens=%s" % (dtype, d, H, lens), flush=True)
+    dt, b, cap, g = {"fp32": torch.float32, "bf16": torch.bfloat16}[dtype], len(lens), max(lens), torch.Generator().manual_seed(251)
+    Q, K, V = (torch.randn(b, H, cap, d, generator=g).to(dt).to(gpu_device) for _ in range(3))
+    lse = (4 + torch.rand(b, H, cap, generator=g)).to(gpu_device)
+    ctx = vatp.vatp_create(0)
+    try:
+        p = vatp.Params(b, H, d, dt, 0, 0, cap, lens, lens)
+        ws = torch.empty(vatp.vatp_workspace_bytes(ctx, p, vatp.binding.CALL_PREFILL_SCORE), dtype=torch.uint8, device=gpu_device)
+        S, S_over, nrm = torch.zeros_like(lse), lse.clone(), torch.zeros_like(lse)
+        vatp.vatp_prefill_score_lse(ctx, p, Q, K, V, lse, S, nrm, ws)
+        vatp.vatp_prefill_score_lse(ctx, p, Q, K, V, S_over, S_over, nrm, ws)
+        torch.cuda.synchronize()
+    finally:
+        vatp.vatp_destroy(ctx)
+    for i, L in enumerate(lens):
+        assert torch.equal(S[i, :, :L], S_over[i, :, :L])
+        t = (Q[i, :, :L].cpu().double() @ K[i, :, :L].cpu().double().transpose(-1, -2).contiguous()) / d ** 0.5
+        want = torch.exp(t - lse[i, :, :L].cpu().double().unsqueeze(-1)).tril().sum(dim=1)
+        for h in range(H):
+            parity.assert_scores_close(S[i, h, :L].cpu().numpy(), want[h].numpy(), parity.rtol_for(dt), "S, sequence %d head %d" % (i, h))
