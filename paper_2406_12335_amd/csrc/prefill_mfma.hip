@@ -126,11 +126,31 @@ struct Pending {                 // a finished pair of 32x32 tiles awaiting its 
 struct WindowPass {
     int window;                  // w
     float *hist;                 // [units, w + 1, cap] attention rows of the window, may be NULL
-    float *lse_part;             // [n_splits, units, part_rows] partial row statistics of the window's rows
+    unsigned *lse_part;          // [n_splits, units, part_rows] partial row statistics of the window's rows (pack_partial)
     int part_rows, n_splits, split_stages;  // key ranges per query block, 64-row stages per range
     int n_qb;                    // query blocks per head that can touch the window
     bool one_block;              // column sums: a workgroup takes one block of keys, not a pair
 };
+
+// The partial sum 2^m * l of a row over one range of keys (m whole) in 32 bits: as the float that it is, exactly, while its
+// exponent allows; beyond 2^100 either way its logarithm v, marked by the sign bit, with v's sign in the next bit and the
+// exponent of |v| (64 and more) counted from 2^1.  A logarithm for every range would round each of them: errors against 64
+// bits of the column sums past the sinks, 8 heads x 9000 rows, window of 400 (ranges of 512 keys), 1.69e-7 against 0.80e-7,
+// with ranges of 2048 keys 1.39e-7.
+__device__ __forceinline__ unsigned pack_partial(float m, float l)
+{
+    if (fabsf(m) <= 100.f) return __float_as_uint(ldexpf(l, static_cast<int>(m)));
+    const unsigned v = __float_as_uint(m + __log2f(l));
+    return 0x80000000u | (v & 0x80000000u) >> 1 | ((v & 0x7fffffffu) - (128u << 23));
+}
+__device__ __forceinline__ bool packed_as_log(unsigned u) { return (u & 0x80000000u) != 0; }
+// (m, l) of a packed partial sum
+__device__ __forceinline__ float2 unpack_partial(unsigned u)
+{
+    if (packed_as_log(u))
+        return make_float2(__uint_as_float((u & 0x40000000u) << 1 | ((u & 0x3fffffffu) + (128u << 23))), 1.f);
+    return make_float2(static_cast<float>(static_cast<int>(u >> 23) - 127), __uint_as_float((u & 0x7fffffu) | 0x3f800000u));
+}
 
 template <bool kColsum>
 struct Running {                 // per column block: rowstat (m, l) or colsum partial sum
@@ -139,7 +159,8 @@ struct Running {                 // per column block: rowstat (m, l) or colsum p
 
 // The exponentials of a pending pair, cut into 16 pieces so that one piece can follow each
 // MFMA of the next pair; finish() runs what is left after piece 15.
-template <bool kColsum>
+// kWhole: the row statistics are kept relative to a whole number, the maximum rounded up (pack_partial).
+template <bool kColsum, bool kWhole = false>
 struct Epilogue {
     float ref[2], corr[2], part[2], tmax[2];
 
@@ -175,7 +196,7 @@ struct Epilogue {
             } else if (i == 2) {
 #pragma unroll
                 for (int cb = 0; cb < 2; ++cb) {
-                    ref[cb] = fmaxf(run.m[cb], tmax[cb] * scale);
+                    ref[cb] = fmaxf(run.m[cb], kWhole ? ceilf(tmax[cb] * scale) : tmax[cb] * scale);
                     corr[cb] = fast_exp2(run.m[cb] - ref[cb]);
                     part[cb] = 0.f;
                 }
@@ -518,7 +539,7 @@ __global__ __launch_bounds__(256 * kHalves) void prefill_mfma_kernel(const bf16_
                                                               : 0x80000000u;
                             }
                         }
-                        Epilogue<kColsum> epi;
+                        Epilogue<kColsum, kSplitKeys> epi;
 #pragma unroll
                         for (int s = 0; s < kSteps; ++s)
 #pragma unroll
@@ -596,7 +617,7 @@ __global__ __launch_bounds__(256 * kHalves) void prefill_mfma_kernel(const bf16_
                         for (; t <= t_end; ++t) { stage_sync(t); do_stage(t, std::true_type{}, store_tag); }   // ragged tail
                     }
                     // the last pair still waits for its exponentials
-                    Epilogue<kColsum> epi;
+                    Epilogue<kColsum, kSplitKeys> epi;
 #pragma unroll
                     for (int i = 0; i < 16; ++i)
                         epi.template piece<decltype(store_tag)::value>(i, pend, run, scale_log2, hist_rsrc, cap * 4);
@@ -619,7 +640,7 @@ __global__ __launch_bounds__(256 * kHalves) void prefill_mfma_kernel(const bf16_
                             else do_stage(t, std::false_type{}, add_tag{});
                         }
                         if (idle) continue;
-                        Epilogue<kColsum> epi;
+                        Epilogue<kColsum, kSplitKeys> epi;
 #pragma unroll
                         for (int i = 0; i < 16; ++i) epi.template piece<2>(i, pend, run, scale_log2, hist_rsrc, cap * 4, group_sum[1]);
                         epi.finish(pend, run, scale_log2);
@@ -694,7 +715,7 @@ __global__ __launch_bounds__(256 * kHalves) void prefill_mfma_kernel(const bf16_
                     if constexpr (kSplitKeys) {
                         if (idx >= q_first)
                             win.lse_part[(static_cast<size_t>(pair % win.n_splits) * n_units + unit) * win.part_rows + idx - q_first] =
-                                fin_m[cb] + __log2f(fin_l[cb]);
+                                pack_partial(fin_m[cb], fin_l[cb]);
                     } else if (!kColsum) lse_u[idx] = fin_m[cb] + __log2f(fin_l[cb]);
                     else if (kGrouped && splits > 1)     // partial sum [split, K/V head, cap], mean taken by the merge kernel
                         S[(static_cast<size_t>(split) * (n_units / splits) + unit) * cap + idx] = fin_l[cb];
@@ -731,10 +752,10 @@ int split_stages_for(int n_stages, int part_rows, int cap, int q_units)
     return stages < kSplitStages ? stages : kSplitStages;
 }
 
-// lse2_j = log2 sum_s 2^(part_s[j]) over the key ranges s that begin at or before row j, for the
+// lse2_j = log2 of the sum of the partial sums of the key ranges that begin at or before row j, for the
 // window's queries; the few rows before the window that share its first 64-row stage get 0 (they
 // are streamed, masked, by the column-sum pass and must not be NaN).
-__global__ __launch_bounds__(256) void merge_split_lse_kernel(const float *__restrict__ lse_part,
+__global__ __launch_bounds__(256) void merge_split_lse_kernel(const unsigned *__restrict__ lse_part,
                                                               float *__restrict__ lse2, BatchMeta meta,
                                                               int n_heads, int n_units, int cap, int window,
                                                               int part_rows, int n_splits, int split_stages)
@@ -747,18 +768,32 @@ __global__ __launch_bounds__(256) void merge_split_lse_kernel(const float *__res
     float out = 0.f;
     if (j >= q_first) {
         const int used = min(n_splits, j / (split_stages * kStage) + 1);
-        float m = -INFINITY, l = 0.f;
+        const unsigned *row = lse_part + unit * part_rows + j - q_first;
+        const size_t next = static_cast<size_t>(n_units) * part_rows;
+        float m = 0.f, l = 0.f;
+        bool logs = false;
         for (int s0 = 0; s0 < used; s0 += 8) {
-            float v[8], top = m;
+            unsigned raw[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u)                 // all loads first (ranges past the last one: that one again)
-                v[u] = lse_part[(static_cast<size_t>(min(s0 + u, used - 1)) * n_units + unit) * part_rows + j - q_first];
+            for (int u = 0; u < 8; ++u) raw[u] = row[min(s0 + u, used - 1) * next];     // all loads first
 #pragma unroll
-            for (int u = 0; u < 8; ++u) top = fmaxf(top, v[u]);
-            l *= exp2f(m - top);
-#pragma unroll
-            for (int u = 0; u < 8; ++u) l += s0 + u < used ? exp2f(v[u] - top) : 0.f;
-            m = top;
+            for (int u = 0; u < 8; ++u) {
+                logs |= packed_as_log(raw[u]);
+                l += s0 + u < used ? __uint_as_float(raw[u]) : 0.f;
+            }
+        }
+        if (logs) {
+            m = -INFINITY;
+            for (int s = 0; s < used; ++s) m = fmaxf(m, unpack_partial(row[s * next]).x);
+            l = 0.f;
+            for (int s = 0; s < used; ++s) {
+                const float2 v = unpack_partial(row[s * next]);
+                l += v.y * exp2f(v.x - m);
+            }
+        } else {                                            // (up to 2048 ranges of at most 2^112 each)
+            int e;
+            l = frexpf(l, &e);
+            m = static_cast<float>(e);
         }
         out = m + log2f(l);
     }
@@ -795,7 +830,7 @@ hipError_t launch_window(const void *Q, const void *K, const void *V, float *S, 
     WindowPass win;
     win.window = window;
     win.hist = hist;
-    win.lse_part = lse_part;
+    win.lse_part = reinterpret_cast<unsigned *>(lse_part);
     const int n_stages = (g.max_len + kStage - 1) / kStage;
     win.part_rows = window < g.max_len ? window + 1 : g.max_len;
     win.split_stages = split_stages_for(n_stages, win.part_rows, g.cap, q_units);
@@ -806,7 +841,7 @@ hipError_t launch_window(const void *Q, const void *K, const void *V, float *S, 
                        dim3(256), 0, st, q, k, lse2, S, meta, q_heads, q_units, g.cap, n_blocks, g.scale_log2, win, nullptr,
                        nullptr, 0, g.group, 1);
     const int merge_rows = window + 1 + kStage;
-    hipLaunchKernelGGL(merge_split_lse_kernel, dim3((merge_rows + 255) / 256, q_units), dim3(256), 0, st, lse_part, lse2,
+    hipLaunchKernelGGL(merge_split_lse_kernel, dim3((merge_rows + 255) / 256, q_units), dim3(256), 0, st, win.lse_part, lse2,
                        meta, q_heads, q_units, g.cap, window, win.part_rows, win.n_splits, win.split_stages);
     // Blocks of keys are paired so that workgroups have equal work.  Up to half the prompt, most blocks meet the whole
     // window, the first ones the most of it, and one block to a workgroup puts twice as many of them on the chip to write

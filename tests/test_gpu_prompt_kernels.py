@@ -1,4 +1,5 @@
 """Prompt scores of the kernel variants a grid of some size selects, at the edges of their tiles."""
+import math
 import sys
 
 import pytest
@@ -80,6 +81,62 @@ def test_bf16_scores_on_a_small_grid(gpu_device, d, H, g):
 ])
 def test_bf16_window_key_ranges(gpu_device, d, H, g, window, lens):
     _check_scores(gpu_device, "bf16", d, g, H, lens, window, [(b, H - 1 if b % 2 else 0) for b in range(len(lens))], 231 + g)
+
+
+def _window_rows(Q, K, V, w, dev):
+    """S, the attention rows of the window, and the masked logits of these rows in float64: one sequence, ungrouped heads."""
+    _, H, L, d = Q.shape
+    cache = PrunedKVCache(1, H, d, Q.dtype, 0, 0, [L], dev, window=w)
+    try:
+        cache.prefill_score(Q.to(dev), K.to(dev), V.to(dev), [L])
+        torch.cuda.synchronize()
+        S, rows = cache.S_prompt[0].cpu(), cache.hist_prompt[0].cpu().double()
+    finally:
+        cache.close()
+    first = max(0, L - 1 - w)
+    t = (Q[0, :, first:].double() @ K[0].double().transpose(-1, -2).contiguous()) / d ** 0.5
+    t.masked_fill_(torch.arange(L) > torch.arange(first, L).unsqueeze(1), -math.inf)
+    return S, torch.where(t > -math.inf, rows[:, :L - first], torch.zeros(())), t
+
+
+# The statistics of a row, however many ranges its keys are cut into (16 heads: several), are rounded to a float once.  An
+# attention row sums to 2^(error of its statistic): here two keys, in different ranges, hold nine tenths and one tenth of every
+# row, the others nothing, so that no long sum adds errors of its own.  In units in the last place of the statistic, times ln 2:
+# one rounding has a standard deviation of 1 / sqrt 12, the larger exponential of either pass, good to one unit in its last
+# place (2^-24 of the value, 2^-20 ln 2 being the unit here), adds 0.05 each; over 3200 rows the deviation is known to 1.3 %,
+# four times which is allowed: 0.316.  A second rounding per range makes it sqrt(1 + 0.9^2) / sqrt 12 = 0.39.
+@pytest.mark.parametrize("d", [128, 64])
+def test_window_row_statistics_are_rounded_once(gpu_device, d):
+    H, L, w = 16, 2048, 199
+    print("[case] rounding of windowed row statistics d=%d" % d, flush=True)
+    gen = torch.Generator().manual_seed(261)
+    Q, K, V = (torch.randn(1, H, L, d, generator=gen) for _ in range(3))
+    u = d ** 0.5 * torch.nn.functional.normalize(torch.randn(1, H, 1, d, generator=gen), dim=-1)
+    Q += 4 * d ** -0.5 * u
+    K -= 15 * u
+    K[:, :, :1], K[:, :, 700:701] = 2.5 * u, 2 * u
+    Q, K, V = (t.bfloat16() for t in (Q, K, V))
+    _, rows, t = _window_rows(Q, K, V, w, gpu_device)
+    unit = math.log(2) * torch.exp2(torch.floor(torch.log2(torch.logsumexp(t, -1) / math.log(2))) - 23)
+    spread = ((rows.sum(-1) - 1) / unit).square().mean().sqrt().item()
+    assert spread <= 1.053 * math.sqrt(1 / 12 + 2 * 0.05 ** 2), spread
+
+
+# several key ranges per row whose sums lie beyond 2^100 or below 2^-100 in some heads and not in others
+@pytest.mark.parametrize("d", [128, 64])
+def test_window_key_ranges_of_large_and_small_sums(gpu_device, d):
+    H, L, w = 4, 1500, 30
+    print("[case] large and small sums of key ranges d=%d" % d, flush=True)
+    gen = torch.Generator().manual_seed(271)
+    Q, K, V = (torch.randn(1, H, L, d, generator=gen) for _ in range(3))
+    u = d ** 0.5 * torch.nn.functional.normalize(torch.randn(1, H, 1, d, generator=gen), dim=-1)
+    Q += 8 * d ** -0.5 * u
+    K = (0.2 * K + u * torch.tensor([12.0, -12.0, 9.0, -9.0]).view(1, H, 1, 1)).bfloat16()      # (logits about 8 times that)
+    S, rows, t = _window_rows(Q.bfloat16(), K, V.bfloat16(), w, gpu_device)
+    want = torch.softmax(t, -1)
+    for h in range(H):
+        parity.assert_scores_close(rows[h].numpy(), want[h].numpy(), parity.rtol_for(torch.bfloat16), "rows, head %d" % h)
+        parity.assert_scores_close(S[h].numpy(), want[h].sum(0).numpy(), parity.rtol_for(torch.bfloat16), "S, head %d" % h)
 
 
 # row log-sum-exps handed in: taken as they are by the direct kernels, converted first where they lie under an output; the
