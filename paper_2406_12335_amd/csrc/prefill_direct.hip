@@ -212,7 +212,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_direct_kernel(const T 
     float m[kCols], l[kCols];                    // rowstat: running maximum and sum; colsum: l is the column sum
     float group_sum[kHist ? kCols : 1][16];      // with attention rows: the tile's weights over the group so far
 #pragma unroll
-    for (int c = 0; c < kCols; ++c) { m[c] = -1e30f; l[c] = 0.f; }
+    for (int c = 0; c < kCols; ++c) { m[c] = kLowestLogit; l[c] = 0.f; }
     if constexpr (kHist) {
 #pragma unroll
         for (int c = 0; c < kCols; ++c)

@@ -423,7 +423,7 @@ __global__ __launch_bounds__(256 * kHalves) void prefill_mfma_kernel(const bf16_
 #pragma unroll
                     for (int s = 0; s < kSteps / 2; ++s) Bf[cb][part * (kSteps / 2) + s] = as_bf16x8(s_own[slot_of(n, 2 * s + g)]);
                 }
-            run.m[0] = run.m[1] = -1e30f;
+            run.m[0] = run.m[1] = kLowestLogit;
             run.l[0] = run.l[1] = 0.f;
             run.col[0] = run.col[1] = 0.f;
         }

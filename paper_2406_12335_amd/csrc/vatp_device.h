@@ -408,6 +408,9 @@ __device__ __forceinline__ float group_weight(const float (&t)[kMaxG], const flo
 // kernels take natural logarithms, as an attention kernel hands them over.
 constexpr float kLog2e = 1.44269504088896340736f;
 enum { kPassRowstat = 1, kPassColsum = 2 };
+// Where the running maximum of a row's logits starts: finite, so that masked logits (-inf) stay zeros relative to it, and
+// below every logit, so that a row of very low ones has its sum.
+constexpr float kLowestLogit = -3.402823466e38f;
 
 hipError_t launch_prefill_direct(int dtype, int head_dim, const void *Q, const void *K, const void *V, float *S, float *nrm,
                                  float *lse2, bool natural_lse, float *s_part, int pass, int window, float *hist,

@@ -163,3 +163,26 @@ def test_row_lse_under_an_output(gpu_device, dtype, d, H, lens):
         want = torch.exp(t - lse[i, :, :L].cpu().double().unsqueeze(-1)).tril().sum(dim=1)
         for h in range(H):
             parity.assert_scores_close(S[i, h, :L].cpu().numpy(), want[h].numpy(), parity.rtol_for(dt), "S, sequence %d head %d" % (i, h))
+
+
+# logits far below any that occur: every row's weight is the first key's (the products are powers of two, so that nothing is
+# rounded); direct and staged kernels, a window's key ranges
+@pytest.mark.parametrize("dtype,d,B,H,L,window", [
+    ("fp32", 64, 1, 2, 100, None), ("fp32", 128, 1, 1, 300, 40), ("fp32", 128, 8, 32, 300, None), ("bf16", 64, 1, 2, 100, None),
+    ("bf16", 128, 1, 3, 300, None), ("bf16", 64, 2, 128, 300, None), ("bf16", 128, 3, 64, 300, None), ("bf16", 64, 9, 64, 300, None),
+    ("bf16", 64, 1, 2, 1500, 30), ("bf16", 128, 1, 2, 1500, 30),
+])
+def test_very_low_logits(gpu_device, dtype, d, B, H, L, window):
+    print("[case] low logits %s d=%d B=%d H=%d L=%d window=%s" % (dtype, d, B, H, L, window), flush=True)
+    dt = {"fp32": torch.float32, "bf16": torch.bfloat16}[dtype]
+    Q, K = (torch.zeros(B, H, L, d, dtype=dt, device=gpu_device) for _ in range(2))
+    Q[..., 3], K[..., 3], K[:, :, 0, 3] = 2.0 ** 52, -2.0 ** 54, -2.0 ** 53
+    cache = PrunedKVCache(B, H, d, dt, 0, 0, [L] * B, gpu_device, window=window)
+    try:
+        cache.prefill_score(Q, K, K, [L] * B)
+        S = cache.S_prompt[:, :, :L].cpu()
+    finally:
+        cache.close()
+    want = torch.zeros(B, H, L)
+    want[:, :, 0] = L if window is None else window + 1
+    assert torch.equal(S, want)
