@@ -50,21 +50,10 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 template <typename T, int kCols, int kSteps>
 __device__ __forceinline__ void mfma_chunk(const uint4 &a, const uint4 (&bf)[kCols][kSteps], int s, floatx16 (&acc)[kCols])
 {
-    if constexpr (sizeof(T) == 2) {
 #pragma unroll
-        for (int c = 0; c < kCols; ++c)
-            acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(a), as_bf16x8(bf[c][s]), acc[c], 0, 0, 0);
-    } else {
-        auto step = [&](unsigned x, auto part) __attribute__((always_inline)) {
+    for (int e = 0; e < kMfmasPerChunk<T>; ++e)
 #pragma unroll
-            for (int c = 0; c < kCols; ++c)
-                acc[c] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(x), __uint_as_float(part(bf[c][s])), acc[c], 0, 0, 0);
-        };
-        step(a.x, [](const uint4 &b) { return b.x; });
-        step(a.y, [](const uint4 &b) { return b.y; });
-        step(a.z, [](const uint4 &b) { return b.z; });
-        step(a.w, [](const uint4 &b) { return b.w; });
-    }
+        for (int c = 0; c < kCols; ++c) acc[c] = mfma_piece<T>(a, bf[c][s], e, acc[c]);
 }
 
 enum { kRowstat, kColsumPlain, kColsumHist };      // passes
@@ -291,7 +280,8 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_direct_kernel(const T 
             if constexpr (kColsum) {
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
-                    const float p = fast_exp2(fmaf(acc[c][v], scale, -lse_v[v]));
+                    // (weights that are stored keep their value below 2^-126: 0.5 % of a pass that stores its rows)
+                    const float x = fmaf(acc[c][v], scale, -lse_v[v]), p = kHist ? exp2f(x) : fast_exp2(x);
                     l[c] += p;
                     if constexpr (kHist) group_sum[c][v] += p;
                 }
@@ -332,11 +322,28 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_direct_kernel(const T 
         if constexpr (!kColsum) s_max[2 * wave + g][kTileRows * c + n] = m[c];
     }
     __syncthreads();
-    if (tid < kBlock && base0 + tid < len) {
-        float sum = 0.f;
-        if constexpr (kColsum) {
+    float sum = 0.f;
+    if constexpr (kColsum) {
+        // (every wavefront adds them all up, so that each knows whether one is too small, without another barrier)
+        auto total = [&]() __attribute__((always_inline)) {
+            float x = 0.f;
 #pragma unroll
-            for (int w = 0; w < 2 * kWaves; ++w) sum += s_part[w][tid];
+            for (int w = 0; w < 2 * kWaves; ++w) x += s_part[w][lane % kBlock];
+            return x;
+        };
+        sum = total();
+        if (!kHist && __any(base0 + lane % kBlock < len && sum < kSubnormalLoss)) {
+            lds_barrier();
+#pragma unroll 1
+            for (int c = 0; c < kCols; ++c)
+                s_part[2 * wave + g][kTileRows * c + n] = column_sum_subnormal<T, D, false>(
+                    stat, strm, lse_u, scale, a.lse_scale, 0.f, base0 + kTileRows * c, len, cap, q_first, heads, t_first + wave, kWaves, lane);
+            lds_barrier();
+            sum = total();
+        }
+    }
+    if (tid < kBlock && base0 + tid < len) {
+        if constexpr (kColsum) {
             // (several workgroups: partial sum [split, K/V head, cap], the mean is taken by the merge kernel)
             if (a.splits > 1) S[(static_cast<size_t>(split) * a.n_units + unit) * cap + base0 + tid] = sum;
             else S[unit * cap + base0 + tid] = sum * inv_group;

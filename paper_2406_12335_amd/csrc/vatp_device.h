@@ -284,6 +284,78 @@ typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16;
 __device__ __forceinline__ bf16x8 as_bf16x8(const uint4 &u) { return __builtin_bit_cast(bf16x8, u); }
 __device__ __forceinline__ constexpr int acc_row(int v) { return 8 * (v / 4) + (v % 4); }
+// MFMA e of those that contract a 16-byte chunk per lane of either operand (bf16 one, fp32 four)
+template <typename T> constexpr int kMfmasPerChunk = sizeof(T) == 2 ? 1 : 4;
+template <typename T>
+__device__ __forceinline__ floatx16 mfma_piece(const uint4 &a, const uint4 &b, int e, const floatx16 &acc)
+{
+    if constexpr (sizeof(T) == 2) return __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(a), as_bf16x8(b), acc, 0, 0, 0);
+    const unsigned x = e == 0 ? a.x : e == 1 ? a.y : e == 2 ? a.z : a.w, y = e == 0 ? b.x : e == 1 ? b.y : e == 2 ? b.z : b.w;
+    return __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(x), __uint_as_float(y), acc, 0, 0, 0);
+}
+
+// The passes over a prompt form their exponentials with v_exp_f32, which returns 0 below 2^-126.  A column sum of up to 2^26
+// weights loses less than 2^-100 by it: from this limit on that is less than a quarter of its own last place.  A sum below is formed once
+// more by column_sum_subnormal, with weights down to 2^-149.
+constexpr float kSubnormalLoss = 0x1p-72f;
+
+// One wavefront's share of the scores (Eq. 2, Eq. 3) of the 32 keys from col0 on: the query rows of tiles t_begin,
+// t_begin + t_step, ... of 32, for the `heads` query heads from `queries` on.  Lane (g, n) returns the sum over its 16 rows
+// of every tile for key col0 + n; kRows: where hist is not null, the attention weights (the heads' sums, divided by 2^lse_add)
+// are stored as well.  Operands come straight from memory, in few registers, and nothing is overlapped: for scores that hardly
+// ever occur.
+template <typename T, int D, bool kRows>
+__device__ __forceinline__ float column_sum_subnormal(const uint4 *keys, const uint4 *queries, const float *lse, float scale,
+                                                      float lse_scale, float lse_add, int col0, int len, int cap, int q_first,
+                                                      int heads, int t_begin, int t_step, int lane, float *hist = nullptr)
+{
+    constexpr int kChunks = D * static_cast<int>(sizeof(T)) / 16;
+    const int g = lane >> 5, n = lane & 31, col = col0 + n;
+    const uint4 *key = keys + static_cast<size_t>(min(col, len - 1)) * kChunks + g;
+    float sum = 0.f;
+    // one tile of one query head: term(v, row, weight)
+    auto tile = [&](int t, int h, auto term) __attribute__((always_inline)) {
+        const uint4 *row = queries + (static_cast<size_t>(h) * cap + min(t * 32 + n, len - 1)) * kChunks + g;
+        floatx16 acc;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+#pragma unroll 1
+        for (int s = 0; s < kChunks / 2; ++s) {
+            const uint4 a = row[2 * s], b = key[2 * s];
+#pragma unroll
+            for (int e = 0; e < kMfmasPerChunk<T>; ++e) acc = mfma_piece<T>(a, b, e, acc);
+        }
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int r = t * 32 + 4 * g + acc_row(v);
+            const float l = fmaf(lse[static_cast<size_t>(h) * cap + min(r, len - 1)], lse_scale, lse_add);
+            term(v, r, r >= col && r >= q_first && r < len ? exp2f(fmaf(acc[v], scale, -l)) : 0.f);
+        }
+    };
+    if constexpr (!kRows) {
+#pragma unroll 1
+        for (int h = 0; h < heads; ++h)
+#pragma unroll 1
+            for (int t = t_begin; t * 32 < len; t += t_step) tile(t, h, [&](int, int, float p) { sum += p; });
+        return sum;
+    }
+#pragma unroll 1
+    for (int t = t_begin; t * 32 < len; t += t_step) {
+        float w[16];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) w[v] = 0.f;
+#pragma unroll 1
+        for (int h = 0; h < heads; ++h) tile(t, h, [&](int v, int, float p) { w[v] += p; });
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int r = t * 32 + 4 * g + acc_row(v);
+            if (hist && col < len && r >= col && r >= q_first && r < len) hist[static_cast<size_t>(r - q_first) * cap + col] = w[v];
+            sum += w[v];
+        }
+    }
+    return sum;
+}
+
 // Rows of kChunks 16-byte chunks staged in LDS: where chunk c of row r sits, so that 16 consecutive rows that read one chunk
 // index hit 16 different 16-byte slots of the 64 banks (two 128-byte rows share a span of the banks: there the row pair
 // is what is permuted by).

@@ -186,3 +186,38 @@ def test_very_low_logits(gpu_device, dtype, d, B, H, L, window):
     want = torch.zeros(B, H, L)
     want[:, :, 0] = L if window is None else window + 1
     assert torch.equal(S, want)
+
+
+# weights and scores below the smallest normal number keep their value: one coordinate, keys but the first 2^-128 .. 2^-143 of it.
+# The exponent is good to a unit of 2^-17 (rounding it) plus 2^-25 of itself (the scale's), times ln 2: 8e-6; every weight is
+# a multiple of 2^-149.  (bf16 heads of 128: on the small grids.)
+@pytest.mark.parametrize("dtype,d,B,H,g,L,window", [
+    ("fp32", 64, 1, 2, 1, 100, None), ("fp32", 128, 1, 1, 3, 300, 40), ("fp32", 128, 8, 32, 1, 300, None), ("fp32", 64, 1, 2, 1, 77, 5),
+    ("bf16", 64, 1, 2, 1, 100, None), ("bf16", 128, 1, 3, 1, 300, None), ("bf16", 64, 1, 1, 8, 1100, None),
+    ("bf16", 64, 4, 64, 1, 80, None), ("bf16", 64, 2, 128, 1, 300, None), ("bf16", 64, 9, 64, 1, 310, None),
+    ("bf16", 64, 2, 64, 4, 290, None), ("bf16", 64, 32, 8, 2, 600, None),
+    ("bf16", 64, 1, 2, 1, 1500, 30), ("bf16", 64, 3, 2, 2, 700, 90),
+])
+def test_weights_below_the_normal_range(gpu_device, dtype, d, B, H, g, L, window):
+    print("[case] denormal weights %s d=%d B=%d H=%d g=%d L=%d window=%s" % (dtype, d, B, H, g, L, window), flush=True)
+    dt = {"fp32": torch.float32, "bf16": torch.bfloat16}[dtype]
+    Q, K = (torch.zeros(B, n, L, d, dtype=dt) for n in (H * g, H))
+    Q[..., 3] = 1
+    acc = -8.0 * ({64: 89, 128: 126}[d] + (torch.arange(L) * 7) % 11).view(1, 1, L) * torch.ones(B, H, 1)
+    acc[:, 1::2] = acc[:, 1::2].flip(-1)
+    acc[:, :, 0] = 0
+    K[..., 3] = acc.to(dt)
+    cache = PrunedKVCache(B, H, d, dt, 0, 0, [L] * B, gpu_device, window=window, q_per_kv=g)
+    try:
+        cache.prefill_score(Q.to(gpu_device), K.to(gpu_device), K.to(gpu_device), [L] * B)
+        S = cache.S_prompt[:, :, :L].cpu().double()
+        hist = cache.hist_prompt[:, :, :, :L].cpu().double() if window is not None else None
+    finally:
+        cache.close()
+    p = torch.exp(acc.double() / d ** 0.5)
+    first = 0 if window is None else L - 1 - window
+    rows = (L - torch.arange(L).clamp(min=first)).double()
+    assert ((S - rows * p).abs() <= 1e-5 * rows * p + rows * 2.0 ** -149).all()
+    if window is not None:
+        seen = torch.arange(L) <= torch.arange(first, L).unsqueeze(1)
+        assert ((hist - p.unsqueeze(2)).abs() <= 1e-5 * p.unsqueeze(2) + 2.0 ** -149)[:, :, seen].all()
