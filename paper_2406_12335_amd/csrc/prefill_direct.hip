@@ -43,6 +43,7 @@ namespace vatp {
 namespace {
 
 constexpr int kTileRows = 32;      // rows of a tile, streamed and stationary
+constexpr unsigned kGridX = 1u << 22;      // workgroups of a launch in x (a dimension holds 2^32 work items), the rest in y
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
@@ -90,7 +91,9 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_direct_kernel(const T 
 
     // Units in the fast dimension: workgroups go to the 8 XCDs round-robin, so with a unit count that is a multiple of 8
     // a unit's workgroups meet in one L2 and with fewer units they spread over the chip.  The longest columns first.
-    const int slot = blockIdx.x % (a.n_units * a.splits), rank = blockIdx.x / (a.n_units * a.splits);
+    const unsigned id = blockIdx.x + blockIdx.y * kGridX, slots = a.n_units * a.splits;
+    const int slot = id % slots, rank = id / slots;
+    if (rank >= a.n_blocks) return;
     const int unit_i = slot % a.n_units, split = slot / a.n_units;
     const int blk = kColsum ? rank : a.n_blocks - 1 - rank;
     const int len = meta.len[unit_i / a.n_heads];
@@ -368,7 +371,9 @@ void launch_pass(const T *Q, const T *K, const T *V, float *S, float *nrm, float
         a.splits = 1;
     }
     a.n_blocks = (max_len + kTileRows * kCols - 1) / (kTileRows * kCols);
-    hipLaunchKernelGGL((prefill_direct_kernel<T, D, kPass, kCols, kWaves, kStaged>), dim3(static_cast<unsigned>(a.n_units) * a.splits * a.n_blocks),
+    // (at most 2^14 units times query heads of a group, 2^17 blocks)
+    const unsigned n = static_cast<unsigned>(a.n_units) * a.splits * a.n_blocks;
+    hipLaunchKernelGGL((prefill_direct_kernel<T, D, kPass, kCols, kWaves, kStaged>), dim3(n < kGridX ? n : kGridX, (n + kGridX - 1) / kGridX),
                        dim3(64 * kWaves), 0, st, Q, K, V, lse2, S, nrm, hist, meta, a);
 }
 

@@ -145,3 +145,46 @@ def test_decode_and_evict_on_a_cache_of_a_million_rows(gpu_device, dtype, d):
     parity.assert_scores_close(No[0, 0, :n0].cpu().numpy(), nrm_or[got], rtol, "nrm of the survivors")
     pos_ref = np.concatenate([np.arange(n0), [n0 + 5]])
     np.testing.assert_array_equal(po[0, 0, :n0].cpu().numpy(), pos_ref[got])
+
+
+def _window_of_one(Q, K, units, lens, dtype, d, B, H, cap, dev):
+    """Scores and attention rows of a window of one step of the given (sequence, head) units against a float64 softmax."""
+    ctx = vatp.vatp_create(0)
+    try:
+        p = vatp.Params(B, H, d, dtype, 0, 0, cap, lens)
+        ws = torch.empty(vatp.vatp_workspace_bytes(ctx, p, vatp.binding.CALL_PREFILL_SCORE_WINDOW), dtype=torch.uint8, device=dev)
+        S, nrm, hist = (torch.empty(B, H, cap, device=dev) for _ in range(3))
+        vatp.vatp_prefill_score_window(ctx, p, Q, K, K, 0, S, nrm, hist, ws)
+        torch.cuda.synchronize()
+    finally:
+        vatp.vatp_destroy(ctx)
+    for b, h in units:
+        L = lens[b]
+        t = (K[b, h, :L].double() * Q[b, h, L - 1].double()).sum(-1) / d ** 0.5
+        want = torch.softmax(t, 0).cpu().numpy()
+        parity.assert_scores_close(S[b, h, :L].cpu().numpy(), want, parity.rtol_for(dtype), "S, sequence %d head %d" % (b, h))
+        parity.assert_scores_close(hist[b, h, :L].cpu().numpy(), want, parity.rtol_for(dtype), "row, sequence %d head %d" % (b, h))
+        want = K[b, h, :L].double().abs().sum(-1).cpu().numpy()
+        parity.assert_scores_close(nrm[b, h, :L].cpu().numpy(), want, parity.rtol_for(dtype), "nrm, sequence %d head %d" % (b, h))
+
+
+def test_windowed_prompts_of_2_28_rows_in_all(gpu_device):
+    """256 sequences of 64 heads of 16384 rows (most of them empty): 2^23 workgroups of 512 work items in a launch.  One
+    tensor of 69 GB is queries, keys and values."""
+    B, H, cap, d = 256, 64, 16384, 64
+    _say("2^28 windowed rows")
+    X = torch.empty(B, H, cap, d, device=gpu_device)
+    g = torch.Generator(device=gpu_device).manual_seed(23)
+    X[0].normal_(generator=g)
+    X[255].normal_(generator=g)
+    _window_of_one(X, X, [(0, 0), (0, 63), (255, 31)], [16384] + [0] * 254 + [1000], torch.float32, d, B, H, cap, gpu_device)
+
+
+@pytest.mark.parametrize("dtype,d", [(torch.float32, 64), (torch.bfloat16, 64), (torch.bfloat16, 128)])
+def test_windowed_prompt_of_two_million_rows(gpu_device, dtype, d):
+    """One head of 2097217 rows: 65538 blocks of 32 keys, and bf16 rows beyond the 32-bit offsets of the staged kernels."""
+    L = (1 << 21) + 65
+    _say("windowed prompt of %d rows, %s d=%d" % (L, dtype, d))
+    g = torch.Generator(device=gpu_device).manual_seed(29)
+    X = torch.randn(1, 1, L, d, generator=g, device=gpu_device).to(dtype)
+    _window_of_one(X, X, [(0, 0)], [L], dtype, d, 1, 1, L, gpu_device)
