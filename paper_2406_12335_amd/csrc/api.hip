@@ -244,14 +244,15 @@ vatp_status prefill_score_impl(vatp_ctx *ctx, const vatp_params *p, const void *
         for (int pass : {kPassRowstat, kPassColsum}) {          // (the column sums need the row statistics)
             if (e != hipSuccess || (have_lse && pass == kPassRowstat)) continue;
             const bool staged = window < 0 && p->dtype == VATP_BF16 && prefill_mfma_fills(p->head_dim, pass, pr.g);
-            // Row statistics handed in: the direct kernels take them as they are (unless an output lies over them, since
-            // workgroups write outputs while others still read).  Measured, with the conversion in a launch of its own /
+            // Row statistics handed in: the direct kernels take them as they are (unless an output or the partial sums lie over
+            // them, since workgroups write these while others still read).  Measured, with the conversion in a launch of its own /
             // without: 4 heads of 64 x 256 fp32 rows 12.1 / 8.0 us, 2 x 8 x 4 query heads x 700 rows 20.5 / 17.8, 32 heads x
             // 2000 rows 36.4 / 34.9.  The staged kernels copy them to LDS and have no instruction to spare for them: there
             // the launch takes 5.6 of 586 us, at 8 x 8 x 4 query heads x 4001 rows.
             const size_t bytes = units * p->cap * sizeof(float);
             const bool natural = have_lse && !staged && !overlap(lse, bytes * pr.g.group, S, bytes) &&
-                                 !overlap(lse, bytes * pr.g.group, nrm, bytes);
+                                 !overlap(lse, bytes * pr.g.group, nrm, bytes) &&
+                                 !(s_part && overlap(lse, bytes * pr.g.group, s_part, bytes * pr.g.group));
             if (have_lse && !natural) e = launch_lse_to_base2(lse, lse2, pr.meta, pr.g, stream);
             if (e != hipSuccess) break;
             if (staged)

@@ -165,6 +165,51 @@ def test_row_lse_under_an_output(gpu_device, dtype, d, H, lens):
             parity.assert_scores_close(S[i, h, :L].cpu().numpy(), want[h].numpy(), parity.rtol_for(dt), "S, sequence %d head %d" % (i, h))
 
 
+# the same for a group's query heads, whose statistics take `group` times the room of an output: either output over some part of
+# them, and they in the part of the workspace that takes the partial sums of a head dealt out to several workgroups
+@pytest.mark.parametrize("over", ["S first", "S last", "nrm first", "nrm last", "partial sums"])
+@pytest.mark.parametrize("dtype,d,H,g,lens", [("fp32", 64, 2, 1, [65, 1, 256]), ("fp32", 64, 1, 4, [600]), ("bf16", 128, 1, 8, [1030]),
+                                              ("bf16", 64, 2, 3, [130, 33])])
+def test_row_lse_of_a_group_under_other_buffers(gpu_device, dtype, d, H, g, lens, over):
+    print("[case] lse under %s %s d=%d H=%d g=%d lens=%s" % (over, dtype, d, H, g, lens), flush=True)
+    dt, b, cap, gen = {"fp32": torch.float32, "bf16": torch.bfloat16}[dtype], len(lens), max(lens), torch.Generator().manual_seed(253)
+    Q = torch.randn(b, H * g, cap, d, generator=gen).to(dt)
+    K, V = (torch.randn(b, H, cap, d, generator=gen).to(dt) for _ in range(2))
+    lse = 4 + torch.rand(b, H * g, cap, generator=gen)
+    n, out = lse.numel(), b * H * cap
+    Qd, Kd, Vd, lse_d = (t.to(gpu_device) for t in (Q, K, V, lse))
+    ctx = vatp.vatp_create(0)
+    try:
+        p = vatp.Params(b, H, d, dt, 0, 0, cap, lens, lens, q_per_kv=g)
+        need = vatp.vatp_workspace_bytes(ctx, p, vatp.binding.CALL_PREFILL_SCORE)
+        ws = torch.empty(need + 4 * n, dtype=torch.uint8, device=gpu_device)
+        S, nrm = torch.zeros(b, H, cap, device=gpu_device), torch.zeros(b, H, cap, device=gpu_device)
+        vatp.vatp_prefill_score_lse(ctx, p, Qd, Kd, Vd, lse_d, S, nrm, ws)
+        S_over, nrm_over = torch.zeros_like(S), torch.zeros_like(nrm)
+        if over == "partial sums":
+            start = (4 * n + 255) // 256 * 256                 # (behind the base-2 statistics)
+            under = ws[start:start + 4 * n].view(torch.float32).view_as(lse_d).copy_(lse_d)
+        else:
+            under = lse_d.clone()
+            first = 0 if over.endswith("first") else n - out
+            part = under.view(-1)[first:first + out].view(b, H, cap)
+            if over.startswith("S"):
+                S_over = part
+            else:
+                nrm_over = part
+        vatp.vatp_prefill_score_lse(ctx, p, Qd, Kd, Vd, under, S_over, nrm_over, ws)
+        torch.cuda.synchronize()
+    finally:
+        vatp.vatp_destroy(ctx)
+    for i, L in enumerate(lens):
+        assert torch.equal(S[i, :, :L], S_over[i, :, :L]) and torch.equal(nrm[i, :, :L], nrm_over[i, :, :L])
+        Kg = K[i, :, :L].double().repeat_interleave(g, 0)
+        t = (Q[i, :, :L].double() @ Kg.transpose(-1, -2).contiguous()) / d ** 0.5
+        want = torch.exp(t - lse[i, :, :L].double().unsqueeze(-1)).tril().sum(dim=1).view(H, g, L).mean(1)
+        for h in range(H):
+            parity.assert_scores_close(S[i, h, :L].cpu().numpy(), want[h].numpy(), parity.rtol_for(dt), "S, sequence %d head %d" % (i, h))
+
+
 # logits far below any that occur: every row's weight is the first key's (the products are powers of two, so that nothing is
 # rounded); direct and staged kernels, a window's key ranges
 @pytest.mark.parametrize("dtype,d,B,H,L,window", [
