@@ -219,6 +219,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_direct_kernel(const T 
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[c][v] = 0.f;
         // the tile's row statistics arrive one per lane and go through the wavefront's own LDS row (no barrier)
+        if constexpr (kStaged || kColsum) lds_wave_order();
         if constexpr (kColsum) s_lse[wave][n] = lse_next * a.lse_scale;
         const bool more = i + 1 < n_items;
         int t_next = t, h_next = h;
@@ -229,12 +230,15 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_direct_kernel(const T 
             if (kColsum) lse_next = lse_u[static_cast<size_t>(h_next) * cap + min(t_next * kTileRows + n, len - 1)];
         }
         if constexpr (kStaged) {
-            // (the wavefront's own LDS tile: its LDS operations are in order, no barrier)
+            // (the wavefront's own LDS tile)
 #pragma unroll
             for (int i = 0; i < kLoads; ++i) {
                 const int p = 64 * i + lane, r = p / kChunks;
                 s_tile[wave][r * kChunks + tile_slot<kChunks>(r, p % kChunks)] = af[i];
             }
+        }
+        if constexpr (kStaged || kColsum) lds_wave_order();
+        if constexpr (kStaged) {
             if (more) {
 #pragma unroll
                 for (int i = 0; i < kLoads; ++i) af[i] = piece(src_next, t_next, i);

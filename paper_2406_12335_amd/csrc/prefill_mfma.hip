@@ -403,24 +403,24 @@ __global__ __launch_bounds__(256 * kHalves, D == 64 && kColsum && kHalves == 1 &
 
         // stationary operand: 2 column blocks x kSteps MFMA steps, 8 bf16 per lane each.  Read in order, half of the
         // chunks of 32 rows (one column block) at a time, and brought into the operand's layout by way of this wavefront's
-        // quarter of the ring's last slot, which no copy fills before the first stage has been published; LDS operations
-        // of a wavefront are in order, so without a barrier.  (Straight from memory a load touched 64 rows, 64 accesses
+        // quarter of the ring's last slot, which no copy fills before the first stage has been published; the
+        // exchange is one of lanes of a wavefront, without a barrier.  (Straight from memory a load touched 64 rows, 64 accesses
         // to the vector cache.  Measured, both passes: 32 heads x 4096 rows 161.5 -> 158.2 us, 64 heads of 64 x 2048 68.9 ->
         // 65.5, 512 heads of 1024..8192 rows 3794 -> 3757.)
         constexpr int kPart = kChunksPerRow / 2, kPartRows = 64 / kPart, kPartLoads = 32 / kPartRows;
         static_assert(kAhead < kRing && 32 * kPart * 16 * 4 * kHalves <= kSlotBytes, "a piece of the last slot per wavefront");
         const int pr = lane / kPart, pc = lane % kPart;
         if (qh == 0) {
-            uint4 raw[2][2][kPartLoads];
+            bf16x8 raw[2][2][kPartLoads];
 #pragma unroll
             for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
                 for (int part = 0; part < 2; ++part)
 #pragma unroll
                     for (int i = 0; i < kPartLoads; ++i)
-                        raw[cb][part][i] = stat[static_cast<size_t>(min(w0 + 32 * cb + kPartRows * i + pr, len - 1)) * kChunksPerRow +
-                                                part * kPart + pc];
-            uint4 *s_own = &stage[kRing - 1][wave * 32 * kPart];
+                        raw[cb][part][i] = as_bf16x8(stat[static_cast<size_t>(min(w0 + 32 * cb + kPartRows * i + pr, len - 1)) *
+                                                              kChunksPerRow + part * kPart + pc]);
+            bf16x8 *s_own = reinterpret_cast<bf16x8 *>(&stage[kRing - 1][wave * 32 * kPart]);
             auto slot_of = [](int r, int c) { return r * kPart + (c ^ ((kPart == 8 ? r >> 1 : r >> 2) & (kPart - 1))); };
 #pragma unroll
             for (int cb = 0; cb < 2; ++cb)
@@ -428,8 +428,10 @@ __global__ __launch_bounds__(256 * kHalves, D == 64 && kColsum && kHalves == 1 &
                 for (int part = 0; part < 2; ++part) {
 #pragma unroll
                     for (int i = 0; i < kPartLoads; ++i) s_own[slot_of(kPartRows * i + pr, pc)] = raw[cb][part][i];
+                    lds_wave_order();
 #pragma unroll
-                    for (int s = 0; s < kSteps / 2; ++s) Bf[cb][part * (kSteps / 2) + s] = as_bf16x8(s_own[slot_of(n, 2 * s + g)]);
+                    for (int s = 0; s < kSteps / 2; ++s) Bf[cb][part * (kSteps / 2) + s] = s_own[slot_of(n, 2 * s + g)];
+                    lds_wave_order();
                 }
             run.m[0] = run.m[1] = kLowestLogit;
             run.l[0] = run.l[1] = 0.f;
