@@ -6,6 +6,7 @@ import pytest
 import torch
 
 import parity
+import vatp_synth as vs
 from oracle import vatp_oracle as orc
 import paper_2406_12335_amd as vatp
 from paper_2406_12335_amd.runner import PrunedKVCache
@@ -138,3 +139,19 @@ def test_infinity_in_the_new_value_row_stays_an_infinity(gpu_device, dtype, d, g
     want = torch.zeros(d, dtype=torch.bool)
     want[3] = True
     assert torch.equal(torch.isinf(out.cpu()), want.expand(1, 2 * g, d)) and not torch.isnan(out).any()
+
+
+# the same launch with a history window, whose rows come by way of the ring's columns: shares of more rows than a workgroup
+# holds in registers (2048, of more than 8 query heads 512), by one workgroup per head and by sixteen
+@pytest.mark.parametrize("dtype,d,b,H,g,L,window", [
+    ("bf16", 64, 1, 1, 1, 35000, 5), ("fp32", 128, 1, 64, 8, 2300, 9), ("bf16", 64, 1, 32, 16, 700, 12), ("bf16", 128, 8, 64, 1, 2200, 3),
+])
+def test_windowed_second_launch_with_large_shares(gpu_device, dtype, d, b, H, g, L, window):
+    print("[case] windowed shares %s d=%d b=%d H=%d g=%d L=%d w=%d" % (dtype, d, b, H, g, L, window), flush=True)
+    cfg = vs.scaled(vs.CONFIGS["llama7b_layer"], batch=b, n_heads=H, head_dim=d, dtype=dtype, q_per_kv=g, prompt_len=L,
+                    decode_steps=window + 4, recent=40)
+    inp = vs.make_inputs(cfg, seed=71, device=gpu_device)
+    inp.budgets = [L * 97 // 100] * b
+    rep = parity.run_trajectory(inp, gpu_device, units=[(0, 0)] if b * H == 1 else [(0, 1), (b - 1, H - 1)], fused=True, window=window)
+    print("report %r" % rep, flush=True)
+    assert rep.admitted_near_ties <= 1

@@ -24,9 +24,9 @@ def _say(msg):
 CASES = [
     # dtype, d, K/V heads, g, prompt length, batch
     ("fp32", 64, 2, 2, 200, 1),
-    ("bf16", 128, 2, 4, 333, 1),        # matrix-core passes, 8-wavefront workgroups, ragged last block
+    ("bf16", 128, 2, 4, 333, 1),        # a small grid: direct kernels, ragged last block
     ("bf16", 128, 3, 3, 700, 2),        # a group size that is not a power of two
-    ("bf16", 128, 40, 8, 520, 1),       # 4-wavefront workgroups in both passes
+    ("bf16", 128, 40, 8, 520, 1),       # staged kernels, 4-wavefront workgroups in both passes
     ("bf16", 64, 2, 8, 150, 1),
     ("fp32", 128, 1, 5, 97, 2),
     ("bf16", 128, 2, 16, 400, 1),       # the largest group: 16 query heads per K/V head

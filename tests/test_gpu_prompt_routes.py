@@ -1,0 +1,139 @@
+"""Prompt scores on the kernels that a plain small call does not reach: staged grids of eight-wavefront workgroups, row log-sum-exps
+handed in on staged grids, history windows on the direct kernels."""
+import pytest
+import torch
+
+import parity
+import paper_2406_12335_amd as vatp
+import vatp_synth as vs
+from oracle import vatp_oracle as orc
+
+pytestmark = pytest.mark.gpu
+
+
+def _inputs(dtype, d, g, H, lens, seed):
+    cfg = vs.scaled(vs.CONFIGS["llama7b_layer"], batch=len(lens), n_heads=H, head_dim=d, dtype=dtype, q_per_kv=g,
+                    prompt_len=max(lens), decode_steps=0, n_sinks=1)
+    inp = vs.make_inputs(cfg, seed=seed)
+    for t in (inp.Q, inp.K, inp.V):
+        for b, L in enumerate(lens):
+            t[b, :, L:] = 77.0                  # (rows past the end hold junk)
+    return inp, cfg.torch_dtype()
+
+
+def _call(name, dev, inp, dt, d, g, H, lens, cap, *extra):
+    """S and nrm of one prompt call; rows past the end keep what they held."""
+    B = len(lens)
+    which = vatp.binding.CALL_PREFILL_SCORE_WINDOW if name.endswith("window") else vatp.binding.CALL_PREFILL_SCORE
+    ctx = vatp.vatp_create(0)
+    try:
+        p = vatp.Params(B, H, d, dt, 0, 0, cap, lens, None, q_per_kv=g)
+        ws = torch.empty(vatp.vatp_workspace_bytes(ctx, p, which), dtype=torch.uint8, device=dev)
+        S, nrm = (torch.full((B, H, cap), -3.0, device=dev) for _ in range(2))
+        head, tail = ([], list(extra)) if name.endswith("window") else (list(extra), [])
+        if name.endswith("window"):
+            window, hist = tail
+            getattr(vatp, name)(ctx, p, *inp, window, S, nrm, hist, ws)
+        else:
+            getattr(vatp, name)(ctx, p, *inp, *head, S, nrm, ws)
+        torch.cuda.synchronize()
+    finally:
+        vatp.vatp_destroy(ctx)
+    for b, L in enumerate(lens):
+        assert torch.all(S[b, :, L:] == -3.0) and torch.all(nrm[b, :, L:] == -3.0)
+    return S, nrm
+
+
+def _check(S, nrm, inp, dt, lens, units, want):
+    for b, h in units:
+        L = lens[b]
+        parity.assert_scores_close(S[b, h, :L].cpu().numpy(), want(b, h, L), parity.rtol_for(dt), "S len %d head %d" % (L, h))
+        parity.assert_scores_close(nrm[b, h, :L].cpu().numpy(), orc.l1norm(inp.V[b, h, :L].double().numpy()), parity.rtol_for(dt), "nrm")
+
+
+# Staged grids of eight-wavefront workgroups: heads times pairs of 256-row blocks (of a group: times the workgroups that share its
+# query heads) between 192 and 256, at rows of 64 between 240 and 256; ragged ends, short sequences beside the long one
+STAGED = [
+    (64, 64, 1, [1990]), (64, 64, 1, [2047]), (64, 10, 1, [1800, 1, 63, 65, 129, 257]), (64, 4, 8, [2047, 65]),
+    (128, 32, 1, [4001]), (128, 6, 1, [2900, 1, 63, 65, 129, 257]), (128, 8, 4, [4001]), (128, 3, 8, [2049, 300]),
+]
+
+
+def _staged_units(H, lens):
+    return [(b, 0 if b % 2 else H - 1) for b in range(len(lens))]
+
+
+@pytest.mark.parametrize("d,H,g,lens", STAGED)
+def test_staged_scores_of_eight_wavefront_workgroups(gpu_device, d, H, g, lens):
+    print("[case] staged d=%d H=%d g=%d lens=%s" % (d, H, g, lens), flush=True)
+    inp, dt = _inputs("bf16", d, g, H, lens, 301)
+    S, nrm = _call("vatp_prefill_score", gpu_device, [t.to(gpu_device) for t in (inp.Q, inp.K, inp.V)], dt, d, g, H, lens, max(lens))
+    _check(S, nrm, inp, dt, lens, _staged_units(H, lens),
+           lambda b, h, L: orc.prefill_scores_group(inp.Q[b, h * g:(h + 1) * g, :L].double().numpy(), inp.K[b, h, :L].double().numpy()))
+
+
+# the same with row log-sum-exps handed in, which a launch of its own takes to base 2; and four-wavefront workgroups (512 and
+# more), a group's query heads walked by one workgroup (8 sequences of 22 heads, 3 pairs each) or dealt out to two (of 16 heads)
+@pytest.mark.parametrize("d,H,g,lens", STAGED + [(d, H, 2, [1300, 1, 64, 255, 513, 7, 33, 800]) for d in (64, 128) for H in (16, 22)])
+def test_staged_scores_from_given_row_lse(gpu_device, d, H, g, lens):
+    print("[case] staged, lse given d=%d H=%d g=%d lens=%s" % (d, H, g, lens), flush=True)
+    inp, dt = _inputs("bf16", d, g, H, lens, 303)
+    lse = 4 + torch.rand(len(lens), H * g, max(lens), generator=torch.Generator().manual_seed(7))
+    units = _staged_units(H, lens)
+    for b, h in units:                           # true ones where they are checked
+        for r in range(h * g, (h + 1) * g):
+            lse[b, r, :lens[b]] = torch.from_numpy(orc.row_lse(inp.Q[b, r, :lens[b]].double().numpy(), inp.K[b, h, :lens[b]].double().numpy())).float()
+    S, nrm = _call("vatp_prefill_score_lse", gpu_device, [t.to(gpu_device) for t in (inp.Q, inp.K, inp.V)], dt, d, g, H, lens, max(lens),
+                   lse.to(gpu_device))
+
+    def want(b, h, L):
+        return sum(orc.prefill_scores_given_lse(inp.Q[b, r, :L].double().numpy(), inp.K[b, h, :L].double().numpy(), lse[b, r, :L].double().numpy())
+                   for r in range(h * g, (h + 1) * g)) / g
+
+    _check(S, nrm, inp, dt, lens, units, want)
+
+
+# bf16 windows whose attention rows lie beyond 32-bit offsets run on the direct kernels.  The rows are short, the room for them is
+# not: (window + 257) * capacity * 4 bytes is 2^31 and more.  With the attention rows stored and without, on grids of 32 and (from
+# 512 blocks of 64 rows on) of 64 columns, and a window longer than any prompt.
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H,g,lens,window,cap,rows", [
+    (1, 1, [700], 130, 1400000, True), (1, 2, [333], 130, 1400000, True), (2, 1, [300, 65], 400, 820000, False),
+    (1, 3, [700], 130, 1400000, False), (16, 1, [2100], 1900, 250000, False), (8, 2, [2100], 1900, 250000, False),
+    (2, 1, [2048, 1, 31, 33], 262144, 2048, False), (2, 2, [2048, 1], 262144, 2048, False),
+])
+def test_bf16_windows_beyond_32_bit_offsets(gpu_device, d, H, g, lens, window, cap, rows):
+    print("[case] direct window d=%d H=%d g=%d lens=%s window=%d cap=%d rows=%s" % (d, H, g, lens, window, cap, rows), flush=True)
+    assert (window + 257) * cap * 4 >= 1 << 31
+    inp, dt = _inputs("bf16", d, g, H, lens, 307)
+    held = []
+    for t in (inp.Q, inp.K, inp.V):
+        big = torch.empty(len(lens), t.shape[1], cap, d, dtype=dt, device=gpu_device)
+        big[:, :, :max(lens)] = t.to(gpu_device)
+        held.append(big)
+    hist = torch.full((len(lens), H, window + 1, cap), -2.0, device=gpu_device) if rows else None
+    S, nrm = _call("vatp_prefill_score_window", gpu_device, held, dt, d, g, H, lens, cap, window, hist)
+    units = _staged_units(H, lens)
+    want = {(b, h): orc.prefill_window_group(inp.Q[b, h * g:(h + 1) * g, :lens[b]].double().numpy(),
+                                             inp.K[b, h, :lens[b]].double().numpy(), window) for b, h in units}
+    _check(S, nrm, inp, dt, lens, units, lambda b, h, L: want[b, h][0])
+    for b, h in units if rows else []:
+        L = lens[b]
+        first = max(0, L - 1 - window)
+        got = hist[b, h, :, :L + 1].cpu().numpy()
+        for j in range(first, L):
+            parity.assert_scores_close(got[j - first, :j + 1], want[b, h][1][j - first, :j + 1], parity.rtol_for(dt), "row %d" % j)
+            assert (got[j - first, j + 1:] == -2.0).all()
+
+
+# fp32 windows without attention rows: grids of 32 columns, and of 64 from 1024 blocks of 64 rows on
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("H,g", [(2, 1), (2, 3), (16, 1), (16, 2)])
+def test_fp32_window_scores_only(gpu_device, d, H, g):
+    lens, window = [513, 1, 31, 32, 33, 64, 65, 255], 100
+    print("[case] fp32 window, scores only d=%d H=%d g=%d" % (d, H, g), flush=True)
+    inp, dt = _inputs("fp32", d, g, H, lens, 311)
+    S, nrm = _call("vatp_prefill_score_window", gpu_device, [t.to(gpu_device) for t in (inp.Q, inp.K, inp.V)], dt, d, g, H, lens, max(lens),
+                   window, None)
+    _check(S, nrm, inp, dt, lens, _staged_units(H, lens),
+           lambda b, h, L: orc.prefill_window_group(inp.Q[b, h * g:(h + 1) * g, :L].double().numpy(), inp.K[b, h, :L].double().numpy(), window)[0])
