@@ -213,9 +213,10 @@ __device__ __forceinline__ int group_value(int lane, int i)
 // forms the logits of all g query heads of the group against it (the point of sharing a K/V head:
 // the cache is read once per group, not once per query head).  Logits and chunk statistics are kept
 // per query head ([g, cap] and [g, chunks] per unit); with an output pointer each head's share of
-// its attention output as well.  Instantiated for groups of up to kMaxG = 2, 4, 8 and 16: what a thread keeps per query
-// head (its slice of the outputs, 8 registers) decides how many wavefronts, and so how many bytes, are in flight.  The
-// V rows are requested once the K rows are used up (requested with them, 4 % slower: registers again).  Measured, with
+// its attention output as well.  Instantiated for groups of up to kMaxG = 2, 4, 8 and 16.  Of what a thread keeps per
+// query head (its slice of the outputs, 8 registers in bf16) a smaller one saves the arithmetic, and registers, so wavefronts,
+// where these are what is short: with outputs and bf16 rows of 128, 132 registers and three wavefronts per SIMD up to 8 query
+// heads, 192 and two for 16; rows of 64, 84, 84, 108 and 176.  The V rows are requested once the K rows are used up (requested with them, 4 % slower: registers again).  Measured, with
 // outputs, against one instantiation for every group and reductions across lanes through LDS: 16 sequences of 8 heads x 4
 // query heads, 307..2457 rows, 64.5 -> 33.6 us per fused step; 4 x 4 heads x 8 query heads x 4096 rows 48.4 -> 26.9.
 template <typename T, int D, int kMaxG, bool kAttend, bool kStream>

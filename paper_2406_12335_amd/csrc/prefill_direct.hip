@@ -23,8 +23,8 @@
 // wavefront writing and reading its tile for itself.  In fp32 it is the matrix cores (64 cycles for 2 contraction
 // elements: a tile of 32 x 32 x 128 takes 4096 cycles against 320 of vector work), and fp32 MFMAs do not overlap with
 // vector instructions: a register-only loop reaches 155 TFLOP/s, 129 with two FMAs per MFMA and 118 with four.
-// Measured against 64 x 64 tiles of fp32 FMAs: 4 heads of 64 x 256 rows 69.5 -> 13.7 us; 64 heads x 2048 rows
-// 1015 -> 328 us with 64 elements (105 TFLOP/s over both passes), 1871 -> 650 us with 128.
+// Measured against 64 x 64 tiles of fp32 FMAs: 4 heads of 64 x 256 rows 69.5 -> 11.9 us; 64 heads x 2048 rows
+// 1015 -> 319 us with 64 elements (108 TFLOP/s over both passes), 1871 -> 650 us with 128.
 //
 // History-window scores (Eq. 3 after the prompt: only the last w+1 query rows count) use the same two kernels with
 // `window` = w >= 0: query tiles wholly before row len-1-w are skipped, and colsum also stores the window's attention

@@ -82,8 +82,9 @@ constexpr int kSlotValu = VATP_SLOT_VALU;    // vector instructions asked for af
 
 // What the head dimension decides.  A wavefront's 1 KiB copy instruction covers 4 rows of 128 elements or 8 of 64,
 // a tile takes 8 or 4 MFMA steps, so at 64 every MFMA carries twice the exponentials and the vector ALU alone bounds
-// the pass; the smaller operand leaves room for three wavefronts per SIMD.  Measured, 4 x 16 heads of 64, 2048 rows:
-// 0.069 ms for both passes and the norms, 0.99 ms with fp32 FMAs.
+// the pass.  Four-wavefront workgroups without a window fit three wavefronts per SIMD (146 registers in the row statistics,
+// 168 in the column sums), eight-wavefront ones two (184 in the column sums).  Measured, 4 x 16 heads of 64, 2048 rows:
+// 0.065 ms for both passes and the norms, 0.99 ms with fp32 FMAs.
 template <int D>
 struct Rows {
     static constexpr int kChunks = D * 2 / 16;          // 16-byte chunks per row
@@ -250,8 +251,8 @@ __device__ __forceinline__ void value_norms_64(const uint4 *__restrict__ Vu, flo
     }
 }
 
-// (Column sums of heads of 64 in 4-wavefront workgroups: 168 registers, three wavefronts per SIMD, is asked for since the
-// compiler takes one more for a group otherwise.)
+// (Column sums of heads of 64 in 4-wavefront workgroups are held to 168 registers, the most with which three wavefronts share
+// a SIMD: they need 167, with a group 168.)
 template <int D, bool kColsum, int kHalves, bool kWindow = false, bool kGrouped = false>
 __global__ __launch_bounds__(256 * kHalves, D == 64 && kColsum && kHalves == 1 && !kWindow ? 3 : 1) void prefill_mfma_kernel(const bf16_t *__restrict__ Q,
                                                            const bf16_t *__restrict__ K,

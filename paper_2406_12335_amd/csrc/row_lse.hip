@@ -1,5 +1,4 @@
-// Per-row preparation of the prompt pass: row log-sum-exps that come from outside.  (The other per-row quantity, the
-// norm of the value rows, is formed by row_norm inside the column-sum passes and the decode kernels.)
+// Per-row preparation of the prompt pass: row log-sum-exps that come from outside.
 #include "vatp_device.h"
 
 namespace vatp {

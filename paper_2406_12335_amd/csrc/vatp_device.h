@@ -484,10 +484,10 @@ __device__ __forceinline__ float group_weight(const float (&t)[kMaxG], const flo
 }
 
 // ---- host-side launchers, one per source file --------------------------------------
-// window >= 0: history-window scores (Eq. 3), the window's attention rows go to hist (may be NULL)
 // The two passes of the prompt scores (either may run on the staged or on the direct kernels; both leave the row
 // statistics in lse2, and the column sums come with the value-row norms).  With natural_lse the column sums of the direct
-// kernels take natural logarithms, as an attention kernel hands them over.
+// kernels take natural logarithms, as an attention kernel hands them over.  window >= 0: history-window scores (Eq. 3), the
+// window's attention rows go to hist (may be NULL).
 constexpr float kLog2e = 1.44269504088896340736f;
 enum { kPassRowstat = 1, kPassColsum = 2 };
 // Where the running maximum of a row's logits starts: finite, so that masked logits (-inf) stay zeros relative to it, and

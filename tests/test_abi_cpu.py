@@ -159,7 +159,7 @@ def test_built_library_matches_its_sources():
     assert build.is_current()
     d0 = build.source_digest()
     assert d0 == build.source_digest() and len(d0) == 64
-    victim = os.path.join(build.CSRC, "l1norm.hip")
+    victim = os.path.join(build.CSRC, "row_lse.hip")
     backup = victim + ".bak_test"
     shutil.copy2(victim, backup)
     try:
