@@ -33,7 +33,7 @@ import vatp_synth as vs  # noqa: E402
 
 HBM_PEAK_GBPS = 8000.0
 MFMA_BF16_PEAK_TFLOPS = 2500.0
-FP32_VECTOR_PEAK_TFLOPS = 157.3
+MFMA_FP32_PEAK_TFLOPS = 157.3
 
 
 def algorithmic_flops_prefill(cfg, lens, window=None):
@@ -81,6 +81,28 @@ def fused_step_kernels(cfg, lens, budgets, window):
         return "decode_prune_one_kernel"
     first = "decode_logits_group_kernel" if cfg.q_per_kv > 1 else "decode_logits_kernel"
     return first + " + decode_prune_kernel"
+
+
+def prompt_score_kernels(cfg, lens, window):
+    """Names of the kernels one prompt-scoring call launches for this workload (the library's rule: bf16 passes whose
+    workgroups fill the chip, and bf16 windows, on the staged kernels, everything else on the direct ones)."""
+    pairs = ((max(lens) + 255) // 256 + 1) // 2                  # a workgroup's work: two blocks of 256 rows
+    units, g = cfg.batch * cfg.n_heads, cfg.q_per_kv
+    splits = next((s for s in range(1, g + 1) if g % s == 0 and 8 * pairs * ((units * s + 7) // 8) >= 512), g)
+
+    def kernel(heads):
+        even = 240 if cfg.head_dim == 64 else 192
+        jobs = units * heads * pairs
+        fills = jobs >= even if jobs <= 256 else jobs >= 2 * even
+        if window is not None:                                   # (attention rows within 32-bit offsets)
+            fills = (window + 257) * max(lens) * 4 < 1 << 31
+        return "prefill_mfma_kernel" if cfg.dtype == "bf16" and fills else "prefill_direct_kernel"
+
+    rowstat, colsum = kernel(g), kernel(splits)
+    if window is None:
+        return "%s<rowstat> + %s<colsum, value norms inside>" % (rowstat, colsum)
+    ranges = " over key ranges + merge_split_lse_kernel" if rowstat == "prefill_mfma_kernel" else ""
+    return "%s<rowstat>%s + %s<colsum, attention rows and value norms inside>" % (rowstat, ranges, colsum)
 
 
 def measure(args, workload, steps, warmup, main_line):
@@ -300,18 +322,15 @@ def measure(args, workload, steps, warmup, main_line):
     sel_bytes *= cfg.layers
 
     mfma = cfg.dtype == "bf16"
-    peak_tf = MFMA_BF16_PEAK_TFLOPS if mfma else FP32_VECTOR_PEAK_TFLOPS
+    peak_tf = MFMA_BF16_PEAK_TFLOPS if mfma else MFMA_FP32_PEAK_TFLOPS
     # (only for the named workloads as they are: an overridden shape, grouped queries or a window have no profile)
     as_named = window is None and cfg == vs.CONFIGS.get(cfg.name)
     profiled = PROFILED_TRAFFIC_BYTES.get(cfg.name if as_named else None, {})
     traffic = profiled.get("bytes_per_call", {})
     prefill_tflops = flops / (prefill_ms * 1e-3) / 1e12 if prefill_ms > 0 else 0.0
-    # (bf16 grids too small for the chip take the direct kernels as well; the large named workloads do not)
-    prefill_kernels = "prefill_mfma_kernel<rowstat> + prefill_mfma_kernel<colsum, value norms inside>" \
-        if mfma else "prefill_direct_kernel<rowstat> + prefill_direct_kernel<colsum, value norms inside>"
-    roof_prefill = {"kernel": "vatp_prefill_score = " + prefill_kernels if window is None
-                    else "vatp_prefill_score_window = rowstat over key ranges + merge + colsum with rows and norms",
-                    "bound": "mfma" if mfma else "alu",
+    roof_prefill = {"kernel": ("vatp_prefill_score = " if window is None else "vatp_prefill_score_window = ") +
+                    prompt_score_kernels(cfg, lens, window),
+                    "bound": "mfma",
                     "achieved": round(prefill_tflops, 3), "peak": peak_tf, "unit": "TFLOP/s",
                     "frac": round(prefill_tflops / peak_tf, 5), "traffic": traffic.get("prefill_score"),
                     "avg_launch_ms": round(prefill_ms / cfg.layers, 5),
