@@ -57,6 +57,17 @@ __device__ __forceinline__ void mfma_chunk(const uint4 &a, const uint4 (&bf)[kCo
         for (int c = 0; c < kCols; ++c) acc[c] = mfma_piece<T>(a, bf[c][s], e, acc[c]);
 }
 
+// sum of the wavefronts' shares, by halves
+template <int kN>
+__device__ __forceinline__ float sum_by_halves(float (&v)[kN])
+{
+#pragma unroll
+    for (int half = kN / 2; half > 0; half /= 2)
+#pragma unroll
+        for (int i = 0; i < half; ++i) v[i] += v[i + half];
+    return v[0];
+}
+
 enum { kRowstat, kColsumPlain, kColsumHist };      // passes
 
 struct DirectArgs {
@@ -285,13 +296,17 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_direct_kernel(const T 
 #pragma unroll
         for (int c = 0; c < kCols; ++c) {
             if constexpr (kColsum) {
+                // (a sum of the tile first: one rounding per tile in what is added up over a prompt, and not one per row.  Scores of 8
+                // bf16 heads of 128 x 2000 rows, relative error against 64 bits 8.8e-8 row by row, 6.7e-8 so, 7.3e-8 on the staged kernels)
+                float part = 0.f;
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
-                    // (weights that are stored keep their value below 2^-126: 0.5 % of a pass that stores its rows)
+                    // (weights that are stored keep their value below 2^-126: up to 5 % of a pass that stores its rows)
                     const float x = fmaf(acc[c][v], scale, -lse_v[v]), p = kHist ? exp2f(x) : fast_exp2(x);
-                    l[c] += p;
+                    part += p;
                     if constexpr (kHist) group_sum[c][v] += p;
                 }
+                l[c] += part;
                 if constexpr (kHist) {
                     if (h == heads - 1) {
                         const int col = base0 + kTileRows * c + n;
@@ -333,10 +348,10 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_direct_kernel(const T 
     if constexpr (kColsum) {
         // (every wavefront adds them all up, so that each knows whether one is too small, without another barrier)
         auto total = [&]() __attribute__((always_inline)) {
-            float x = 0.f;
+            float x[2 * kWaves];
 #pragma unroll
-            for (int w = 0; w < 2 * kWaves; ++w) x += s_part[w][lane % kBlock];
-            return x;
+            for (int w = 0; w < 2 * kWaves; ++w) x[w] = s_part[w][lane % kBlock];
+            return sum_by_halves(x);
         };
         sum = total();
         if (!kHist && __any(base0 + lane % kBlock < len && sum < kSubnormalLoss)) {
@@ -358,8 +373,10 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_direct_kernel(const T 
             float top = s_max[0][tid];
 #pragma unroll
             for (int w = 1; w < 2 * kWaves; ++w) top = fmaxf(top, s_max[w][tid]);
+            float x[2 * kWaves];
 #pragma unroll
-            for (int w = 0; w < 2 * kWaves; ++w) sum += s_part[w][tid] * fast_exp2(s_max[w][tid] - top);
+            for (int w = 0; w < 2 * kWaves; ++w) x[w] = s_part[w][tid] * fast_exp2(s_max[w][tid] - top);
+            sum = sum_by_halves(x);
             lse2[unit * cap + base0 + tid] = top + __log2f(sum);
         }
     }

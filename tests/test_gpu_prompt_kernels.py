@@ -210,6 +210,31 @@ def test_row_lse_of_a_group_under_other_buffers(gpu_device, dtype, d, H, g, lens
             parity.assert_scores_close(S[i, h, :L].cpu().numpy(), want[h].numpy(), parity.rtol_for(dt), "S, sequence %d head %d" % (i, h))
 
 
+# Column sums of the direct kernels add up a tile's 16 rows, then the tiles that a wavefront has, then the wavefronts' lane halves by
+# halves.  All weights of a head are one number here (all logits 0, one log-sum-exp), the last key's score, so that nothing else is
+# rounded.  In units of 2^-24 of the whole, a chain of n equal numbers may be off by (2 + ... + n) / n: 8.4 for the rows, 4.4 for up to
+# 8 tiles with 8 wavefronts, 4.9 for up to 9 with 4, 4 or 3 for the halves: 17.  Added row by row (up to 64.5), numbers whose low bits
+# keep falling away on one side are 23 to 36 off in some heads.
+@pytest.mark.parametrize("dtype,d,H,L", [("bf16", 128, 8, 2048), ("bf16", 64, 8, 2047), ("fp32", 64, 8, 2048), ("fp32", 128, 8, 2000),
+                                         ("bf16", 128, 32, 1152), ("bf16", 64, 32, 1100), ("fp32", 64, 64, 1152), ("fp32", 128, 64, 1001)])
+def test_equal_weights_are_summed_with_few_roundings(gpu_device, dtype, d, H, L):
+    print("[case] equal weights %s d=%d H=%d L=%d" % (dtype, d, H, L), flush=True)
+    dt = {"fp32": torch.float32, "bf16": torch.bfloat16}[dtype]
+    X = torch.zeros(1, H, L, d, dtype=dt, device=gpu_device)
+    lse = (3 + torch.arange(H, device=gpu_device).view(1, H, 1) * 0.173).float().expand(1, H, L).contiguous()
+    ctx = vatp.vatp_create(0)
+    try:
+        p = vatp.Params(1, H, d, dt, 0, 0, L, [L], [L])
+        ws = torch.empty(vatp.vatp_workspace_bytes(ctx, p, vatp.binding.CALL_PREFILL_SCORE), dtype=torch.uint8, device=gpu_device)
+        S, nrm = torch.zeros_like(lse), torch.zeros_like(lse)
+        vatp.vatp_prefill_score_lse(ctx, p, X, X, X, lse, S, nrm, ws)
+        S = S[0].cpu().double()
+    finally:
+        vatp.vatp_destroy(ctx)
+    off = (S / (S[:, -1:] * torch.arange(L, 0, -1)) - 1).abs().max().item()
+    assert off <= 17 * 2.0 ** -24, off * 2.0 ** 24
+
+
 # logits far below any that occur: every row's weight is the first key's (the products are powers of two, so that nothing is
 # rounded); direct and staged kernels, a window's key ranges
 @pytest.mark.parametrize("dtype,d,B,H,L,window", [
