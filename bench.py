@@ -463,23 +463,23 @@ DEFAULT_WORKLOAD = "llama7b_stack"
 # HBM bytes per call of an entry point (fetch + write, all of its kernels), as counted by rocprofv3 --pmc
 # FETCH_SIZE / WRITE_SIZE runs of this file and scaled by what the same counters read for the plain copy of
 # --copy-calibration.  NOT measured by the run that prints them: a static table, copied from the committed
-# summary named in "source", which also gives the commands and the commit of the kernels they were counted on.
+# summary named in "source", which also gives the commands.
 PROFILED_TRAFFIC_BYTES = {
     "llama7b_stack": {"source": "profiles/llama7b_stack_profile.md",
-                      "bytes_per_call": {"prefill_score": 2066138097, "decode_step": 57657290, "select_compact": 232478387,
-                                         "decode_prune_step": 71321155}},
+                      "bytes_per_call": {"prefill_score": 2021565035, "decode_step": 57647982, "select_compact": 232475962,
+                                         "decode_prune_step": 71322724}},
     "llama7b_layer": {"source": "profiles/llama7b_layer_profile.md",
-                      "bytes_per_call": {"prefill_score": 185835398, "decode_step": 18042753, "select_compact": 72825985,
-                                         "decode_prune_step": 21342131}},
+                      "bytes_per_call": {"prefill_score": 189013853, "decode_step": 18034283, "select_compact": 72825381,
+                                         "decode_prune_step": 21309150}},
     "long32k": {"source": "profiles/long32k_profile.md",
-                "bytes_per_call": {"prefill_score": 2388075236, "decode_step": 28734910, "select_compact": 116525482,
-                                   "decode_prune_step": 35609948}},
+                "bytes_per_call": {"prefill_score": 2379230108, "decode_step": 28726205, "select_compact": 116525762,
+                                   "decode_prune_step": 35557798}},
     "ragged16": {"source": "profiles/ragged16_profile.md",
-                 "bytes_per_call": {"prefill_score": 5967520750, "decode_step": 204590432, "select_compact": 830405693,
-                                    "decode_prune_step": 250674872}},
+                 "bytes_per_call": {"prefill_score": 5964700605, "decode_step": 204579868, "select_compact": 830402426,
+                                    "decode_prune_step": 250654032}},
     "tiny": {"source": "profiles/tiny_profile.md",
-             "bytes_per_call": {"prefill_score": 2462884, "decode_step": 258267, "select_compact": 594541,
-                                "decode_prune_step": 525967}},
+             "bytes_per_call": {"prefill_score": 1993742, "decode_step": 252113, "select_compact": 594534,
+                                "decode_prune_step": 473411}},
 }
 
 
