@@ -328,6 +328,9 @@ __global__ __launch_bounds__(256 * kHalves, D == 64 && kColsum && kHalves == 1 &
     // Copy stage t (kSlotRows streamed rows) into ring slot `slot`.  This wavefront moves rows
     // 16*wave .. 16*wave+15, four or eight rows (1 KiB) per instruction.  Rows past the end of the
     // sequence are redirected to its last row (any finite data: they are masked later).
+    // (The load needs one wait state after what wrote m0, and five after a vector instruction that wrote its scalar base, as when
+    // the base comes back from a lane of a spill register, which the compiler does not see inside assembly: s_nop 3
+    // with the move before it makes five.)
     auto copy_stage = [&](int t, int slot) {
 #pragma unroll
         for (int i = 0; i < R::kCopies; ++i) {
@@ -336,14 +339,14 @@ __global__ __launch_bounds__(256 * kHalves, D == 64 && kColsum && kHalves == 1 &
             const int grow = min(t * kSlotRows + r, len - 1);
             const unsigned voff = static_cast<unsigned>(grow) * (kD * 2) + c * 16;
             const unsigned m0v = lds_stage0 + slot * kSlotBytes + (16 * wave + R::kCopyRows * i) * (kD * 2);
-            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(m0v), "v"(voff), "s"(strm)
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(m0v), "v"(voff), "s"(strm)
                          : "memory");
         }
         if (kColsum && cw == 0) {
             const int grow = min(t * kSlotRows + kStage * half + lane, len - 1);
             const unsigned voff = static_cast<unsigned>(grow) * 4;
             const unsigned m0v = lds_lse0 + (slot * kSlotRows + kStage * half) * 4;
-            asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dword %1, %2" ::"s"(m0v), "v"(voff), "s"(lse_u)
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dword %1, %2" ::"s"(m0v), "v"(voff), "s"(lse_u)
                          : "memory");
         }
     };
