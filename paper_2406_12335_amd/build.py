@@ -38,6 +38,7 @@ def sources():
 # accumulators stay in architectural VGPRs so the exponentials can read them directly.
 EXTRA_FLAGS = {
     "prefill_mfma.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form"],
+    "prefill_wide.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form"],
     "prefill_direct.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form"],
 }
 

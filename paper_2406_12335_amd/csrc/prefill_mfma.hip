@@ -1,4 +1,6 @@
-// Prompt-pass scoring on the matrix cores (bf16 inputs, head_dim 64 or 128, gfx950).
+// Prompt-pass scoring on the matrix cores (bf16 inputs, gfx950): history windows, and heads of 64 without one (heads of 128 without
+// a window: prefill_wide.hip, whose layout was slower here: 4 x 16 heads of 64 x 2048 rows 65.4 -> 71.9 us, 32 x 4096 106.9 ->
+// 114.1; only 32 x 16384 gained, 1385 -> 1359).
 //
 // Accumulated attention score after the prompt (paper Eq. 2 with t = L-1):
 //     S_i = sum_{j>=i} a_i^j ,   a^j = softmax over keys i<=j of c*<q_j,k_i>   (Eq. 1).
@@ -57,20 +59,13 @@
 // agree: lane half g takes the 16-byte chunk  2s + g  of a row for MFMA step s.
 #include <type_traits>
 
-#include "vatp_device.h"
+#include "prefill_stage.h"
 
 namespace vatp {
 
 namespace {
 
-typedef __attribute__((address_space(3))) char lds_char;
-
-constexpr int kStage = 64;         // streamed rows per LDS stage
-constexpr int kRing = 4;           // LDS stage buffers
-constexpr unsigned kComputeUnits = 256;
-constexpr int kAhead = kRing - 1;  // stages in flight beyond the one being consumed
 constexpr int kWaveCols = 64;      // stationary rows per wavefront
-constexpr int kBlockCols = 256;    // stationary rows per workgroup
 #ifndef VATP_LEAD_VALU
 #define VATP_LEAD_VALU 12
 #endif
@@ -79,23 +74,6 @@ constexpr int kBlockCols = 256;    // stationary rows per workgroup
 #endif
 constexpr int kLeadValu = VATP_LEAD_VALU;    // vector instructions asked for between the LDS reads and the first MFMA
 constexpr int kSlotValu = VATP_SLOT_VALU;    // vector instructions asked for after every MFMA
-
-// What the head dimension decides.  A wavefront's 1 KiB copy instruction covers 4 rows of 128 elements or 8 of 64,
-// a tile takes 8 or 4 MFMA steps, so at 64 every MFMA carries twice the exponentials and the vector ALU alone bounds
-// the pass.  Four-wavefront workgroups without a window fit three wavefronts per SIMD (146 registers in the row statistics,
-// 168 in the column sums), eight-wavefront ones two (184 in the column sums).  Measured, 4 x 16 heads of 64, 2048 rows:
-// 0.065 ms for both passes and the norms, 0.99 ms with fp32 FMAs.
-template <int D>
-struct Rows {
-    static constexpr int kChunks = D * 2 / 16;          // 16-byte chunks per row
-    static constexpr int kSteps = D / 16;               // MFMA steps per 32 x 32 tile
-    static constexpr int kStageBytes = kStage * D * 2;  // 16 or 8 KiB
-    static constexpr int kCopyRows = 64 / kChunks;      // rows per copy instruction
-    static constexpr int kCopies = 16 / kCopyRows;      // copy instructions per wavefront and stage
-    static constexpr int kPieces = 16 / (2 * kSteps);   // sixteenths of the pending pair's work after every MFMA
-};
-
-__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // Scheduling request for two MFMA slots: one MFMA, V0 vector-ALU instructions, one MFMA, V1
 // vector-ALU instructions (0x008 MFMA, 0x002 VALU).
@@ -106,14 +84,6 @@ __device__ __forceinline__ void sched_two_slots()
     __builtin_amdgcn_sched_group_barrier(0x002, V0, 0);
     __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
     __builtin_amdgcn_sched_group_barrier(0x002, V1, 0);
-}
-
-// Wait until at most kPending of this wavefront's vector-memory operations are outstanding,
-// then meet the other wavefronts.  The "memory" clobber keeps LDS reads below it.
-template <int kPending>
-__device__ __forceinline__ void wait_copies_then_barrier()
-{
-    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kPending) : "memory");
 }
 
 template <bool kColsum>
@@ -228,29 +198,6 @@ struct Epilogue {
     }
 };
 
-// Norms of 64 consecutive value rows by one wavefront.  Same arithmetic wherever norms are formed (row_norm): D / 8 lanes per
-// row, 8 elements each in order, then an all-reduce over the row's lanes; all loads of a lane are
-// issued before the first is used.
-template <int D, int kNorm>
-__device__ __forceinline__ void value_norms_64(const uint4 *__restrict__ Vu, float *__restrict__ nu, int row0, int len,
-                                               int lane)
-{
-    using R = Rows<D>;
-    const int sub = lane % R::kChunks, rr = lane / R::kChunks;
-    uint4 raw[R::kChunks];
-#pragma unroll
-    for (int p = 0; p < R::kChunks; ++p) {
-        const int row = row0 + R::kCopyRows * p + rr;
-        raw[p] = row < len ? Vu[static_cast<size_t>(row) * R::kChunks + sub] : make_uint4(0, 0, 0, 0);
-    }
-#pragma unroll
-    for (int p = 0; p < R::kChunks; ++p) {
-        const int row = row0 + R::kCopyRows * p + rr;
-        const float value = row_norm<bf16_t, R::kChunks>(kNorm, raw[p]);
-        if (sub == 0 && row < len) nu[row] = value;
-    }
-}
-
 // (Column sums of heads of 64 in 4-wavefront workgroups are held to 168 registers, the most with which three wavefronts share
 // a SIMD: they need 167, with a group 168.)
 template <int D, bool kColsum, int kHalves, bool kWindow = false, bool kGrouped = false>
@@ -328,9 +275,6 @@ __global__ __launch_bounds__(256 * kHalves, D == 64 && kColsum && kHalves == 1 &
     // Copy stage t (kSlotRows streamed rows) into ring slot `slot`.  This wavefront moves rows
     // 16*wave .. 16*wave+15, four or eight rows (1 KiB) per instruction.  Rows past the end of the
     // sequence are redirected to its last row (any finite data: they are masked later).
-    // (The load needs one wait state after what wrote m0, and five after a vector instruction that wrote its scalar base, as when
-    // the base comes back from a lane of a spill register, which the compiler does not see inside assembly: s_nop 3
-    // with the move before it makes five.)
     auto copy_stage = [&](int t, int slot) {
 #pragma unroll
         for (int i = 0; i < R::kCopies; ++i) {
@@ -339,15 +283,13 @@ __global__ __launch_bounds__(256 * kHalves, D == 64 && kColsum && kHalves == 1 &
             const int grow = min(t * kSlotRows + r, len - 1);
             const unsigned voff = static_cast<unsigned>(grow) * (kD * 2) + c * 16;
             const unsigned m0v = lds_stage0 + slot * kSlotBytes + (16 * wave + R::kCopyRows * i) * (kD * 2);
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(m0v), "v"(voff), "s"(strm)
-                         : "memory");
+            copy_to_lds<4>(m0v, voff, strm);
         }
         if (kColsum && cw == 0) {
             const int grow = min(t * kSlotRows + kStage * half + lane, len - 1);
             const unsigned voff = static_cast<unsigned>(grow) * 4;
             const unsigned m0v = lds_lse0 + (slot * kSlotRows + kStage * half) * 4;
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dword %1, %2" ::"s"(m0v), "v"(voff), "s"(lse_u)
-                         : "memory");
+            copy_to_lds<1>(m0v, voff, lse_u);
         }
     };
     // copies per stage issued by this wavefront (column group 0 also brings the lse values)
@@ -450,10 +392,10 @@ __global__ __launch_bounds__(256 * kHalves, D == 64 && kColsum && kHalves == 1 &
                 const uint4 *Vu = reinterpret_cast<const uint4 *>(V + unit * cap * kD);
                 float *nu = nrm + unit * cap;
                 switch (norm) {
-                case VATP_NORM_L1: value_norms_64<D, VATP_NORM_L1>(Vu, nu, w0, len, lane); break;
-                case VATP_NORM_L2: value_norms_64<D, VATP_NORM_L2>(Vu, nu, w0, len, lane); break;
-                case VATP_NORM_LINF: value_norms_64<D, VATP_NORM_LINF>(Vu, nu, w0, len, lane); break;
-                default: value_norms_64<D, VATP_NORM_NONE>(Vu, nu, w0, len, lane); break;
+                case VATP_NORM_L1: value_norms<D, VATP_NORM_L1, 64 / R::kCopyRows>(Vu, nu, w0, len, lane); break;
+                case VATP_NORM_L2: value_norms<D, VATP_NORM_L2, 64 / R::kCopyRows>(Vu, nu, w0, len, lane); break;
+                case VATP_NORM_LINF: value_norms<D, VATP_NORM_LINF, 64 / R::kCopyRows>(Vu, nu, w0, len, lane); break;
+                default: value_norms<D, VATP_NORM_NONE, 64 / R::kCopyRows>(Vu, nu, w0, len, lane); break;
                 }
             }
         }
@@ -939,26 +881,10 @@ hipError_t launch_merge_group_partials(const float *s_part, float *S, int splits
 
 namespace {
 
-inline int block_pairs(const Geometry &g) { return ((g.max_len + kBlockCols - 1) / kBlockCols + 1) / 2; }
-
-// Grouped column sums: a K/V head's query heads are walked by one workgroup (no partial sums) when that
-// still fills the chip; otherwise they are dealt out to `splits` workgroups -- the smallest divisor of
-// the group size that does -- whose partial sums a small kernel adds.
-inline int colsum_splits(const Geometry &g)
-{
-    int splits = 1;
-    for (int s = 1; s <= g.group; ++s)
-        if (g.group % s == 0) {
-            splits = s;
-            if (8u * block_pairs(g) * ((g.batch * g.n_heads * s + 7) / 8) >= 2u * kComputeUnits) break;
-        }
-    return splits;
-}
-
-template <int D>
 hipError_t launch_full(const void *Q, const void *K, const void *V, float *S, float *nrm, float *lse2, float *s_part, int passes,
                        const BatchMeta &meta, const Geometry &g, hipStream_t st)
 {
+    constexpr int D = 64;
     if (g.max_len <= 0) return hipSuccess;
     const int n_blocks = (g.max_len + kBlockCols - 1) / kBlockCols;
     const int n_pairs = block_pairs(g);
@@ -1016,8 +942,8 @@ bool prefill_mfma_fills(int head_dim, int pass, const Geometry &g)
 hipError_t launch_prefill_mfma(int head_dim, const void *Q, const void *K, const void *V, float *S, float *nrm, float *lse2,
                                float *s_part, int passes, const BatchMeta &meta, const Geometry &g, hipStream_t st)
 {
-    return head_dim == 64 ? launch_full<64>(Q, K, V, S, nrm, lse2, s_part, passes, meta, g, st)
-                          : launch_full<128>(Q, K, V, S, nrm, lse2, s_part, passes, meta, g, st);
+    return head_dim == 64 ? launch_full(Q, K, V, S, nrm, lse2, s_part, passes, meta, g, st)
+                          : launch_prefill_wide(Q, K, V, S, nrm, lse2, s_part, passes, meta, g, st);
 }
 
 }  // namespace vatp

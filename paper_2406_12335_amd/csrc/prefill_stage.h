@@ -1,0 +1,93 @@
+// What the staged prompt kernels share: the ring of LDS stages that the streamed rows pass through, and the norms of the value rows.
+#pragma once
+
+#include "vatp_device.h"
+
+namespace vatp {
+
+typedef __attribute__((address_space(3))) char lds_char;
+
+constexpr int kStage = 64;         // streamed rows per LDS stage
+constexpr int kRing = 4;           // LDS stage buffers
+constexpr unsigned kComputeUnits = 256;
+constexpr int kAhead = kRing - 1;  // stages in flight beyond the one being consumed
+constexpr int kBlockCols = 256;    // stationary rows per workgroup
+
+// What the head dimension decides.  A wavefront's 1 KiB copy instruction covers 4 rows of 128 elements or 8 of 64,
+// a tile takes 8 or 4 MFMA steps, so at 64 every MFMA carries twice the exponentials and the vector ALU alone bounds
+// the pass.  Four-wavefront workgroups without a window fit three wavefronts per SIMD (146 registers in the row statistics,
+// 168 in the column sums), eight-wavefront ones two (184 in the column sums).  Measured, 4 x 16 heads of 64, 2048 rows:
+// 0.065 ms for both passes and the norms, 0.99 ms with fp32 FMAs.
+template <int D>
+struct Rows {
+    static constexpr int kChunks = D * 2 / 16;          // 16-byte chunks per row
+    static constexpr int kSteps = D / 16;               // MFMA steps per 32 x 32 tile
+    static constexpr int kStageBytes = kStage * D * 2;  // 16 or 8 KiB
+    static constexpr int kCopyRows = 64 / kChunks;      // rows per copy instruction
+    static constexpr int kCopies = 16 / kCopyRows;      // copy instructions per wavefront and stage
+    static constexpr int kPieces = 16 / (2 * kSteps);   // sixteenths of the pending pair's work after every MFMA
+};
+
+__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+
+// One copy global -> LDS by the load unit: each lane's kDwords * 4 bytes at base + off land at LDS address `to` + that many bytes per
+// lane.  The load needs one wait state after what wrote m0, and five after a vector instruction that wrote its scalar base (as
+// when the base comes back from a lane of a spill register), which the compiler does not see inside assembly: s_nop 3 with
+// the move before it makes five.
+template <int kDwords>
+__device__ __forceinline__ void copy_to_lds(unsigned to, unsigned off, const void *base)
+{
+    static_assert(kDwords == 1 || kDwords == 4, "global_load_lds_dword or global_load_lds_dwordx4");
+    if constexpr (kDwords == 4)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(to), "v"(off), "s"(base) : "memory");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dword %1, %2" ::"s"(to), "v"(off), "s"(base) : "memory");
+}
+
+// Wait until at most kPending of this wavefront's vector-memory operations are outstanding,
+// then meet the other wavefronts.  The "memory" clobber keeps LDS reads below it.
+template <int kPending>
+__device__ __forceinline__ void wait_copies_then_barrier()
+{
+    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kPending) : "memory");
+}
+
+// Norms of kLoads times kCopyRows consecutive value rows by one wavefront.  Same arithmetic wherever norms are formed (row_norm):
+// D / 8 lanes per row, 8 elements each in order, then an all-reduce over the row's lanes; all loads of a lane are
+// issued before the first is used.
+template <int D, int kNorm, int kLoads>
+__device__ __forceinline__ void value_norms(const uint4 *__restrict__ Vu, float *__restrict__ nu, int row0, int len, int lane)
+{
+    using R = Rows<D>;
+    const int sub = lane % R::kChunks, rr = lane / R::kChunks;
+    uint4 raw[kLoads];
+#pragma unroll
+    for (int p = 0; p < kLoads; ++p) {
+        const int row = row0 + R::kCopyRows * p + rr;
+        raw[p] = row < len ? Vu[static_cast<size_t>(row) * R::kChunks + sub] : make_uint4(0, 0, 0, 0);
+    }
+#pragma unroll
+    for (int p = 0; p < kLoads; ++p) {
+        const int row = row0 + R::kCopyRows * p + rr;
+        const float value = row_norm<bf16_t, R::kChunks>(kNorm, raw[p]);
+        if (sub == 0 && row < len) nu[row] = value;
+    }
+}
+
+inline int block_pairs(const Geometry &g) { return ((g.max_len + kBlockCols - 1) / kBlockCols + 1) / 2; }
+
+// Grouped column sums: a K/V head's query heads are walked by one workgroup (no partial sums) when that
+// still fills the chip; otherwise they are dealt out to `splits` workgroups -- the smallest divisor of
+// the group size that does -- whose partial sums a small kernel adds.
+inline int colsum_splits(const Geometry &g)
+{
+    int splits = 1;
+    for (int s = 1; s <= g.group; ++s)
+        if (g.group % s == 0) {
+            splits = s;
+            if (8u * block_pairs(g) * ((g.batch * g.n_heads * s + 7) / 8) >= 2u * kComputeUnits) break;
+        }
+    return splits;
+}
+
+}  // namespace vatp

@@ -1,0 +1,612 @@
+// Prompt-pass scoring on the matrix cores, wide wavefront tiles (bf16, heads of 128, gfx950): row statistics and column sums of the
+// causal softmax without a history window, for grids that fill the chip.
+//
+//   rowstat  queries stationary, keys streamed:  per query j  lse2_j = log2 sum_{i<=j} 2^(t_ji)
+//   colsum   keys stationary, queries streamed:  S_i = sum_{j>=i} 2^(t_ji - lse2_j), and the norms of the value rows
+// with t = c*log2(e)*<q,k> (paper Eq. 1, 2).  The L x L matrix is never stored.
+//
+// What bounds it: on long prompts these passes run at the chip's power limit.  Counters of the 32 x 32 x 16 kernels that were
+// here before, 32 heads x 32768 rows: matrix pipe busy 58 % at 1.78 GHz of 2.4, and whatever kept the pipe busier (operands
+// fetched earlier, a ring that runs on from block to block) lowered the clock by as much.  So the kernel is laid out for fewer
+// joules per logit:
+//  * v_mfma_f32_16x16x32_bf16 instead of 32x32x16: half the accumulator traffic per product (MFMAs alone, operands from
+//    LDS, random data: 1.56 -> 1.71 PFLOP/s),
+//  * 128 stationary rows per wavefront instead of 64: an operand read from LDS serves eight MFMAs of 16 cycles instead of two of
+//    32, half the LDS reads,
+//  * row statistics relative to a reference fixed by the first keys instead of a running maximum: a seventh fewer vector
+//    instructions.
+// Loops of MFMAs, exponentials and LDS reads alone, one box: 32 x 32 tiles, 64 columns 1233 TFLOP/s, 16 x 16 tiles, 64 columns
+// 1309, 16 x 16 tiles, 128 columns 1365.  Now: pipe busy 56 and 54 % at 2.03 and 2.06 GHz.  Measured, both passes, before / now:
+// 32 heads x 32768 rows 7865 / 7333 us, 512 heads of 1024..8192 rows 3638 / 3448, 32 x 4096 153.4 / 147.0, 128 x 2048 180.5 / 172.0,
+// 512 x 200 37.7 / 35.0; column sums alone, 64 K/V heads of 4 query heads x 4001 rows 565 / 550.  Where it costs: ragged short
+// sequences, 256 heads of 150..1200 rows 104.3 / 106.3.  Blocks of 512 rows in eight-wavefront workgroups (half the copies into LDS)
+// were no faster at 32768 rows (7390) and slower below (128 x 4096 566 -> 608).
+// On one layer of 4096 rows the clock is 2.3 GHz and the pipe busy a third of the time: there it is the start of every block.
+//
+// Skeleton.  A workgroup of 4 (8) wavefronts owns 256 stationary rows: two column groups of 128, kept in registers as the B
+// operand, times 2 (4) parts of 32 rows each of a ring slot of 64 (128) streamed rows, the A operand.  Slots are filled three
+// ahead by global_load_lds_dwordx4 from inline assembly, their completion tracked by hand (s_waitcnt vmcnt), one barrier per
+// slot; the stationary rows come through the ring as well.  A wavefront takes its 32 rows of a slot as two units of 16: 8 column
+// tiles of 16 x 16, 4 MFMAs deep.  Lane (g = lane / 16, n = lane % 16) holds rows 4 g .. 4 g + 3 of column 16 c + n in tile c, so row
+// statistics and column sums are reductions inside the lane; the four lane groups and the parts are merged once per
+// block.  While the MFMAs of a unit run, the lane works through the exponentials of the unit before, one after every MFMA;
+// the order is laid down slot by slot (sched_barrier), since the scheduler left to itself bunches them.  Stages across the
+// diagonal are worked off apart, without the columns that are masked altogether.
+// Registers are the limit: 242 to 256 of the 256 that two wavefronts per SIMD may have, and a single one in scratch memory
+// costs 10 to 20 us a launch (32 x 4096 rows 147 -> 164): lane values that are cheap to form are formed anew, behind an
+// empty assembly statement that keeps the compiler from holding on to them.
+//
+// Blocks x and n_blocks-1-x are paired per workgroup, so that every workgroup has equal work.  Grouped queries (kGrouped): row
+// statistics per query head; the column sums of a K/V head walk the queries of its heads one after the other into the
+// same sums, on small grids dealt out to `splits` workgroups whose partial sums a small kernel adds.
+//
+// The contraction index may be permuted freely as long as both operands agree: lane group g takes the 16-byte chunk 4 s + g of a row
+// for MFMA step s.
+#include <type_traits>
+#include <utility>
+
+#include "prefill_stage.h"
+
+namespace vatp {
+
+namespace {
+
+constexpr int kWaveCols = 128;     // stationary rows per wavefront
+constexpr int kTiles = kWaveCols / 16;
+constexpr int kPartRows = 32;      // streamed rows of a slot per wavefront
+
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
+
+// body(integral_constant 0), ..., body(integral_constant kN - 1)
+template <int... kI, typename F>
+__device__ __forceinline__ void static_for(std::integer_sequence<int, kI...>, F &&body)
+{
+    (body(std::integral_constant<int, kI>{}), ...);
+}
+template <int kN, typename F>
+__device__ __forceinline__ void static_for(F &&body) { static_for(std::make_integer_sequence<int, kN>{}, body); }
+
+struct Unit {                      // logits of 16 streamed rows by 128 columns: tile c, row 4 g + v
+    floatx4 tile[kTiles];
+};
+
+// Per column tile of a lane.  Column sums: col.  Row statistics: the sum l of 2^(t - m).
+struct Running { float m[kTiles], l[kTiles], col[kTiles]; };
+
+// The vector work of a finished unit, dealt out to the kSlots MFMAs of the next one: weights of column tile after column tile.  The
+// weights of a stage are added up (part) before they join the running sums: one rounding of those per stage.
+// kFresh: the first of a stage.  kReference (row statistics): the unit sets the reference m.  It may stay what the first keys of a
+// lane make it: sums of weights up to 2^127 above it keep their precision, and where the lane's first rows are all masked, so are
+// the later ones.  It is a whole number: what takes a sum from one reference to another is a power of two, exactly.
+template <bool kColsum, int kSlots>
+struct VectorWork {
+    float part[kTiles];
+
+    template <int j, bool kFresh, bool kReference>
+    __device__ __forceinline__ void slot(const Unit &done, const floatx4 &lse, Running &run, float scale)
+    {
+        constexpr int kPer = 32 / kSlots;
+        static_for<kPer>([&](auto e) __attribute__((always_inline)) {
+            constexpr int k = kPer * j + decltype(e)::value, c = k / 4, v = k % 4;
+            if constexpr (kReference && v == 0) {
+                const floatx4 &t = done.tile[c];
+                run.m[c] = fmaxf(ceilf(fmaxf(fmaxf(t[0], t[1]), fmaxf(t[2], t[3])) * scale), kLowestLogit);
+            }
+            const float p = fast_exp2(fmaf(done.tile[c][v], scale, kColsum ? -lse[v] : -run.m[c]));
+            if constexpr (kFresh && v == 0) part[c] = p;
+            else part[c] += p;
+            asm volatile("" : "+v"(part[c]));          // (keeps what has been added up in this slot)
+        });
+    }
+    __device__ __forceinline__ void finish(Running &run)
+    {
+#pragma unroll
+        for (int c = 0; c < kTiles; ++c) (kColsum ? run.col[c] : run.l[c]) += part[c];
+    }
+};
+
+// Row statistics (m, l) of the 32 rows from row0 on, by one wavefront, with a running maximum and operands straight from memory:
+// for rows whose sum left the range of a float relative to the fixed reference, which takes a logit 88 (in nats) above all
+// the first keys'.  Lane (g, n) of the 32 x 32 tiles returns its share of row row0 + n.
+__device__ __forceinline__ float2 row_statistics_again(const uint4 *queries, const uint4 *keys, float scale, int row0, int len, int lane)
+{
+    constexpr int kChunks = 16;
+    const int g = lane >> 5, n = lane & 31, row = row0 + n;
+    const uint4 *query = queries + static_cast<size_t>(min(row, len - 1)) * kChunks + g;
+    float m = kLowestLogit, l = 0.f;
+#pragma unroll 1
+    for (int t = 0; t * 32 <= min(row0 + 31, len - 1); ++t) {
+        const uint4 *key = keys + static_cast<size_t>(min(t * 32 + n, len - 1)) * kChunks + g;
+        floatx16 acc;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+#pragma unroll 1
+        for (int s = 0; s < kChunks / 2; ++s)
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(key[2 * s]), as_bf16x8(query[2 * s]), acc, 0, 0, 0);
+        float ref = m;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            acc[v] = t * 32 + 4 * g + acc_row(v) <= row ? acc[v] * scale : -INFINITY;
+            ref = fmaxf(ref, acc[v]);
+        }
+        l *= fast_exp2(m - ref);
+        m = ref;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) l += fast_exp2(acc[v] - m);
+    }
+    return make_float2(m, l);
+}
+
+template <bool kColsum, int kWaves, int kColGroups, bool kGrouped>
+__global__ __launch_bounds__(64 * kWaves, 2) void prefill_wide_kernel(const bf16_t *__restrict__ Q,
+                                                                        const bf16_t *__restrict__ K, float *__restrict__ lse2,
+                                                                        float *__restrict__ S, BatchMeta meta, int n_heads,
+                                                                        int n_units, int cap, int n_blocks, float scale_log2,
+                                                                        const bf16_t *__restrict__ V, float *__restrict__ nrm,
+                                                                        int norm, int group, int splits)
+{
+    static_assert(!kGrouped || kColsum, "only the column sums loop over a group's query heads");
+    constexpr int D = 128, kChunks = D / 8, kSteps = D / 32, kSlots = kTiles * kSteps;
+    constexpr int kBlock = kWaveCols * kColGroups;                        // stationary rows per workgroup
+    constexpr int kParts = kWaves / kColGroups, kSlotRows = kPartRows * kParts, kSlotBytes = kSlotRows * D * 2;
+    constexpr int kOwnRows = kSlotRows / kWaves, kCopyRows = 64 / kChunks, kCopies = kOwnRows / kCopyRows;
+    constexpr int kPending = kCopies + (kColsum ? 1 : 0);                 // copies of a wavefront per slot
+    __shared__ uint4 stage[kRing][kSlotRows * kChunks];   // filled by the load unit
+    __shared__ __attribute__((aligned(16))) float lse_stage[kRing][kSlotRows];
+    __shared__ float merge_buf[kColsum ? 1 : 2][kParts - 1][kBlock];
+
+    // All block pairs of one unit get ids that are equal mod 8: workgroups go to the 8 XCDs round-robin, and the unit's
+    // streamed matrix is pulled into one L2 instead of into all eight.
+    const int n_pairs = (n_blocks + 1) / 2;
+    const int xcd = blockIdx.x & 7, in_xcd = blockIdx.x >> 3;
+    const int slot_i = xcd + 8 * (in_xcd / n_pairs);
+    const int pair = in_xcd % n_pairs;
+    if (slot_i >= n_units) return;
+    // (grouped column sums on a small grid: `splits` workgroups share a K/V head; n_units then counts K/V heads x splits)
+    const int unit_i = kGrouped ? __builtin_amdgcn_readfirstlane(slot_i / splits) : slot_i;
+    const int split = kGrouped ? slot_i - unit_i * splits : 0;
+    const int len = meta.len[unit_i / n_heads];
+    const size_t unit = static_cast<size_t>(unit_i);
+    // query head u belongs to K/V head u / group; the row statistics have one unit per query head, the column sums one per K/V head
+    const bf16_t *const stat = (kColsum ? K : Q) + unit * cap * D;
+    const bf16_t *const strm0 = kColsum ? Q + unit * group * cap * D : K + unit / group * cap * D;
+    float *const lse_u0 = lse2 + (kColsum ? unit * group : unit) * cap;
+    const bf16_t *strm = strm0;
+    float *lse_u = lse_u0;
+
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int cw = wave % kColGroups, part = wave / kColGroups;      // column group, part of a slot's rows
+    const int lane = tid & 63, g = lane >> 4, n = lane & 15;
+    const unsigned lds_stage0 = static_cast<unsigned>(reinterpret_cast<size_t>((lds_char *)(char *)&stage[0][0]));
+    const unsigned lds_lse0 = static_cast<unsigned>(reinterpret_cast<size_t>((lds_char *)(char *)&lse_stage[0][0]));
+
+    // Copy stage t (kSlotRows streamed rows) into ring slot `slot`: this wavefront moves kOwnRows rows, four (1 KiB) per
+    // instruction, and, alike with others, 64 row log-sum-exps.  Rows past the end of the sequence are redirected to its last
+    // row (masked later).
+    // (What an instruction adds to row and chunk are constants: its lane values are formed from two registers every time; kept, they
+    // would take eight.)
+    const int copy_row = kOwnRows * wave + lane / kChunks, copy_chunk = tile_slot<kChunks>(copy_row, lane % kChunks) * 16;
+    auto copy_rows = [&](const bf16_t *rows, int t, int slot) __attribute__((always_inline)) {
+        int row = copy_row, chunk = copy_chunk;
+        if constexpr (kGrouped) {                                  // (from the lane every time: there these two registers are one too many)
+            int own_lane = lane;
+            asm volatile("" : "+v"(own_lane));
+            row = kOwnRows * wave + own_lane / kChunks;
+            chunk = tile_slot<kChunks>(row, own_lane % kChunks) * 16;
+        } else {
+            asm volatile("" : "+v"(row), "+v"(chunk));
+        }
+#pragma unroll
+        for (int i = 0; i < kCopies; ++i) {
+            // (row inside the stage: row + kCopyRows * i; the global chunk for this lane's LDS chunk is its tile_slot)
+            const unsigned voff = static_cast<unsigned>(min(t * kSlotRows + row + kCopyRows * i, len - 1)) * (D * 2) + (chunk ^ (64 * i));
+            const unsigned m0v = lds_stage0 + slot * kSlotBytes + (kOwnRows * wave + kCopyRows * i) * (D * 2);
+            copy_to_lds<4>(m0v, voff, rows);
+        }
+    };
+    auto copy_stage = [&](int t, int slot) __attribute__((always_inline)) {
+        copy_rows(strm, t, slot);
+        if constexpr (kColsum) {
+            const int r = kStage * (wave * (kSlotRows / kStage) / kWaves);
+            const unsigned voff = static_cast<unsigned>(min(t * kSlotRows + r + lane, len - 1)) * 4;
+            const unsigned m0v = lds_lse0 + (slot * kSlotRows + r) * 4;
+            copy_to_lds<1>(m0v, voff, lse_u);
+        }
+    };
+
+    // A job is one block of stationary rows; with grouped queries it is walked once per query head
+    // (`run` and the stationary operand live on from one head to the next).
+    const int n_qh = kGrouped ? __builtin_amdgcn_readfirstlane(group / splits) : 1;
+    bf16x8 Bf[kTiles][kSteps] = {};
+    Running run;
+    for (int it = 0, n_it = 2 * n_qh; it < n_it; ++it) {
+        const int job = kGrouped ? (it >= n_qh ? 1 : 0) : it, qh = kGrouped ? it - job * n_qh : 0;
+        const int blk = job == 0 ? pair : n_blocks - 1 - pair;
+        if (job == 1 && blk == pair) break;            // odd count: the middle block once
+        const int base0 = blk * kBlock;
+        if (base0 >= len) continue;
+        const int w0 = base0 + cw * kWaveCols;         // first stationary row of this wavefront
+        const int t_begin = kColsum ? base0 / kSlotRows : 0;
+        const int t_end = (kColsum ? len - 1 : min(base0 + kBlock - 1, len - 1)) / kSlotRows;      // inclusive
+        if constexpr (kGrouped) {
+            strm = strm0 + static_cast<size_t>(split * n_qh + qh) * cap * D;
+            lse_u = lse_u0 + static_cast<size_t>(split * n_qh + qh) * cap;
+        }
+        // Where stage t sits.  The block of stationary rows comes through the first kBlockSlots slots, once per block, and the
+        // first stages through those that are left at the same time.
+        constexpr int kBlockSlots = kBlock / kSlotRows, kFree = kRing - kBlockSlots;
+        auto slot_of = [&](int t) { return (t - t_begin + kBlockSlots) & (kRing - 1); };
+        if (qh == 0) {
+#pragma unroll
+            for (int k = 0; k < kBlockSlots; ++k) copy_rows(stat, blk * kBlockSlots + k, k);
+        }
+#pragma unroll
+        for (int k = 0; k < kFree; ++k)
+            if (t_begin + k <= t_end) copy_stage(t_begin + k, slot_of(t_begin + k));
+        if (qh == 0) {
+            // Stationary operand: 8 column tiles x kSteps MFMA steps, 8 bf16 per lane each.
+            if (kFree > 0 && t_begin + kFree - 1 <= t_end) wait_copies_then_barrier<kFree * kPending>(); else wait_copies_then_barrier<0>();
+            const uint4 *const rows = &stage[0][cw * kWaveCols * kChunks];
+#pragma unroll
+            for (int c = 0; c < kTiles; ++c)
+#pragma unroll
+                for (int s = 0; s < kSteps; ++s)
+                    Bf[c][s] = as_bf16x8(rows[(16 * c + n) * kChunks + tile_slot<kChunks>(n, 4 * s + g)]);
+            // (complete here, before the slots are filled again, and where the compiler can see it: otherwise it
+            // waits inside the stage loop)
+#pragma unroll
+            for (int c = 0; c < kTiles; ++c)
+#pragma unroll
+                for (int s = 0; s < kSteps; ++s) asm volatile("" ::"v"(Bf[c][s]));
+            lds_barrier();
+#pragma unroll
+            for (int c = 0; c < kTiles; ++c) { run.m[c] = kLowestLogit; run.l[c] = 0.f; run.col[c] = 0.f; }
+        }
+#pragma unroll
+        for (int k = kFree; k < kAhead; ++k)
+            if (t_begin + k <= t_end) copy_stage(t_begin + k, slot_of(t_begin + k));
+
+        // The column sums visit every block of keys once: they also leave the norms of the value rows of the block
+        // (paper Eq. 4), while the first stages are on their way; 32 rows (of 128 elements) at a time beside the stationary operand.
+        if constexpr (kColsum) {
+            if (V != nullptr && qh == 0 && split == 0) {
+                const uint4 *Vu = reinterpret_cast<const uint4 *>(V + unit * cap * D);
+                float *nu = nrm + unit * cap;
+                constexpr int kRows = 8 * kCopyRows;
+#pragma unroll 1
+                for (int row0 = base0 + kRows * wave; row0 < base0 + kBlock; row0 += kRows * kWaves) {
+                    switch (norm) {
+                    case VATP_NORM_L1: value_norms<D, VATP_NORM_L1, 8>(Vu, nu, row0, len, lane); break;
+                    case VATP_NORM_L2: value_norms<D, VATP_NORM_L2, 8>(Vu, nu, row0, len, lane); break;
+                    case VATP_NORM_LINF: value_norms<D, VATP_NORM_LINF, 8>(Vu, nu, row0, len, lane); break;
+                    default: value_norms<D, VATP_NORM_NONE, 8>(Vu, nu, row0, len, lane); break;
+                    }
+                }
+            }
+        }
+        // The two units of a stage.  While the MFMAs of one run, the vector work of the other (unit 1 of the stage
+        // before, or unit 0 of this one) is done.
+        Unit acc[2];
+        floatx4 lse = {0.f, 0.f, 0.f, 0.f};                // column sums: row log-sum-exps of the unit whose vector work is next
+
+        // Publish stage t: it is complete once only the copies of younger stages are outstanding.
+        // Then the slot freed by stage t-1 (every wavefront is past it now) takes stage t+3.
+        auto stage_sync = [&](int t) {
+            if (__builtin_expect(t + kAhead <= t_end, 1)) {
+                wait_copies_then_barrier<2 * kPending>();
+                copy_stage(t + kAhead, slot_of(t + kAhead));
+            } else {
+                if (t_end - t >= 2) wait_copies_then_barrier<2 * kPending>();
+                else if (t_end - t == 1) wait_copies_then_barrier<kPending>();
+                else wait_copies_then_barrier<0>();
+            }
+        };
+        // Operand chunks of the unit of 16 streamed rows from row r0 of a slot on
+        // (chunk 4 s + g of row n; its place differs from that of chunk g by a constant)
+        const int unit_place = n * kChunks * 16 + tile_slot<kChunks>(n, g) * 16;
+        auto load_unit = [&](bf16x8 (&a)[kSteps], int slot, int r0) __attribute__((always_inline)) {
+            int place = unit_place;
+            asm volatile("" : "+v"(place));
+            const char *const rows = reinterpret_cast<const char *>(&stage[slot][r0 * kChunks]);
+#pragma unroll
+            for (int s = 0; s < kSteps; ++s) a[s] = as_bf16x8(*reinterpret_cast<const uint4 *>(rows + (place ^ (64 * s))));
+        };
+        auto load_lse = [&](int slot, int r0) __attribute__((always_inline)) {
+            const float4 x = *reinterpret_cast<const float4 *>(&lse_stage[slot][r0 + 4 * g]);
+            lse = floatx4{x.x, x.y, x.z, x.w};
+        };
+        // A stage without masked logits, branch-free; kFirst: no unit is pending (and the row statistics have no reference yet).
+        // kTail: its rows reach past the end of the sequence; their row log-sum-exps become infinite, the weights 0.
+        auto do_stage = [&](int t, auto first_tag, auto tail_tag) __attribute__((always_inline)) {
+            constexpr bool kFirst = decltype(first_tag)::value, kTail = decltype(tail_tag)::value;
+            const int slot = slot_of(t);
+            // the instantiations must not share a hoisted prefix (the scale is re-read through an opaque asm, so that nothing
+            // that uses it can move up)
+            float scale = scale_log2;
+            asm volatile("; stage variant %1" : "+s"(scale) : "n"(kFirst ? 1 : kTail ? 2 : 0));
+            VectorWork<kColsum, kSlots> work;
+            static_for<2>([&](auto unit_tag) __attribute__((always_inline)) {
+                constexpr int u = decltype(unit_tag)::value;
+                Unit &next = acc[u], &done = acc[1 - u];
+                bf16x8 a[kSteps];
+                load_unit(a, slot, kPartRows * part + 16 * u);
+                __builtin_amdgcn_sched_barrier(0);
+                static_for<kSlots>([&](auto slot_tag) __attribute__((always_inline)) {
+                    constexpr int j = decltype(slot_tag)::value, s = j / kTiles, c = j % kTiles;
+                    if constexpr (s == 0) next.tile[c] = floatx4{0.f, 0.f, 0.f, 0.f};
+                    next.tile[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[s], Bf[c][s], next.tile[c], 0, 0, 0);
+                    if constexpr (!kFirst || u == 1)
+                        work.template slot<j, (kFirst ? u == 1 : u == 0), !kColsum && kFirst>(done, lse, run, scale);
+                    if constexpr (kColsum && j == kSlots - 1) {
+                        load_lse(slot, kPartRows * part + 16 * u);
+                        if constexpr (kTail) {
+                            const int left = len - (t * kSlotRows + kPartRows * part + 16 * u + 4 * g);       // rows from the lane's first on
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) lse[v] = v < left ? lse[v] : INFINITY;
+                        }
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+            });
+            work.finish(run);
+        };
+        // the vector work of the last stage's unit 1, with no MFMAs beside it
+        auto complete = [&]() __attribute__((always_inline)) {
+            VectorWork<kColsum, kSlots> work;
+            __builtin_amdgcn_sched_barrier(0);
+            static_for<kSlots>([&](auto j) __attribute__((always_inline)) {
+                work.template slot<decltype(j)::value, true, false>(acc[1], lse, run, scale_log2);
+                if constexpr (decltype(j)::value % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+            });
+            work.finish(run);
+        };
+        // A stage across the diagonal or the end of the sequence: 16 rows by 128 or, where the other 64 columns are masked altogether,
+        // by 64 columns at a time, the vector work after its MFMAs.  The reference of the row statistics moves here.
+        // rowstat: streamed = keys, stationary = queries; a key counts iff key <= query
+        // colsum : streamed = queries, stationary = keys
+        auto do_masked = [&](int t) __attribute__((always_inline)) {
+            const int slot = slot_of(t);
+#pragma unroll 1
+            for (int u = 0; u < 2; ++u) {
+                const int r0 = kPartRows * part + 16 * u, row0 = t * kSlotRows + r0;       // first row of the unit in the slot, of all
+                if (kColsum && row0 >= len) break;
+                bf16x8 a[kSteps];
+                load_unit(a, slot, r0);
+                if constexpr (kColsum) load_lse(slot, r0);
+                // the logits of tiles kFrom .. kFrom + kCount - 1, masked, and their vector work
+                auto columns = [&](auto from_tag, auto count_tag) __attribute__((always_inline)) {
+                    constexpr int kFrom = decltype(from_tag)::value, kCount = decltype(count_tag)::value;
+                    floatx4 tile[kCount];
+#pragma unroll
+                    for (int c = 0; c < kCount; ++c) tile[c] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int s = 0; s < kSteps; ++s)
+#pragma unroll
+                        for (int c = 0; c < kCount; ++c)
+                            tile[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[s], Bf[kFrom + c][s], tile[c], 0, 0, 0);
+                    int first = row0 + 4 * g, left = len - first;          // first row this lane holds, rows from there on
+                    asm volatile("" : "+v"(left));
+#pragma unroll
+                    for (int c = 0; c < kCount; ++c) {
+                        int d0 = w0 + 16 * (kFrom + c) + n - first;        // lane's stationary index minus that row
+                        asm volatile("" : "+v"(d0));                       // (formed here: kept outside the loops it takes registers)
+                        float x[4], p[4];
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            const bool ok = kColsum ? v >= d0 && v < left : v <= d0;
+                            x[v] = ok ? tile[c][v] : -INFINITY;
+                        }
+                        float &m = run.m[kFrom + c], &sum = kColsum ? run.col[kFrom + c] : run.l[kFrom + c];
+                        if constexpr (!kColsum) {
+                            const float ref = fmaxf(m, ceilf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])) * scale_log2));
+                            sum *= fast_exp2(m - ref);
+                            m = ref;
+                        }
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) p[v] = fast_exp2(fmaf(x[v], scale_log2, kColsum ? -lse[v] : -m));
+                        sum += (p[0] + p[1]) + (p[2] + p[3]);
+                    }
+                };
+                using std::integral_constant;
+                constexpr int kHalf = kTiles / 2;
+                if constexpr (kColsum) {                       // (beside row log-sum-exps, all eight tiles do not fit the registers)
+                    columns(integral_constant<int, 0>{}, integral_constant<int, kHalf>{});
+                    if (row0 + 15 >= w0 + 16 * kHalf) columns(integral_constant<int, kHalf>{}, integral_constant<int, kHalf>{});
+                } else if (row0 < w0 + 16 * kHalf) {
+                    columns(integral_constant<int, 0>{}, integral_constant<int, kTiles>{});
+                } else {
+                    columns(integral_constant<int, kHalf>{}, integral_constant<int, kHalf>{});
+                }
+            }
+        };
+        // Every wavefront walks the same stages (same number of barriers).  Its rows of stage t are R = t * kSlotRows + 32 * part ..
+        // R + 31; they are below, across or above the diagonal of its 128 columns.
+        {
+            const int r_part = kPartRows * part;
+            auto floor_div = [](int a) { return a < 0 ? -1 : a / kSlotRows; };
+            int t = t_begin;
+            if (w0 >= len) {
+                for (; t <= t_end; ++t) stage_sync(t);              // no valid stationary row
+            } else if constexpr (!kColsum) {
+                const int t_full = floor_div(w0 - kPartRows - r_part), t_last = min(floor_div(w0 + kWaveCols - kPartRows - r_part), t_end);
+                if (t <= t_full) {
+                    stage_sync(t);
+                    do_stage(t, std::true_type{}, std::false_type{});
+                    for (++t; t <= t_full; ++t) { stage_sync(t); do_stage(t, std::false_type{}, std::false_type{}); }
+                    complete();
+                }
+                for (; t <= t_last; ++t) { stage_sync(t); do_masked(t); }
+                for (; t <= t_end; ++t) stage_sync(t);               // keys past the diagonal
+            } else {
+                const int t_first = floor_div(w0 - r_part + kSlotRows - 1), t_full = floor_div(w0 + kWaveCols - r_part + kSlotRows - 1);
+                const int t_whole = floor_div(len - kPartRows - r_part);                   // last stage whose rows are all valid
+                for (; t < t_first && t <= t_end; ++t) stage_sync(t);                      // queries before the diagonal
+                for (; t < t_full && t <= t_end; ++t) { stage_sync(t); do_masked(t); }
+                if (t <= t_whole) {
+                    stage_sync(t);
+                    do_stage(t, std::true_type{}, std::false_type{});
+                    for (++t; t <= t_whole; ++t) { stage_sync(t); do_stage(t, std::false_type{}, std::false_type{}); }
+                    if (t <= t_end) {                                 // the last stage, ragged; this wavefront may have no rows of it
+                        stage_sync(t);
+                        if (t * kSlotRows + r_part < len) do_stage(t, std::false_type{}, std::true_type{});
+                        ++t;
+                    }
+                    complete();
+                }
+                for (; t <= t_end; ++t) { stage_sync(t); do_masked(t); }
+            }
+        }
+
+        if (qh == n_qh - 1) {
+            // Merge the four lane groups (same columns, complementary rows): lane (g, n) keeps tiles 2 g and 2 g + 1.  Then the
+            // parts, through LDS.
+            const bool upper = g >= 2, odd = (g & 1) != 0;
+            auto pick = [](bool second, float a0, float a1) { return second ? a1 : a0; };
+            float fin_l[2], fin_m[2] = {0.f, 0.f};
+            if constexpr (kColsum) {
+                float half[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    half[c] = pick(upper, run.col[c], run.col[4 + c]) + __shfl_xor(pick(upper, run.col[4 + c], run.col[c]), 32);
+#pragma unroll
+                for (int c = 0; c < 2; ++c)
+                    fin_l[c] = pick(odd, half[c], half[2 + c]) + __shfl_xor(pick(odd, half[2 + c], half[c]), 16);
+            } else {
+                auto join = [](float m, float l, float m_o, float l_o, float &m_out, float &l_out) {
+                    m_out = fmaxf(m, m_o);
+                    l_out = l * fast_exp2(m - m_out) + l_o * fast_exp2(m_o - m_out);
+                };
+                float m4[4], l4[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    join(pick(upper, run.m[c], run.m[4 + c]), pick(upper, run.l[c], run.l[4 + c]),
+                         __shfl_xor(pick(upper, run.m[4 + c], run.m[c]), 32), __shfl_xor(pick(upper, run.l[4 + c], run.l[c]), 32),
+                         m4[c], l4[c]);
+#pragma unroll
+                for (int c = 0; c < 2; ++c)
+                    join(pick(odd, m4[c], m4[2 + c]), pick(odd, l4[c], l4[2 + c]), __shfl_xor(pick(odd, m4[2 + c], m4[c]), 16),
+                         __shfl_xor(pick(odd, l4[2 + c], l4[c]), 16), fin_m[c], fin_l[c]);
+            }
+            const int col0 = cw * kWaveCols + 32 * g + n;           // this lane's columns in the block: col0, col0 + 16
+            if (part > 0) {
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    merge_buf[0][part - 1][col0 + 16 * c] = fin_l[c];
+                    if (!kColsum) merge_buf[1][part - 1][col0 + 16 * c] = fin_m[c];
+                }
+            }
+            __syncthreads();
+            if (part == 0) {
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    float l[kParts], m[kParts];
+                    l[0] = fin_l[c];
+                    m[0] = fin_m[c];
+#pragma unroll
+                    for (int p = 1; p < kParts; ++p) {
+                        l[p] = merge_buf[0][p - 1][col0 + 16 * c];
+                        m[p] = kColsum ? 0.f : merge_buf[1][p - 1][col0 + 16 * c];
+                        if (!kColsum) fin_m[c] = fmaxf(fin_m[c], m[p]);
+                    }
+#pragma unroll
+                    for (int p = 0; p < kParts; ++p)
+                        if (!kColsum) l[p] *= fast_exp2(m[p] - fin_m[c]);
+                    fin_l[c] = kParts == 2 ? l[0] + l[1] : (l[0] + l[1]) + (l[kParts - 2] + l[kParts - 1]);
+                }
+                // sums that left the range of a float are formed again, 32 rows (those of lane group cb) at a time
+                if constexpr (!kColsum) {
+                    // (infinite, or NaN after a merge, which this file is compiled not to expect: seen in the bits alone)
+                    auto lost = [](float x) {
+                        unsigned bits = __float_as_uint(x);
+                        asm volatile("" : "+v"(bits));
+                        return (bits & 0x7f800000u) == 0x7f800000u;
+                    };
+                    const bool again = (base0 + col0 < len && lost(fin_l[0])) || (base0 + col0 + 16 < len && lost(fin_l[1]));
+#pragma unroll 1
+                    for (int cb = 0; cb < kWaveCols / 32; ++cb) {
+                        if (!__any(g == cb && again)) continue;
+                        int own_lane = threadIdx.x & 63;
+                        asm volatile("" : "+v"(own_lane));      // (keeps what is derived from it out of the registers of the loops above)
+                        const float2 x = row_statistics_again(reinterpret_cast<const uint4 *>(stat), reinterpret_cast<const uint4 *>(strm), scale_log2, w0 + 32 * cb, len, own_lane);
+                        const float m_o = __shfl_xor(x.x, 32), l_o = __shfl_xor(x.y, 32), m = fmaxf(x.x, m_o);
+                        const float l = x.y * fast_exp2(x.x - m) + l_o * fast_exp2(m_o - m);
+#pragma unroll
+                        for (int c = 0; c < 2; ++c) {
+                            const float m_c = __shfl(m, n + 16 * c), l_c = __shfl(l, n + 16 * c);
+                            if (g == cb) { fin_m[c] = m_c; fin_l[c] = l_c; }
+                        }
+                    }
+                }
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    const int idx = base0 + col0 + 16 * c;
+                    if (idx >= len) continue;
+                    if constexpr (!kColsum) {
+                        int e;
+                        const float f = frexpf(fin_l[c], &e);          // (the logarithm of a number between 1/2 and 1 rounds the least)
+                        lse_u[idx] = (fin_m[c] + static_cast<float>(e)) + __log2f(f);
+                    } else if (kGrouped && splits > 1) {               // partial sum [split, K/V head, cap], mean taken by the merge kernel
+                        S[(static_cast<size_t>(split) * (n_units / splits) + unit) * cap + idx] = fin_l[c];
+                    } else {
+                        S[unit * cap + idx] = kGrouped ? fin_l[c] * (1.f / static_cast<float>(group)) : fin_l[c];      // (the group mean)
+                    }
+                }
+            }
+        }
+        // every wavefront must be done reading the ring before the next job refills it (all
+        // copies have landed by now; the result stores need not have)
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    }
+}
+
+template <int kWaves, int kColGroups>
+void launch_rowstat(const bf16_t *q, const bf16_t *k, float *S, float *lse2, const BatchMeta &meta, const Geometry &g, hipStream_t st)
+{
+    constexpr int kBlock = kWaveCols * kColGroups;
+    const int units = g.batch * g.n_heads * g.group, n_blocks = (g.max_len + kBlock - 1) / kBlock;
+    hipLaunchKernelGGL((prefill_wide_kernel<false, kWaves, kColGroups, false>), dim3(8u * ((n_blocks + 1) / 2) * ((units + 7) / 8)),
+                       dim3(64 * kWaves), 0, st, q, k, lse2, S, meta, g.n_heads * g.group, units, g.cap, n_blocks, g.scale_log2, nullptr,
+                       nullptr, 0, g.group, 1);
+}
+template <int kWaves, int kColGroups, bool kGrouped>
+void launch_colsum(const bf16_t *q, const bf16_t *k, const bf16_t *v, float *dst, float *nrm, float *lse2, int splits,
+                   const BatchMeta &meta, const Geometry &g, hipStream_t st)
+{
+    constexpr int kBlock = kWaveCols * kColGroups;
+    const int slots = g.batch * g.n_heads * splits, n_blocks = (g.max_len + kBlock - 1) / kBlock;
+    hipLaunchKernelGGL((prefill_wide_kernel<true, kWaves, kColGroups, kGrouped>), dim3(8u * ((n_blocks + 1) / 2) * ((slots + 7) / 8)),
+                       dim3(64 * kWaves), 0, st, q, k, lse2, dst, meta, g.n_heads, slots, g.cap, n_blocks, g.scale_log2, v, nrm, g.norm,
+                       g.group, splits);
+}
+
+}  // namespace
+
+// Two wavefronts per SIMD either way: two 4-wavefront workgroups per compute unit when the grid is large enough to keep pairs of
+// them resident, else 8-wavefront workgroups.  One unit per query head in the row statistics, one per K/V head in the column sums.
+hipError_t launch_prefill_wide(const void *Q, const void *K, const void *V, float *S, float *nrm, float *lse2, float *s_part, int passes,
+                               const BatchMeta &meta, const Geometry &g, hipStream_t st)
+{
+    if (g.max_len <= 0) return hipSuccess;
+    const bf16_t *q = static_cast<const bf16_t *>(Q), *k = static_cast<const bf16_t *>(K), *v = static_cast<const bf16_t *>(V);
+    const int splits = s_part != nullptr ? colsum_splits(g) : 1;
+    if (passes & kPassRowstat) {
+        const unsigned wgs = 8u * block_pairs(g) * ((g.batch * g.n_heads * g.group + 7) / 8);
+        if (wgs >= 2u * kComputeUnits) launch_rowstat<4, 2>(q, k, S, lse2, meta, g, st);
+        else launch_rowstat<8, 2>(q, k, S, lse2, meta, g, st);
+    }
+    if (!(passes & kPassColsum)) return hipGetLastError();
+    float *dst = splits > 1 ? s_part : S;
+    const unsigned wgs = 8u * block_pairs(g) * ((g.batch * g.n_heads * splits + 7) / 8);
+    if (g.group > 1) {
+        if (wgs >= 2u * kComputeUnits) launch_colsum<4, 2, true>(q, k, v, dst, nrm, lse2, splits, meta, g, st);
+        else launch_colsum<8, 2, true>(q, k, v, dst, nrm, lse2, splits, meta, g, st);
+    } else {
+        if (wgs >= 2u * kComputeUnits) launch_colsum<4, 2, false>(q, k, v, dst, nrm, lse2, splits, meta, g, st);
+        else launch_colsum<8, 2, false>(q, k, v, dst, nrm, lse2, splits, meta, g, st);
+    }
+    if (splits > 1) return launch_merge_group_partials(s_part, S, splits, meta, g, st);
+    return hipGetLastError();
+}
+
+}  // namespace vatp

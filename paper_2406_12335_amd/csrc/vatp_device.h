@@ -507,6 +507,8 @@ hipError_t launch_lse_to_base2(const float *lse, float *lse2, const BatchMeta &m
 // (s_part: room for group * units * cap floats of partial column sums when query heads are grouped, else unused)
 hipError_t launch_prefill_mfma(int head_dim, const void *Q, const void *K, const void *V, float *S, float *nrm, float *lse2,
                                float *s_part, int pass, const BatchMeta &meta, const Geometry &g, hipStream_t st);
+hipError_t launch_prefill_wide(const void *Q, const void *K, const void *V, float *S, float *nrm, float *lse2, float *s_part, int pass,
+                               const BatchMeta &meta, const Geometry &g, hipStream_t st);
 // whether the grid of a pass is one the staged kernels run well
 bool prefill_mfma_fills(int head_dim, int pass, const Geometry &g);
 

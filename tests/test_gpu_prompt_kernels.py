@@ -291,3 +291,37 @@ def test_weights_below_the_normal_range(gpu_device, dtype, d, B, H, g, L, window
     if window is not None:
         seen = torch.arange(L) <= torch.arange(first, L).unsqueeze(1)
         assert ((hist - p.unsqueeze(2)).abs() <= 1e-5 * p.unsqueeze(2) + 2.0 ** -149)[:, :, seen].all()
+
+
+# Grids that fill the chip, heads of 128: workgroups of four wavefronts (first list) and of eight, blocks of 256 rows in two column
+# groups of 128, ring slots of 64 and 128 rows in parts of 32, units of 16
+@pytest.mark.parametrize("H,g,lens", [
+    (32, 1, [300, 1, 16, 17, 31, 32, 33, 127, 128, 129, 255, 256, 257, 271, 272, 273]), (32, 2, [769, 1, 63, 64, 65, 385, 513, 640]),
+    (28, 1, [1025, 895, 127, 129, 160]), (10, 3, [1313, 1, 511, 513, 1151, 1185, 97, 260])])
+def test_wide_tiles(gpu_device, H, g, lens):
+    _check_scores(gpu_device, "bf16", 128, g, H, lens, None, [(b, H - 1 if b % 2 else 0) for b in range(len(lens))], 301 + g)
+
+
+# Row statistics are kept relative to the first keys of a row: sums that leave a float's range are formed again
+@pytest.mark.parametrize("H,lens", [(32, [300, 1, 259, 128] * 2), (16, [1100, 300, 520])])
+def test_logits_far_above_those_of_the_first_keys(gpu_device, H, lens):
+    gen = torch.Generator().manual_seed(5)
+    B, L = len(lens), max(lens)
+    Q, K, V = (torch.randn(B, H, L, 128, generator=gen) for _ in range(3))
+    Q[..., 0] = 32.0
+    K[..., 0] = 0.0
+    for row, far in ((17, 10.0), (100, 49.0), (203, 74.0), (258, 98.0), (519, 110.0)):     # base-2 logits of 41, 200, 302, 400 and 449
+        if row < L:
+            K[:, :, row, 0] = far
+    Q, K, V = Q.bfloat16(), K.bfloat16(), V.bfloat16()
+    cache = PrunedKVCache(B, H, 128, torch.bfloat16, 0, 0, [L] * B, gpu_device)
+    try:
+        cache.prefill_score(Q.to(gpu_device), K.to(gpu_device), V.to(gpu_device), lens)
+        S = cache.S_prompt.cpu()
+    finally:
+        cache.close()
+    for b in range(B):
+        for h in (0, H - 1):
+            n = lens[b]
+            want = orc.prefill_scores_group(Q[b, h:h + 1, :n].double().numpy(), K[b, h, :n].double().numpy())
+            parity.assert_scores_close(S[b, h, :n].numpy(), want, parity.rtol_for(torch.bfloat16), "len %d head %d" % (n, h))
