@@ -74,10 +74,13 @@ def algorithmic_bytes_window(cfg, n_rows, window, rows_moved):
 
 def fused_step_kernels(cfg, lens, budgets, window):
     """Names of the kernels one vatp_decode_prune_step call launches for this workload (the library's rule:
-    a single launch with one workgroup per head when there are at least 128 heads of at most 1024 rows and
-    neither grouped queries nor a history window; otherwise the logits launch plus the evict-and-copy launch)."""
+    a single launch with one workgroup per head, without grouped queries and history window, for up to 256 heads of at most
+    256 KiB of K rows and for 128 heads and more of at most 1024 rows; otherwise the logits launch plus the
+    evict-and-copy launch)."""
     rows = max(min(L, B) for L, B in zip(lens, budgets)) + 1
-    if window is None and cfg.q_per_kv == 1 and cfg.batch * cfg.n_heads >= 128 and rows <= 1024:
+    heads, row_bytes = cfg.batch * cfg.n_heads, cfg.head_dim * (2 if cfg.dtype == "bf16" else 4)
+    short = rows <= 2048 and ((heads <= 256 and rows * row_bytes <= 256 << 10) or (heads >= 128 and rows <= 1024))
+    if window is None and cfg.q_per_kv == 1 and short:
         return "decode_prune_one_kernel"
     first = "decode_logits_group_kernel" if cfg.q_per_kv > 1 else "decode_logits_kernel"
     return first + " + decode_prune_kernel"

@@ -384,12 +384,15 @@ vatp_status decode_prune_impl(vatp_ctx *ctx, const vatp_params *p, const void *q
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     BatchMeta budgets = pr.meta;
     for (int b = 0; b < p->batch; ++b) budgets.aux[b] = p->budget[b];
-    // One launch with a workgroup per head when there are enough heads to fill the chip that way and
-    // each is short enough for a single workgroup to stream quickly (measured per step at 256 heads x 820 rows:
-    // 22 against 30 us with 32 layers' caches in turn; slower than two launches
-    // at 32 heads x 2049 rows, 23 against 14 us).
-    const bool one = !out && !win.hist && pr.g.group == 1 && kv_units >= 128 && pr.g.max_len <= 1024 &&
-                     pr.g.max_len <= decode_prune_one_max_rows();
+    // One launch with a workgroup per head when each head is short enough for a single workgroup to stream quickly: up to 256 KiB of
+    // K rows (1024 rows of 256 bytes) while the workgroups share no compute unit, and up to 1024 rows of any size from 128 heads on.
+    // Measured per step, two launches / one: 4 fp32 heads of 64 x 129 rows 12.4 / 8.2 us, 32 heads of 128 x 251 rows 11.5 / 7.9, x 1001
+    // rows 11.3 / 8.9, 96 x 1001 13.2 / 10.4, 256 heads of 64 x 2046 rows 19.6 / 18.1, but 512 x 1251 24.6 / 26.6; 8 fp32 heads of 128
+    // (512-byte rows) x 501 11.5 / 9.6, but x 1001 11.4 / 12.0; 32 heads of 128 x 2049 rows 14 / 23; 256 heads x 820 rows with 32 layers'
+    // caches in turn 30 / 22.
+    const size_t row_bytes = static_cast<size_t>(p->head_dim) * (p->dtype == VATP_BF16 ? 2 : 4);
+    const bool one = !out && !win.hist && pr.g.group == 1 && pr.g.max_len <= decode_prune_one_max_rows() &&
+                     ((kv_units <= 256 && pr.g.max_len * row_bytes <= (256u << 10)) || (kv_units >= 128 && pr.g.max_len <= 1024));
     if (one) {
         BudgetList blist;
         memcpy(blist.v, budgets.aux, sizeof(blist.v));

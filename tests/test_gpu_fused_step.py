@@ -24,7 +24,7 @@ def _say(msg):
     ("tiny", {}),
     ("llama7b_layer", dict(n_heads=4, prompt_len=777, decode_steps=24)),
     ("ragged16", dict(batch=6, n_heads=2, decode_steps=10, recent=8, ragged=(1, 600))),
-    # 128 heads or more with short caches take the single-launch route
+    # (all of these are short enough for the single-launch route; 128 heads and more)
     ("tiny", dict(batch=4, n_heads=32, prompt_len=96, decode_steps=12, recent=8)),
     ("llama7b_layer", dict(batch=2, n_heads=64, prompt_len=150, decode_steps=8, recent=16)),
 ])
@@ -72,7 +72,7 @@ def _seed_state(caches, lens, g, d, tdt, dev, weak_rows=None):
     ("fp32", 64, 3, [129, 40, 128], [129, 129, 129], 8, 0, 10),
     ("bf16", 64, 3, [513, 512, 100], [513, 513, 513], 32, 4, 9),
     ("fp32", 128, 3, [70, 70, 3], [70, 70, 70], 5, 1, 8),
-    # 128 heads and more: the steps without attention output take the single-launch route
+    # (the steps without attention output of all these take the single-launch route; 128 heads and more)
     ("bf16", 128, 43, [300, 290, 64], [300, 300, 70], 16, 2, 8),
     ("fp32", 64, 64, [1000, 129], [1000, 140], 8, 0, 7),
     ("bf16", 64, 32, [5, 130, 129, 257], [9, 130, 200, 257], 3, 1, 9),
@@ -83,6 +83,10 @@ def _seed_state(caches, lens, g, d, tdt, dev, weak_rows=None):
     ("bf16", 64, 64, [700, 690], [700, 700], 200, 1, 9),       # much longer: part of the window is copied afterwards
     ("fp32", 128, 64, [300, 100], [300, 300], 40, 0, 9),       # 32 lanes per row
     ("bf16", 128, 65, [1023, 1000], [1023, 1023], 64, 2, 6),   # 1024 rows after the append: the route's limit
+    ("bf16", 128, 3, [1023, 600], [1023, 1023], 64, 2, 6),
+    ("bf16", 64, 3, [2047, 1030], [2047, 2047], 64, 2, 6),     # rows of 128 bytes: 2048
+    ("fp32", 128, 3, [511, 64], [511, 511], 30, 2, 6),         # of 512 bytes: 512, one more takes two launches
+    ("fp32", 128, 3, [512, 511], [512, 512], 30, 2, 6),
 ])
 def test_fused_step_is_bit_identical_to_the_two_call_route(gpu_device, dtype, d, H, lens, budgets, R, F, steps):
     """Same K, V, S, nrm, pos, kept_idx and attention output as vatp_decode_attend_step followed by
