@@ -130,8 +130,8 @@ struct Running {                 // per column block: rowstat (m, l) or colsum p
 
 // The exponentials of a pending pair, cut into 16 pieces so that one piece can follow each
 // MFMA of the next pair; finish() runs what is left after piece 15.
-// kWhole: the row statistics are kept relative to a whole number, the maximum rounded up (pack_partial).
-template <bool kColsum, bool kWhole = false>
+// Row statistics are kept relative to a whole number.  kMoving: the maximum so far, rounded up; otherwise what an earlier pair left.
+template <bool kColsum, bool kMoving>
 struct Epilogue {
     float ref[2], corr[2], part[2], tmax[2];
 
@@ -157,6 +157,12 @@ struct Epilogue {
                 else if constexpr (kStore == 2)
                     group_sum[cb][i] += pr;
             }
+        } else if constexpr (!kMoving) {
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb) {
+                const float pr = fast_exp2(fmaf(p.acc[cb][i], scale, -run.m[cb]));
+                part[cb] = i == 0 ? pr : part[cb] + pr;
+            }
         } else {
             if (i < 2) {                                   // tile maximum of column block i
                 // a linear chain, so that every two steps fuse into one three-operand maximum
@@ -167,7 +173,7 @@ struct Epilogue {
             } else if (i == 2) {
 #pragma unroll
                 for (int cb = 0; cb < 2; ++cb) {
-                    ref[cb] = fmaxf(run.m[cb], kWhole ? ceilf(tmax[cb] * scale) : tmax[cb] * scale);
+                    ref[cb] = fmaxf(run.m[cb], ceilf(tmax[cb] * scale));
                     corr[cb] = fast_exp2(run.m[cb] - ref[cb]);
                     part[cb] = 0.f;
                 }
@@ -184,6 +190,9 @@ struct Epilogue {
         if constexpr (kColsum) {
             run.col[0] += part[0];
             run.col[1] += part[1];
+        } else if constexpr (!kMoving) {
+            run.l[0] += part[0];
+            run.l[1] += part[1];
         } else {
 #pragma unroll
             for (int v = 13; v < 16; ++v)
@@ -455,6 +464,9 @@ __global__ __launch_bounds__(256 * kHalves, D == 64 && kColsum && kHalves == 1 &
                 auto do_stage = [&](int t, auto masked_tag, auto store_tag) __attribute__((always_inline)) {
                     constexpr bool kMasked = decltype(masked_tag)::value;
                     constexpr int kStoreMode = decltype(store_tag)::value;
+                    // (the reference of the row statistics: set by the first stage, left alone by full ones, as far as the heads of 64
+                    // without a window go, where vector instructions bound the pass: 253 -> 206 of them a stage)
+                    constexpr bool kMoving = !kColsum && (kWindow || kMasked);
                     const int slot = kBand ? (cur_v & (kRing - 1)) : ((t - t_begin) & (kRing - 1));
                     const int s0 = t * kSlotRows + kStage * half;   // first streamed row of the sub-stage
                     // the two instantiations must not share a hoisted prefix: the pending pair's
@@ -496,7 +508,7 @@ __global__ __launch_bounds__(256 * kHalves, D == 64 && kColsum && kHalves == 1 &
                                                               : 0x80000000u;
                             }
                         }
-                        Epilogue<kColsum, kSplitKeys> epi;
+                        Epilogue<kColsum, kMoving> epi;
 #pragma unroll
                         for (int s = 0; s < kSteps; ++s)
 #pragma unroll
@@ -570,6 +582,7 @@ __global__ __launch_bounds__(256 * kHalves, D == 64 && kColsum && kHalves == 1 &
                         for (; t <= t_end; ++t) stage_sync(t);              // no valid stationary row
                     } else if constexpr (!kColsum) {
                         // (a range of keys may end before the diagonal or begin after it)
+                        if (!kWindow && t <= t_first && t <= t_end && (t < t_first || on_diag)) { stage_sync(t); do_stage(t, std::true_type{}, store_tag); ++t; }
                         for (; t < t_first && t <= t_end; ++t) { stage_sync(t); do_stage(t, std::false_type{}, store_tag); }
                         if (on_diag && t == t_first && t <= t_end) { stage_sync(t); do_stage(t, std::true_type{}, store_tag); ++t; }
                         for (; t <= t_end; ++t) stage_sync(t);               // keys past the diagonal
@@ -582,7 +595,7 @@ __global__ __launch_bounds__(256 * kHalves, D == 64 && kColsum && kHalves == 1 &
                         for (; t <= t_end; ++t) { stage_sync(t); do_stage(t, std::true_type{}, store_tag); }   // ragged tail
                     }
                     // the last pair still waits for its exponentials
-                    Epilogue<kColsum, kSplitKeys> epi;
+                    Epilogue<kColsum, true> epi;
 #pragma unroll
                     for (int i = 0; i < 16; ++i)
                         epi.template piece<decltype(store_tag)::value>(i, pend, run, scale_log2, hist_rsrc, cap * 4);
@@ -605,7 +618,7 @@ __global__ __launch_bounds__(256 * kHalves, D == 64 && kColsum && kHalves == 1 &
                             else do_stage(t, std::false_type{}, add_tag{});
                         }
                         if (idle) continue;
-                        Epilogue<kColsum, kSplitKeys> epi;
+                        Epilogue<kColsum, true> epi;
 #pragma unroll
                         for (int i = 0; i < 16; ++i) epi.template piece<2>(i, pend, run, scale_log2, hist_rsrc, cap * 4, group_sum[1]);
                         epi.finish(pend, run, scale_log2);
@@ -672,6 +685,23 @@ __global__ __launch_bounds__(256 * kHalves, D == 64 && kColsum && kHalves == 1 &
                 }
             }
         }
+        // sums that left the range of a float are formed again (infinite, or NaN after a merge, which this file is compiled not to
+        // expect: seen in the bits alone)
+        if constexpr (!kColsum && !kWindow) {
+            if (half == 0) {
+#pragma unroll
+                for (int cb = 0; cb < 2; ++cb) {
+                    unsigned bits = __float_as_uint(fin_l[cb]);
+                    asm volatile("" : "+v"(bits));
+                    if (!__any(w0 + 32 * cb + n < len && (bits & 0x7f800000u) == 0x7f800000u)) continue;
+                    int own_lane = threadIdx.x & 63;
+                    asm volatile("" : "+v"(own_lane));      // (keeps what is derived from it out of the registers of the loops above)
+                    const float2 x = row_statistics_again<D>(stat, reinterpret_cast<const uint4 *>(strm), scale_log2, w0 + 32 * cb, len, own_lane);
+                    fin_m[cb] = x.x;
+                    fin_l[cb] = x.y;
+                }
+            }
+        }
         if constexpr (kRepair) {
             if (half == 0) {
 #pragma unroll
@@ -700,7 +730,7 @@ __global__ __launch_bounds__(256 * kHalves, D == 64 && kColsum && kHalves == 1 &
                         if (idx >= q_first)
                             win.lse_part[(static_cast<size_t>(pair % win.n_splits) * n_units + unit) * win.part_rows + idx - q_first] =
                                 pack_partial(fin_m[cb], fin_l[cb]);
-                    } else if (!kColsum) lse_u[idx] = fin_m[cb] + __log2f(fin_l[cb]);
+                    } else if (!kColsum) lse_u[idx] = sum_log2(fin_m[cb], fin_l[cb]);
                     else if (kGrouped && splits > 1)     // partial sum [split, K/V head, cap], mean taken by the merge kernel
                         S[(static_cast<size_t>(split) * (n_units / splits) + unit) * cap + idx] = fin_l[cb];
                     else S[unit * cap + idx] = (kGrouped && !kWindow) ? fin_l[cb] * inv_group : fin_l[cb];   // (windowed groups: weights already divided)

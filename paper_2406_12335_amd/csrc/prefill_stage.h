@@ -74,6 +74,48 @@ __device__ __forceinline__ void value_norms(const uint4 *__restrict__ Vu, float 
     }
 }
 
+// Row statistics (m, l) of the 32 rows from row0 on, by one wavefront, with a running maximum and operands straight from memory:
+// for rows whose sum left the range of a float relative to the fixed reference, which takes a logit 88 (in nats) above all
+// the first keys'.  Lanes n and n + 32 return row row0 + n.
+template <int D>
+__device__ __forceinline__ float2 row_statistics_again(const uint4 *queries, const uint4 *keys, float scale, int row0, int len, int lane)
+{
+    constexpr int kChunks = D / 8;
+    const int g = lane >> 5, n = lane & 31, row = row0 + n;
+    const uint4 *query = queries + static_cast<size_t>(min(row, len - 1)) * kChunks + g;
+    float m = kLowestLogit, l = 0.f;
+#pragma unroll 1
+    for (int t = 0; t * 32 <= min(row0 + 31, len - 1); ++t) {
+        const uint4 *key = keys + static_cast<size_t>(min(t * 32 + n, len - 1)) * kChunks + g;
+        floatx16 acc;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+#pragma unroll 1
+        for (int s = 0; s < kChunks / 2; ++s)
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(key[2 * s]), as_bf16x8(query[2 * s]), acc, 0, 0, 0);
+        float ref = m;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            acc[v] = t * 32 + 4 * g + acc_row(v) <= row ? acc[v] * scale : -INFINITY;
+            ref = fmaxf(ref, acc[v]);
+        }
+        l *= fast_exp2(m - ref);
+        m = ref;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) l += fast_exp2(acc[v] - m);
+    }
+    const float m_o = __shfl_xor(m, 32), l_o = __shfl_xor(l, 32), ref = fmaxf(m, m_o);
+    return make_float2(ref, l * fast_exp2(m - ref) + l_o * fast_exp2(m_o - ref));
+}
+
+// log2 of 2^m * l, m whole (the logarithm of a number between 1/2 and 1 rounds the least)
+__device__ __forceinline__ float sum_log2(float m, float l)
+{
+    int e;
+    const float f = frexpf(l, &e);
+    return (m + static_cast<float>(e)) + __log2f(f);
+}
+
 inline int block_pairs(const Geometry &g) { return ((g.max_len + kBlockCols - 1) / kBlockCols + 1) / 2; }
 
 // Grouped column sums: a K/V head's query heads are walked by one workgroup (no partial sums) when that

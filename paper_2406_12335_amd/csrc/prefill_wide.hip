@@ -105,38 +105,6 @@ struct VectorWork {
     }
 };
 
-// Row statistics (m, l) of the 32 rows from row0 on, by one wavefront, with a running maximum and operands straight from memory:
-// for rows whose sum left the range of a float relative to the fixed reference, which takes a logit 88 (in nats) above all
-// the first keys'.  Lane (g, n) of the 32 x 32 tiles returns its share of row row0 + n.
-__device__ __forceinline__ float2 row_statistics_again(const uint4 *queries, const uint4 *keys, float scale, int row0, int len, int lane)
-{
-    constexpr int kChunks = 16;
-    const int g = lane >> 5, n = lane & 31, row = row0 + n;
-    const uint4 *query = queries + static_cast<size_t>(min(row, len - 1)) * kChunks + g;
-    float m = kLowestLogit, l = 0.f;
-#pragma unroll 1
-    for (int t = 0; t * 32 <= min(row0 + 31, len - 1); ++t) {
-        const uint4 *key = keys + static_cast<size_t>(min(t * 32 + n, len - 1)) * kChunks + g;
-        floatx16 acc;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-#pragma unroll 1
-        for (int s = 0; s < kChunks / 2; ++s)
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(key[2 * s]), as_bf16x8(query[2 * s]), acc, 0, 0, 0);
-        float ref = m;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            acc[v] = t * 32 + 4 * g + acc_row(v) <= row ? acc[v] * scale : -INFINITY;
-            ref = fmaxf(ref, acc[v]);
-        }
-        l *= fast_exp2(m - ref);
-        m = ref;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) l += fast_exp2(acc[v] - m);
-    }
-    return make_float2(m, l);
-}
-
 template <bool kColsum, int kWaves, int kColGroups, bool kGrouped>
 __global__ __launch_bounds__(64 * kWaves, 2) void prefill_wide_kernel(const bf16_t *__restrict__ Q,
                                                                         const bf16_t *__restrict__ K, float *__restrict__ lse2,
@@ -528,12 +496,11 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_wide_kernel(const bf16
                         if (!__any(g == cb && again)) continue;
                         int own_lane = threadIdx.x & 63;
                         asm volatile("" : "+v"(own_lane));      // (keeps what is derived from it out of the registers of the loops above)
-                        const float2 x = row_statistics_again(reinterpret_cast<const uint4 *>(stat), reinterpret_cast<const uint4 *>(strm), scale_log2, w0 + 32 * cb, len, own_lane);
-                        const float m_o = __shfl_xor(x.x, 32), l_o = __shfl_xor(x.y, 32), m = fmaxf(x.x, m_o);
-                        const float l = x.y * fast_exp2(x.x - m) + l_o * fast_exp2(m_o - m);
+                        const float2 x = row_statistics_again<D>(reinterpret_cast<const uint4 *>(stat), reinterpret_cast<const uint4 *>(strm),
+                                                                 scale_log2, w0 + 32 * cb, len, own_lane);
 #pragma unroll
                         for (int c = 0; c < 2; ++c) {
-                            const float m_c = __shfl(m, n + 16 * c), l_c = __shfl(l, n + 16 * c);
+                            const float m_c = __shfl(x.x, n + 16 * c), l_c = __shfl(x.y, n + 16 * c);
                             if (g == cb) { fin_m[c] = m_c; fin_l[c] = l_c; }
                         }
                     }
@@ -543,9 +510,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_wide_kernel(const bf16
                     const int idx = base0 + col0 + 16 * c;
                     if (idx >= len) continue;
                     if constexpr (!kColsum) {
-                        int e;
-                        const float f = frexpf(fin_l[c], &e);          // (the logarithm of a number between 1/2 and 1 rounds the least)
-                        lse_u[idx] = (fin_m[c] + static_cast<float>(e)) + __log2f(f);
+                        lse_u[idx] = sum_log2(fin_m[c], fin_l[c]);
                     } else if (kGrouped && splits > 1) {               // partial sum [split, K/V head, cap], mean taken by the merge kernel
                         S[(static_cast<size_t>(split) * (n_units / splits) + unit) * cap + idx] = fin_l[c];
                     } else {

@@ -303,18 +303,19 @@ def test_wide_tiles(gpu_device, H, g, lens):
 
 
 # Row statistics are kept relative to the first keys of a row: sums that leave a float's range are formed again
-@pytest.mark.parametrize("H,lens", [(32, [300, 1, 259, 128] * 2), (16, [1100, 300, 520])])
-def test_logits_far_above_those_of_the_first_keys(gpu_device, H, lens):
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("H,lens", [(32, [300, 1, 259, 128] * 2), (16, [1100, 300, 520]), (25, [1100, 300, 520, 900])])
+def test_logits_far_above_those_of_the_first_keys(gpu_device, d, H, lens):
     gen = torch.Generator().manual_seed(5)
     B, L = len(lens), max(lens)
-    Q, K, V = (torch.randn(B, H, L, 128, generator=gen) for _ in range(3))
-    Q[..., 0] = 32.0
+    Q, K, V = (torch.randn(B, H, L, d, generator=gen) for _ in range(3))
+    Q[..., 0] = 32.0 * math.sqrt(d / 128)
     K[..., 0] = 0.0
     for row, far in ((17, 10.0), (100, 49.0), (203, 74.0), (258, 98.0), (519, 110.0)):     # base-2 logits of 41, 200, 302, 400 and 449
         if row < L:
             K[:, :, row, 0] = far
     Q, K, V = Q.bfloat16(), K.bfloat16(), V.bfloat16()
-    cache = PrunedKVCache(B, H, 128, torch.bfloat16, 0, 0, [L] * B, gpu_device)
+    cache = PrunedKVCache(B, H, d, torch.bfloat16, 0, 0, [L] * B, gpu_device)
     try:
         cache.prefill_score(Q.to(gpu_device), K.to(gpu_device), V.to(gpu_device), lens)
         S = cache.S_prompt.cpu()
