@@ -285,15 +285,14 @@ __global__ __launch_bounds__(256 * kHalves, D == 64 && kColsum && kHalves == 1 &
     // 16*wave .. 16*wave+15, four or eight rows (1 KiB) per instruction.  Rows past the end of the
     // sequence are redirected to its last row (any finite data: they are masked later).
     auto copy_stage = [&](int t, int slot) {
+        unsigned voff[R::kCopies];
 #pragma unroll
         for (int i = 0; i < R::kCopies; ++i) {
             const int r = 16 * wave + R::kCopyRows * i + lane / kChunksPerRow;      // row inside the stage
             const int c = tile_slot<kChunksPerRow>(r, lane % kChunksPerRow);          // global chunk for this lane's LDS chunk
-            const int grow = min(t * kSlotRows + r, len - 1);
-            const unsigned voff = static_cast<unsigned>(grow) * (kD * 2) + c * 16;
-            const unsigned m0v = lds_stage0 + slot * kSlotBytes + (16 * wave + R::kCopyRows * i) * (kD * 2);
-            copy_to_lds<4>(m0v, voff, strm);
+            voff[i] = static_cast<unsigned>(min(t * kSlotRows + r, len - 1)) * (kD * 2) + c * 16;
         }
+        copies_to_lds<R::kCopies, R::kCopyRows * kD * 2>(lds_stage0 + slot * kSlotBytes + 16 * wave * (kD * 2), voff, strm);
         if (kColsum && cw == 0) {
             const int grow = min(t * kSlotRows + kStage * half + lane, len - 1);
             const unsigned voff = static_cast<unsigned>(grow) * 4;

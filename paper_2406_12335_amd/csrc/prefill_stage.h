@@ -44,6 +44,23 @@ __device__ __forceinline__ void copy_to_lds(unsigned to, unsigned off, const voi
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dword %1, %2" ::"s"(to), "v"(off), "s"(base) : "memory");
 }
 
+// kN copies of 16 bytes per lane that land kStep bytes apart, waiting once
+template <int kN, int kStep>
+__device__ __forceinline__ void copies_to_lds(unsigned to, const unsigned (&off)[kN], const void *base)
+{
+    static_assert(kN == 2 || kN == 4, "copies of a slot per wavefront");
+    if constexpr (kN == 4)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %5\n\t"
+                     "s_add_u32 m0, m0, %6\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %5\n\t"
+                     "s_add_u32 m0, m0, %6\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %3, %5\n\t"
+                     "s_add_u32 m0, m0, %6\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %4, %5"
+                     ::"s"(to), "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(base), "n"(kStep) : "memory", "scc");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %3\n\t"
+                     "s_add_u32 m0, m0, %4\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3"
+                     ::"s"(to), "v"(off[0]), "v"(off[1]), "s"(base), "n"(kStep) : "memory", "scc");
+}
+
 // Wait until at most kPending of this wavefront's vector-memory operations are outstanding,
 // then meet the other wavefronts.  The "memory" clobber keeps LDS reads below it.
 template <int kPending>
