@@ -99,7 +99,8 @@ def prompt_score_kernels(cfg, lens, window):
         fills = jobs >= even if jobs <= 256 else jobs >= 2 * even
         if window is not None:                                   # (attention rows within 32-bit offsets)
             fills = (window + 257) * max(lens) * 4 < 1 << 31
-        return "prefill_mfma_kernel" if cfg.dtype == "bf16" and fills else "prefill_direct_kernel"
+        staged = "prefill_wide_kernel" if cfg.head_dim == 128 and window is None else "prefill_mfma_kernel"
+        return staged if cfg.dtype == "bf16" and fills else "prefill_direct_kernel"
 
     rowstat, colsum = kernel(g), kernel(splits)
     if window is None:
@@ -469,20 +470,20 @@ DEFAULT_WORKLOAD = "llama7b_stack"
 # summary named in "source", which also gives the commands.
 PROFILED_TRAFFIC_BYTES = {
     "llama7b_stack": {"source": "profiles/llama7b_stack_profile.md",
-                      "bytes_per_call": {"prefill_score": 2021565035, "decode_step": 57647982, "select_compact": 232475962,
-                                         "decode_prune_step": 71322724}},
+                      "bytes_per_call": {"prefill_score": 1938511959, "decode_step": 57647770, "select_compact": 232475470,
+                                         "decode_prune_step": 71322375}},
     "llama7b_layer": {"source": "profiles/llama7b_layer_profile.md",
-                      "bytes_per_call": {"prefill_score": 189013853, "decode_step": 18034283, "select_compact": 72825381,
-                                         "decode_prune_step": 21309150}},
+                      "bytes_per_call": {"prefill_score": 174329609, "decode_step": 18034233, "select_compact": 72825229,
+                                         "decode_prune_step": 21309079}},
     "long32k": {"source": "profiles/long32k_profile.md",
-                "bytes_per_call": {"prefill_score": 2379230108, "decode_step": 28726205, "select_compact": 116525762,
-                                   "decode_prune_step": 35557798}},
+                "bytes_per_call": {"prefill_score": 2677423416, "decode_step": 28726249, "select_compact": 116516182,
+                                   "decode_prune_step": 35557748}},
     "ragged16": {"source": "profiles/ragged16_profile.md",
-                 "bytes_per_call": {"prefill_score": 5964700605, "decode_step": 204579868, "select_compact": 830402426,
-                                    "decode_prune_step": 250654032}},
+                 "bytes_per_call": {"prefill_score": 6288619567, "decode_step": 204579756, "select_compact": 830402199,
+                                    "decode_prune_step": 250652932}},
     "tiny": {"source": "profiles/tiny_profile.md",
-             "bytes_per_call": {"prefill_score": 1993742, "decode_step": 252113, "select_compact": 594534,
-                                "decode_prune_step": 473411}},
+             "bytes_per_call": {"prefill_score": 1993740, "decode_step": 252119, "select_compact": 594534,
+                                "decode_prune_step": 295460}},
 }
 
 
