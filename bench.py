@@ -94,9 +94,13 @@ def prompt_score_kernels(cfg, lens, window):
     splits = next((s for s in range(1, g + 1) if g % s == 0 and 8 * pairs * ((units * s + 7) // 8) >= 512), g)
 
     def kernel(heads):
-        even = 240 if cfg.head_dim == 64 else 192
-        jobs = units * heads * pairs
-        fills = jobs >= even if jobs <= 256 else jobs >= 2 * even
+        jobs, rows = units * heads * pairs, cfg.n_heads * heads * sum(lens)
+        two = jobs > 256
+        if cfg.head_dim == 64:
+            fills = jobs >= (480 if two else 240) or (pairs >= 8 and rows >= 512 * (432 if two else 216))
+        else:
+            long = pairs >= (6 if two else 8) and jobs >= (328 if two else 168)
+            fills = jobs >= (384 if two else 192) or (long and rows >= 512 * (300 if two else 164))
         if window is not None:                                   # (attention rows within 32-bit offsets)
             fills = (window + 257) * max(lens) * 4 < 1 << 31
         staged = "prefill_wide_kernel" if cfg.head_dim == 128 and window is None else "prefill_mfma_kernel"

@@ -243,7 +243,7 @@ vatp_status prefill_score_impl(vatp_ctx *ctx, const vatp_params *p, const void *
         float *s_part = pr.g.group > 1 && window < 0 ? parts : nullptr;
         for (int pass : {kPassRowstat, kPassColsum}) {          // (the column sums need the row statistics)
             if (e != hipSuccess || (have_lse && pass == kPassRowstat)) continue;
-            const bool staged = window < 0 && p->dtype == VATP_BF16 && prefill_mfma_fills(p->head_dim, pass, pr.g);
+            const bool staged = window < 0 && p->dtype == VATP_BF16 && prefill_mfma_fills(p->head_dim, pass, pr.meta, pr.g);
             // Row statistics handed in: the direct kernels take them as they are (unless an output or the partial sums lie over
             // them, since workgroups write these while others still read).  Measured, with the conversion in a launch of its own /
             // without: 4 heads of 64 x 256 fp32 rows 12.1 / 8.0 us, 2 x 8 x 4 query heads x 700 rows 20.5 / 17.8, 32 heads x

@@ -958,14 +958,31 @@ hipError_t launch_full(const void *Q, const void *K, const void *V, float *S, fl
 
 // A launch whose eight-wavefront workgroups cover fewer compute units takes as long as a full one (a workgroup's two
 // blocks are one chain), and between one and two of them per compute unit as long as two.  The direct kernels spread
-// the same work over 32- and 64-row workgroups at 0.75 (64 elements: 0.94) of the rate.  Measured, both passes, rows of
-// 128, staged / direct: 32 heads x 2048 rows (128 workgroups) 90 / 73 us, 32 x 4096 (256) 160 / 212, 40 x 4096 (320)
-// 295 / 265, 128 x 1024 (256) 72 / 94; rows of 64: 32 x 2048 67 / 46, 32 x 4096 111 / 122.
-bool prefill_mfma_fills(int head_dim, int pass, const Geometry &g)
+// the same work over 32- and 64-row workgroups; of these short prompts cost them less of their rate than long ones, and
+// they lose where a head count leaves some of the eight dies a head more than others.  So two pairs of lines, the lower
+// one for long prompts whose rows, counted one by one, fill the workgroups' blocks (a ragged batch, or a prompt that
+// ends early in its last pair of blocks, has fewer).  Measured, both passes, staged / direct:
+//   rows of 128, long   20 heads x 4096 rows (160 workgroups) 136 / 132 us, 21 (168) 136 / 156, 23 (184) 138 / 168,
+//                       22 x 3600 (176) 124 / 121, 23 x 3800 (184) 129 / 156, 28 x 3000 (168) 108 / 106; 40 x 4096
+//                       (320) 271 / 246, 41 (328) 273 / 330, 43 (344) 274 / 352, 42 x 3600 (336) 246 / 241, 57 x 2700
+//                       (342) 200 / 250, 61 x 3000 (366) 217 / 342, 21 x 8192 (336) 485 / 562
+//   rows of 128, short  32 x 2048 (128) 82 / 64, 44 x 2048 (176) 84 / 86, 176 x 512 (176) 47 / 42; 88 x 2048 (352)
+//                       168 / 160, 92 x 2048 (368) 169 / 178, 176 x 1024 (352) 117 / 107, 360 x 512 (360) 95 / 83
+//   rows of 64, long    27 x 4096 (216) 104 / 116, 29 (232) 104 / 125, 28 x 3600 (224) 98 / 91; 52 x 4096 (416) 205 / 202,
+//                       54 (432) 205 / 224, 52 x 3590 (416) 192 / 160
+//   rows of 64, short   32 x 2048 (128) 67 / 46, 58 x 2048 (232) 64 / 69, 232 x 512 (232) 35 / 31; 108 x 2048 (432)
+//                       125 / 120, 232 x 1024 (464) 87 / 76
+bool prefill_mfma_fills(int head_dim, int pass, const BatchMeta &meta, const Geometry &g)
 {
-    const long units = static_cast<long>(g.batch) * g.n_heads * (pass == kPassRowstat ? g.group : colsum_splits(g));
-    const long jobs = units * block_pairs(g), even = head_dim == 64 ? 240 : 192;
-    return jobs <= kComputeUnits ? jobs >= even : jobs >= 2 * even;
+    const long heads = static_cast<long>(g.n_heads) * (pass == kPassRowstat ? g.group : colsum_splits(g));
+    const long jobs = heads * g.batch * block_pairs(g), even = head_dim == 64 ? 240 : 192;
+    const bool two = jobs > kComputeUnits;
+    if (jobs >= (two ? 2 * even : even)) return true;
+    if (block_pairs(g) < (head_dim == 128 && two ? 6 : 8)) return false;
+    long rows = 0;
+    for (int b = 0; b < g.batch; ++b) rows += heads * meta.len[b];
+    if (head_dim == 64) return rows >= 2 * kBlockCols * (two ? 432 : 216);
+    return jobs >= (two ? 328 : 168) && rows >= 2 * kBlockCols * (two ? 300 : 164);
 }
 
 hipError_t launch_prefill_mfma(int head_dim, const void *Q, const void *K, const void *V, float *S, float *nrm, float *lse2,

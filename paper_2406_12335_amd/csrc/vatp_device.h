@@ -510,7 +510,7 @@ hipError_t launch_prefill_mfma(int head_dim, const void *Q, const void *K, const
 hipError_t launch_prefill_wide(const void *Q, const void *K, const void *V, float *S, float *nrm, float *lse2, float *s_part, int pass,
                                const BatchMeta &meta, const Geometry &g, hipStream_t st);
 // whether the grid of a pass is one the staged kernels run well
-bool prefill_mfma_fills(int head_dim, int pass, const Geometry &g);
+bool prefill_mfma_fills(int head_dim, int pass, const BatchMeta &meta, const Geometry &g);
 
 // history-window prompt scores on the matrix cores (bf16); lse_part: workspace of
 // prefill_window_splits(cap) * units * cap floats; usable if prefill_mfma_window_fits(window, cap, units)

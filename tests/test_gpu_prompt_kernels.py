@@ -302,6 +302,15 @@ def test_wide_tiles(gpu_device, H, g, lens):
     _check_scores(gpu_device, "bf16", 128, g, H, lens, None, [(b, H - 1 if b % 2 else 0) for b in range(len(lens))], 301 + g)
 
 
+# The fewest heads of long prompts that workgroups of two blocks take, in one round of workgroups and in two, one head fewer and
+# too few rows
+@pytest.mark.parametrize("d,H,lens", [(128, 20, [4000]), (128, 21, [4000]), (128, 21, [3998]), (128, 54, [2800]), (128, 55, [2800]),
+                                      (128, 28, [2800, 2700]), (128, 27, [2900, 1100]), (64, 26, [4096]), (64, 27, [4096]),
+                                      (64, 53, [4096]), (64, 54, [4096])])
+def test_long_prompts_of_few_heads(gpu_device, d, H, lens):
+    _check_scores(gpu_device, "bf16", d, 1, H, lens, None, [(b, H - 1) for b in range(len(lens))], 331 + H)
+
+
 # Row statistics are kept relative to the first keys of a row: sums that leave a float's range are formed again
 @pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("H,lens", [(32, [300, 1, 259, 128] * 2), (16, [1100, 300, 520]), (25, [1100, 300, 520, 900])])
