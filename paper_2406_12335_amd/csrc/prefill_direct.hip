@@ -361,7 +361,8 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_direct_kernel(const T 
                 s_part[2 * wave + g][kTileRows * c + n] = column_sum_subnormal<T, D, false>(
                     stat, strm, lse_u, scale, a.lse_scale, 0.f, base0 + kTileRows * c, len, cap, q_first, heads, t_first + wave, kWaves, lane);
             lds_barrier();
-            sum = total();
+            const float again = total();
+            if (sum < kSubnormalLoss) sum = again;
         }
     }
     if (tid < kBlock && base0 + tid < len) {

@@ -716,7 +716,8 @@ __global__ __launch_bounds__(256 * kHalves, D == 64 && kColsum && kHalves == 1 &
                         stat, reinterpret_cast<const uint4 *>(strm0 + head * kD), lse_u0 + head, scale_log2, 1.f, kBand ? log2_group : 0.f,
                         w0 + 32 * cb, len, cap, q_first, heads, max(w0 + 32 * cb, q_first) / 32, 1, own_lane,
                         with_hist ? win.hist + unit * static_cast<size_t>(win.window + 1) * cap : nullptr);
-                    fin_l[cb] = part + __shfl_xor(part, 32);
+                    const float again = part + __shfl_xor(part, 32);
+                    if (fin_l[cb] < kSubnormalLoss) fin_l[cb] = again;
                 }
             }
         }

@@ -306,7 +306,7 @@ __device__ __forceinline__ floatx16 mfma_piece(const uint4 &a, const uint4 &b, i
 
 // The passes over a prompt form their exponentials with v_exp_f32, which returns 0 below 2^-126.  A column sum of up to 2^26
 // weights loses less than 2^-100 by it: from this limit on that is less than a quarter of its own last place.  A sum below is formed once
-// more by column_sum_subnormal, with weights down to 2^-149.
+// more by column_sum_subnormal, with weights down to 2^-149; the other sums of its block stay as they are.
 constexpr float kSubnormalLoss = 0x1p-72f;
 
 // One wavefront's share of the scores (Eq. 2, Eq. 3) of the 32 keys from col0 on: the query rows of tiles t_begin,
@@ -346,7 +346,11 @@ __device__ __forceinline__ float column_sum_subnormal(const uint4 *keys, const u
 #pragma unroll 1
         for (int h = 0; h < heads; ++h)
 #pragma unroll 1
-            for (int t = t_begin; t * 32 < len; t += t_step) tile(t, h, [&](int, int, float p) { sum += p; });
+            for (int t = t_begin; t * 32 < len; t += t_step) {
+                float part = 0.f;                      // (one rounding of the sum per tile)
+                tile(t, h, [&](int, int, float p) { part += p; });
+                sum += part;
+            }
         return sum;
     }
 #pragma unroll 1
@@ -356,12 +360,14 @@ __device__ __forceinline__ float column_sum_subnormal(const uint4 *keys, const u
         for (int v = 0; v < 16; ++v) w[v] = 0.f;
 #pragma unroll 1
         for (int h = 0; h < heads; ++h) tile(t, h, [&](int v, int, float p) { w[v] += p; });
+        float part = 0.f;
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const int r = t * 32 + 4 * g + acc_row(v);
             if (hist && col < len && r >= col && r >= q_first && r < len) hist[static_cast<size_t>(r - q_first) * cap + col] = w[v];
-            sum += w[v];
+            part += w[v];
         }
+        sum += part;
     }
     return sum;
 }

@@ -293,6 +293,31 @@ def test_weights_below_the_normal_range(gpu_device, dtype, d, B, H, g, L, window
         assert ((hist - p.unsqueeze(2)).abs() <= 1e-5 * p.unsqueeze(2) + 2.0 ** -149)[:, :, seen].all()
 
 
+# Small sums are formed once more for a block of keys at a time; the other keys of the block keep their sums.  Odd keys have weights near
+# 2^-144 here; the even ones one weight in a head, and their sums are bounded as above: 17, on the staged kernels of heads of 64, which add
+# tile after tile to one sum of up to 32, (2 + ... + 32) / 32 in the place of 4.9: 29.
+@pytest.mark.parametrize("dtype,d,H,L", [("bf16", 128, 8, 1801), ("bf16", 64, 8, 1801), ("fp32", 64, 8, 1801), ("fp32", 128, 8, 1001), ("bf16", 128, 32, 1151),
+                                         ("bf16", 64, 32, 1101), ("fp32", 64, 64, 1151), ("bf16", 64, 258, 1001), ("bf16", 64, 120, 1001)])
+def test_small_sums_beside_others(gpu_device, dtype, d, H, L):
+    print("[case] small sums beside others %s d=%d H=%d L=%d" % (dtype, d, H, L), flush=True)
+    dt = {"fp32": torch.float32, "bf16": torch.bfloat16}[dtype]
+    Q, K = (torch.zeros(1, H, L, d, dtype=dt, device=gpu_device) for _ in range(2))
+    Q[..., 0], K[:, :, 1::2, 0] = 8.0, -100 * math.sqrt(d) / 8
+    lse = ((torch.arange(H, device=gpu_device) % 64).view(1, H, 1) * 0.0173).float().expand(1, H, L).contiguous()
+    ctx = vatp.vatp_create(0)
+    try:
+        p = vatp.Params(1, H, d, dt, 0, 0, L, [L], [L])
+        ws = torch.empty(vatp.vatp_workspace_bytes(ctx, p, vatp.binding.CALL_PREFILL_SCORE), dtype=torch.uint8, device=gpu_device)
+        S, nrm = torch.zeros_like(lse), torch.zeros_like(lse)
+        vatp.vatp_prefill_score_lse(ctx, p, Q, K, K, lse, S, nrm, ws)
+        S = S[0].cpu().double()
+    finally:
+        vatp.vatp_destroy(ctx)
+    assert (S[:, 1::2] > 0).all() and (S[:, 1::2] < 2.0 ** -130).all()
+    off = (S[:, ::2] / (S[:, -1:] * torch.arange(L, 0, -2)) - 1).abs().max().item()
+    assert off <= (29 if d == 64 and H > 100 else 17) * 2.0 ** -24, off * 2.0 ** 24
+
+
 # Grids that fill the chip, heads of 128: workgroups of four wavefronts (first list) and of eight, blocks of 256 rows in two column
 # groups of 128, ring slots of 64 and 128 rows in parts of 32, units of 16
 @pytest.mark.parametrize("H,g,lens", [
