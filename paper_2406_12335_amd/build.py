@@ -33,9 +33,10 @@ def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 
 
-# per-file additions.  The prompt passes never produce a NaN by construction (masked logits are
-# -inf and are only ever added to finite values), which lets fmax compile to bare v_max; their
-# accumulators stay in architectural VGPRs so the exponentials can read them directly.
+# per-file additions.  The prompt passes never produce a NaN from finite logits by construction (masked logits
+# are -inf and are only ever added to finite values; sums of weights that overflow are formed again
+# before anything is made of them), which lets fmax compile to bare v_max; their accumulators stay in
+# architectural VGPRs so the exponentials can read them directly.
 EXTRA_FLAGS = {
     "prefill_mfma.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form"],
     "prefill_wide.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form"],

@@ -130,7 +130,8 @@ struct Running {                 // per column block: rowstat (m, l) or colsum p
 
 // The exponentials of a pending pair, cut into 16 pieces so that one piece can follow each
 // MFMA of the next pair; finish() runs what is left after piece 15.
-// Row statistics are kept relative to a whole number.  kMoving: the maximum so far, rounded up; otherwise what an earlier pair left.
+// Row statistics are kept relative to a whole number.  kMoving: the maximum so far, rounded up; otherwise what an earlier pair left,
+// unless weights have outgrown it (kMostAboveReference).
 template <bool kColsum, bool kMoving>
 struct Epilogue {
     float ref[2], corr[2], part[2], tmax[2];
@@ -191,6 +192,23 @@ struct Epilogue {
             run.col[0] += part[0];
             run.col[1] += part[1];
         } else if constexpr (!kMoving) {
+            if (__builtin_expect(__any(fmaxf(part[0], part[1]) > kMostAboveReference), 0)) {
+#pragma unroll
+                for (int cb = 0; cb < 2; ++cb) {
+                    float top = p.acc[cb][0];
+#pragma unroll
+                    for (int v = 1; v < 16; ++v) top = fmaxf(top, p.acc[cb][v]);
+                    const float above = fmaxf(run.m[cb], ceilf(top * scale));
+                    part[cb] = 0.f;
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        part[cb] += fast_exp2(fmaf(p.acc[cb][v], scale, -above));
+                        asm volatile("" : "+v"(part[cb]));     // (one after the other: no more registers than the stage takes)
+                    }
+                    run.l[cb] *= fast_exp2(run.m[cb] - above);
+                    run.m[cb] = above;
+                }
+            }
             run.l[0] += part[0];
             run.l[1] += part[1];
         } else {
@@ -519,9 +537,12 @@ __global__ __launch_bounds__(256 * kHalves, D == 64 && kColsum && kHalves == 1 &
                                     epi.template piece<kStoreMode>((2 * s + cb) * R::kPieces + i, pend, run, scale, hist_rsrc,
                                                                    cap * 4, group_sum[kBand ? 1 - kb : 0]);
                             }
-                        epi.finish(pend, run, scale);
+                        // (the row statistics' fixed reference is looked after behind the scheduled block, which it ends)
+                        constexpr bool kFixed = !kColsum && !kMoving;
+                        if constexpr (!kFixed) epi.finish(pend, run, scale);
                         // keep the pending pair's results inside this block (no sinking past it)
                         if constexpr (kColsum) asm volatile("" : "+v"(run.col[0]), "+v"(run.col[1]));
+                        else if constexpr (kFixed) asm volatile("" : "+v"(epi.part[0]), "+v"(epi.part[1]));
                         else asm volatile("" : "+v"(run.l[0]), "+v"(run.l[1]), "+v"(run.m[0]), "+v"(run.m[1]));
                         // Issue order asked of the scheduler: a short run of the pending pair's vector
                         // work, then one MFMA per slice of exponentials.  (LDS reads are left to the
@@ -534,6 +555,7 @@ __global__ __launch_bounds__(256 * kHalves, D == 64 && kColsum && kHalves == 1 &
                             sched_two_slots<kSlot, kSlot>(); sched_two_slots<kSlot, kSlot>();
                             sched_two_slots<kSlot, kSlot>(); sched_two_slots<kSlot, kSlot>();
                         }
+                        if constexpr (kFixed) epi.finish(pend, run, scale);
                         if constexpr (kRepair && kWindow) {
                             float low = next.acc[0][0], high = next.lse[0];
 #pragma unroll
@@ -681,23 +703,6 @@ __global__ __launch_bounds__(256 * kHalves, D == 64 && kColsum && kHalves == 1 &
                     } else {
                         fin_l[cb] += l_o;
                     }
-                }
-            }
-        }
-        // sums that left the range of a float are formed again (infinite, or NaN after a merge, which this file is compiled not to
-        // expect: seen in the bits alone)
-        if constexpr (!kColsum && !kWindow) {
-            if (half == 0) {
-#pragma unroll
-                for (int cb = 0; cb < 2; ++cb) {
-                    unsigned bits = __float_as_uint(fin_l[cb]);
-                    asm volatile("" : "+v"(bits));
-                    if (!__any(w0 + 32 * cb + n < len && (bits & 0x7f800000u) == 0x7f800000u)) continue;
-                    int own_lane = threadIdx.x & 63;
-                    asm volatile("" : "+v"(own_lane));      // (keeps what is derived from it out of the registers of the loops above)
-                    const float2 x = row_statistics_again<D>(stat, reinterpret_cast<const uint4 *>(strm), scale_log2, w0 + 32 * cb, len, own_lane);
-                    fin_m[cb] = x.x;
-                    fin_l[cb] = x.y;
                 }
             }
         }

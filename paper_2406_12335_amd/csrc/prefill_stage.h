@@ -91,39 +91,16 @@ __device__ __forceinline__ void value_norms(const uint4 *__restrict__ Vu, float 
     }
 }
 
-// Row statistics (m, l) of the 32 rows from row0 on, by one wavefront, with a running maximum and operands straight from memory:
-// for rows whose sum left the range of a float relative to the fixed reference, which takes a logit 88 (in nats) above all
-// the first keys'.  Lanes n and n + 32 return row row0 + n.
-template <int D>
-__device__ __forceinline__ float2 row_statistics_again(const uint4 *queries, const uint4 *keys, float scale, int row0, int len, int lane)
-{
-    constexpr int kChunks = D / 8;
-    const int g = lane >> 5, n = lane & 31, row = row0 + n;
-    const uint4 *query = queries + static_cast<size_t>(min(row, len - 1)) * kChunks + g;
-    float m = kLowestLogit, l = 0.f;
-#pragma unroll 1
-    for (int t = 0; t * 32 <= min(row0 + 31, len - 1); ++t) {
-        const uint4 *key = keys + static_cast<size_t>(min(t * 32 + n, len - 1)) * kChunks + g;
-        floatx16 acc;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-#pragma unroll 1
-        for (int s = 0; s < kChunks / 2; ++s)
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_bf16x8(key[2 * s]), as_bf16x8(query[2 * s]), acc, 0, 0, 0);
-        float ref = m;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            acc[v] = t * 32 + 4 * g + acc_row(v) <= row ? acc[v] * scale : -INFINITY;
-            ref = fmaxf(ref, acc[v]);
-        }
-        l *= fast_exp2(m - ref);
-        m = ref;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) l += fast_exp2(acc[v] - m);
-    }
-    const float m_o = __shfl_xor(m, 32), l_o = __shfl_xor(l, 32), ref = fmaxf(m, m_o);
-    return make_float2(ref, l * fast_exp2(m - ref) + l_o * fast_exp2(m_o - ref));
-}
+// Row statistics without a window are sums of weights 2^(t - m) relative to a whole number m that the first keys set.  The maximum of
+// every tile instead costs an eighth more vector instructions; leaving m alone whatever follows loses rows: the exponent of a key that lies x
+// above m is rounded like x (rows of 1024 keys that one leads, first keys far below, root mean square error of the sum, x = 12: 1.9e-7, 52:
+// 6.9e-7, 72: 1.5e-6), and a sum worth 2^126 and more at m is lost when the lanes' sums are brought to one reference by factors
+// that may be 0 (v_exp_f32, below 2^-126).  So m moves up where a lane's weights of one stage add up to more than this: exponents stay below
+// 16 (the same errors: 1.9e-7, 3.4e-8, 3.4e-8; a reference in every tile 1.4e-7, 1.0e-8, 1.0e-8), sums below 2^35, and a factor of 0
+// takes away less than 2^-90 of a row's sum.  From 2^24 on: 4.0e-7 at x = 18..23 (now 0.9e-7).  Both passes of 32 heads of 128 x 4096 rows, unit
+// normal q and k, logits of standard deviation 5 nats without sinks, which is what it costs most on: 146 us without any look, 174, from 2^24 on
+// 157; of 3 nats and less, and 8 nats and more between the first keys and the others, as without; logits that rise by 15 nats a stage 249.
+constexpr float kMostAboveReference = 65536.f;
 
 // log2 of 2^m * l, m whole (the logarithm of a number between 1/2 and 1 rounds the least)
 __device__ __forceinline__ float sum_log2(float m, float l)

@@ -13,8 +13,8 @@
 //    LDS, random data: 1.56 -> 1.71 PFLOP/s),
 //  * 128 stationary rows per wavefront instead of 64: an operand read from LDS serves eight MFMAs of 16 cycles instead of two of
 //    32, half the LDS reads,
-//  * row statistics relative to a reference fixed by the first keys instead of a running maximum: a seventh fewer vector
-//    instructions.
+//  * row statistics relative to a reference that the first keys set and that moves only where weights outgrow it, instead of a
+//    running maximum: an eighth fewer vector instructions.
 // Loops of MFMAs, exponentials and LDS reads alone, one box: 32 x 32 tiles, 64 columns 1233 TFLOP/s, 16 x 16 tiles, 64 columns
 // 1309, 16 x 16 tiles, 128 columns 1365.  Now: pipe busy 56 and 54 % at 2.03 and 2.06 GHz.  Measured, both passes, before / now:
 // 32 heads x 32768 rows 7865 / 7333 us, 512 heads of 1024..8192 rows 3638 / 3448, 32 x 4096 153.4 / 147.0, 128 x 2048 180.5 / 172.0,
@@ -73,14 +73,40 @@ struct Unit {                      // logits of 16 streamed rows by 128 columns:
 // Per column tile of a lane.  Column sums: col.  Row statistics: the sum l of 2^(t - m).
 struct Running { float m[kTiles], l[kTiles], col[kTiles]; };
 
+// Maximum over the four lane groups, which hold the same columns
+__device__ __forceinline__ float across_groups_max(float x)
+{
+    const unsigned bits = __float_as_uint(x);
+    const auto half = __builtin_amdgcn_permlane32_swap(bits, bits, false, false);
+    const unsigned y = __float_as_uint(fmaxf(__uint_as_float(half[0]), __uint_as_float(half[1])));
+    const auto row = __builtin_amdgcn_permlane16_swap(y, y, false, false);
+    return fmaxf(__uint_as_float(row[0]), __uint_as_float(row[1]));
+}
+
+// The reference m of a column moves up to the maximum of four more logits, rounded up; what takes a sum along is returned.
+__device__ __forceinline__ float move_reference(float &m, const floatx4 &t, float scale)
+{
+    const float ref = fmaxf(m, ceilf(fmaxf(fmaxf(t[0], t[1]), fmaxf(t[2], t[3])) * scale)), fit = fast_exp2(m - ref);
+    m = ref;
+    return fit;
+}
+__device__ __forceinline__ float weights(const floatx4 &t, float scale, float m)
+{
+    float p[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) p[v] = fast_exp2(fmaf(t[v], scale, -m));
+    return (p[0] + p[1]) + (p[2] + p[3]);
+}
+
 // The vector work of a finished unit, dealt out to the kSlots MFMAs of the next one: weights of column tile after column tile.  The
 // weights of a stage are added up (part) before they join the running sums: one rounding of those per stage.
-// kFresh: the first of a stage.  kReference (row statistics): the unit sets the reference m.  It may stay what the first keys of a
-// lane make it: sums of weights up to 2^127 above it keep their precision, and where the lane's first rows are all masked, so are
-// the later ones.  It is a whole number: what takes a sum from one reference to another is a power of two, exactly.
+// kFresh: the first of a stage.  kReference (row statistics): the unit sets the reference m (where the lane's first rows are all
+// masked, so are the later ones).  It is a whole number: what takes a sum from one reference to another is a power of two, exactly.
+// Row statistics: what a stage adds up joins the running sums as the next one's weights take its place (kFirst: there was none), once it
+// is known whether any of it (most, of the column tiles) has outgrown the reference.
 template <bool kColsum, int kSlots>
 struct VectorWork {
-    float part[kTiles];
+    float part[kTiles], most;
 
     template <int j, bool kFresh, bool kReference>
     __device__ __forceinline__ void slot(const Unit &done, const floatx4 &lse, Running &run, float scale)
@@ -90,12 +116,21 @@ struct VectorWork {
             constexpr int k = kPer * j + decltype(e)::value, c = k / 4, v = k % 4;
             if constexpr (kReference && v == 0) {
                 const floatx4 &t = done.tile[c];
-                run.m[c] = fmaxf(ceilf(fmaxf(fmaxf(t[0], t[1]), fmaxf(t[2], t[3])) * scale), kLowestLogit);
+                const float top = across_groups_max(fmaxf(fmaxf(t[0], t[1]), fmaxf(t[2], t[3])));
+                run.m[c] = fmaxf(ceilf(top * scale), kLowestLogit);
             }
             const float p = fast_exp2(fmaf(done.tile[c][v], scale, kColsum ? -lse[v] : -run.m[c]));
+            if constexpr (!kColsum && kFresh && !kReference && v == 0) {
+                run.l[c] += part[c];
+                asm volatile("" : "+v"(run.l[c]));
+            }
             if constexpr (kFresh && v == 0) part[c] = p;
             else part[c] += p;
             asm volatile("" : "+v"(part[c]));          // (keeps what has been added up in this slot)
+            if constexpr (!kColsum && !kFresh && v == 3 && c % 2 == 1) {
+                most = c == 1 ? fmaxf(part[0], part[1]) : fmaxf(fmaxf(most, part[c - 1]), part[c]);
+                asm volatile("" : "+v"(most));
+            }
         });
     }
     __device__ __forceinline__ void finish(Running &run)
@@ -284,6 +319,55 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_wide_kernel(const bf16
             const float4 x = *reinterpret_cast<const float4 *>(&lse_stage[slot][r0 + 4 * g]);
             lse = floatx4{x.x, x.y, x.z, x.w};
         };
+        VectorWork<kColsum, kSlots> work;
+        // Row statistics, before stage t (while its operands are on their way): has what the stage before has added up outgrown the reference
+        // of any column (kMostAboveReference)?  Then the references move up to what the running sums have come to, which makes further
+        // moves rare, and where the weights still lie far above (kFarAbove), to their maximum.  These are formed again, of two units (of
+        // one after the first stage), from memory: the logits have made room for others.  A negative part marks the columns concerned.
+        constexpr float kFarAbove = 256.f;
+        auto settle = [&](int t) __attribute__((always_inline)) {
+            if (__builtin_expect(__any(work.most > kMostAboveReference), 0)) {
+#pragma unroll
+                for (int c = 0; c < kTiles; ++c) {
+                    const int up = run.l[c] > 4.f ? __builtin_amdgcn_frexp_expf(run.l[c]) : 0;
+                    run.m[c] += static_cast<float>(up);
+                    run.l[c] = __builtin_amdgcn_ldexpf(run.l[c], -up);
+                    const float now = __builtin_amdgcn_ldexpf(work.part[c], -up);
+                    work.part[c] = now > kFarAbove ? -0.f : now;
+                }
+                int own_lane = threadIdx.x & 63;
+                asm volatile("" : "+v"(own_lane));                     // (formed here: kept outside the loops it takes registers)
+#pragma unroll 1
+                for (int u = t >= 2 ? -1 : 0; u <= 0; ++u) {
+                    const int row = (t - 1) * kSlotRows + kPartRows * part + (kSlotRows - 16) * u + (own_lane & 15);
+                    const uint4 *const src = reinterpret_cast<const uint4 *>(strm) + static_cast<size_t>(row) * kChunks + (own_lane >> 4);
+                    bf16x8 a[kSteps];
+#pragma unroll
+                    for (int s = 0; s < kSteps; ++s) a[s] = as_bf16x8(src[4 * s]);
+                    // (complete here, in every case: otherwise the compiler waits inside the stage loop)
+#pragma unroll
+                    for (int s = 0; s < kSteps; ++s) asm volatile("" ::"v"(a[s]));
+                    static_for<kTiles>([&](auto tile_tag) __attribute__((always_inline)) {
+                        constexpr int c = decltype(tile_tag)::value;
+                        const bool outgrown = __float_as_int(work.part[c]) < 0;
+                        if (__any(outgrown)) {
+                            floatx4 x = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                            for (int s = 0; s < kSteps; ++s) x = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[s], Bf[c][s], x, 0, 0, 0);
+                            float m = run.m[c], l = run.l[c], sum = -work.part[c];
+                            const float fit = move_reference(m, x, scale_log2);
+                            sum = fmaf(sum, fit, weights(x, scale_log2, m));
+                            run.m[c] = outgrown ? m : run.m[c];
+                            run.l[c] = outgrown ? l * fit : l;
+                            work.part[c] = outgrown ? -sum : work.part[c];
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    });
+                }
+#pragma unroll
+                for (int c = 0; c < kTiles; ++c) work.part[c] = fabsf(work.part[c]);
+            }
+        };
         // A stage without masked logits, branch-free; kFirst: no unit is pending (and the row statistics have no reference yet).
         // kTail: its rows reach past the end of the sequence; their row log-sum-exps become infinite, the weights 0.
         auto do_stage = [&](int t, auto first_tag, auto tail_tag) __attribute__((always_inline)) {
@@ -293,12 +377,13 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_wide_kernel(const bf16
             // that uses it can move up)
             float scale = scale_log2;
             asm volatile("; stage variant %1" : "+s"(scale) : "n"(kFirst ? 1 : kTail ? 2 : 0));
-            VectorWork<kColsum, kSlots> work;
             static_for<2>([&](auto unit_tag) __attribute__((always_inline)) {
                 constexpr int u = decltype(unit_tag)::value;
                 Unit &next = acc[u], &done = acc[1 - u];
                 bf16x8 a[kSteps];
                 load_unit(a, slot, kPartRows * part + 16 * u);
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (!kColsum && !kFirst && u == 0) settle(t);
                 __builtin_amdgcn_sched_barrier(0);
                 static_for<kSlots>([&](auto slot_tag) __attribute__((always_inline)) {
                     constexpr int j = decltype(slot_tag)::value, s = j / kTiles, c = j % kTiles;
@@ -317,17 +402,28 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_wide_kernel(const bf16
                     __builtin_amdgcn_sched_barrier(0);
                 });
             });
-            work.finish(run);
+            if constexpr (kColsum) work.finish(run);
+            else if constexpr (kFirst) work.most = 0.f;
         };
-        // the vector work of the last stage's unit 1, with no MFMAs beside it
-        auto complete = [&]() __attribute__((always_inline)) {
-            VectorWork<kColsum, kSlots> work;
+        // the vector work of the last stage's (t) unit 1, with no MFMAs beside it
+        auto complete = [&](int t) __attribute__((always_inline)) {
             __builtin_amdgcn_sched_barrier(0);
-            static_for<kSlots>([&](auto j) __attribute__((always_inline)) {
-                work.template slot<decltype(j)::value, true, false>(acc[1], lse, run, scale_log2);
-                if constexpr (decltype(j)::value % 4 == 3) __builtin_amdgcn_sched_barrier(0);
-            });
-            work.finish(run);
+            if constexpr (kColsum) {
+                static_for<kSlots>([&](auto j) __attribute__((always_inline)) {
+                    work.template slot<decltype(j)::value, true, false>(acc[1], lse, run, scale_log2);
+                    if constexpr (decltype(j)::value % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+                });
+                work.finish(run);
+            } else {
+                settle(t + 1);
+                work.finish(run);
+#pragma unroll
+                for (int c = 0; c < kTiles; ++c) {
+                    const float fit = move_reference(run.m[c], acc[1].tile[c], scale_log2);
+                    run.l[c] = fmaf(run.l[c], fit, weights(acc[1].tile[c], scale_log2, run.m[c]));
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
         };
         // A stage across the diagonal or the end of the sequence: 16 rows by 128 or, where the other 64 columns are masked altogether,
         // by 64 columns at a time, the vector work after its MFMAs.  The reference of the row statistics moves here.
@@ -402,7 +498,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_wide_kernel(const bf16
                     stage_sync(t);
                     do_stage(t, std::true_type{}, std::false_type{});
                     for (++t; t <= t_full; ++t) { stage_sync(t); do_stage(t, std::false_type{}, std::false_type{}); }
-                    complete();
+                    complete(t_full);
                 }
                 for (; t <= t_last; ++t) { stage_sync(t); do_masked(t); }
                 for (; t <= t_end; ++t) stage_sync(t);               // keys past the diagonal
@@ -420,7 +516,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_wide_kernel(const bf16
                         if (t * kSlotRows + r_part < len) do_stage(t, std::false_type{}, std::true_type{});
                         ++t;
                     }
-                    complete();
+                    complete(t - 1);
                 }
                 for (; t <= t_end; ++t) { stage_sync(t); do_masked(t); }
             }
@@ -481,29 +577,6 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_wide_kernel(const bf16
                     for (int p = 0; p < kParts; ++p)
                         if (!kColsum) l[p] *= fast_exp2(m[p] - fin_m[c]);
                     fin_l[c] = kParts == 2 ? l[0] + l[1] : (l[0] + l[1]) + (l[kParts - 2] + l[kParts - 1]);
-                }
-                // sums that left the range of a float are formed again, 32 rows (those of lane group cb) at a time
-                if constexpr (!kColsum) {
-                    // (infinite, or NaN after a merge, which this file is compiled not to expect: seen in the bits alone)
-                    auto lost = [](float x) {
-                        unsigned bits = __float_as_uint(x);
-                        asm volatile("" : "+v"(bits));
-                        return (bits & 0x7f800000u) == 0x7f800000u;
-                    };
-                    const bool again = (base0 + col0 < len && lost(fin_l[0])) || (base0 + col0 + 16 < len && lost(fin_l[1]));
-#pragma unroll 1
-                    for (int cb = 0; cb < kWaveCols / 32; ++cb) {
-                        if (!__any(g == cb && again)) continue;
-                        int own_lane = threadIdx.x & 63;
-                        asm volatile("" : "+v"(own_lane));      // (keeps what is derived from it out of the registers of the loops above)
-                        const float2 x = row_statistics_again<D>(reinterpret_cast<const uint4 *>(stat), reinterpret_cast<const uint4 *>(strm),
-                                                                 scale_log2, w0 + 32 * cb, len, own_lane);
-#pragma unroll
-                        for (int c = 0; c < 2; ++c) {
-                            const float m_c = __shfl(x.x, n + 16 * c), l_c = __shfl(x.y, n + 16 * c);
-                            if (g == cb) { fin_m[c] = m_c; fin_l[c] = l_c; }
-                        }
-                    }
                 }
 #pragma unroll
                 for (int c = 0; c < 2; ++c) {

@@ -336,7 +336,7 @@ def test_long_prompts_of_few_heads(gpu_device, d, H, lens):
     _check_scores(gpu_device, "bf16", d, 1, H, lens, None, [(b, H - 1) for b in range(len(lens))], 331 + H)
 
 
-# Row statistics are kept relative to the first keys of a row: sums that leave a float's range are formed again
+# Row statistics are kept relative to the first keys of a row until later ones outgrow them
 @pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("H,lens", [(32, [300, 1, 259, 128] * 2), (16, [1100, 300, 520]), (25, [1100, 300, 520, 900])])
 def test_logits_far_above_those_of_the_first_keys(gpu_device, d, H, lens):
@@ -360,3 +360,70 @@ def test_logits_far_above_those_of_the_first_keys(gpu_device, d, H, lens):
             n = lens[b]
             want = orc.prefill_scores_group(Q[b, h:h + 1, :n].double().numpy(), K[b, h, :n].double().numpy())
             parity.assert_scores_close(S[b, h, :n].numpy(), want, parity.rtol_for(torch.bfloat16), "len %d head %d" % (n, h))
+
+
+def _planted(B, H, L, d, logits):
+    """Q and K with base-2 logits logits[b][h][key] for every row, 0 for the other keys, in two coordinates."""
+    Q, K = torch.zeros(B, H, L, d), torch.zeros(B, H, L, d)
+    Q[..., 0] = Q[..., 1] = 8.0
+    for b in range(B):
+        for h in range(H):
+            for key, t in logits(b, h):
+                x = torch.tensor(t * math.log(2) * math.sqrt(d) / 8)
+                K[b, h, key, 0] = x.bfloat16()
+                K[b, h, key, 1] = x - x.bfloat16()
+    return Q.bfloat16(), K.bfloat16()
+
+
+# Two keys that lead a row, in lanes (first and second pair: lane groups; third: parts of a slot) or stages (fourth: a full one and
+# the diagonal's) whose first keys lie more than 126 apart, workgroups of four wavefronts and of eight
+@pytest.mark.parametrize("d,H", [(128, 43), (128, 16), (64, 43), (64, 20)])
+@pytest.mark.parametrize("high,low", [(127.0, 126.5), (130.0, 125.0), (128.0, 120.0), (149.0, 140.0)])
+def test_leading_keys_in_different_lanes(gpu_device, d, H, high, low):
+    print("[case] leading keys d=%d H=%d %s %s" % (d, H, high, low), flush=True)
+    where = [(0, 134), (5, 129), (32, 130), (700, 130), (67, 131), (130, 700)]
+    B, L = len(where), 1024
+    Q, K = _planted(B, H, L, d, lambda b, h: [(where[b][0], high), (where[b][1], low)])
+    cache = PrunedKVCache(B, H, d, torch.bfloat16, 0, 0, [L] * B, gpu_device)
+    try:
+        cache.prefill_score(Q.to(gpu_device), K.to(gpu_device), K.to(gpu_device), [L] * B)
+        S = cache.S_prompt.cpu()
+    finally:
+        cache.close()
+    for b in range(B):
+        want = orc.prefill_scores_group(Q[b, :1].double().numpy(), K[b, 0].double().numpy())
+        for h in (0, H - 1):
+            parity.assert_scores_close(S[b, h].numpy(), want, parity.rtol_for(torch.bfloat16), "keys %s head %d" % (where[b], h))
+    # a row's weights add up to 1: its statistic, of up to 149, is rounded to 2^-17 (half a unit), times ln 2; two exponentials
+    # good to a unit each
+    assert ((S.double().sum(-1) / L - 1).abs() <= 2.0 ** -17 * math.log(2) + 2.0 ** -21).all()
+
+
+# One key near 0 leads rows whose other keys lie `below` it: its exponent is rounded to half a unit of what it lies above the
+# reference, at most 16 (2^-21); with that key the reference, to 2^-25.  The scale's rounding moves the logit by 2^-25 of itself
+# (at most 4), exponential, sum, logarithm and the statistic, below 4, are good to 2^-22 each.
+@pytest.mark.parametrize("d,H", [(128, 258), (128, 96), (64, 258), (64, 120)])
+@pytest.mark.parametrize("below", [12, 40, 72, 110, 200])
+def test_row_statistics_of_rows_that_one_key_leads(gpu_device, d, H, below):
+    print("[case] one leading key d=%d H=%d %d below" % (d, H, below), flush=True)
+    L, lead = 1024, 200
+    heads = [(7 * h % 32) / 8 - 2 for h in range(H)]
+    Q, K = _planted(1, H, L, d, lambda b, h: [(lead, heads[h])])
+    low = torch.tensor(-below * math.log(2) * math.sqrt(d) / 8).bfloat16()
+    K[:, :, :lead, 0] = low
+    K[:, :, lead + 1:, 0] = low
+    ctx = vatp.vatp_create(0)
+    try:
+        p = vatp.Params(1, H, d, torch.bfloat16, 0, 0, L, [L], [L])
+        ws = torch.zeros(vatp.vatp_workspace_bytes(ctx, p, vatp.binding.CALL_PREFILL_SCORE), dtype=torch.uint8, device=gpu_device)
+        S, nrm = torch.zeros(H, L, device=gpu_device), torch.zeros(H, L, device=gpu_device)
+        Qd, Kd = Q.to(gpu_device), K.to(gpu_device)
+        vatp.vatp_prefill_score(ctx, p, Qd, Kd, Kd, S, nrm, ws)
+        torch.cuda.synchronize()
+        got = ws[:4 * H * L].view(torch.float32).view(H, L).cpu().double()       # (row statistics lie first)
+    finally:
+        vatp.vatp_destroy(ctx)
+    t = 8 * K[0, :, :, :2].double().sum(-1) / math.sqrt(d)                       # (every row has the same logits)
+    want = torch.logcumsumexp(t, -1)[:, lead:] / math.log(2)
+    off = (got[:, lead:] - want).abs().max().item()
+    assert off <= (2.0 ** -21 if below <= 16 else 2.0 ** -25) + 2.0 ** -23 + 4 * 2.0 ** -22, off
