@@ -61,12 +61,12 @@ __device__ __forceinline__ void copies_to_lds(unsigned to, const unsigned (&off)
                      ::"s"(to), "v"(off[0]), "v"(off[1]), "s"(base), "n"(kStep) : "memory", "scc");
 }
 
-// Wait until at most kPending of this wavefront's vector-memory operations are outstanding,
-// then meet the other wavefronts.  The "memory" clobber keeps LDS reads below it.
+// Wait until at most kPending of this wavefront's vector-memory operations are outstanding and its LDS reads complete (the slot they read
+// from may be filled again behind the barrier), then meet the other wavefronts.  The "memory" clobber keeps LDS reads below it.
 template <int kPending>
 __device__ __forceinline__ void wait_copies_then_barrier()
 {
-    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kPending) : "memory");
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(kPending) : "memory");
 }
 
 // Norms of kLoads times kCopyRows consecutive value rows by one wavefront.  Same arithmetic wherever norms are formed (row_norm):
