@@ -281,7 +281,10 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_direct_kernel(const T 
         }
         // first streamed row this lane holds (the others follow at acc_row(v)), and the masks of the tiles that need them
         const int r0 = t * kTileRows + 4 * g;
-        if (t * kTileRows < base0 + kBlock || t * kTileRows + kTileRows > len || (kColsum && t * kTileRows < q_first)) {
+        // (one condition, not three branches: the compiler counts the wait states between the last MFMA and what reads its result along
+        // one of the ways that lead there, which with short blocks between the two need not be the shortest)
+        const bool masked = (t * kTileRows < base0 + kBlock) | (t * kTileRows + kTileRows > len) | (kColsum && t * kTileRows < q_first);
+        if (masked) {
 #pragma unroll
             for (int c = 0; c < kCols; ++c) {
                 const int col = base0 + kTileRows * c + n;
