@@ -73,6 +73,14 @@ struct Unit {                      // logits of 16 streamed rows by 128 columns:
 // Per column tile of a lane.  Column sums: col.  Row statistics: the sum l of 2^(t - m).
 struct Running { float m[kTiles], l[kTiles], col[kTiles]; };
 
+// The lane's number formed here: what is derived from it takes no register of the loops before
+__device__ __forceinline__ int own_lane_here()
+{
+    unsigned ones = ~0u;
+    asm volatile("" : "+s"(ones));
+    return static_cast<int>(__builtin_amdgcn_mbcnt_hi(ones, __builtin_amdgcn_mbcnt_lo(ones, 0)));
+}
+
 // Maximum over the four lane groups, which hold the same columns
 __device__ __forceinline__ float across_groups_max(float x)
 {
@@ -335,8 +343,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_wide_kernel(const bf16
                     const float now = __builtin_amdgcn_ldexpf(work.part[c], -up);
                     work.part[c] = now > kFarAbove ? -0.f : now;
                 }
-                int own_lane = threadIdx.x & 63;
-                asm volatile("" : "+v"(own_lane));                     // (formed here: kept outside the loops it takes registers)
+                const int own_lane = own_lane_here();
 #pragma unroll 1
                 for (int u = t >= 2 ? -1 : 0; u <= 0; ++u) {
                     const int row = (t - 1) * kSlotRows + kPartRows * part + (kSlotRows - 16) * u + (own_lane & 15);
@@ -394,7 +401,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_wide_kernel(const bf16
                     if constexpr (kColsum && j == kSlots - 1) {
                         load_lse(slot, kPartRows * part + 16 * u);
                         if constexpr (kTail) {
-                            const int left = len - (t * kSlotRows + kPartRows * part + 16 * u + 4 * g);       // rows from the lane's first on
+                            const int left = len - (t * kSlotRows + kPartRows * part + 16 * u + 4 * (own_lane_here() >> 4));    // rows from the lane's first on
 #pragma unroll
                             for (int v = 0; v < 4; ++v) lse[v] = v < left ? lse[v] : INFINITY;
                         }
@@ -522,6 +529,14 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_wide_kernel(const bf16
             }
         }
 
+        auto store_sum = [&](int idx, float sum) __attribute__((always_inline)) {
+            if (kGrouped && splits > 1)                                // partial sum [split, K/V head, cap], mean taken by the merge kernel
+                S[(static_cast<size_t>(split) * (n_units / splits) + unit) * cap + idx] = sum;
+            else
+                S[unit * cap + idx] = kGrouped ? sum * (1.f / static_cast<float>(group)) : sum;      // (the group mean)
+        };
+        // (a sum to be formed again, below; by its bits, so that a NaN is none)
+        auto small = [](float sum) { return __float_as_uint(sum) < __float_as_uint(kSubnormalLoss); };
         if (qh == n_qh - 1) {
             // Merge the four lane groups (same columns, complementary rows): lane (g, n) keeps tiles 2 g and 2 g + 1.  Then the
             // parts, through LDS.
@@ -581,20 +596,34 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_wide_kernel(const bf16
 #pragma unroll
                 for (int c = 0; c < 2; ++c) {
                     const int idx = base0 + col0 + 16 * c;
+                    if constexpr (kColsum) merge_buf[0][0][col0 + 16 * c] = idx < len ? fin_l[c] : 1.f;
                     if (idx >= len) continue;
-                    if constexpr (!kColsum) {
-                        lse_u[idx] = sum_log2(fin_m[c], fin_l[c]);
-                    } else if (kGrouped && splits > 1) {               // partial sum [split, K/V head, cap], mean taken by the merge kernel
-                        S[(static_cast<size_t>(split) * (n_units / splits) + unit) * cap + idx] = fin_l[c];
-                    } else {
-                        S[unit * cap + idx] = kGrouped ? fin_l[c] * (1.f / static_cast<float>(group)) : fin_l[c];      // (the group mean)
-                    }
+                    if constexpr (!kColsum) lse_u[idx] = sum_log2(fin_m[c], fin_l[c]);
+                    else if (!small(fin_l[c])) store_sum(idx, fin_l[c]);
                 }
             }
         }
         // every wavefront must be done reading the ring before the next job refills it (all
         // copies have landed by now; the result stores need not have)
         asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        // Sums small enough to miss weights below 2^-126 are formed again, 32 keys at a time, by all wavefronts.  Where every sum is (a first
+        // key 76 nats above the others) that takes long: 32 heads x 4096 rows 154 -> 664 us, 21 x 4096 138 -> 623 (on the direct kernels 678).
+        if constexpr (kColsum) {
+            if (qh == n_qh - 1) {
+#pragma unroll 1
+                for (int cb = wave; cb < kBlock / 32; cb += kWaves) {
+                    const int own_lane = own_lane_here(), col = base0 + 32 * cb, idx = col + (own_lane & 31);
+                    const float sum = merge_buf[0][0][32 * cb + (own_lane & 31)];
+                    if (!__any(small(sum))) continue;
+                    const size_t head = static_cast<size_t>(split * n_qh) * cap;
+                    const float part_sum = column_sum_subnormal<bf16_t, D, false>(
+                        reinterpret_cast<const uint4 *>(stat), reinterpret_cast<const uint4 *>(strm0 + head * D), lse_u0 + head, scale_log2, 1.f,
+                        0.f, col, len, cap, 0, n_qh, col / 32, 1, own_lane);
+                    const float again = part_sum + __shfl_xor(part_sum, 32);
+                    if (own_lane < 32 && small(sum)) store_sum(idx, again);
+                }
+            }
+        }
     }
 }
 

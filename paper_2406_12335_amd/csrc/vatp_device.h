@@ -326,6 +326,10 @@ __device__ __forceinline__ float column_sum_subnormal(const uint4 *keys, const u
     // one tile of one query head: term(v, row, weight)
     auto tile = [&](int t, int h, auto term) __attribute__((always_inline)) {
         const uint4 *row = queries + (static_cast<size_t>(h) * cap + min(t * 32 + n, len - 1)) * kChunks + g;
+        // (all of the tile's row log-sum-exps before the first is used, and no branches: 16 round trips one after the other else)
+        float lse_v[16];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) lse_v[v] = lse[static_cast<size_t>(h) * cap + min(t * 32 + 4 * g + acc_row(v), len - 1)];
         floatx16 acc;
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[v] = 0.f;
@@ -338,8 +342,8 @@ __device__ __forceinline__ float column_sum_subnormal(const uint4 *keys, const u
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             const int r = t * 32 + 4 * g + acc_row(v);
-            const float l = fmaf(lse[static_cast<size_t>(h) * cap + min(r, len - 1)], lse_scale, lse_add);
-            term(v, r, r >= col && r >= q_first && r < len ? exp2f(fmaf(acc[v], scale, -l)) : 0.f);
+            const float x = fmaf(acc[v], scale, -fmaf(lse_v[v], lse_scale, lse_add));
+            term(v, r, exp2f(r >= col && r >= q_first && r < len ? x : -INFINITY));
         }
     };
     if constexpr (!kRows) {

@@ -260,12 +260,14 @@ def test_very_low_logits(gpu_device, dtype, d, B, H, L, window):
 
 # weights and scores below the smallest normal number keep their value: one coordinate, keys but the first 2^-128 .. 2^-143 of it.
 # The exponent is good to a unit of 2^-17 (rounding it) plus 2^-25 of itself (the scale's), times ln 2: 8e-6; every weight is
-# a multiple of 2^-149.  (bf16 heads of 128: on the small grids.)
+# a multiple of 2^-149.  (Windows of bf16 heads of 128 do without.)
 @pytest.mark.parametrize("dtype,d,B,H,g,L,window", [
     ("fp32", 64, 1, 2, 1, 100, None), ("fp32", 128, 1, 1, 3, 300, 40), ("fp32", 128, 8, 32, 1, 300, None), ("fp32", 64, 1, 2, 1, 77, 5),
     ("bf16", 64, 1, 2, 1, 100, None), ("bf16", 128, 1, 3, 1, 300, None), ("bf16", 64, 1, 1, 8, 1100, None),
     ("bf16", 64, 4, 64, 1, 80, None), ("bf16", 64, 2, 128, 1, 300, None), ("bf16", 64, 9, 64, 1, 310, None),
     ("bf16", 64, 2, 64, 4, 290, None), ("bf16", 64, 32, 8, 2, 600, None),
+    ("bf16", 128, 20, 26, 1, 310, None), ("bf16", 128, 25, 16, 1, 270, None), ("bf16", 128, 8, 32, 2, 290, None), ("bf16", 128, 32, 16, 2, 290, None),
+    ("bf16", 128, 13, 16, 2, 290, None),
     ("bf16", 64, 1, 2, 1, 1500, 30), ("bf16", 64, 3, 2, 2, 700, 90),
 ])
 def test_weights_below_the_normal_range(gpu_device, dtype, d, B, H, g, L, window):
@@ -295,9 +297,11 @@ def test_weights_below_the_normal_range(gpu_device, dtype, d, B, H, g, L, window
 
 # Small sums are formed once more for a block of keys at a time; the other keys of the block keep their sums.  Odd keys have weights near
 # 2^-144 here; the even ones one weight in a head, and their sums are bounded as above: 17, on the staged kernels of heads of 64, which add
-# tile after tile to one sum of up to 32, (2 + ... + 32) / 32 in the place of 4.9: 29.
+# tile after tile to one sum of up to 32, (2 + ... + 32) / 32 in the place of 4.9: 29; on those of heads of 128 8 rows, 10 stages of 64 or 8 of 128,
+# lane groups by halves and up to 4 parts: 4.4 + 5.4 + 4: 14.
 @pytest.mark.parametrize("dtype,d,H,L", [("bf16", 128, 8, 1801), ("bf16", 64, 8, 1801), ("fp32", 64, 8, 1801), ("fp32", 128, 8, 1001), ("bf16", 128, 32, 1151),
-                                         ("bf16", 64, 32, 1101), ("fp32", 64, 64, 1151), ("bf16", 64, 258, 1001), ("bf16", 64, 120, 1001)])
+                                         ("bf16", 64, 32, 1101), ("fp32", 64, 64, 1151), ("bf16", 64, 258, 1001), ("bf16", 64, 120, 1001),
+                                         ("bf16", 128, 516, 601), ("bf16", 128, 110, 1001)])
 def test_small_sums_beside_others(gpu_device, dtype, d, H, L):
     print("[case] small sums beside others %s d=%d H=%d L=%d" % (dtype, d, H, L), flush=True)
     dt = {"fp32": torch.float32, "bf16": torch.bfloat16}[dtype]
