@@ -98,6 +98,13 @@ __device__ __forceinline__ float move_reference(float &m, const floatx4 &t, floa
     m = ref;
     return fit;
 }
+__device__ __forceinline__ float largest(const float (&x)[kTiles])
+{
+    float most = x[0];
+#pragma unroll
+    for (int c = 1; c < kTiles; ++c) most = fmaxf(most, x[c]);
+    return most;
+}
 __device__ __forceinline__ float weights(const floatx4 &t, float scale, float m)
 {
     float p[4];
@@ -424,12 +431,18 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_wide_kernel(const bf16
             } else {
                 settle(t + 1);
                 work.finish(run);
+                const Unit &done = acc[1];
 #pragma unroll
-                for (int c = 0; c < kTiles; ++c) {
-                    const float fit = move_reference(run.m[c], acc[1].tile[c], scale_log2);
-                    run.l[c] = fmaf(run.l[c], fit, weights(acc[1].tile[c], scale_log2, run.m[c]));
-                    __builtin_amdgcn_sched_barrier(0);
+                for (int c = 0; c < kTiles; ++c) work.part[c] = weights(done.tile[c], scale_log2, run.m[c]);
+                if (__builtin_expect(__any(largest(work.part) > kMostAboveReference), 0)) {
+#pragma unroll
+                    for (int c = 0; c < kTiles; ++c) {
+                        run.l[c] *= move_reference(run.m[c], done.tile[c], scale_log2);
+                        work.part[c] = weights(done.tile[c], scale_log2, run.m[c]);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
                 }
+                work.finish(run);
             }
         };
         // A stage across the diagonal or the end of the sequence: 16 rows by 128 or, where the other 64 columns are masked altogether,
