@@ -87,6 +87,12 @@ def _seed_state(caches, lens, g, d, tdt, dev, weak_rows=None):
     ("bf16", 64, 3, [2047, 1030], [2047, 2047], 64, 2, 6),     # rows of 128 bytes: 2048
     ("fp32", 128, 3, [511, 64], [511, 511], 30, 2, 6),         # of 512 bytes: 512, one more takes two launches
     ("fp32", 128, 3, [512, 511], [512, 512], 30, 2, 6),
+    # two launches with and without attention output: just past the limits of the other row sizes, and past 256 heads (256 take one)
+    ("bf16", 128, 3, [1024, 600], [1024, 1024], 64, 2, 6),
+    ("bf16", 64, 3, [2048, 1030], [2048, 2048], 64, 2, 6),
+    ("fp32", 64, 3, [1024, 64], [1024, 1024], 64, 2, 6),
+    ("bf16", 64, 128, [1500, 1100], [1500, 1500], 64, 2, 3),
+    ("bf16", 64, 129, [1500, 1100], [1500, 1500], 64, 2, 3),
 ])
 def test_fused_step_is_bit_identical_to_the_two_call_route(gpu_device, dtype, d, H, lens, budgets, R, F, steps):
     """Same K, V, S, nrm, pos, kept_idx and attention output as vatp_decode_attend_step followed by

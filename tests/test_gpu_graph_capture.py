@@ -29,14 +29,15 @@ def _state(cache):
     return [x[c][:, :, :n].clone() for x in (cache.K, cache.V, cache.S, cache.nrm, cache.pos)] + [cache.kept_idx[:, :, :n].clone()]
 
 
-@pytest.mark.parametrize("q_per_kv", [1, 4])
-def test_prompt_pass_prune_and_fused_steps_replay_from_a_graph(gpu_device, q_per_kv):
+# (fused steps in one launch, in two for groups and for more than 1024 rows of 256 bytes)
+@pytest.mark.parametrize("q_per_kv,prompt_len", [(1, 600), (4, 600), (1, 2200)])
+def test_prompt_pass_prune_and_fused_steps_replay_from_a_graph(gpu_device, q_per_kv, prompt_len):
     dev = gpu_device
     steps = 6                   # an even number: the cache sets end where they started, so every replay starts alike
-    cfg = vs.scaled(vs.CONFIGS["llama7b_layer"], n_heads=4, prompt_len=600, decode_steps=steps, q_per_kv=q_per_kv)
+    cfg = vs.scaled(vs.CONFIGS["llama7b_layer"], n_heads=4, prompt_len=prompt_len, decode_steps=steps, q_per_kv=q_per_kv)
     inp = vs.make_inputs(cfg, seed=9)
     tensors = tuple(t.to(dev) for t in (inp.Q, inp.K, inp.V, inp.qd, inp.kd, inp.vd))
-    _say("graph capture, q_per_kv=%d" % q_per_kv)
+    _say("graph capture, q_per_kv=%d, %d rows" % (q_per_kv, prompt_len))
     cache = PrunedKVCache(1, 4, 128, torch.bfloat16, 2, cfg.recent, inp.budgets, dev, q_per_kv=q_per_kv)
     try:
         # eager run: the reference result (also allocates the prompt-side buffers the runner keeps)
