@@ -72,41 +72,31 @@ def algorithmic_bytes_window(cfg, n_rows, window, rows_moved):
     return 12 * n_rows + 4 * window + 8 * rows_moved
 
 
+def _params(cfg, lens, budgets):
+    import paper_2406_12335_amd as vatp
+    rows = max(max(lens), max(budgets)) + 1
+    return vatp.Params(cfg.batch, cfg.n_heads, cfg.head_dim, cfg.torch_dtype(), cfg.n_sinks, cfg.recent, rows, lens, budgets,
+                       q_per_kv=cfg.q_per_kv)
+
+
 def fused_step_kernels(cfg, lens, budgets, window):
-    """Names of the kernels one vatp_decode_prune_step call launches for this workload (the library's rule:
-    a single launch with one workgroup per head, without grouped queries and history window, for up to 256 heads of at most
-    256 KiB of K rows and for 128 heads and more of at most 1024 rows; otherwise the logits launch plus the
-    evict-and-copy launch)."""
-    rows = max(min(L, B) for L, B in zip(lens, budgets)) + 1
-    heads, row_bytes = cfg.batch * cfg.n_heads, cfg.head_dim * (2 if cfg.dtype == "bf16" else 4)
-    short = rows <= 2048 and ((heads <= 256 and rows * row_bytes <= 256 << 10) or (heads >= 128 and rows <= 1024))
-    if window is None and cfg.q_per_kv == 1 and short:
+    """Names of the kernels one vatp_decode_prune_step call launches for this workload, by the library's word."""
+    from paper_2406_12335_amd import binding
+    p = _params(cfg, [min(L, B) for L, B in zip(lens, budgets)], budgets)
+    if binding.vatp_route(p, binding.CALL_DECODE_PRUNE_STEP, -1 if window is None else window) & binding.ROUTE_ONE_LAUNCH:
         return "decode_prune_one_kernel"
     first = "decode_logits_group_kernel" if cfg.q_per_kv > 1 else "decode_logits_kernel"
     return first + " + decode_prune_kernel"
 
 
 def prompt_score_kernels(cfg, lens, window):
-    """Names of the kernels one prompt-scoring call launches for this workload (the library's rule: bf16 passes whose
-    workgroups fill the chip, and bf16 windows, on the staged kernels, everything else on the direct ones)."""
-    pairs = ((max(lens) + 255) // 256 + 1) // 2                  # a workgroup's work: two blocks of 256 rows
-    units, g = cfg.batch * cfg.n_heads, cfg.q_per_kv
-    splits = next((s for s in range(1, g + 1) if g % s == 0 and 8 * pairs * ((units * s + 7) // 8) >= 512), g)
-
-    def kernel(heads):
-        jobs, rows = units * heads * pairs, cfg.n_heads * heads * sum(lens)
-        two = jobs > 256
-        if cfg.head_dim == 64:
-            fills = jobs >= (480 if two else 240) or (pairs >= 8 and rows >= 512 * (432 if two else 216))
-        else:
-            long = pairs >= (6 if two else 8) and jobs >= (328 if two else 168)
-            fills = jobs >= (384 if two else 192) or (long and rows >= 512 * (300 if two else 164))
-        if window is not None:                                   # (attention rows within 32-bit offsets)
-            fills = (window + 257) * max(lens) * 4 < 1 << 31
-        staged = "prefill_wide_kernel" if cfg.head_dim == 128 and window is None else "prefill_mfma_kernel"
-        return staged if cfg.dtype == "bf16" and fills else "prefill_direct_kernel"
-
-    rowstat, colsum = kernel(g), kernel(splits)
+    """Names of the kernels one prompt-scoring call launches for this workload, by the library's word."""
+    from paper_2406_12335_amd import binding
+    call = binding.CALL_PREFILL_SCORE if window is None else binding.CALL_PREFILL_SCORE_WINDOW
+    route = binding.vatp_route(_params(cfg, lens, lens), call, -1 if window is None else window)
+    staged = "prefill_wide_kernel" if cfg.head_dim == 128 and window is None else "prefill_mfma_kernel"
+    rowstat = staged if route & binding.ROUTE_STAGED_ROWS else "prefill_direct_kernel"
+    colsum = staged if route & binding.ROUTE_STAGED_SUMS else "prefill_direct_kernel"
     if window is None:
         return "%s<rowstat> + %s<colsum, value norms inside>" % (rowstat, colsum)
     ranges = " over key ranges + merge_split_lse_kernel" if rowstat == "prefill_mfma_kernel" else ""

@@ -122,6 +122,16 @@ vatp_status vatp_validate(const vatp_params *p, int which_call);
 size_t vatp_workspace_bytes(const vatp_ctx *ctx, const vatp_params *p, int which_call);
 
 /*
+ * Which kernels call `which_call` takes for `p`, for reports: the sum of the values that apply, or a negative
+ * vatp_status on invalid params.  window: the call's history window, -1 without one (the decode call's attention
+ * output is taken to be NULL).  Touches no device.
+ */
+enum { VATP_ROUTE_STAGED_ROWS = 1,     /* prompt: row statistics on the staged kernels, not the direct ones */
+       VATP_ROUTE_STAGED_SUMS = 2,     /* prompt: column sums likewise                                      */
+       VATP_ROUTE_ONE_LAUNCH = 4 };    /* vatp_decode_prune_step: one launch, not two                       */
+int vatp_route(const vatp_params *p, int which_call, int32_t window);
+
+/*
  * Prompt pass (Eq. 1 and Eq. 2 with t = len-1; Eq. 4's norm).
  * For every unit:  S[i]   = sum_{j=i}^{len-1} softmax_{i'<=j}(c <q_j, k_i'>)[i]
  *                  nrm[i] = |V[i]|_1 (or the norm `norm` selects)  for i < len[b].

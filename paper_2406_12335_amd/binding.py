@@ -24,7 +24,9 @@ VATP_MAX_BATCH, VATP_MAX_UNITS, VATP_MAX_GROUP = 256, 16384, 16
 VATP_STATIC_SCRATCH_BYTES = 16777216
 OK, E_NULL, E_SHAPE, E_DTYPE, E_BUDGET, E_WORKSPACE, E_DEVICE = 0, -1, -2, -3, -4, -5, -6
 
-EXPORTS = ("vatp_create", "vatp_destroy", "vatp_strerror", "vatp_validate", "vatp_workspace_bytes",
+ROUTE_STAGED_ROWS, ROUTE_STAGED_SUMS, ROUTE_ONE_LAUNCH = 1, 2, 4
+
+EXPORTS = ("vatp_create", "vatp_destroy", "vatp_strerror", "vatp_validate", "vatp_workspace_bytes", "vatp_route",
            "vatp_prefill_score", "vatp_prefill_score_lse", "vatp_decode_step", "vatp_decode_attend_step", "vatp_select_compact",
            "vatp_decode_prune_step", "vatp_decode_prune_step_static", "vatp_prefill_score_window", "vatp_select_compact_window",
            "vatp_decode_prune_step_window")
@@ -69,6 +71,8 @@ def load() -> ctypes.CDLL:
     L.vatp_strerror.restype = ctypes.c_char_p
     L.vatp_validate.argtypes = [pp, ctypes.c_int]
     L.vatp_validate.restype = ctypes.c_int
+    L.vatp_route.argtypes = [pp, ctypes.c_int, ctypes.c_int32]
+    L.vatp_route.restype = ctypes.c_int
     L.vatp_workspace_bytes.argtypes = [_vp, pp, ctypes.c_int]
     L.vatp_workspace_bytes.restype = ctypes.c_size_t
     L.vatp_prefill_score.argtypes = [_vp, pp] + [_vp] * 5 + [_vp, ctypes.c_size_t, _vp]
@@ -163,6 +167,10 @@ def vatp_destroy(ctx) -> None:
 
 def vatp_validate(p: Params, which_call: int) -> int:
     return int(load().vatp_validate(p.ref(), which_call))
+
+
+def vatp_route(p: Params, which_call: int, window: int = -1) -> int:
+    return int(load().vatp_route(p.ref(), which_call, window))
 
 
 def vatp_workspace_bytes(ctx, p: Params, which_call: int) -> int:

@@ -115,6 +115,34 @@ inline bool wrong_device(const vatp_ctx *ctx)
     return cur != ctx->device;
 }
 
+// windowed prompts on the staged kernels
+inline bool staged_window(const vatp_params *p, const Geometry &g, int window)
+{
+    return p->dtype == VATP_BF16 && prefill_mfma_window_fits(window, p->cap, p->batch * p->n_heads * g.group);
+}
+// a pass over a prompt without a window: on the staged kernels where its grid fills the chip with them, else on the direct ones
+inline bool staged_pass(const vatp_params *p, const Prepared &pr, int pass)
+{
+    return p->dtype == VATP_BF16 && prefill_mfma_fills(p->head_dim, pass, pr.meta, pr.g);
+}
+// The fused step (without attention output and history) in one launch with a workgroup per head when each head is short enough for a
+// single workgroup to stream quickly: up to 256 KiB of K rows (1024 rows of 256 bytes) while the workgroups share no compute unit, and up
+// to 1024 rows of any size from 128 heads on.
+// Measured per step, two launches / one: 4 fp32 heads of 64 x 129 rows 12.4 / 8.2 us, 32 heads of 128 x 251 rows 11.5 / 7.9, x 1001
+// rows 11.3 / 8.9, 96 x 1001 13.2 / 10.4, 256 heads of 64 x 2046 rows 19.6 / 18.1, but 512 x 1251 24.6 / 26.6; 8 fp32 heads of 128
+// (512-byte rows) x 501 11.5 / 9.6, but x 1001 11.4 / 12.0; 32 heads of 128 x 2049 rows 14 / 23.  With 32 layers' caches in turn, so that
+// rows come from memory, enqueued call by call (and replayed from a graph, without the host's 9 to 12 us per call of two launches):
+// 256 heads x 820 rows 30 / 22, 64 x 1001 13.6 / 12.5 (13.7 / 12.6), 32 x 501 11.8 / 9.2 (9.9 / 8.9), 32 x 1001 11.8 / 11.5 (11.4 / 11.5),
+// 16 x 781 11.8 / 9.3 (8.4 / 9.1), 16 x 1001 11.9 / 11.0 (9.0 / 10.8), 4 x 1001 11.7 / 9.0 (8.6 / 8.8): a compute unit's share of the
+// memory's rate is what few heads lose on, and where the host is fast enough to show it, 16 x 1001 9.5 / 10.9 on another machine.
+inline bool in_one_launch(const vatp_params *p, const Geometry &g)
+{
+    const int kv_units = p->batch * p->n_heads;
+    const size_t row_bytes = static_cast<size_t>(p->head_dim) * (p->dtype == VATP_BF16 ? 2 : 4);
+    return g.group == 1 && g.max_len <= decode_prune_one_max_rows() &&
+           ((kv_units <= 256 && g.max_len * row_bytes <= (256u << 10)) || (kv_units >= 128 && g.max_len <= 1024));
+}
+
 inline bool misaligned(const void *ptr, size_t a) { return (reinterpret_cast<uintptr_t>(ptr) & (a - 1)) != 0; }
 
 }  // namespace
@@ -178,6 +206,24 @@ void vatp_destroy(vatp_ctx *ctx)
 
 vatp_status vatp_validate(const vatp_params *p, int which_call) { return check_params(p, which_call); }
 
+int vatp_route(const vatp_params *p, int which_call, int32_t window)
+{
+    const vatp_status st = check_params(p, which_call);
+    if (st != VATP_OK) return st;
+    Prepared pr;
+    prepare(p, which_call, nullptr, &pr);
+    switch (which_call) {
+    case VATP_CALL_PREFILL_SCORE:
+        return (staged_pass(p, pr, kPassRowstat) ? VATP_ROUTE_STAGED_ROWS : 0) | (staged_pass(p, pr, kPassColsum) ? VATP_ROUTE_STAGED_SUMS : 0);
+    case VATP_CALL_PREFILL_SCORE_WINDOW:
+        return window >= 0 && staged_window(p, pr.g, window) ? VATP_ROUTE_STAGED_ROWS | VATP_ROUTE_STAGED_SUMS : 0;
+    case VATP_CALL_DECODE_PRUNE_STEP:
+        return window < 0 && in_one_launch(p, pr.g) ? VATP_ROUTE_ONE_LAUNCH : 0;
+    default:
+        return 0;
+    }
+}
+
 size_t vatp_workspace_bytes(const vatp_ctx *, const vatp_params *p, int which_call)
 {
     if (check_params(p, which_call) != VATP_OK) return 0;
@@ -236,19 +282,18 @@ vatp_status prefill_score_impl(vatp_ctx *ctx, const vatp_params *p, const void *
     // what follows lse2 in the workspace: partial row statistics of a window, or room for partial column sums of a group
     float *parts = lse2 + align_up(units * pr.g.group * p->cap * sizeof(float)) / sizeof(float);
     hipError_t e = hipSuccess;
-    if (window >= 0 && p->dtype == VATP_BF16 && prefill_mfma_window_fits(window, p->cap, static_cast<int>(units * pr.g.group))) {
+    if (window >= 0 && staged_window(p, pr.g, window)) {
         e = launch_prefill_mfma_window(p->head_dim, Q, K, V, S, nrm, lse2, parts, window, hist, pr.meta, pr.g, stream);
     } else {
-        // each pass on the staged kernels where its grid fills the chip with them, else on the direct ones
         float *s_part = pr.g.group > 1 && window < 0 ? parts : nullptr;
         for (int pass : {kPassRowstat, kPassColsum}) {          // (the column sums need the row statistics)
             if (e != hipSuccess || (have_lse && pass == kPassRowstat)) continue;
-            const bool staged = window < 0 && p->dtype == VATP_BF16 && prefill_mfma_fills(p->head_dim, pass, pr.meta, pr.g);
+            const bool staged = window < 0 && staged_pass(p, pr, pass);
             // Row statistics handed in: the direct kernels take them as they are (unless an output or the partial sums lie over
             // them, since workgroups write these while others still read).  Measured, with the conversion in a launch of its own /
             // without: 4 heads of 64 x 256 fp32 rows 12.1 / 8.0 us, 2 x 8 x 4 query heads x 700 rows 20.5 / 17.8, 32 heads x
-            // 2000 rows 36.4 / 34.9.  The staged kernels copy them to LDS and have no instruction to spare for them: there
-            // the launch takes 5.6 of 586 us, at 8 x 8 x 4 query heads x 4001 rows.
+            // 2000 rows 36.4 / 34.9.  The staged kernels copy them to LDS and take them in base 2: there the launch takes 5.2 of
+            // 555 us, at 8 x 8 x 4 query heads x 4001 rows.
             const size_t bytes = units * p->cap * sizeof(float);
             const bool natural = have_lse && !staged && !overlap(lse, bytes * pr.g.group, S, bytes) &&
                                  !overlap(lse, bytes * pr.g.group, nrm, bytes) &&
@@ -384,15 +429,7 @@ vatp_status decode_prune_impl(vatp_ctx *ctx, const vatp_params *p, const void *q
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     BatchMeta budgets = pr.meta;
     for (int b = 0; b < p->batch; ++b) budgets.aux[b] = p->budget[b];
-    // One launch with a workgroup per head when each head is short enough for a single workgroup to stream quickly: up to 256 KiB of
-    // K rows (1024 rows of 256 bytes) while the workgroups share no compute unit, and up to 1024 rows of any size from 128 heads on.
-    // Measured per step, two launches / one: 4 fp32 heads of 64 x 129 rows 12.4 / 8.2 us, 32 heads of 128 x 251 rows 11.5 / 7.9, x 1001
-    // rows 11.3 / 8.9, 96 x 1001 13.2 / 10.4, 256 heads of 64 x 2046 rows 19.6 / 18.1, but 512 x 1251 24.6 / 26.6; 8 fp32 heads of 128
-    // (512-byte rows) x 501 11.5 / 9.6, but x 1001 11.4 / 12.0; 32 heads of 128 x 2049 rows 14 / 23; 256 heads x 820 rows with 32 layers'
-    // caches in turn 30 / 22.
-    const size_t row_bytes = static_cast<size_t>(p->head_dim) * (p->dtype == VATP_BF16 ? 2 : 4);
-    const bool one = !out && !win.hist && pr.g.group == 1 && pr.g.max_len <= decode_prune_one_max_rows() &&
-                     ((kv_units <= 256 && pr.g.max_len * row_bytes <= (256u << 10)) || (kv_units >= 128 && pr.g.max_len <= 1024));
+    const bool one = !out && !win.hist && in_one_launch(p, pr.g);
     if (one) {
         BudgetList blist;
         memcpy(blist.v, budgets.aux, sizeof(blist.v));

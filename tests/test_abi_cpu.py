@@ -169,3 +169,31 @@ def test_built_library_matches_its_sources():
     finally:
         shutil.move(backup, victim)
     assert build.source_digest() == d0 and build.is_current()
+
+
+def test_route_reports_the_kernels_a_call_takes():
+    """At the edges of the rules; the GPU tests of these sizes check the results."""
+    def prompt(heads, rows, d=128, dtype=vatp.VATP_BF16, batch=1, g=1, window=None):
+        p = _params(batch=batch, n_heads=heads, head_dim=d, dtype=dtype, cap=rows, len=[rows] * batch, budget=[rows] * batch, q_per_kv=g)
+        call = binding.CALL_PREFILL_SCORE if window is None else binding.CALL_PREFILL_SCORE_WINDOW
+        return vatp.vatp_route(p, call, -1 if window is None else window)
+
+    both = binding.ROUTE_STAGED_ROWS | binding.ROUTE_STAGED_SUMS
+    assert prompt(32, 4096) == both and prompt(32, 4096, dtype=vatp.VATP_F32) == 0
+    assert prompt(20, 4000) == 0 and prompt(21, 4000) == both and prompt(21, 3998) == 0
+    assert prompt(54, 2800) == 0 and prompt(55, 2800) == both
+    assert prompt(26, 4096, d=64) == 0 and prompt(27, 4096, d=64) == both
+    assert prompt(8, 4096, g=4) == both and prompt(2, 256) == 0
+    assert prompt(2, 300, window=30) == both and prompt(2, 300, dtype=vatp.VATP_F32, window=30) == 0
+
+    def step(heads, held, d=128, dtype=vatp.VATP_BF16, g=1, window=-1):
+        p = _params(batch=1, n_heads=heads, head_dim=d, dtype=dtype, cap=held + 1, len=[held], budget=[held], q_per_kv=g)
+        return vatp.vatp_route(p, binding.CALL_DECODE_PRUNE_STEP, window)
+
+    one = binding.ROUTE_ONE_LAUNCH
+    assert step(4, 1023) == one and step(4, 1024) == 0 and step(4, 2047, d=64) == one and step(4, 2048, d=64) == 0
+    assert step(4, 511, dtype=vatp.VATP_F32) == one and step(4, 512, dtype=vatp.VATP_F32) == 0
+    assert step(256, 1500, d=64) == one and step(257, 1500, d=64) == 0 and step(257, 1023, d=64) == one
+    assert step(4, 100, g=2) == 0 and step(4, 100, window=10) == 0
+    p = _params(head_dim=96)
+    assert vatp.vatp_route(p, binding.CALL_PREFILL_SCORE) == binding.E_SHAPE
