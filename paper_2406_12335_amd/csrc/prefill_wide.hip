@@ -32,7 +32,7 @@
 // block.  While the MFMAs of a unit run, the lane works through the exponentials of the unit before, one after every MFMA;
 // the order is laid down slot by slot (sched_barrier), since the scheduler left to itself bunches them.  Stages across the
 // diagonal are worked off apart, without the columns that are masked altogether.
-// Registers are the limit: 242 to 256 of the 256 that two wavefronts per SIMD may have, and a single one in scratch memory
+// Registers are the limit: 253 to 256 of the 256 that two wavefronts per SIMD may have, and a single one in scratch memory
 // costs 10 to 20 us a launch (32 x 4096 rows 147 -> 164): lane values that are cheap to form are formed anew, behind an
 // empty assembly statement that keeps the compiler from holding on to them.
 //
@@ -155,7 +155,7 @@ struct VectorWork {
     }
 };
 
-template <bool kColsum, int kWaves, int kColGroups, bool kGrouped>
+template <bool kColsum, int kWaves, bool kGrouped>
 __global__ __launch_bounds__(64 * kWaves, 2) void prefill_wide_kernel(const bf16_t *__restrict__ Q,
                                                                         const bf16_t *__restrict__ K, float *__restrict__ lse2,
                                                                         float *__restrict__ S, BatchMeta meta, int n_heads,
@@ -165,7 +165,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_wide_kernel(const bf16
 {
     static_assert(!kGrouped || kColsum, "only the column sums loop over a group's query heads");
     constexpr int D = 128, kChunks = D / 8, kSteps = D / 32, kSlots = kTiles * kSteps;
-    constexpr int kBlock = kWaveCols * kColGroups;                        // stationary rows per workgroup
+    constexpr int kBlock = kBlockCols, kColGroups = kBlock / kWaveCols;   // stationary rows per workgroup, column groups
     constexpr int kParts = kWaves / kColGroups, kSlotRows = kPartRows * kParts, kSlotBytes = kSlotRows * D * 2;
     constexpr int kOwnRows = kSlotRows / kWaves, kCopyRows = 64 / kChunks, kCopies = kOwnRows / kCopyRows;
     constexpr int kPending = kCopies + (kColsum ? 1 : 0);                 // copies of a wavefront per slot
@@ -640,24 +640,20 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_wide_kernel(const bf16
     }
 }
 
-template <int kWaves, int kColGroups>
-void launch_rowstat(const bf16_t *q, const bf16_t *k, float *S, float *lse2, const BatchMeta &meta, const Geometry &g, hipStream_t st)
+template <int kWaves>
+void launch_rowstat(const bf16_t *q, const bf16_t *k, float *lse2, const BatchMeta &meta, const Geometry &g, hipStream_t st)
 {
-    constexpr int kBlock = kWaveCols * kColGroups;
-    const int units = g.batch * g.n_heads * g.group, n_blocks = (g.max_len + kBlock - 1) / kBlock;
-    hipLaunchKernelGGL((prefill_wide_kernel<false, kWaves, kColGroups, false>), dim3(8u * ((n_blocks + 1) / 2) * ((units + 7) / 8)),
-                       dim3(64 * kWaves), 0, st, q, k, lse2, S, meta, g.n_heads * g.group, units, g.cap, n_blocks, g.scale_log2, nullptr,
-                       nullptr, 0, g.group, 1);
+    const int units = g.batch * g.n_heads * g.group, n_blocks = (g.max_len + kBlockCols - 1) / kBlockCols;
+    hipLaunchKernelGGL((prefill_wide_kernel<false, kWaves, false>), dim3(8u * block_pairs(g) * ((units + 7) / 8)), dim3(64 * kWaves), 0, st, q, k,
+                       lse2, nullptr, meta, g.n_heads * g.group, units, g.cap, n_blocks, g.scale_log2, nullptr, nullptr, 0, g.group, 1);
 }
-template <int kWaves, int kColGroups, bool kGrouped>
+template <int kWaves, bool kGrouped>
 void launch_colsum(const bf16_t *q, const bf16_t *k, const bf16_t *v, float *dst, float *nrm, float *lse2, int splits,
                    const BatchMeta &meta, const Geometry &g, hipStream_t st)
 {
-    constexpr int kBlock = kWaveCols * kColGroups;
-    const int slots = g.batch * g.n_heads * splits, n_blocks = (g.max_len + kBlock - 1) / kBlock;
-    hipLaunchKernelGGL((prefill_wide_kernel<true, kWaves, kColGroups, kGrouped>), dim3(8u * ((n_blocks + 1) / 2) * ((slots + 7) / 8)),
-                       dim3(64 * kWaves), 0, st, q, k, lse2, dst, meta, g.n_heads, slots, g.cap, n_blocks, g.scale_log2, v, nrm, g.norm,
-                       g.group, splits);
+    const int slots = g.batch * g.n_heads * splits, n_blocks = (g.max_len + kBlockCols - 1) / kBlockCols;
+    hipLaunchKernelGGL((prefill_wide_kernel<true, kWaves, kGrouped>), dim3(8u * block_pairs(g) * ((slots + 7) / 8)), dim3(64 * kWaves), 0, st, q, k,
+                       lse2, dst, meta, g.n_heads, slots, g.cap, n_blocks, g.scale_log2, v, nrm, g.norm, g.group, splits);
 }
 
 }  // namespace
@@ -672,18 +668,18 @@ hipError_t launch_prefill_wide(const void *Q, const void *K, const void *V, floa
     const int splits = s_part != nullptr ? colsum_splits(g) : 1;
     if (passes & kPassRowstat) {
         const unsigned wgs = 8u * block_pairs(g) * ((g.batch * g.n_heads * g.group + 7) / 8);
-        if (wgs >= 2u * kComputeUnits) launch_rowstat<4, 2>(q, k, S, lse2, meta, g, st);
-        else launch_rowstat<8, 2>(q, k, S, lse2, meta, g, st);
+        if (wgs >= 2u * kComputeUnits) launch_rowstat<4>(q, k, lse2, meta, g, st);
+        else launch_rowstat<8>(q, k, lse2, meta, g, st);
     }
     if (!(passes & kPassColsum)) return hipGetLastError();
     float *dst = splits > 1 ? s_part : S;
     const unsigned wgs = 8u * block_pairs(g) * ((g.batch * g.n_heads * splits + 7) / 8);
     if (g.group > 1) {
-        if (wgs >= 2u * kComputeUnits) launch_colsum<4, 2, true>(q, k, v, dst, nrm, lse2, splits, meta, g, st);
-        else launch_colsum<8, 2, true>(q, k, v, dst, nrm, lse2, splits, meta, g, st);
+        if (wgs >= 2u * kComputeUnits) launch_colsum<4, true>(q, k, v, dst, nrm, lse2, splits, meta, g, st);
+        else launch_colsum<8, true>(q, k, v, dst, nrm, lse2, splits, meta, g, st);
     } else {
-        if (wgs >= 2u * kComputeUnits) launch_colsum<4, 2, false>(q, k, v, dst, nrm, lse2, splits, meta, g, st);
-        else launch_colsum<8, 2, false>(q, k, v, dst, nrm, lse2, splits, meta, g, st);
+        if (wgs >= 2u * kComputeUnits) launch_colsum<4, false>(q, k, v, dst, nrm, lse2, splits, meta, g, st);
+        else launch_colsum<8, false>(q, k, v, dst, nrm, lse2, splits, meta, g, st);
     }
     if (splits > 1) return launch_merge_group_partials(s_part, S, splits, meta, g, st);
     return hipGetLastError();
