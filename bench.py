@@ -464,20 +464,20 @@ DEFAULT_WORKLOAD = "llama7b_stack"
 # summary named in "source", which also gives the commands.
 PROFILED_TRAFFIC_BYTES = {
     "llama7b_stack": {"source": "profiles/llama7b_stack_profile.md",
-                      "bytes_per_call": {"prefill_score": 1938511959, "decode_step": 57647770, "select_compact": 232475470,
-                                         "decode_prune_step": 71322375}},
+                      "bytes_per_call": {"prefill_score": 1938501310, "decode_step": 57647823, "select_compact": 232475584,
+                                         "decode_prune_step": 71322413}},
     "llama7b_layer": {"source": "profiles/llama7b_layer_profile.md",
-                      "bytes_per_call": {"prefill_score": 174329609, "decode_step": 18034233, "select_compact": 72825229,
-                                         "decode_prune_step": 21309079}},
+                      "bytes_per_call": {"prefill_score": 174840364, "decode_step": 18034182, "select_compact": 72825287,
+                                         "decode_prune_step": 21309039}},
     "long32k": {"source": "profiles/long32k_profile.md",
-                "bytes_per_call": {"prefill_score": 2677423416, "decode_step": 28726249, "select_compact": 116516182,
-                                   "decode_prune_step": 35557748}},
+                "bytes_per_call": {"prefill_score": 2439272591, "decode_step": 28726112, "select_compact": 116540315,
+                                   "decode_prune_step": 35557680}},
     "ragged16": {"source": "profiles/ragged16_profile.md",
-                 "bytes_per_call": {"prefill_score": 6288619567, "decode_step": 204579756, "select_compact": 830402199,
-                                    "decode_prune_step": 250652932}},
+                 "bytes_per_call": {"prefill_score": 6292269957, "decode_step": 204579838, "select_compact": 830402622,
+                                    "decode_prune_step": 250655639}},
     "tiny": {"source": "profiles/tiny_profile.md",
-             "bytes_per_call": {"prefill_score": 1993740, "decode_step": 252119, "select_compact": 594534,
-                                "decode_prune_step": 295460}},
+             "bytes_per_call": {"prefill_score": 1979400, "decode_step": 252122, "select_compact": 594533,
+                                "decode_prune_step": 295459}},
 }
 
 
