@@ -95,12 +95,13 @@ __device__ __forceinline__ void value_norms(const uint4 *__restrict__ Vu, float 
 // every tile instead costs an eighth more vector instructions; leaving m alone whatever follows loses rows: the exponent of a key that lies x
 // above m is rounded like x (rows of 1024 keys that one leads, first keys far below, root mean square error of the sum, x = 12: 1.9e-7, 52:
 // 6.9e-7, 72: 1.5e-6), and a sum worth 2^126 and more at m is lost when the lanes' sums are brought to one reference by factors
-// that may be 0 (v_exp_f32, below 2^-126).  So m moves up where a lane's weights of one stage add up to more than this: exponents stay below
-// 16 (the same errors: 1.9e-7, 3.4e-8, 3.4e-8; a reference in every tile 1.4e-7, 1.0e-8, 1.0e-8), sums below 2^35, and a factor of 0
-// takes away less than 2^-90 of a row's sum.  From 2^24 on: 4.0e-7 at x = 18..23 (now 0.9e-7).  Both passes of 32 heads of 128 x 4096 rows, unit
-// normal q and k, logits of standard deviation 5 nats without sinks, which is what it costs most on: 146 us without any look, 174, from 2^24 on
-// 157; of 3 nats and less, and 8 nats and more between the first keys and the others, as without; logits that rise by 15 nats a stage 249.
-constexpr float kMostAboveReference = 65536.f;
+// that may be 0 (v_exp_f32, below 2^-126).  So m moves up where a lane's weights of one stage add up to more than kMostAboveReference, and
+// weights above kFarAbove are formed again: exponents stay below 24 (the same errors: 1.9e-7, 3.4e-8, 3.4e-8, at x = 18..23 4.0e-7; a
+// reference in every tile 1.4e-7, 1.0e-8, 1.0e-8, 1.6e-7), sums below 2^43, and a factor of 0 takes away less than 2^-80 of a row's sum.
+// Measured, both passes of 32 heads of 128 x 4096 rows: without any look 146 us on logits of a standard deviation of 3 or 5 nats without
+// sinks, now 150 and 151, with kFarAbove at 2^16 148 and 174; logits that rise by 15 nats a stage 250.
+constexpr float kMostAboveReference = 0x1p16f;
+constexpr float kFarAbove = 0x1p24f;
 
 // log2 of 2^m * l, m whole (the logarithm of a number between 1/2 and 1 rounds the least)
 __device__ __forceinline__ float sum_log2(float m, float l)

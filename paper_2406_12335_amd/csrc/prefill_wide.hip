@@ -336,20 +336,21 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_wide_kernel(const bf16
         };
         VectorWork<kColsum, kSlots> work;
         // Row statistics, before stage t (while its operands are on their way): has what the stage before has added up outgrown the reference
-        // of any column (kMostAboveReference)?  Then the references move up to what the running sums have come to, which makes further
-        // moves rare, and where the weights still lie far above (kFarAbove), to their maximum.  These are formed again, of two units (of
-        // one after the first stage), from memory: the logits have made room for others.  A negative part marks the columns concerned.
-        constexpr float kFarAbove = 256.f;
+        // of any column (kMostAboveReference)?  Then the references move up to what the sums have come to, exactly.  Weights that lie farther
+        // above (kFarAbove) are formed again at their own maximum, of two units (of one after the first stage), from memory: the logits have
+        // made room for others.  A negative part marks the columns concerned.
         auto settle = [&](int t) __attribute__((always_inline)) {
-            if (__builtin_expect(__any(work.most > kMostAboveReference), 0)) {
+            if (__builtin_expect(!__any(work.most > kMostAboveReference), 1)) return;
 #pragma unroll
-                for (int c = 0; c < kTiles; ++c) {
-                    const int up = run.l[c] > 4.f ? __builtin_amdgcn_frexp_expf(run.l[c]) : 0;
-                    run.m[c] += static_cast<float>(up);
-                    run.l[c] = __builtin_amdgcn_ldexpf(run.l[c], -up);
-                    const float now = __builtin_amdgcn_ldexpf(work.part[c], -up);
-                    work.part[c] = now > kFarAbove ? -0.f : now;
-                }
+            for (int c = 0; c < kTiles; ++c) {
+                const bool far = work.part[c] > kFarAbove;
+                const float total = run.l[c] + (far ? 0.f : work.part[c]);
+                const int up = total > 4.f ? __builtin_amdgcn_frexp_expf(total) : 0;
+                run.m[c] += static_cast<float>(up);
+                run.l[c] = __builtin_amdgcn_ldexpf(run.l[c], -up);
+                work.part[c] = far ? -0.f : __builtin_amdgcn_ldexpf(work.part[c], -up);
+            }
+            if (__any(work.most > kFarAbove)) {
                 const int own_lane = own_lane_here();
 #pragma unroll 1
                 for (int u = t >= 2 ? -1 : 0; u <= 0; ++u) {

@@ -404,10 +404,10 @@ def test_leading_keys_in_different_lanes(gpu_device, d, H, high, low):
 
 
 # One key near 0 leads rows whose other keys lie `below` it: its exponent is rounded to half a unit of what it lies above the
-# reference, at most 16 (2^-21); with that key the reference, to 2^-25.  The scale's rounding moves the logit by 2^-25 of itself
+# reference, at most 16 or 24 (2^-21, 2^-20); with that key the reference, to 2^-25.  The scale's rounding moves the logit by 2^-25 of itself
 # (at most 4), exponential, sum, logarithm and the statistic, below 4, are good to 2^-22 each.
 @pytest.mark.parametrize("d,H", [(128, 258), (128, 96), (64, 258), (64, 120)])
-@pytest.mark.parametrize("below", [12, 40, 72, 110, 200])
+@pytest.mark.parametrize("below", [12, 20, 40, 72, 110, 200])
 def test_row_statistics_of_rows_that_one_key_leads(gpu_device, d, H, below):
     print("[case] one leading key d=%d H=%d %d below" % (d, H, below), flush=True)
     L, lead = 1024, 200
@@ -430,4 +430,4 @@ def test_row_statistics_of_rows_that_one_key_leads(gpu_device, d, H, below):
     t = 8 * K[0, :, :, :2].double().sum(-1) / math.sqrt(d)                       # (every row has the same logits)
     want = torch.logcumsumexp(t, -1)[:, lead:] / math.log(2)
     off = (got[:, lead:] - want).abs().max().item()
-    assert off <= (2.0 ** -21 if below <= 16 else 2.0 ** -25) + 2.0 ** -23 + 4 * 2.0 ** -22, off
+    assert off <= (2.0 ** -21 if below <= 12 else 2.0 ** -20 if below <= 20 else 2.0 ** -25) + 2.0 ** -23 + 4 * 2.0 ** -22, off
