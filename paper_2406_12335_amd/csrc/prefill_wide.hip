@@ -205,7 +205,8 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_wide_kernel(const bf16
     // (What an instruction adds to row and chunk are constants: its lane values are formed from two registers every time; kept, they
     // would take eight.)
     const int copy_row = kOwnRows * wave + lane / kChunks, copy_chunk = tile_slot<kChunks>(copy_row, lane % kChunks) * 16;
-    auto copy_rows = [&](const bf16_t *rows, int t, int slot) __attribute__((always_inline)) {
+    // (from_zero_tag: they may begin before the sequence)
+    auto copy_rows = [&](const bf16_t *rows, int first, int slot, auto from_zero_tag) __attribute__((always_inline)) {
         int row = copy_row, chunk = copy_chunk;
         if constexpr (kGrouped) {                                  // (from the lane every time: there these two registers are one too many)
             int own_lane = lane;
@@ -218,13 +219,15 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_wide_kernel(const bf16
 #pragma unroll
         for (int i = 0; i < kCopies; ++i) {
             // (row inside the stage: row + kCopyRows * i; the global chunk for this lane's LDS chunk is its tile_slot)
-            const unsigned voff = static_cast<unsigned>(min(t * kSlotRows + row + kCopyRows * i, len - 1)) * (D * 2) + (chunk ^ (64 * i));
+            int r = min(first + row + kCopyRows * i, len - 1);
+            if constexpr (decltype(from_zero_tag)::value) r = max(r, 0);
+            const unsigned voff = static_cast<unsigned>(r) * (D * 2) + (chunk ^ (64 * i));
             const unsigned m0v = lds_stage0 + slot * kSlotBytes + (kOwnRows * wave + kCopyRows * i) * (D * 2);
             copy_to_lds<4>(m0v, voff, rows);
         }
     };
     auto copy_stage = [&](int t, int slot) __attribute__((always_inline)) {
-        copy_rows(strm, t, slot);
+        copy_rows(strm, t * kSlotRows, slot, std::false_type{});
         if constexpr (kColsum) {
             const int r = kStage * (wave * (kSlotRows / kStage) / kWaves);
             const unsigned voff = static_cast<unsigned>(min(t * kSlotRows + r + lane, len - 1)) * 4;
@@ -235,6 +238,9 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_wide_kernel(const bf16
 
     // A job is one block of stationary rows; with grouped queries it is walked once per query head
     // (`run` and the stationary operand live on from one head to the next).
+    // The row statistics' blocks end with the sequence and begin before it: of a block with few rows all keys up to them would be
+    // walked by wavefronts of 128 columns, at the end all there are, at the start next to none.  (By 32 rows, as the stages are cut.)
+    const int shift = kColsum ? 0 : (kBlock - 1 - (len - 1) % kBlock) / kPartRows * kPartRows;
     const int n_qh = kGrouped ? __builtin_amdgcn_readfirstlane(group / splits) : 1;
     bf16x8 Bf[kTiles][kSteps] = {};
     Running run;
@@ -242,8 +248,8 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_wide_kernel(const bf16
         const int job = kGrouped ? (it >= n_qh ? 1 : 0) : it, qh = kGrouped ? it - job * n_qh : 0;
         const int blk = job == 0 ? pair : n_blocks - 1 - pair;
         if (job == 1 && blk == pair) break;            // odd count: the middle block once
-        const int base0 = blk * kBlock;
-        if (base0 >= len) continue;
+        if (blk * kBlock >= len) continue;
+        const int base0 = blk * kBlock - shift;
         const int w0 = base0 + cw * kWaveCols;         // first stationary row of this wavefront
         const int t_begin = kColsum ? base0 / kSlotRows : 0;
         const int t_end = (kColsum ? len - 1 : min(base0 + kBlock - 1, len - 1)) / kSlotRows;      // inclusive
@@ -257,7 +263,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_wide_kernel(const bf16
         auto slot_of = [&](int t) { return (t - t_begin + kBlockSlots) & (kRing - 1); };
         if (qh == 0) {
 #pragma unroll
-            for (int k = 0; k < kBlockSlots; ++k) copy_rows(stat, blk * kBlockSlots + k, k);
+            for (int k = 0; k < kBlockSlots; ++k) copy_rows(stat, base0 + kSlotRows * k, k, std::bool_constant<!kColsum>{});
         }
 #pragma unroll
         for (int k = 0; k < kFree; ++k)
@@ -612,8 +618,9 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_wide_kernel(const bf16
                     const int idx = base0 + col0 + 16 * c;
                     if constexpr (kColsum) merge_buf[0][0][col0 + 16 * c] = idx < len ? fin_l[c] : 1.f;
                     if (idx >= len) continue;
-                    if constexpr (!kColsum) lse_u[idx] = sum_log2(fin_m[c], fin_l[c]);
-                    else if (!small(fin_l[c])) store_sum(idx, fin_l[c]);
+                    if constexpr (!kColsum) {
+                        if (idx >= 0) lse_u[idx] = sum_log2(fin_m[c], fin_l[c]);
+                    } else if (!small(fin_l[c])) store_sum(idx, fin_l[c]);
                 }
             }
         }
