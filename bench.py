@@ -188,7 +188,7 @@ def measure(args, workload, steps, warmup, main_line):
         # the vendor library's bf16 GEMM (8192^3, random operands): what the matrix cores sustain here on a plain product
         ga = torch.randn(8192, 8192, device=dev).to(torch.bfloat16)
         gb = torch.randn(8192, 8192, device=dev).to(torch.bfloat16)
-        for _ in range(3):
+        for _ in range(60):                       # (until the clock has settled: the first five run at three quarters of the rate)
             gc = torch.matmul(ga, gb)
         torch.cuda.synchronize()
         c0.record()
