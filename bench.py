@@ -464,20 +464,20 @@ DEFAULT_WORKLOAD = "llama7b_stack"
 # summary named in "source", which also gives the commands.
 PROFILED_TRAFFIC_BYTES = {
     "llama7b_stack": {"source": "profiles/llama7b_stack_profile.md",
-                      "bytes_per_call": {"prefill_score": 1938501310, "decode_step": 57647823, "select_compact": 232475584,
-                                         "decode_prune_step": 71322413}},
+                      "bytes_per_call": {"prefill_score": 1942245085, "decode_step": 57648090, "select_compact": 232476172,
+                                         "decode_prune_step": 71323009}},
     "llama7b_layer": {"source": "profiles/llama7b_layer_profile.md",
-                      "bytes_per_call": {"prefill_score": 174840364, "decode_step": 18034182, "select_compact": 72825287,
-                                         "decode_prune_step": 21309039}},
+                      "bytes_per_call": {"prefill_score": 174106985, "decode_step": 18034249, "select_compact": 72825285,
+                                         "decode_prune_step": 21309111}},
     "long32k": {"source": "profiles/long32k_profile.md",
-                "bytes_per_call": {"prefill_score": 2439272591, "decode_step": 28726112, "select_compact": 116540315,
-                                   "decode_prune_step": 35557680}},
+                "bytes_per_call": {"prefill_score": 2426863723, "decode_step": 28726138, "select_compact": 116523438,
+                                   "decode_prune_step": 35557707}},
     "ragged16": {"source": "profiles/ragged16_profile.md",
-                 "bytes_per_call": {"prefill_score": 6292269957, "decode_step": 204579838, "select_compact": 830402622,
-                                    "decode_prune_step": 250655639}},
+                 "bytes_per_call": {"prefill_score": 6181109104, "decode_step": 204579857, "select_compact": 830402455,
+                                    "decode_prune_step": 250654529}},
     "tiny": {"source": "profiles/tiny_profile.md",
-             "bytes_per_call": {"prefill_score": 1979400, "decode_step": 252122, "select_compact": 594533,
-                                "decode_prune_step": 295459}},
+             "bytes_per_call": {"prefill_score": 1979752, "decode_step": 252127, "select_compact": 594535,
+                                "decode_prune_step": 295460}},
 }
 
 

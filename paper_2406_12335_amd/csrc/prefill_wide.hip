@@ -16,7 +16,7 @@
 //  * row statistics relative to a reference that the first keys set and that moves only where weights outgrow it, instead of a
 //    running maximum: an eighth fewer vector instructions.
 // Loops of MFMAs, exponentials and LDS reads alone, one box: 32 x 32 tiles, 64 columns 1233 TFLOP/s, 16 x 16 tiles, 64 columns
-// 1309, 16 x 16 tiles, 128 columns 1365.  Now: pipe busy 54 and 53 % at 1.9 GHz with counters on.  Measured, both passes, before / now:
+// 1309, 16 x 16 tiles, 128 columns 1365.  Now: pipe busy 53 and 51 % at 2.05 GHz.  Measured, both passes, before / now:
 // 32 heads x 32768 rows 7943 / 7469 us, 512 heads of 1024..8192 rows 3633 / 3470, 32 x 4096 155.7 / 148.3, 128 x 2048 176 / 175, 512 x 520
 // 124 / 117, 512 x 200 37.7 / 35.2, 256 heads of 150..1200 rows 118 / 116; column sums alone, from given row log-sum-exps, 64 K/V heads of
 // 4 query heads x 4001 rows 572 / 558.  Where it costs: 512 heads of 150..1200 rows 169 / 173.  Blocks of 512 rows in eight-wavefront
