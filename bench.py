@@ -93,7 +93,13 @@ def prompt_score_kernels(cfg, lens, window):
     """Names of the kernels one prompt-scoring call launches for this workload, by the library's word."""
     from paper_2406_12335_amd import binding
     call = binding.CALL_PREFILL_SCORE if window is None else binding.CALL_PREFILL_SCORE_WINDOW
-    route = binding.vatp_route(_params(cfg, lens, lens), call, -1 if window is None else window)
+    p = _params(cfg, lens, lens)
+    if window is None and cfg.q_per_kv <= 1:
+        # (a workspace with room for more than row statistics is one for a single pass)
+        two_passes = (cfg.batch * cfg.n_heads * p.c.cap * 4 + 255) // 256 * 256
+        if binding.vatp_workspace_bytes(None, p, call) > two_passes:
+            return "prefill_onepass_kernel<scores and value norms>"
+    route = binding.vatp_route(p, call, -1 if window is None else window)
     staged = "prefill_wide_kernel" if cfg.head_dim == 128 and window is None else "prefill_mfma_kernel"
     rowstat = staged if route & binding.ROUTE_STAGED_ROWS else "prefill_direct_kernel"
     colsum = staged if route & binding.ROUTE_STAGED_SUMS else "prefill_direct_kernel"

@@ -118,13 +118,18 @@ vatp_status vatp_validate(const vatp_params *p, int which_call);
 
 /* Bytes of device workspace call `which_call` needs for `p` (0 on invalid params).
  * `ctx` may be NULL.  The workspace must be 256-byte aligned; its contents on entry do
- * not matter and are undefined on return. */
+ * not matter and are undefined on return.
+ * For VATP_CALL_PREFILL_SCORE the size may hold room for row totals, with which vatp_prefill_score forms
+ * the logits once instead of twice (bf16, prompts of 257 and more rows that fill the chip, no grouped queries); a smaller
+ * workspace, of at least batch * n_heads * q_per_kv * cap floats (twice that with grouped queries; a multiple of 256 bytes),
+ * is accepted as well and keeps the call to two passes. */
 size_t vatp_workspace_bytes(const vatp_ctx *ctx, const vatp_params *p, int which_call);
 
 /*
  * Which kernels call `which_call` takes for `p`, for reports: the sum of the values that apply, or a negative
  * vatp_status on invalid params.  window: the call's history window, -1 without one (the decode call's attention
- * output is taken to be NULL).  Touches no device.
+ * output is taken to be NULL).  Touches no device.  A prompt: the kernels of two passes, which a call in one pass
+ * (see vatp_workspace_bytes) takes for heads whose sums leave the range that one pass holds.
  */
 enum { VATP_ROUTE_STAGED_ROWS = 1,     /* prompt: row statistics on the staged kernels, not the direct ones */
        VATP_ROUTE_STAGED_SUMS = 2,     /* prompt: column sums likewise                                      */

@@ -40,6 +40,7 @@ def sources():
 EXTRA_FLAGS = {
     "prefill_mfma.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form"],
     "prefill_wide.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form"],
+    "prefill_onepass.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "prefill_direct.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form"],
 }
 

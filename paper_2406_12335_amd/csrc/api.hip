@@ -11,6 +11,7 @@ using namespace vatp;
 struct vatp_ctx {
     int device;
     void *scratch;       // this device's copy of the static scratch array (address looked up at creation)
+    bool whole;          // a whole MI355X, no partition of one: 256 compute units
 };
 
 // Scratch memory of vatp_decode_prune_step_static, the entry point for callers that cannot allocate: a
@@ -125,6 +126,11 @@ inline bool staged_pass(const vatp_params *p, const Prepared &pr, int pass)
 {
     return p->dtype == VATP_BF16 && prefill_mfma_fills(p->head_dim, pass, pr.meta, pr.g);
 }
+// a prompt without a window and without row log-sum-exps handed in: in one pass over its logits
+inline bool one_pass_fits(const vatp_params *p, const Prepared &pr)
+{
+    return p->dtype == VATP_BF16 && prefill_onepass_fits(p->head_dim, pr.meta, pr.g);
+}
 // The fused step (without attention output and history) in one launch with a workgroup per head when each head is short enough for a
 // single workgroup to stream quickly: up to 256 KiB of K rows (1024 rows of 256 bytes) while the workgroups share no compute unit, and up
 // to 1024 rows of any size from 128 heads on.
@@ -141,6 +147,15 @@ inline bool in_one_launch(const vatp_params *p, const Geometry &g)
     const size_t row_bytes = static_cast<size_t>(p->head_dim) * (p->dtype == VATP_BF16 ? 2 : 4);
     return g.group == 1 && g.max_len <= decode_prune_one_max_rows() &&
            ((kv_units <= 256 && g.max_len * row_bytes <= (256u << 10)) || (kv_units >= 128 && g.max_len <= 1024));
+}
+
+// Workspace of the prompt passes of their own: lse2[units, cap], and as much again for partial column sums of a group, or with a window
+// partial row statistics per range of keys
+inline size_t prompt_base_bytes(const vatp_params *p, bool window)
+{
+    const size_t rows = static_cast<size_t>(p->batch) * p->n_heads * (p->q_per_kv > 1 ? p->q_per_kv : 1) * p->cap * sizeof(float);
+    if (window) return align_up(rows) + align_up(prefill_window_splits(p->cap) * rows);
+    return align_up(rows) * (p->q_per_kv > 1 ? 2 : 1);
 }
 
 inline bool misaligned(const void *ptr, size_t a) { return (reinterpret_cast<uintptr_t>(ptr) & (a - 1)) != 0; }
@@ -185,6 +200,8 @@ vatp_status vatp_create(vatp_ctx **ctx, int device)
     }
     void *ptr = nullptr;
     const hipError_t e = hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch));
+    int compute_units = 0;
+    if (hipDeviceGetAttribute(&compute_units, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) (void)hipGetLastError();
     if (prev != device) (void)hipSetDevice(prev);
     if (e != hipSuccess || !ptr) {
         (void)hipGetLastError();
@@ -194,6 +211,7 @@ vatp_status vatp_create(vatp_ctx **ctx, int device)
     if (!c) return VATP_E_DEVICE;
     c->device = device;
     c->scratch = ptr;
+    c->whole = compute_units >= 256;
     *ctx = c;
     return VATP_OK;
 }
@@ -230,11 +248,13 @@ size_t vatp_workspace_bytes(const vatp_ctx *, const vatp_params *p, int which_ca
     // everything kept in the workspace is per query head
     const size_t units = static_cast<size_t>(p->batch) * p->n_heads * (p->q_per_kv > 1 ? p->q_per_kv : 1);
     switch (which_call) {
-    case VATP_CALL_PREFILL_SCORE:           // lse2[units, cap] (+ as much again for partial column sums of a group)
-        return align_up(units * p->cap * sizeof(float)) * (p->q_per_kv > 1 ? 2 : 1);
-    case VATP_CALL_PREFILL_SCORE_WINDOW:    // ... + partial row statistics per range of keys
-        return align_up(units * p->cap * sizeof(float)) +
-               align_up(static_cast<size_t>(prefill_window_splits(p->cap)) * units * p->cap * sizeof(float));
+    case VATP_CALL_PREFILL_SCORE: {
+        Prepared pr;
+        prepare(p, which_call, nullptr, &pr);
+        return prompt_base_bytes(p, false) + (one_pass_fits(p, pr) ? prefill_onepass_workspace_bytes(p->head_dim, pr.g) : 0);
+    }
+    case VATP_CALL_PREFILL_SCORE_WINDOW:
+        return prompt_base_bytes(p, true);
     case VATP_CALL_DECODE_STEP: {           // logits[units, cap] + per-chunk softmax statistics
         const size_t chunks = (static_cast<size_t>(p->cap) + kDecodeChunk - 1) / kDecodeChunk;
         return align_up(units * p->cap * sizeof(float)) + align_up(units * chunks * sizeof(float2));
@@ -272,7 +292,7 @@ vatp_status prefill_score_impl(vatp_ctx *ctx, const vatp_params *p, const void *
     if (st != VATP_OK) return st;
     if (wrong_device(ctx)) return VATP_E_DEVICE;
     if (misaligned(Q, 16) || misaligned(K, 16) || misaligned(V, 16) || misaligned(hist, 4)) return VATP_E_SHAPE;
-    const size_t need = vatp_workspace_bytes(ctx, p, window < 0 ? VATP_CALL_PREFILL_SCORE : VATP_CALL_PREFILL_SCORE_WINDOW);
+    const size_t need = prompt_base_bytes(p, window >= 0);
     if (!ws || ws_bytes < need || misaligned(ws, kAlign)) return VATP_E_WORKSPACE;
     Prepared pr;
     prepare(p, VATP_CALL_PREFILL_SCORE, nullptr, &pr);
@@ -282,7 +302,10 @@ vatp_status prefill_score_impl(vatp_ctx *ctx, const vatp_params *p, const void *
     // what follows lse2 in the workspace: partial row statistics of a window, or room for partial column sums of a group
     float *parts = lse2 + align_up(units * pr.g.group * p->cap * sizeof(float)) / sizeof(float);
     hipError_t e = hipSuccess;
-    if (window >= 0 && staged_window(p, pr.g, window)) {
+    const bool one_pass = window < 0 && !have_lse && one_pass_fits(p, pr) && ctx->whole;
+    if (one_pass && ws_bytes >= need + prefill_onepass_workspace_bytes(p->head_dim, pr.g)) {
+        e = launch_prefill_onepass(p->head_dim, Q, K, V, S, nrm, lse2, static_cast<char *>(ws) + need, pr.meta, pr.g, stream);
+    } else if (window >= 0 && staged_window(p, pr.g, window)) {
         e = launch_prefill_mfma_window(p->head_dim, Q, K, V, S, nrm, lse2, parts, window, hist, pr.meta, pr.g, stream);
     } else {
         float *s_part = pr.g.group > 1 && window < 0 ? parts : nullptr;

@@ -1,0 +1,688 @@
+// Prompt-pass scoring in one pass over the logits (bf16, gfx950): row statistics, column sums and value norms of the causal softmax without a
+// history window, where each query head has its own keys.
+//
+// The scores S_i = sum_{j>=i} 2^t_ji / T_j, T_j = sum_{i<=j} 2^t_ji (paper Eq. 1, 2) need every row's total T_j before any of its
+// weights can be added up, so a kernel that owns rows or columns forms the logits twice.  Here a workgroup keeps 256 keys of a head in
+// registers, streams the queries past them and HOLDS the weights of two stages (96 or 128 rows) while the workgroups of the head, its gang,
+// add up the rows' totals in memory: in stage i the weights of stage i are formed, the row sums of stage i - 1 are added to the totals and
+// read back complete, and the weights of stage i - 2, divided by theirs, are added to the column sums.  One product and one
+// exponential per logit instead of two.
+//
+// What bounds it: instruction issue.  In a loop of its MFMAs, exponentials and LDS reads alone, two wavefronts to a SIMD, 96 rows take 3100 cycles
+// at d = 128 (a 16 x 16 x 32 MFMA holds up the vector unit 12 cycles, an exponential 9, any other vector instruction 3 to 4) and 2400 at d = 64;
+// with the copies, totals, norms and the barrier the stage takes 4300 to 4800 (d = 64, 128 rows: 4700), and about as long as the exchange of the
+// totals, which the stage after waits for.  (32 x 32 x 16 MFMAs save 3 % of the cycles and lower the clock from 2.0 to 1.7 GHz; the
+// other way round, keys streamed past queries, needs the same.)  Measured, kernels of two passes / this one, in turn on one card, back to back:
+// 32 heads x 4096 rows 143.5 / 126.4 us, 64 heads of 64 x 2048 64.3 / 54.4; 128 x 4096 551 / 477, 64 x 8192 1034 / 880, 64 x 2048 89 / 75,
+// 512 heads of 64 x 100..4000 389 / 344.  Errors against 64 bits (relative, root mean square): 32 x 4096 6.9e-8 / 6.5e-8, 64 x 2048 7.9e-8 / 7.3e-8,
+// 128 x 1000 7.0e-8 / 5.9e-8, 512 x 400 9.9e-8 / 8.4e-8, 32 x 8192 without sinks 6.5e-8 / 3.3e-8, 64 heads of 64 x 2048 6.4e-8 / 4.6e-8.
+//
+// A gang takes two heads of one length.  Its workgroup w owns block w of the first one's keys and walks the queries from the last down to the
+// diagonal, then block n - 1 - w of the second one's and walks from the diagonal to the last query: every workgroup has the
+// same number of stages, all are at the same rows of a head at the same time, and the pipeline runs on from one head to the next.
+//
+// Totals are sums of integers, so that the order of the additions does not show: a row has four 64-bit words for contributions of four ranges
+// of magnitude, each contribution (a float) exact in its word's unit but the smallest, and each word counts its contributions in its top
+// byte.  A row is complete when the counts add up to the workgroups that meet it; no flags, no fences.
+//
+// What the words cannot hold (totals outside 2^-13 .. 2^81 of the head's reference, sums not finite) or what loses precision (weights far above
+// a low reference, column sums that weights below 2^-126 could add to) marks the head, and the kernels of two passes, launched behind this one
+// and over at once otherwise (3.5 us for both), form it again.  So do heads whose gang did not come together: a workgroup waits kPatience
+// at most, as when kernels of other streams hold compute units that its gang needs, and from then on nobody in the launch waits.
+// Where every head is formed again the call takes as long as both: 32 heads x 4096 rows, logits of the sinks 220 bits above the others', 150 / 278 us.
+// Logits of a standard deviation of 5 nats without sinks, or rising along the prompt by 15 nats a stage, are held.
+//
+// Wavefronts 0 .. 3 take rows 0 .. 47 (63) of a stage, 4 .. 7 the others, 64 keys each, as 16 x 16 tiles: keys are the A operand, kept in registers,
+// so a lane (g = lane / 16, n = lane % 16) has row n and keys 4 g .. 4 g + 3 of a tile, and row sums and column sums are additions inside the lane.
+// Besides, the first four copy query rows, 4 and 5 see to the norms of value rows, 6 and 7 to the totals; each role has its own copy of the
+// loop (with branches instead 64 / 73 us at 64 heads of 64 x 2048).  Lane values are formed anew where they are needed: kept, they pushed the weights into scratch memory
+// (249 registers of 256 at d = 128).  The totals are not waited for by the tellers' partners on their SIMDs: priorities 2, 1 and 0 for
+// totals, norms and copies (127 / 123 us at 32 x 4096 without the middle one).
+#include "prefill_stage.h"
+
+namespace vatp {
+
+namespace {
+
+typedef unsigned long long total_t;
+
+constexpr int kKeys = 256;         // keys per workgroup
+constexpr int units_of(int head_dim) { return head_dim == 64 ? 4 : 3; }         // of 16 query rows, to a wavefront and stage
+constexpr int rows_of(int head_dim) { return 2 * 16 * units_of(head_dim); }      // query rows per stage
+constexpr int kWaves = 8;
+constexpr int kSlots = 3;          // stages of query rows in LDS
+enum { kCopier, kNormer, kTeller };        // what a wavefront sees to besides: query rows, norms of value rows, totals
+
+// kN copies of 16 bytes per lane, 1 KiB apart in memory and in LDS (the instruction's offset counts in both)
+template <int kN>
+__device__ __forceinline__ void copy_run_to_lds(unsigned to, const unsigned (&off)[kN], const void *base)
+{
+    static_assert(kN == 2 || kN == 4, "copies of a run");
+    if constexpr (kN == 2)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %3\n\tglobal_load_lds_dwordx4 %2, %3 offset:1024"
+                     ::"s"(to), "v"(off[0]), "v"(off[1]), "s"(base) : "memory");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %1, %5\n\tglobal_load_lds_dwordx4 %2, %5 offset:1024\n\t"
+                     "global_load_lds_dwordx4 %3, %5 offset:2048\n\tglobal_load_lds_dwordx4 %4, %5 offset:3072"
+                     ::"s"(to), "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(base) : "memory");
+}
+
+// A row's total is kept as integers in four words: contributions below 2^6, 2^31, 2^56 and 2^81 in units of 2^-43, 2^-18, 2^7 and 2^32,
+// each with a count of contributions in its top byte.
+constexpr int kWords = 4, kFirstTop = 6, kWordBits = 25, kFirstScale = 43;
+constexpr unsigned kTooLarge = (127u + kFirstTop + kWordBits * (kWords - 1)) << 23;      // (bits of 2^81)
+constexpr float kLeastTotal = 0x1p-13f;
+constexpr float kBelowTop = 40.f;
+// Weights far above the reference have their exponents rounded like the distance.  Where the reference is low that is coarser than the
+// logits themselves are, which are rounded like their distance from 0.
+constexpr float kLowReference = -8.f, kMostAbove = 0x1p24f;
+constexpr unsigned long long kPatience = 400000;      // ticks of 10 ns that a workgroup waits for the others
+
+__device__ __forceinline__ total_t load_total(const total_t *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+template <int D>
+__global__ __launch_bounds__(64 * kWaves, 2) void prefill_onepass_kernel(const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K,
+                                                                         const bf16_t *__restrict__ V, float *__restrict__ S,
+                                                                         float *__restrict__ nrm, float *__restrict__ lse2, total_t *__restrict__ totals,
+                                                                         unsigned *__restrict__ flags, BatchMeta meta, int n_heads,
+                                                                         int n_gangs, int cap, int cap_rows, int spread_log2, int depth,
+                                                                         float scale_log2, int norm)
+{
+    constexpr int kUnits = units_of(D), kRows = rows_of(D);
+    constexpr int kChunks = D / 8, kSteps = D / 32, kCopyRows = 64 / kChunks, kCopies = kRows / 4 / kCopyRows, kHalfRows = 16 * kUnits;
+    constexpr int kKeyCopies = kKeys / 4 / kCopyRows, kSlotBytes = kRows * D * 2;
+    __shared__ uint4 ring[kSlots][kRows * kChunks];
+    __shared__ uint4 keys[kKeys * kChunks];
+    __shared__ uint4 values[2][4][2][64];
+    __shared__ __attribute__((aligned(16))) float parts[2][kRows][4];
+    __shared__ float inv_buf[2][kRows];
+    __shared__ float2 fin[2][kKeys];
+    __shared__ float ref_buf[2];
+    __shared__ unsigned max_inv_buf;
+    __shared__ volatile unsigned gave_up;        // (whoever waited for the others in vain; from then on nobody here waits)
+
+    // ---- which gang, which of its workgroups
+    const int xcd = blockIdx.x & 7, in_xcd = blockIdx.x >> 3, spread = 1 << spread_log2;
+    const int gang = in_xcd / depth * (8 >> spread_log2) + (xcd >> spread_log2);
+    if (gang >= n_gangs) return;
+    const int n_pairs = (n_heads + 1) / 2;
+    const int seq = meta.aux[gang / n_pairs], head = 2 * (gang % n_pairs);
+    const int len = meta.len[seq];
+    const int n_blocks = (len + kKeys - 1) / kKeys, n_tiles = (len + kRows - 1) / kRows;
+    const int w = in_xcd % depth * spread + (xcd & (spread - 1));
+    if (w >= n_blocks) return;
+    const bool two = head + 1 < n_heads;
+    const size_t unit_a = static_cast<size_t>(seq) * n_heads + head;
+    const int blk_a = w, blk_b = n_blocks - 1 - w;
+    const int first_a = blk_a * kKeys / kRows, first_b = blk_b * kKeys / kRows;        // the first stage of rows that meets the block
+    const int n_a = n_tiles - first_a, n_b = two ? n_tiles - first_b : 0, n_produce = n_a + n_b;
+    const int tile_a = n_tiles - 1, tile_b = first_b - n_a;
+    auto contributors = [&](int tile) { return min(n_blocks, (tile * kRows + kRows - 1) / kKeys + 1); };
+    unsigned *const abort_word = flags - 1;
+    flags += unit_a;
+    const size_t head_rows = unit_a * cap;
+    totals += unit_a * cap_rows * kWords;
+    S += head_rows;
+    nrm += head_rows;
+    lse2 += head_rows;
+    const bf16_t *const q_rows = Q + head_rows * D, *const k_rows = K + head_rows * D, *const v_rows = V + head_rows * D;
+    const size_t head_elts = static_cast<size_t>(cap) * D;
+
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = lane >> 4, n = lane & 15;
+    const int kg = wave & 3, half = wave >> 2;                 // 64 keys of the block, 32 rows of a stage
+    const unsigned lds_ring = static_cast<unsigned>(reinterpret_cast<size_t>((lds_char *)(char *)&ring[0][0]));
+    const unsigned lds_keys = static_cast<unsigned>(reinterpret_cast<size_t>((lds_char *)(char *)&keys[0]));
+    const unsigned lds_values = static_cast<unsigned>(reinterpret_cast<size_t>((lds_char *)(char *)&values[0][0][0][0]));
+
+    auto second = [&](int i) { return i >= n_a; };
+    auto tile_of = [&](int i) { return i >= n_a ? tile_b + i : tile_a - i; };
+    auto flag = [&](int which) { __hip_atomic_store(&flags[which], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+
+    auto copy_queries = [&](int i, int slot) __attribute__((always_inline)) {
+        const int first = tile_of(i) * kRows;
+        const bf16_t *const rows = q_rows + (second(i) ? head_elts : 0) + static_cast<size_t>(first) * D;
+        const unsigned to = lds_ring + slot * kSlotBytes + kg * (kRows / 4) * (D * 2);
+        const int lane = own_lane_here(), copy_row = kg * (kRows / 4) + lane / kChunks, copy_chunk = tile_slot<kChunks>(copy_row, lane % kChunks) * 16;
+        const int last = len - 1 - first;
+        // (the chunk turns with the row: by a constant from copy to copy)
+        if (last >= kRows - 1) {
+            const unsigned off = copy_row * (D * 2) + copy_chunk;
+            constexpr int kRun = 4;
+            static_assert(kCopies == (D == 128 ? 6 : 4), "runs of copies");
+            auto turned = [&](int c) { return off ^ (tile_slot<kChunks>(kCopyRows * c, 0) * 16); };
+            if constexpr (D == 128) {
+                const unsigned run[4] = {turned(0), turned(1), turned(2), turned(3)}, rest[2] = {turned(4), turned(5)};
+                copy_run_to_lds(to, run, rows);
+                copy_run_to_lds(to + kRun * 1024, rest, rows + kRun * 512);
+            } else {
+                const unsigned run[4] = {turned(0), turned(1), turned(2), turned(3)};
+                copy_run_to_lds(to, run, rows);
+            }
+        } else {
+#pragma unroll
+            for (int c = 0; c < kCopies; ++c)
+                copy_to_lds<4>(to + c * 1024, static_cast<unsigned>(min(copy_row + kCopyRows * c, last)) * (D * 2) + (copy_chunk ^ (tile_slot<kChunks>(kCopyRows * c, 0) * 16)), rows);
+        }
+    };
+    auto copy_keys = [&](int which, int from, int count) __attribute__((always_inline)) {
+        const bf16_t *const rows = k_rows + (which ? head_elts : 0);
+        const int lane = own_lane_here(), first = (which ? blk_b : blk_a) * kKeys, own = kg * (kKeys / 4) + lane / kChunks;
+        for (int c = from; c < from + count; ++c) {
+            const int row = own + kCopyRows * c;
+            copy_to_lds<4>(lds_keys + (kg * (kKeys / 4) + kCopyRows * c) * (D * 2),
+                           static_cast<unsigned>(min(first + row, len - 1)) * (D * 2) + tile_slot<kChunks>(row, lane % kChunks) * 16, rows);
+        }
+    };
+
+    // ---- start
+    if (half == 1) copy_keys(0, 0, kKeyCopies);
+    else
+        for (int i = 0; i < 2; ++i)
+            if (i < n_produce) copy_queries(i, i);
+    if (wave < (two ? 2 : 1)) {
+        // reference of a head: the largest of 16 x 16 logits
+        const uint4 *const kr = reinterpret_cast<const uint4 *>(k_rows + wave * head_elts) + static_cast<size_t>(min(n, len - 1)) * kChunks + g;
+        const uint4 *const qr = reinterpret_cast<const uint4 *>(q_rows + wave * head_elts) + static_cast<size_t>(max((n + 1) * len / 16 - 1, 0)) * kChunks + g;
+        floatx4 x = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < kSteps; ++s) x = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(kr[4 * s]), as_bf16x8(qr[4 * s]), x, 0, 0, 0);
+        const float top = wave_max(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3]))), mean = wave_sum((x[0] + x[1]) + (x[2] + x[3])) * (1.f / 256.f);
+        const float ref = rintf(fmaxf(mean * scale_log2, fmaf(top, scale_log2, -kBelowTop)));
+        if (lane == 0) ref_buf[wave] = fabsf(ref) < 0x1p20f ? ref : 0.f;
+    } else if (wave == 2) {
+        for (int k = lane; k < 2 * kRows; k += 64) inv_buf[0][k] = 0.f;
+        if (lane == 0) {
+            max_inv_buf = 0;
+            gave_up = __hip_atomic_load(abort_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    wait_copies_then_barrier<0>();
+    const bool stopped = __builtin_amdgcn_readfirstlane(gave_up) != 0;
+    const float ref_a = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, ref_buf[0])));
+    const float ref_b = two ? __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, ref_buf[1]))) : 0.f;
+    if (stopped) {
+        if (tid < (two ? 2 : 1)) flag(tid);
+        return;
+    }
+
+    auto run = [&](auto role_tag) __attribute__((always_inline)) {
+        constexpr int kRole = decltype(role_tag)::value;
+        const int mine = wave & 1;                 // of two wavefronts of a role
+        bf16x8 Kf[4][kSteps];
+        auto load_keys = [&]() __attribute__((always_inline)) {
+            const uint4 *const rows = &keys[kg * 64 * kChunks];
+            const int lane = own_lane_here(), g = lane >> 4, n = lane & 15;
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int s = 0; s < kSteps; ++s) Kf[t][s] = as_bf16x8(rows[(16 * t + n) * kChunks + tile_slot<kChunks>(n, 4 * s + g)]);
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int s = 0; s < kSteps; ++s) asm volatile("" ::"v"(Kf[t][s]));
+        };
+
+        load_keys();
+        floatx4 p[2][kUnits][4];                   // weights: stage mod 2, 16 rows, 16 keys: key 4 g + v, row n
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+#pragma unroll
+            for (int u = 0; u < kUnits; ++u)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) p[r][u][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+        float col[16];                             // of keys 16 t + 4 g + v, at 4 t + v
+#pragma unroll
+        for (int k = 0; k < 16; ++k) col[k] = 0.f;
+        float sum_a = 0.f, sum_a_lo = 0.f, sum = 0.f, sum_lo = 0.f, max_inv = 0.f;      // (sums as two floats)
+        bool amiss = false;                        // a sum beyond what the totals hold
+        bf16x8 q[kSteps];
+        const int unit_place = (kHalfRows * half + n) * kChunks * 16 + tile_slot<kChunks>(n, g) * 16;
+        auto load_step = [&](int slot, int u, int s) __attribute__((always_inline)) {
+            int place = unit_place;
+            asm volatile("" : "+v"(place));
+            q[s] = as_bf16x8(*reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(&ring[slot][u * 16 * kChunks]) + (place ^ (64 * s))));
+        };
+        // The 16 partial sums of a lane over its rows: lane (g, n) gets that of key 16 (n / 4) + 4 g + n % 4 over all 16 lanes' rows
+        auto flush = [&]() __attribute__((always_inline)) {
+            float a[8], b[4], c[2];
+            const int n = own_lane_here() & 15;
+            const bool b3 = n & 8, b2 = n & 4, b1 = n & 2, b0 = n & 1;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const float lo = col[k], hi = col[8 + k];
+                a[k] = (b3 ? hi : lo) + dpp_move<0x128>(b3 ? lo : hi);
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) b[k] = (b2 ? a[4 + k] : a[k]) + dpp_move<kDppMirror8>(b2 ? a[k] : a[4 + k]);
+#pragma unroll
+            for (int k = 0; k < 2; ++k) c[k] = (b1 ? b[2 + k] : b[k]) + dpp_move<kDppSwapQuadHalves>(b1 ? b[k] : b[2 + k]);
+            two_float_add(sum, sum_lo, (b0 ? c[1] : c[0]) + dpp_move<kDppSwapPairs>(b0 ? c[0] : c[1]));
+#pragma unroll
+            for (int k = 0; k < 16; ++k) col[k] = 0.f;
+        };
+        // ---- totals: a wavefront sees to 48 rows of a stage
+        auto total_at = [&](int i, int told) { return totals + (second(i) ? kWords * static_cast<size_t>(cap_rows) : 0) + kWords * (tile_of(i) * kRows + told); };
+        auto load_parts = [&](int i) { return *reinterpret_cast<const float4 *>(&parts[i & 1][min(kHalfRows * mine + own_lane_here(), kRows - 1)][0]); };
+        // Adds what the workgroup's keys contribute to the totals of stage i's rows: the four column groups' sums x
+        auto post = [&](int i, const float4 &x) __attribute__((always_inline)) {
+            const int lane = own_lane_here(), told = kHalfRows * mine + lane, tile = tile_of(i), row = tile * kRows + told;
+            unsigned v = __float_as_uint((x.x + x.y) + (x.z + x.w));
+            total_t *const at = total_at(i, told);
+            const bool own = lane < kHalfRows && row < len;
+            if (contributors(tile) == 1) {
+                if (own) __hip_atomic_store(at, (1ull << 63) | v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            } else {
+                amiss |= own && v >= kTooLarge;              // (by its bits: a NaN too)
+                const float some = __uint_as_float(min(v, kTooLarge - 1));
+                const int exponent = __builtin_amdgcn_frexp_expf(some);
+                int k = 0;
+#pragma unroll
+                for (int j = 0; j < kWords - 1; ++j) k += exponent > kFirstTop + kWordBits * j;
+                const float whole = rintf(__builtin_amdgcn_ldexpf(some, kFirstScale - kWordBits * k));
+                const float top = truncf(whole * 0x1p-32f);
+                const total_t word = (static_cast<total_t>((1u << 24) + static_cast<unsigned>(top)) << 32) | static_cast<unsigned>(fmaf(top, -0x1p32f, whole));
+                if (own) __hip_atomic_fetch_add(at + k, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        };
+        struct Total { uint4 low, high; };
+        bool wide = false;                         // there have been contributions to the upper words
+        auto two_words = [](const total_t *at) {
+            const total_t w0 = load_total(at), w1 = load_total(at + 1);
+            return make_uint4(static_cast<unsigned>(w0), static_cast<unsigned>(w0 >> 32), static_cast<unsigned>(w1), static_cast<unsigned>(w1 >> 32));
+        };
+        // (lanes past the wavefront's rows look at its last one)
+        auto load_totals = [&](int i, bool all) __attribute__((always_inline)) {
+            const total_t *const at = total_at(i, kHalfRows * mine + min(own_lane_here(), kHalfRows - 1));
+            Total x = {two_words(at), make_uint4(0, 0, 0, 0)};
+            if (all) x.high = two_words(at + 2);
+            return x;
+        };
+        auto finish_poll = [&](int i, Total x) __attribute__((always_inline)) {
+            const int told = kHalfRows * mine + min(own_lane_here(), kHalfRows - 1), tile = tile_of(i), row = tile * kRows + told, want = contributors(tile);
+            auto arrived = [&]() {
+                const unsigned count = (x.low.y >> 24) + (x.low.w >> 24) + (x.high.y >> 24) + (x.high.w >> 24);
+                return row >= len || static_cast<int>(count) == (want == 1 ? 128 : want);
+            };
+            if (!__all(arrived())) {
+                const unsigned long long since = __builtin_amdgcn_s_memrealtime();
+                while (!gave_up) {
+                    __builtin_amdgcn_s_sleep(1);
+                    x = load_totals(i, true);
+                    if (__all(arrived())) break;
+                    if (__builtin_amdgcn_s_memrealtime() - since > kPatience ||
+                        __hip_atomic_load(abort_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
+                        const int lane = own_lane_here();
+                        if (lane == 0) {
+                            __hip_atomic_store(abort_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            gave_up = 1;
+                        }
+                        if (lane < (two ? 2 : 1)) flag(lane);
+                        break;
+                    }
+                }
+                wide |= __any((x.high.y | x.high.w) != 0);
+            }
+            float inv = 0.f;
+            if (row < len) {
+                float total = __uint_as_float(x.low.x), least = 0x1p-100f;
+                if (want > 1) {
+                    auto whole = [](unsigned lo, unsigned hi) { return __builtin_fma(static_cast<double>(hi & 0xffffffu), 0x1p32, static_cast<double>(lo)); };
+                    constexpr double kStep = 1u << kWordBits;
+                    double sum = __builtin_fma(whole(x.low.z, x.low.w), kStep, whole(x.low.x, x.low.y));
+                    if (wide) sum = __builtin_fma(__builtin_fma(whole(x.high.z, x.high.w), kStep, whole(x.high.x, x.high.y)), kStep * kStep, sum);
+                    total = static_cast<float>(__builtin_ldexp(sum, -kFirstScale));
+                    least = kLeastTotal;
+                }
+                const float ref = second(i) ? ref_b : ref_a, most = ref < kLowReference ? kMostAbove : 0x1p100f;
+                amiss |= __float_as_uint(total) - __float_as_uint(least) >= __float_as_uint(most) - __float_as_uint(least);
+                if ((second(i) ? blk_b : blk_a) == 0) lse2[(second(i) ? cap : 0) + row] = sum_log2(ref, total);
+                inv = __builtin_amdgcn_rcpf(total);
+                inv = fmaf(fmaf(-total, inv, 1.f), inv, inv);
+                max_inv = fmaxf(max_inv, inv);
+            }
+            inv_buf[i & 1][told] = inv;
+        };
+        // ---- value rows, 4 kCopyRows a stage by two wavefronts, through LDS: copied in stage i, taken in stage i + 3
+        constexpr int kNormStages = 2 * kKeys / (4 * kCopyRows);
+        auto value_row = [&](int i, int c) { return (4 * i + 2 * mine + c) * kCopyRows; };
+        auto copy_values = [&](int i) __attribute__((always_inline)) {
+            const int lane = own_lane_here();
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const int r = value_row(i, c), other = r / kKeys;
+                const unsigned row = min((other ? blk_b : blk_a) * kKeys + r % kKeys + lane / kChunks, len - 1);
+                copy_to_lds<4>(lds_values + ((mine * 4 + (i & 3)) * 2 + c) * 1024, row * (D * 2) + lane % kChunks * 16,
+                               v_rows + (other && two ? head_elts : 0));
+            }
+        };
+        auto take_values = [&](int i) __attribute__((always_inline)) {
+            auto take = [&](auto kind_tag) __attribute__((always_inline)) {
+                const int lane = own_lane_here();
+                const uint4 raw[2] = {values[mine][i & 3][0][lane], values[mine][i & 3][1][lane]};
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    const int r = value_row(i, c), other = r / kKeys, row = (other ? blk_b : blk_a) * kKeys + r % kKeys + lane / kChunks;
+                    const float value = row_norm<bf16_t, kChunks>(decltype(kind_tag)::value, raw[c]);
+                    if (lane % kChunks == 0 && row < len && (two || !other)) nrm[(other ? cap : 0) + row] = value;
+                }
+            };
+            switch (norm) {
+            case VATP_NORM_L1: take(std::integral_constant<int, VATP_NORM_L1>{}); break;
+            case VATP_NORM_L2: take(std::integral_constant<int, VATP_NORM_L2>{}); break;
+            case VATP_NORM_LINF: take(std::integral_constant<int, VATP_NORM_LINF>{}); break;
+            default: take(std::integral_constant<int, VATP_NORM_NONE>{}); break;
+            }
+        };
+
+        // ---- stages
+#pragma unroll
+        for (int s = 0; s < kSteps; ++s) load_step(0, 0, s);
+        // (the first half's wavefronts are the older ones of their SIMDs and would go first all the time; the others wait for the tellers)
+        if (kRole != kCopier) __builtin_amdgcn_s_setprio(kRole == kTeller ? 2 : 1);
+        int slot = 0;                              // i mod kSlots
+        auto stage = [&](auto ring_tag, int i) __attribute__((always_inline)) {
+            constexpr int R = decltype(ring_tag)::value;
+            if (kRole == kCopier || i == n_a) wait_copies_then_barrier<0>(); else lds_barrier();
+            const float *const inv_at = &inv_buf[R][kHalfRows * half + (own_lane_here() & 15)];
+            const float inv[4] = {inv_at[0], inv_at[16], inv_at[32], inv_at[kUnits == 4 ? 48 : 0]};
+            if (kRole == kTeller && i >= 1 && i <= n_produce) post(i - 1, load_parts(i - 1));
+            const int next_slot = slot == kSlots - 1 ? 0 : slot + 1;
+            if (kRole == kCopier && i + 2 < n_produce) copy_queries(i + 2, next_slot == kSlots - 1 ? 0 : next_slot + 1);
+            // (the second head's keys, a few rows a stage: together they would hold up the query rows)
+            if (kRole != kCopier && two) {
+                constexpr int kKeyStages = 8, kPer = kKeyCopies / kKeyStages;
+                if (n_a < kKeyStages + 1) {
+                    if (i == 0) copy_keys(1, 0, kKeyCopies);
+                } else if (i < kKeyStages) {
+                    copy_keys(1, kPer * i, kPer);
+                }
+            }
+            if (kRole == kNormer && i < kNormStages) copy_values(i);
+            if (i - 2 == n_a) {
+                flush();
+                sum_a = sum;
+                sum_a_lo = sum_lo;
+                sum = sum_lo = 0.f;
+            } else if (R == 0 && (i & 6) == 0) {
+                flush();
+            }
+            auto consume = [&](auto pair_tag, auto m_tag) __attribute__((always_inline)) {
+                constexpr int pr = decltype(pair_tag)::value, m = decltype(m_tag)::value, u = pr / 2, t = 2 * (pr % 2) + m / 4, v = m % 4;
+                col[4 * t + v] = fmaf(p[R][u][t][v], inv[u], col[4 * t + v]);
+                asm volatile("" : "+v"(col[4 * t + v]));
+            };
+            if (i == n_a) load_keys();
+            const float ref = second(i) ? ref_b : ref_a;
+            float part[kUnits];
+            static_for<8>([&](auto m) __attribute__((always_inline)) { consume(std::integral_constant<int, 0>{}, m); });
+            // (a weight joins its row's sum one step after it is formed)
+            auto weight = [&](auto pair_tag, auto m_tag) __attribute__((always_inline)) {
+                constexpr int pr = decltype(pair_tag)::value, m = decltype(m_tag)::value, u = pr / 2, k = 8 * (pr % 2) + m, t = k / 4, v = k % 4;
+                float x = fast_exp2(fmaf(p[R][u][t][v], scale_log2, -ref));
+                asm volatile("" : "+v"(x));
+                p[R][u][t][v] = x;
+                if constexpr (k >= 2) {
+                    if constexpr (k == 2) part[u] = p[R][u][0][0] + p[R][u][0][1];
+                    else part[u] += p[R][u][(k - 1) / 4][(k - 1) % 4];
+                    asm volatile("" : "+v"(part[u]));
+                }
+            };
+            Total held;
+            constexpr int kPairs = 2 * kUnits;
+            static_for<kPairs>([&](auto pair_tag) __attribute__((always_inline)) {
+                constexpr int pr = decltype(pair_tag)::value, u = pr / 2;
+                static_for<2 * kSteps>([&](auto m_tag) __attribute__((always_inline)) {
+                    constexpr int m = decltype(m_tag)::value, s = m / 2, t = 2 * (pr % 2) + m % 2, kPer = 8 / (2 * kSteps);
+                    if constexpr (s == 0) p[R][u][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+                    p[R][u][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(Kf[t][s], q[s], p[R][u][t], 0, 0, 0);
+                    // the operand's last use: the next unit's takes its place
+                    if constexpr (pr % 2 == 1 && m % 2 == 1) load_step(u == kUnits - 1 ? next_slot : slot, (u + 1) % kUnits, s);
+                    static_for<kPer>([&](auto e) __attribute__((always_inline)) {
+                        constexpr int k = kPer * m + decltype(e)::value;
+                        if constexpr (pr + 1 < kPairs) consume(std::integral_constant<int, pr + 1>{}, std::integral_constant<int, k>{});
+                        if constexpr (pr > 0) weight(std::integral_constant<int, pr - 1>{}, std::integral_constant<int, k>{});
+                    });
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+                if constexpr (kRole == kTeller && pr == 3) held = load_totals(max(i - 1, 0), wide);
+                if constexpr (kRole == kNormer && pr == 2) {
+                    if (i >= 3 && i < kNormStages + 3) {
+                        if (i < kNormStages) asm volatile("s_waitcnt vmcnt(6)" ::: "memory"); else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                        take_values(i - 3);
+                    }
+                }
+            });
+            static_for<8>([&](auto m) __attribute__((always_inline)) { weight(std::integral_constant<int, kPairs - 1>{}, m); });
+#pragma unroll
+            for (int u = 0; u < kUnits; ++u) part[u] += p[R][u][3][3];
+            // across the diagonal: what lies above it is taken out again
+            const int ahead0 = tile_of(i) * kRows + kHalfRows * half - ((second(i) ? blk_b : blk_a) * kKeys + 64 * kg);
+            if (ahead0 < 63) {
+                const int lane = own_lane_here(), g = lane >> 4, n = lane & 15;
+                // (a tile of 16 x 16 lies below, on or above it)
+#pragma unroll
+                for (int u = 0; u < kUnits; ++u) {
+                    const int on = (ahead0 >> 4) + u;                       // the tile that it crosses
+                    if (on > 3) continue;
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        if (t > on) p[R][u][t] = floatx4{0.f, 0.f, 0.f, 0.f};
+                        if (t == on) {
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) p[R][u][t][v] = n >= 4 * g + v ? p[R][u][t][v] : 0.f;
+                        }
+                    }
+                    part[u] = 0.f;
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) part[u] += (p[R][u][t][0] + p[R][u][t][1]) + (p[R][u][t][2] + p[R][u][t][3]);
+                }
+            }
+            // the rows' sums over the lane groups (of units 0 and 1 in groups 0, 1 and 2, 3; of units 2 and 3 alike)
+            auto across = [](float x, float y) {
+                const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+                const unsigned z = __float_as_uint(__uint_as_float(h[0]) + __uint_as_float(h[1]));
+                const auto r = __builtin_amdgcn_permlane16_swap(z, z, false, false);
+                return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+            };
+            const float low = across(part[0], part[1]), high = across(part[2], part[kUnits - 1]);
+            const int lane = own_lane_here(), g = lane >> 4, n = lane & 15, u = (g >> 1) + 2 * (g & 1);
+            if (u < kUnits) parts[R][kHalfRows * half + 16 * u + n][kg] = g & 1 ? high : low;
+            if (kRole == kTeller && i >= 1 && i <= n_produce) finish_poll(i - 1, held);
+            slot = next_slot;
+        };
+        // (whole rounds of two: a stage too many works on whatever is there, and nobody takes its weights)
+        int n_run = 0;
+        for (; n_run < n_produce; n_run += 2) {
+            stage(std::integral_constant<int, 0>{}, n_run);
+            stage(std::integral_constant<int, 1>{}, n_run + 1);
+        }
+        // ---- the last stages' weights
+        lds_barrier();
+        if (kRole == kTeller && n_run == n_produce) {
+            post(n_produce - 1, load_parts(n_produce - 1));
+            finish_poll(n_produce - 1, load_totals(n_produce - 1, true));
+        }
+        if (kRole == kNormer) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            for (int i = max(n_run - 3, 0); i < min(n_run, kNormStages); ++i) take_values(i);
+        }
+        lds_barrier();
+        static_for<2>([&](auto k_tag) __attribute__((always_inline)) {
+            constexpr int R = decltype(k_tag)::value;
+            const int i = n_run - 2 + R;
+            const float *const inv_at = &inv_buf[R][kHalfRows * half + (own_lane_here() & 15)];
+            const float inv[4] = {inv_at[0], inv_at[16], inv_at[32], inv_at[kUnits == 4 ? 48 : 0]};
+            if (i == n_a && two) {
+                flush();
+                sum_a = sum;
+                sum_a_lo = sum_lo;
+                sum = sum_lo = 0.f;
+            }
+            if (i < n_produce) {
+#pragma unroll
+                for (int u = 0; u < kUnits; ++u)
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) col[4 * t + v] = fmaf(p[R][u][t][v], inv[u], col[4 * t + v]);
+            }
+        });
+
+        // ---- column sums: the two halves of every stage's rows
+        flush();
+        const int lane = own_lane_here(), g = lane >> 4, n = lane & 15;
+        const int key = 64 * kg + 16 * (n >> 2) + 4 * g + (n & 3);
+        if (kRole == kTeller) {
+            const float most = wave_max(max_inv);
+            if (lane == 0) atomicMax(&max_inv_buf, __float_as_uint(most));
+            if (__any(amiss) && lane < (two ? 2 : 1)) flag(lane);
+        }
+        if (half == 1) {
+            fin[0][key] = make_float2(two ? sum_a : sum, two ? sum_a_lo : sum_lo);
+            fin[1][key] = make_float2(sum, sum_lo);
+        }
+        lds_barrier();
+        if (kRole == kCopier) {
+            // (weights below 2^-126 of the reference are lost)
+            const float least = static_cast<float>(len) * 0x1p-100f * __uint_as_float(max_inv_buf);
+            auto store = [&](int which, float hi, float lo) {
+                const int idx = (which ? blk_b : blk_a) * kKeys + key;
+                const float2 rest = fin[which][key];
+                two_float_add(hi, lo, rest.x);
+                const float s = hi + (lo + rest.y);
+                if (idx < len) {
+                    S[(which ? cap : 0) + idx] = s;
+                    if (!(s >= least)) flag(which);
+                }
+            };
+            store(0, two ? sum_a : sum, two ? sum_a_lo : sum_lo);
+            if (two) store(1, sum, sum_lo);
+        } else {
+            // value rows that the stages were too few for
+            constexpr int kLoads = 4;
+            for (int r = min(n_run, kNormStages) * 4 * kCopyRows + kg * kLoads * kCopyRows; r < 2 * kKeys; r += 4 * kLoads * kCopyRows) {
+                const int other = r / kKeys, row0 = (other ? blk_b : blk_a) * kKeys + r % kKeys;
+                if (other && !two) break;
+                const uint4 *const rows = reinterpret_cast<const uint4 *>(v_rows + (other ? head_elts : 0));
+                float *const to = nrm + (other ? cap : 0);
+                switch (norm) {
+                case VATP_NORM_L1: value_norms<D, VATP_NORM_L1, kLoads>(rows, to, row0, len, lane); break;
+                case VATP_NORM_L2: value_norms<D, VATP_NORM_L2, kLoads>(rows, to, row0, len, lane); break;
+                case VATP_NORM_LINF: value_norms<D, VATP_NORM_LINF, kLoads>(rows, to, row0, len, lane); break;
+                default: value_norms<D, VATP_NORM_NONE, kLoads>(rows, to, row0, len, lane); break;
+                }
+            }
+        }
+    };
+    if (half == 0) run(std::integral_constant<int, kCopier>{});
+    else if (wave < 6) run(std::integral_constant<int, kNormer>{});
+    else run(std::integral_constant<int, kTeller>{});
+}
+
+// Totals, flags and the abort word start from 0
+__global__ __launch_bounds__(256) void clear_totals_kernel(uint4 *__restrict__ totals, unsigned *__restrict__ flags, BatchMeta meta, int n_heads, int cap_rows,
+                                                           int stage_rows)
+{
+    const int unit = blockIdx.y, rows = (meta.len[unit / n_heads] + stage_rows - 1) / stage_rows * stage_rows;
+    if (blockIdx.x == 0 && threadIdx.x == 0) flags[unit] = 0;
+    if (blockIdx.x == 0 && unit == 0 && threadIdx.x == 1) flags[-1] = 0;
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < rows * (kWords / 2); i += gridDim.x * 256) totals[static_cast<size_t>(unit) * cap_rows * (kWords / 2) + i] = make_uint4(0, 0, 0, 0);
+}
+
+inline size_t align_256(size_t x) { return (x + 255) / 256 * 256; }
+
+}  // namespace
+
+size_t prefill_onepass_workspace_bytes(int head_dim, const Geometry &g)
+{
+    const int kRows = rows_of(head_dim);
+    const size_t units = static_cast<size_t>(g.batch) * g.n_heads, cap_rows = (static_cast<size_t>(g.cap) + kRows - 1) / kRows * kRows;
+    return align_256(units * cap_rows * kWords * sizeof(total_t)) + align_256((units + 1) * sizeof(unsigned));
+}
+
+namespace {
+
+struct Layout { int n_blocks, gangs, spread_log2, depth, rows; };
+
+// How the gangs lie on the 8 XCDs, to which workgroups go round-robin: 2^spread_log2 of them to a gang, `depth` workgroups of it on each,
+// `rows` gangs one after the other.  As few XCDs as keep the fullest one as empty as can be, so that a gang's query rows pass
+// through few L2s; 16 workgroups of a gang on one of its 32 compute units at most.
+Layout layout_of(const Geometry &g)
+{
+    Layout l{(g.max_len + kKeys - 1) / kKeys, g.batch * ((g.n_heads + 1) / 2), 0, 0, 0};
+    auto depth = [&](int log2) { return (l.n_blocks + (1 << log2) - 1) >> log2; };
+    auto rows = [&](int log2) { return (l.gangs + (8 >> log2) - 1) / (8 >> log2); };
+    while (l.spread_log2 < 3 && depth(l.spread_log2) > 16) ++l.spread_log2;
+    for (int log2 = l.spread_log2 + 1; log2 <= 3; ++log2)
+        if (depth(log2) * rows(log2) < depth(l.spread_log2) * rows(l.spread_log2)) l.spread_log2 = log2;
+    l.depth = depth(l.spread_log2);
+    l.rows = rows(l.spread_log2);
+    return l;
+}
+
+}  // namespace
+
+// Where one pass wins.  A workgroup has a compute unit to itself and begins and ends with about 10 us of latency, which the kernels of two
+// passes share out better; so the chip has to be filled, and filled evenly.  Measured back to back for a third of a second, two passes / one,
+// us (workgroups in brackets):
+//   one round, d = 128  16 x 4096 (128) 104 / 111, 18 x 4096 (144) 121 / 117, 24 x 4096 (192) 138 / 117, 32 x 4096 (256) 147 / 120; 32 x 2048 (128)
+//                       61 / 68, 40 x 2048 (160) 77 / 73, 64 x 2048 (256) 89 / 75; 160 x 512 (160) 39 / 42, 224 x 512 (224) 51 / 45
+//   d = 64              40 x 2048 (160) 53 / 55, 64 x 2048 (256) 64 / 55; 192 x 512 (192) 27 / 29, 256 x 512 (256) 37 / 32
+//   more, d = 128       44 x 3000 (264) 159 / 159, 180 x 700 (270) 74 / 83, 320 x 512 (320) 70 / 78, 352 x 700 (352) 120 / 121, 64 x 4096 (512) 279 / 230,
+//                       64 x 8192 1034 / 880, 256 x 2048 324 / 300, 512 x 1024 225 / 219, 768 x 512 123 / 127
+//   d = 64              40 x 4096 (320) 146 / 162, 112 x 2048 (448) 113 / 100, 256 x 2048 209 / 194, 64 x 8192 679 / 650
+//   gangs that do not divide an XCD's 32 compute units: 128 x 3000 (12 to a gang) 313 / 368, 32 x 12000 (47) 1049 / 1283
+//   64 and more to a gang, whose additions to one total hold each other up: 32 x 16384 1951 / 2056, 32 x 32768 7590 / 10090
+//   unequal lengths     512 heads of 100..4000 (d = 64) 389 / 344, 256 x 500..4000 503 / 483, but 256 x 1024..8192 3349 / 3441
+bool prefill_onepass_fits(int head_dim, const BatchMeta &meta, const Geometry &g)
+{
+    // (a last odd head has a gang to itself, idle half the time)
+    if (g.max_len <= kKeys || g.group > 1 || (g.n_heads % 2 != 0 && g.n_heads < 5)) return false;
+    const Layout l = layout_of(g);
+    const int start = 32768 / g.max_len;        // what beginning and end cost, more the shorter the sequences are
+    double wgs = 0;                    // workgroups, by the time they take of the longest
+    bool ragged = false;
+    for (int b = 0; b < g.batch; ++b) {
+        wgs += 0.5 * g.n_heads * ((meta.len[b] + kKeys - 1) / kKeys) * meta.len[b] / g.max_len;
+        ragged |= meta.len[b] != g.max_len;
+    }
+    if (l.depth * l.rows <= 32) {
+        const bool many = l.n_blocks > (head_dim == 64 ? 48 : 32);
+        return l.n_blocks <= 64 && wgs >= (head_dim == 64 ? 176 : 128) + start && !(many && prefill_mfma_fills(head_dim, kPassRowstat, meta, g));
+    }
+    const int slots = 32 << l.spread_log2;
+    if (l.n_blocks > 32 || (!ragged && slots / l.n_blocks * l.n_blocks * 8 < slots * 7)) return false;
+    if (ragged && head_dim == 128 && g.max_len > 4096) return false;
+    if (l.depth * l.rows <= 64 && !ragged) return wgs >= (head_dim == 64 ? 368 + start : 304 + start * 3 / 2);
+    return wgs >= 512 && g.max_len >= (head_dim == 64 ? 512 : 1024);
+}
+
+hipError_t launch_prefill_onepass(int head_dim, const void *Q, const void *K, const void *V, float *S, float *nrm, float *lse2, void *ws, const BatchMeta &meta,
+                                  const Geometry &g, hipStream_t st)
+{
+    if (g.max_len <= 0) return hipSuccess;
+    const int kRows = rows_of(head_dim), units = g.batch * g.n_heads, cap_rows = (g.cap + kRows - 1) / kRows * kRows;
+    total_t *const totals = static_cast<total_t *>(ws);
+    unsigned *const flags = reinterpret_cast<unsigned *>(static_cast<char *>(ws) + align_256(static_cast<size_t>(units) * cap_rows * kWords * sizeof(total_t))) + 1;
+    hipLaunchKernelGGL(clear_totals_kernel, dim3((g.max_len + 511) / 512, units), dim3(256), 0, st, reinterpret_cast<uint4 *>(totals), flags, meta, g.n_heads, cap_rows,
+                       kRows);
+    BatchMeta order = meta;
+    for (int b = 0; b < g.batch; ++b) {
+        int at = b;
+        for (; at > 0 && meta.len[order.aux[at - 1]] < meta.len[b]; --at) order.aux[at] = order.aux[at - 1];
+        order.aux[at] = b;
+    }
+    const Layout l = layout_of(g);
+    const dim3 grid(8u * l.depth * l.rows);
+    const bf16_t *q = static_cast<const bf16_t *>(Q), *k = static_cast<const bf16_t *>(K), *v = static_cast<const bf16_t *>(V);
+    if (head_dim == 64)
+        hipLaunchKernelGGL((prefill_onepass_kernel<64>), grid, dim3(64 * kWaves), 0, st, q, k, v, S, nrm, lse2, totals, flags, order, g.n_heads, l.gangs, g.cap,
+                           cap_rows, l.spread_log2, l.depth, g.scale_log2, g.norm);
+    else
+        hipLaunchKernelGGL((prefill_onepass_kernel<128>), grid, dim3(64 * kWaves), 0, st, q, k, v, S, nrm, lse2, totals, flags, order, g.n_heads, l.gangs, g.cap,
+                           cap_rows, l.spread_log2, l.depth, g.scale_log2, g.norm);
+    if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    return launch_prefill_mfma(head_dim, Q, K, V, S, nrm, lse2, nullptr, kPassRowstat | kPassColsum, meta, g, st, flags);
+}
+
+}  // namespace vatp

@@ -1,6 +1,9 @@
 // What the staged prompt kernels share: the ring of LDS stages that the streamed rows pass through, and the norms of the value rows.
 #pragma once
 
+#include <type_traits>
+#include <utility>
+
 #include "vatp_device.h"
 
 namespace vatp {
@@ -27,6 +30,25 @@ struct Rows {
     static constexpr int kCopies = 16 / kCopyRows;      // copy instructions per wavefront and stage
     static constexpr int kPieces = 16 / (2 * kSteps);   // sixteenths of the pending pair's work after every MFMA
 };
+
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
+
+// body(integral_constant 0), ..., body(integral_constant kN - 1)
+template <int... kI, typename F>
+__device__ __forceinline__ void static_for(std::integer_sequence<int, kI...>, F &&body)
+{
+    (body(std::integral_constant<int, kI>{}), ...);
+}
+template <int kN, typename F>
+__device__ __forceinline__ void static_for(F &&body) { static_for(std::make_integer_sequence<int, kN>{}, body); }
+
+// The lane's number formed here: what is derived from it takes no register of the loops before
+__device__ __forceinline__ int own_lane_here()
+{
+    unsigned ones = ~0u;
+    asm volatile("" : "+s"(ones));
+    return static_cast<int>(__builtin_amdgcn_mbcnt_hi(ones, __builtin_amdgcn_mbcnt_lo(ones, 0)));
+}
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 

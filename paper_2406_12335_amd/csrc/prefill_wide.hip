@@ -42,9 +42,6 @@
 //
 // The contraction index may be permuted freely as long as both operands agree: lane group g takes the 16-byte chunk 4 s + g of a row
 // for MFMA step s.
-#include <type_traits>
-#include <utility>
-
 #include "prefill_stage.h"
 
 namespace vatp {
@@ -55,31 +52,12 @@ constexpr int kWaveCols = 128;     // stationary rows per wavefront
 constexpr int kTiles = kWaveCols / 16;
 constexpr int kPartRows = 32;      // streamed rows of a slot per wavefront
 
-typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
-
-// body(integral_constant 0), ..., body(integral_constant kN - 1)
-template <int... kI, typename F>
-__device__ __forceinline__ void static_for(std::integer_sequence<int, kI...>, F &&body)
-{
-    (body(std::integral_constant<int, kI>{}), ...);
-}
-template <int kN, typename F>
-__device__ __forceinline__ void static_for(F &&body) { static_for(std::make_integer_sequence<int, kN>{}, body); }
-
 struct Unit {                      // logits of 16 streamed rows by 128 columns: tile c, row 4 g + v
     floatx4 tile[kTiles];
 };
 
 // Per column tile of a lane.  Column sums: col.  Row statistics: the sum l of 2^(t - m).
 struct Running { float m[kTiles], l[kTiles], col[kTiles]; };
-
-// The lane's number formed here: what is derived from it takes no register of the loops before
-__device__ __forceinline__ int own_lane_here()
-{
-    unsigned ones = ~0u;
-    asm volatile("" : "+s"(ones));
-    return static_cast<int>(__builtin_amdgcn_mbcnt_hi(ones, __builtin_amdgcn_mbcnt_lo(ones, 0)));
-}
 
 // Maximum over the four lane groups, which hold the same columns
 __device__ __forceinline__ float across_groups_max(float x)
@@ -161,7 +139,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_wide_kernel(const bf16
                                                                         float *__restrict__ S, BatchMeta meta, int n_heads,
                                                                         int n_units, int cap, int n_blocks, float scale_log2,
                                                                         const bf16_t *__restrict__ V, float *__restrict__ nrm,
-                                                                        int norm, int group, int splits)
+                                                                        int norm, int group, int splits, const unsigned *__restrict__ only)
 {
     static_assert(!kGrouped || kColsum, "only the column sums loop over a group's query heads");
     constexpr int D = 128, kChunks = D / 8, kSteps = D / 32, kSlots = kTiles * kSteps;
@@ -183,6 +161,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_wide_kernel(const bf16
     // (grouped column sums on a small grid: `splits` workgroups share a K/V head; n_units then counts K/V heads x splits)
     const int unit_i = kGrouped ? __builtin_amdgcn_readfirstlane(slot_i / splits) : slot_i;
     const int split = kGrouped ? slot_i - unit_i * splits : 0;
+    if (only != nullptr && only[unit_i] == 0) return;
     const int len = meta.len[unit_i / n_heads];
     const size_t unit = static_cast<size_t>(unit_i);
     // query head u belongs to K/V head u / group; the row statistics have one unit per query head, the column sums one per K/V head
@@ -649,19 +628,20 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_wide_kernel(const bf16
 }
 
 template <int kWaves>
-void launch_rowstat(const bf16_t *q, const bf16_t *k, float *lse2, const BatchMeta &meta, const Geometry &g, hipStream_t st)
+void launch_rowstat(const bf16_t *q, const bf16_t *k, float *lse2, const BatchMeta &meta, const Geometry &g,
+                    const unsigned *only, hipStream_t st)
 {
     const int units = g.batch * g.n_heads * g.group, n_blocks = (g.max_len + kBlockCols - 1) / kBlockCols;
     hipLaunchKernelGGL((prefill_wide_kernel<false, kWaves, false>), dim3(8u * block_pairs(g) * ((units + 7) / 8)), dim3(64 * kWaves), 0, st, q, k,
-                       lse2, nullptr, meta, g.n_heads * g.group, units, g.cap, n_blocks, g.scale_log2, nullptr, nullptr, 0, g.group, 1);
+                       lse2, nullptr, meta, g.n_heads * g.group, units, g.cap, n_blocks, g.scale_log2, nullptr, nullptr, 0, g.group, 1, only);
 }
 template <int kWaves, bool kGrouped>
 void launch_colsum(const bf16_t *q, const bf16_t *k, const bf16_t *v, float *dst, float *nrm, float *lse2, int splits,
-                   const BatchMeta &meta, const Geometry &g, hipStream_t st)
+                   const BatchMeta &meta, const Geometry &g, const unsigned *only, hipStream_t st)
 {
     const int slots = g.batch * g.n_heads * splits, n_blocks = (g.max_len + kBlockCols - 1) / kBlockCols;
     hipLaunchKernelGGL((prefill_wide_kernel<true, kWaves, kGrouped>), dim3(8u * block_pairs(g) * ((slots + 7) / 8)), dim3(64 * kWaves), 0, st, q, k,
-                       lse2, dst, meta, g.n_heads, slots, g.cap, n_blocks, g.scale_log2, v, nrm, g.norm, g.group, splits);
+                       lse2, dst, meta, g.n_heads, slots, g.cap, n_blocks, g.scale_log2, v, nrm, g.norm, g.group, splits, only);
 }
 
 }  // namespace
@@ -669,25 +649,25 @@ void launch_colsum(const bf16_t *q, const bf16_t *k, const bf16_t *v, float *dst
 // Two wavefronts per SIMD either way: two 4-wavefront workgroups per compute unit when the grid is large enough to keep pairs of
 // them resident, else 8-wavefront workgroups.  One unit per query head in the row statistics, one per K/V head in the column sums.
 hipError_t launch_prefill_wide(const void *Q, const void *K, const void *V, float *S, float *nrm, float *lse2, float *s_part, int passes,
-                               const BatchMeta &meta, const Geometry &g, hipStream_t st)
+                               const BatchMeta &meta, const Geometry &g, hipStream_t st, const unsigned *only)
 {
     if (g.max_len <= 0) return hipSuccess;
     const bf16_t *q = static_cast<const bf16_t *>(Q), *k = static_cast<const bf16_t *>(K), *v = static_cast<const bf16_t *>(V);
     const int splits = s_part != nullptr ? colsum_splits(g) : 1;
     if (passes & kPassRowstat) {
         const unsigned wgs = 8u * block_pairs(g) * ((g.batch * g.n_heads * g.group + 7) / 8);
-        if (wgs >= 2u * kComputeUnits) launch_rowstat<4>(q, k, lse2, meta, g, st);
-        else launch_rowstat<8>(q, k, lse2, meta, g, st);
+        if (wgs >= 2u * kComputeUnits) launch_rowstat<4>(q, k, lse2, meta, g, only, st);
+        else launch_rowstat<8>(q, k, lse2, meta, g, only, st);
     }
     if (!(passes & kPassColsum)) return hipGetLastError();
     float *dst = splits > 1 ? s_part : S;
     const unsigned wgs = 8u * block_pairs(g) * ((g.batch * g.n_heads * splits + 7) / 8);
     if (g.group > 1) {
-        if (wgs >= 2u * kComputeUnits) launch_colsum<4, true>(q, k, v, dst, nrm, lse2, splits, meta, g, st);
-        else launch_colsum<8, true>(q, k, v, dst, nrm, lse2, splits, meta, g, st);
+        if (wgs >= 2u * kComputeUnits) launch_colsum<4, true>(q, k, v, dst, nrm, lse2, splits, meta, g, only, st);
+        else launch_colsum<8, true>(q, k, v, dst, nrm, lse2, splits, meta, g, only, st);
     } else {
-        if (wgs >= 2u * kComputeUnits) launch_colsum<4, false>(q, k, v, dst, nrm, lse2, splits, meta, g, st);
-        else launch_colsum<8, false>(q, k, v, dst, nrm, lse2, splits, meta, g, st);
+        if (wgs >= 2u * kComputeUnits) launch_colsum<4, false>(q, k, v, dst, nrm, lse2, splits, meta, g, only, st);
+        else launch_colsum<8, false>(q, k, v, dst, nrm, lse2, splits, meta, g, only, st);
     }
     if (splits > 1) return launch_merge_group_partials(s_part, S, splits, meta, g, st);
     return hipGetLastError();

@@ -9,7 +9,7 @@ import pytest
 
 from paper_2406_12335_amd import build
 
-SOURCES = ["prefill_wide.hip", "prefill_mfma.hip", "prefill_direct.hip", "decode.hip"]
+SOURCES = ["prefill_onepass.hip", "prefill_wide.hip", "prefill_mfma.hip", "prefill_direct.hip", "decode.hip"]
 
 
 @pytest.fixture(scope="module")

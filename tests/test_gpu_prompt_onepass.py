@@ -1,0 +1,159 @@
+"""Prompt scores in one pass over the logits: the kernel at the edges of its tiles, blocks and gangs, what it leaves to the kernels of two
+passes, workspaces without room for it, HIP graphs and two streams at once."""
+import pytest
+import torch
+
+import parity
+import paper_2406_12335_amd as vatp
+import vatp_synth as vs
+from oracle import vatp_oracle as orc
+
+pytestmark = pytest.mark.gpu
+
+
+class _Prompt:
+    def __init__(self, dev, d, H, lens, seed, change=None, norm=vatp.NORM_L1):
+        cfg = vs.scaled(vs.CONFIGS["llama7b_layer"], batch=len(lens), n_heads=H, head_dim=d, prompt_len=max(lens), decode_steps=0, n_sinks=1)
+        self.inp, self.lens, self.H, self.d = vs.make_inputs(cfg, seed=seed), lens, H, d
+        if change is not None:
+            change(self.inp)
+        for t in (self.inp.Q, self.inp.K, self.inp.V):
+            for b, L in enumerate(lens):
+                t[b, :, L:] = 77.0                  # (rows past the end hold junk)
+        self.p = vatp.Params(len(lens), H, d, torch.bfloat16, 0, 0, max(lens), lens, None, norm=norm)
+        self.ctx = vatp.vatp_create(0)
+        self.two_passes = (len(lens) * H * max(lens) * 4 + 255) // 256 * 256
+        need = vatp.vatp_workspace_bytes(self.ctx, self.p, vatp.binding.CALL_PREFILL_SCORE)
+        assert need > self.two_passes, "not a shape that takes one pass"
+        self.ws = torch.full((need,), 0x5a, dtype=torch.uint8, device=dev)
+        self.rows = [t.to(dev) for t in (self.inp.Q, self.inp.K, self.inp.V)]
+        self.S, self.nrm = (torch.full((len(lens), H, max(lens)), -3.0, device=dev) for _ in range(2))
+
+    def run(self, ws=None):
+        vatp.vatp_prefill_score(self.ctx, self.p, *self.rows, self.S, self.nrm, self.ws if ws is None else ws)
+
+    def scores(self):
+        self.run()
+        torch.cuda.synchronize()
+        return self.S.clone()
+
+    def check(self, units):
+        S, nrm = self.S.cpu(), self.nrm.cpu()
+        for b, L in enumerate(self.lens):
+            assert (S[b, :, L:] == -3.0).all() and (nrm[b, :, L:] == -3.0).all()
+        for b, h in units:
+            L = self.lens[b]
+            q, k, v = (t[b, h, :L].double().numpy() for t in (self.inp.Q, self.inp.K, self.inp.V))
+            parity.assert_scores_close(S[b, h, :L].numpy(), orc.prefill_scores_group(q[None], k), parity.rtol_for(torch.bfloat16), "S %d %d" % (b, h))
+            parity.assert_scores_close(nrm[b, h, :L].numpy(), orc.l1norm(v), parity.rtol_for(torch.bfloat16), "nrm %d %d" % (b, h))
+
+    def close(self):
+        torch.cuda.synchronize()
+        vatp.vatp_destroy(self.ctx)
+
+
+# Ends just past a block, a stage, a tile; an odd number of heads (the last one alone in its gang); sequences of one block and of a few
+# rows beside long ones; gangs over one XCD and over several; more gangs than the chip holds at once
+@pytest.mark.parametrize("d,H,lens", [
+    (128, 256, [257]), (128, 255, [300]), (128, 64, [1025]), (128, 37, [2000]), (128, 48, [1290, 1300, 1281, 1216, 1200, 1250, 1, 95]),
+    (128, 256, [1153]), (128, 10, [8000]), (64, 256, [512]), (64, 128, [1000]), (64, 64, [1290, 1300, 1281, 1216, 1200, 1250, 1, 127]),
+    (64, 29, [3970]), (64, 260, [769, 768]),
+])
+def test_scores(gpu_device, d, H, lens):
+    print("[case] one pass d=%d H=%d lens=%s" % (d, H, lens), flush=True)
+    prompt = _Prompt(gpu_device, d, H, lens, 501)
+    try:
+        first = prompt.scores()
+        prompt.check([(b, 0 if b % 2 else H - 1) for b in range(len(lens))] + [(0, 1)])
+        assert torch.equal(prompt.scores(), first)          # (totals do not depend on the order of the additions)
+    finally:
+        prompt.close()
+
+
+def _not_finite(inp):
+    inp.Q[0, 2, 100, 5] = float("nan")
+    inp.K[0, 5, 700, 3] = float("inf")
+
+
+def _far_key(inp):
+    inp.K[0, :, 600] = (inp.Q[0, :, 800].float() * 12).bfloat16()
+
+
+def _strong_sink(inp):
+    inp.K[0, :, 0] = (inp.K[0, :, 0].float() * 8).bfloat16()
+
+
+# (Scores of either way are good to 2e-6: two of them differ by twice that.)
+_APART = 4e-6
+
+
+# Heads that one pass leaves to two, some of a call or all, beside a call that keeps to two passes for want of room for the totals
+@pytest.mark.parametrize("d,H,L", [(128, 40, 2000), (64, 128, 1000)])
+@pytest.mark.parametrize("change", [_not_finite, _far_key, _strong_sink])
+def test_heads_left_to_two_passes(gpu_device, d, H, L, change):
+    print("[case] %s d=%d" % (change.__name__, d), flush=True)
+    prompt = _Prompt(gpu_device, d, H, [L], 503, change)
+    try:
+        got = prompt.scores()[0].cpu()
+        prompt.run(prompt.ws[:prompt.two_passes])
+        torch.cuda.synchronize()
+        want = prompt.S[0].cpu()
+        assert torch.equal(torch.isnan(got), torch.isnan(want)) and torch.equal(torch.isinf(got), torch.isinf(want))
+        finite = torch.isfinite(want)
+        assert bool(finite.any()) and bool(((got - want).abs()[finite] <= _APART * want[finite]).all())
+        if change is not _not_finite:
+            prompt.check([(0, 0), (0, H - 1)])
+    finally:
+        prompt.close()
+
+
+@pytest.mark.parametrize("norm", [vatp.NORM_L2, vatp.NORM_LINF, vatp.NORM_NONE])
+@pytest.mark.parametrize("d,H,L", [(128, 64, 1025), (64, 256, 512), (64, 64, 2048)])
+def test_value_norms(gpu_device, d, H, L, norm):
+    print("[case] norm %d d=%d H=%d L=%d" % (norm, d, H, L), flush=True)
+    prompt = _Prompt(gpu_device, d, H, [L], 505, norm=norm)
+    try:
+        prompt.scores()
+        v = prompt.inp.V.double()
+        want = {vatp.NORM_L2: v.pow(2).sum(-1).sqrt(), vatp.NORM_LINF: v.abs().amax(-1), vatp.NORM_NONE: torch.ones(v.shape[:-1], dtype=torch.float64)}[norm]
+        assert ((prompt.nrm.cpu().double() - want).abs() <= 1e-6 * want).all()
+    finally:
+        prompt.close()
+
+
+def test_in_a_graph(gpu_device):
+    prompt = _Prompt(gpu_device, 128, 64, [1025], 507)
+    try:
+        want = prompt.scores()
+        stream = torch.cuda.Stream()
+        stream.wait_stream(torch.cuda.current_stream())
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            prompt.run()
+        for _ in range(4):
+            prompt.S.fill_(-1.0)
+            prompt.ws.fill_(0x33)
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(prompt.S, want)
+    finally:
+        prompt.close()
+
+
+# Two streams at once: gangs of both share the chip.  One that does not come together in time leaves its heads to two passes.
+def test_two_streams(gpu_device):
+    prompts = [_Prompt(gpu_device, 128, 40, [2000], 509), _Prompt(gpu_device, 64, 128, [1000], 511)]
+    try:
+        want = [p.scores() for p in prompts]
+        streams = [torch.cuda.Stream() for _ in prompts]
+        for _ in range(10):
+            for p, stream in zip(prompts, streams):
+                stream.wait_stream(torch.cuda.current_stream())
+                with torch.cuda.stream(stream):
+                    p.run()
+        torch.cuda.synchronize()
+        for p, w in zip(prompts, want):
+            assert ((p.S - w).abs() <= _APART * w).all()
+    finally:
+        for p in prompts:
+            p.close()
