@@ -331,15 +331,16 @@ def measure(args, workload, steps, warmup, main_line):
     as_named = window is None and cfg == vs.CONFIGS.get(cfg.name)
     profiled = PROFILED_TRAFFIC_BYTES.get(cfg.name if as_named else None, {})
     traffic = profiled.get("bytes_per_call", {})
-    prefill_tflops = flops / (prefill_ms * 1e-3) / 1e12 if prefill_ms > 0 else 0.0
-    roof_prefill = {"kernel": ("vatp_prefill_score = " if window is None else "vatp_prefill_score_window = ") +
-                    prompt_score_kernels(cfg, lens, window),
+    kernels = prompt_score_kernels(cfg, lens, window)
+    passes = 1 if kernels.startswith("prefill_onepass") else 2        # (`flops` counts two contractions)
+    prefill_tflops = flops * passes / 2 / (prefill_ms * 1e-3) / 1e12 if prefill_ms > 0 else 0.0
+    roof_prefill = {"kernel": ("vatp_prefill_score = " if window is None else "vatp_prefill_score_window = ") + kernels,
                     "bound": "mfma",
                     "achieved": round(prefill_tflops, 3), "peak": peak_tf, "unit": "TFLOP/s",
-                    "frac": round(prefill_tflops / peak_tf, 5), "traffic": traffic.get("prefill_score"),
+                    "frac": round(prefill_tflops / peak_tf, 5), "traffic": traffic.get("prefill_score") if passes == 2 else None,
                     "avg_launch_ms": round(prefill_ms / cfg.layers, 5),
-                    # both passes recompute the logits; the rate of distinct (query, key) products is half of `achieved`
-                    "single_pass_TFLOPs": round(prefill_tflops / 2, 3)}
+                    # the rate of distinct (query, key) products: half of `achieved` where two passes form them
+                    "single_pass_TFLOPs": round(prefill_tflops / passes, 3)}
     loop_bytes = fused_bytes if fused else dec_bytes + sel_bytes
     decode_gbps = loop_bytes / (decode_ms * 1e-3) / 1e9 if decode_ms > 0 and T else 0.0
     # the fused call's duration: from the events around the decode loops of the timed steps when that loop ran

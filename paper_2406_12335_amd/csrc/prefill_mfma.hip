@@ -1,6 +1,7 @@
 // Prompt-pass scoring on the matrix cores (bf16 inputs, gfx950): history windows, and heads of 64 without one (heads of 128 without
 // a window: prefill_wide.hip, whose layout was slower here: 4 x 16 heads of 64 x 2048 rows 65.4 -> 71.9 us, 32 x 4096 106.9 ->
-// 114.1; only 32 x 16384 gained, 1385 -> 1359).
+// 114.1; only 32 x 16384 gained, 1385 -> 1359).  Equal prompts of ungrouped heads of 64 that prefill_onepass_fits accepts go to
+// prefill_onepass.hip; of those only the heads that it marks (`only`) come here.
 //
 // Accumulated attention score after the prompt (paper Eq. 2 with t = L-1):
 //     S_i = sum_{j>=i} a_i^j ,   a^j = softmax over keys i<=j of c*<q_j,k_i>   (Eq. 1).

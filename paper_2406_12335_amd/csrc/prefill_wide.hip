@@ -1,5 +1,7 @@
 // Prompt-pass scoring on the matrix cores, wide wavefront tiles (bf16, heads of 128, gfx950): row statistics and column sums of the
-// causal softmax without a history window, for grids that fill the chip.
+// causal softmax without a history window, for grids that fill the chip.  Equal prompts of ungrouped heads that prefill_onepass_fits
+// accepts go to prefill_onepass.hip, and of those only the heads that it marks (`only`) come here; groups, given log-sum-exps, ragged,
+// longer and smaller batches come here whole.
 //
 //   rowstat  queries stationary, keys streamed:  per query j  lse2_j = log2 sum_{i<=j} 2^(t_ji)
 //   colsum   keys stationary, queries streamed:  S_i = sum_{j>=i} 2^(t_ji - lse2_j), and the norms of the value rows
