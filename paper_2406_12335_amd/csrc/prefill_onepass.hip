@@ -27,8 +27,8 @@
 //
 // What the words cannot hold (totals outside 2^-13 .. 2^81 of the head's reference, sums not finite) or what loses precision (weights far above
 // a low reference, column sums that weights below 2^-126 could add to) marks the head, and the kernels of two passes, launched behind this one
-// and over at once otherwise (3.5 us for both), form it again.  So do heads whose gang did not come together: a workgroup waits kPatience
-// at most, as when kernels of other streams hold compute units that its gang needs, and from then on nobody in the launch waits.
+// and over at once otherwise (3.5 us for both), form it again.  So do heads whose gang did not come together: a workgroup waits
+// patience() at most, as when kernels of other streams hold compute units that its gang needs, and from then on nobody in the launch waits.
 // Where every head is formed again the call takes as long as both: 32 heads x 4096 rows, logits of the sinks 220 bits above the others', 150 / 278 us.
 // Logits of a standard deviation of 5 nats without sinks, or rising along the prompt by 15 nats a stage, are held.
 //
@@ -76,7 +76,11 @@ constexpr float kBelowTop = 40.f;
 // Weights far above the reference have their exponents rounded like the distance.  Where the reference is low that is coarser than the
 // logits themselves are, which are rounded like their distance from 0.
 constexpr float kLowReference = -8.f, kMostAbove = 0x1p24f;
-constexpr unsigned long long kPatience = 400000;      // ticks of 10 ns that a workgroup waits for the others
+// How long a workgroup waits for the others, in ticks of 10 ns: the first of a gang on compute units that the one before left idle wait as
+// long as that takes, 0.05 us a row (0.06 where power limits the clock), and up to 0.26 ms behind the longest of a ragged batch.  Much longer
+// waits only delay the two passes where gangs of several streams hold each other's compute units: four streams at once, 16 heads x 8192
+// rows each, two passes 1018 us for the four, one pass with waits of 4 ms 1169, with these 954..974.
+__device__ __forceinline__ unsigned patience(int len) { return max(30000, 8 * len); }
 
 __device__ __forceinline__ total_t load_total(const total_t *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
@@ -309,7 +313,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void prefill_onepass_kernel(const b
                     __builtin_amdgcn_s_sleep(1);
                     x = load_totals(i, true);
                     if (__all(arrived())) break;
-                    if (__builtin_amdgcn_s_memrealtime() - since > kPatience ||
+                    if (__builtin_amdgcn_s_memrealtime() - since > patience(len) ||
                         __hip_atomic_load(abort_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
                         const int lane = own_lane_here();
                         if (lane == 0) {
